@@ -239,3 +239,96 @@ def tolerance(case):
     if case["kind"] == "pool":   # windows that do not overlap only select; the others add a few numbers
         return "exact" if case["method"] == "max" and case["Sh"] == case["Hp"] and case["Sw"] == case["Wp"] else {"rel": 1e-6}
     return {"fp32": {"rel": 5e-6, "max": 4e-5}, "bf16x3": {"rel": 1.8e-5, "max": 1.5e-4}, "bf16": {"rel": 1e-2, "max": 8e-2}}[case["precision"]]
+
+
+def _windows(case):
+    """The taps of a window, in memory order: (column, row, and the slices of a padded plane that the tap meets over all windows)."""
+    c = case
+    fh, fw = (c["Hp"], c["Wp"]) if c["kind"] == "pool" else (c["Hf"], c["Wf"])
+    ho, wo = _out(c["H"], fh, c["Sh"], c["Pt"], c["Pb"]), _out(c["W"], fw, c["Sw"], c["Pl"], c["Pr"])
+    for fj in range(fw):
+        for fi in range(fh):
+            yield fj, fi, slice(fj, fj + (wo - 1) * c["Sw"] + 1, c["Sw"]), slice(fi, fi + (ho - 1) * c["Sh"] + 1, c["Sh"])
+
+
+def _exact_pool(c, s):
+    x, dzdy = s["x"].double(), s["dzdy"].double()
+    pad = (c["Pt"], c["Pb"], c["Pl"], c["Pr"])
+    inside = slice(c["Pl"], c["Pl"] + c["W"]), slice(c["Pt"], c["Pt"] + c["H"])
+    dxp = torch.nn.functional.pad(torch.zeros_like(x), pad)
+    if c["method"] == "max":
+        xp = torch.nn.functional.pad(x, pad, value=-math.inf)
+        y = torch.full_like(dzdy, -math.inf)
+        which = torch.zeros(dzdy.shape, dtype=torch.int32, device=x.device)
+        for t, (_, _, cols, rows) in enumerate(_windows(c)):
+            v = xp[:, :, cols, rows]
+            which.masked_fill_(v > y, t)
+            y = torch.maximum(y, v)
+        for t, (_, _, cols, rows) in enumerate(_windows(c)):
+            dxp[:, :, cols, rows] += dzdy * (which == t)
+    else:
+        xp, ones = torch.nn.functional.pad(x, pad), torch.nn.functional.pad(torch.ones_like(x[:1, :1]), pad)
+        y, count = torch.zeros_like(dzdy), 0
+        for _, _, cols, rows in _windows(c):
+            y += xp[:, :, cols, rows]
+            count = count + ones[:, :, cols, rows]
+        y /= count
+        for _, _, cols, rows in _windows(c):
+            dxp[:, :, cols, rows] += dzdy / count
+    return {"y": y, "dzdx": dxp[:, :, inside[0], inside[1]]}
+
+
+def _exact_conv(c, x, w, b, dzdy, bias):
+    """Forward and the three derivatives as sums over the filter's taps; dzdy None: forward alone."""
+    groups = x.shape[1] // w.shape[1]
+    n, k, df = x.shape[0], w.shape[0], w.shape[1]
+    kg = k // groups
+    xp = torch.nn.functional.pad(x, (c["Pt"], c["Pb"], c["Pl"], c["Pr"]))
+    taps = list(_windows(c))
+    wo, ho = _out(c["W"], c["Wf"], c["Sw"], c["Pl"], c["Pr"]), _out(c["H"], c["Hf"], c["Sh"], c["Pt"], c["Pb"])
+    y = torch.zeros((n, k, wo * ho), dtype=x.dtype, device=x.device)
+    out = {}
+    if dzdy is not None:
+        p = dzdy.reshape(n, k, wo * ho)
+        dxp, dw = torch.zeros_like(xp), torch.zeros_like(w)
+    for fj, fi, cols, rows in taps:
+        for g in range(groups):
+            ch, ks = slice(g * df, (g + 1) * df), slice(g * kg, (g + 1) * kg)
+            patch = xp[:, ch, cols, rows].reshape(n, df, wo * ho)
+            f = w[ks, :, fj, fi].contiguous()
+            y[:, ks] += torch.matmul(f, patch)
+            if dzdy is not None:
+                pg = p[:, ks].contiguous()
+                dw[ks, :, fj, fi] = torch.matmul(pg, patch.transpose(1, 2).contiguous()).sum(0)
+                dxp[:, ch, cols, rows] += torch.matmul(f.t().contiguous(), pg).reshape(n, df, wo, ho)
+    out["y"] = (y + b[:, None]).reshape(n, k, wo, ho) if bias else y.reshape(n, k, wo, ho)
+    if dzdy is not None:
+        out["dzdx"] = dxp[:, :, c["Pl"]:c["Pl"] + c["W"], c["Pt"]:c["Pt"] + c["H"]]
+        out["dzdw"], out["dzdb"] = dw, dzdy.sum((0, 2, 3))
+    return out
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, in 64 bits and plain torch (for every precision: of the inputs as they are)."""
+    c, s = case, prepare(case, seed)
+    if c["kind"] == "pool":
+        return _exact_pool(c, s)
+    x, w, b = s["x"].double(), s["w"].double(), s["b"].double()
+    if c["kind"] == "decoder":
+        # the transpose of a convolution that takes arrays of y's shape to arrays of x's: forward is its derivative with
+        # respect to its input, and the other way round
+        dzdy = s["dzdy"].double()
+        back = {"kind": "train", "H": dzdy.shape[3], "W": dzdy.shape[2], "Hf": c["Hf"], "Wf": c["Wf"], "Sh": c["Uh"], "Sw": c["Uw"],
+                "Pt": c["Ct"], "Pb": c["Cb"], "Pl": c["Cl"], "Pr": c["Cr"]}
+        r = _exact_conv(back, dzdy, w, None, x, False)
+        return {"y": r["dzdx"] + b[:, None, None], "dzdx": r["y"], "dzdf": r["dzdw"], "dzdb": dzdy.sum((0, 2, 3))}
+    if c["kind"] == "serve":
+        return {"y": _exact_conv(c, x, w, b, None, True)["y"].clamp_(min=0.0)}
+    dzdy, out = s["dzdy"].double(), {}
+    if c["relu"]:
+        dzdy = out["dzdp"] = dzdy * (s["kept"] > 0)
+    r = _exact_conv(c, x, w, b, dzdy, True)
+    if c["relu"]:
+        r["y"] = r["y"].clamp_(min=0.0)
+    out.update(r)
+    return out

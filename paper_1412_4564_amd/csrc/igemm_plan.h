@@ -8,6 +8,7 @@
 #include "geom.h"
 #include "kern_igemm.h"
 #include "kern_igemm_bf16.h"
+#include "kern_igemm_split.h"
 
 namespace mcn {
 
@@ -131,12 +132,13 @@ inline ConvView fc_backward_filter_view(const Geom &g) {
 // IG_W*: the WINO kernels (filters x pairs of output rows)
 // IG_96x256: eight waves of 96 filters x 32 pixels each, for 65 to 96 filters per group (a quarter fewer MFMAs than 128-filter tiles)
 enum IgemmShape { IG_128x256 = 0, IG_64x512 = 1, IG_32x256 = 2, IG_64x256 = 3, IG_W128x128 = 4, IG_W64x256 = 5, IG_96x256 = 6,
+                  IG_S64x256 = 7, IG_S128x128 = 8, IG_S128x64 = 9,     // three-plane kernel only
                   IG_NONE = -1 };
 
 struct IgemmPlan {
     int shape;          // IgemmShape
     bool bf16;          // operands rounded to bf16 (kern_igemm_bf16.h); sizes below are then in 32-bit words
-    int planes;         // bf16: 1, or 2 = operands split into hi and lo bf16 planes, three products each
+    int planes;         // bf16: 1; 2 = operands split into hi and lo bf16 planes, three products each; 3 = fp32 operands in three planes
     int fixed;          // index into IGEMM_FIXED: an instantiation with compile-time filter size (0 = none)
     int TK, TQ, NT;
     IgemmParams P;
@@ -214,7 +216,9 @@ inline bool cut_units_bf16(const ConvView &v, int TK, int64_t CP, size_t lds_lef
     for (int NTR = 1; NTR <= T; ++NTR) {
         const int TC = (T + NTR - 1) / NTR;
         if ((int64_t)(NTR - 1) * TC >= T) continue;
-        const size_t lds = 2 * ((size_t)TC * 2 * TK + 2 * (size_t)CP) * 16 * planes;
+        // three planes: the weights do not pass through LDS
+        const size_t lds = planes == 3 ? SPLIT_SLABS * 2 * (size_t)CP * 16 * planes
+                                       : 2 * ((size_t)TC * 2 * TK + 2 * (size_t)CP) * 16 * planes;
         if (lds > lds_left) continue;
         uc->pair_mode = 0; uc->DC = BF_DC; uc->TC = TC; uc->NTR = NTR; uc->NS = TC;
         return true;
@@ -222,9 +226,47 @@ inline bool cut_units_bf16(const ConvView &v, int TK, int64_t CP, size_t lds_lef
     return false;
 }
 
+// Three-plane kernel: block shapes (computing waves WK x WP of MK x MP tiles each), tried in turn.
+struct SplitShape { int shape, WK, WP, MK, MP; };
+constexpr SplitShape SPLIT_SHAPES[] = {{IG_S64x256, 2, 4, 1, 2}, {IG_S128x128, 4, 2, 1, 2}, {IG_S128x64, 4, 2, 1, 1}, {IG_32x256, 1, 8, 1, 1}};
+constexpr int SPLIT_N_SHAPES = 4;
+
+// Estimated time of a three-plane plan in microseconds, and the schedule it is estimated for: `own` whole tiles per block,
+// the rest shared.  Cycles of a step: its MFMAs (32 each, WK*WP/4 waves per SIMD), its LDS reads (128 bytes a cycle for
+// the block) or its weights' way through the L1 (64 bytes a cycle), whichever is longest, a unit's barrier, a tile's set-up and write-out; the fix-up pass as a launch plus its
+// traffic.  Either every block gets the same number of units (left-over tiles shared, fix-up pass), or whole tiles only
+// (up to a handful shared, so that the number of blocks stays a multiple of 8).
+struct SplitSchedule { int nblocks, own; double us; };
+inline SplitSchedule split_schedule(int64_t tiles, int NU, int NS, int64_t slab_bytes, const SplitShape &S, int n_cu) {
+    const double ghz = 2.2;
+    const int TK = S.WK * S.MK * 32, TQ = S.WP * S.MP * 32, waves = S.WK * S.WP;
+    const double mfma = S.MK * S.MP * 6 * 32.0 * waves / 4, lds = waves * 3072.0 * S.MP / 128, l1 = waves * 3072.0 * S.MK / 64;
+    double step = mfma;
+    if (step < 1.2 * lds) step = 1.2 * lds;
+    if (step < 1.2 * l1) step = 1.2 * l1;
+    // bytes that a unit brings into the compute unit, at about 40 a cycle
+    const double fetch = ((double)NS * 3 * 2 * TK * 16 + (double)slab_bytes) / 40.0;
+    double unit = NS * step * 1.15 + 200.0;
+    if (unit < fetch) unit = fetch;
+    const double tile_over = 2000.0 + TK * TQ * 4.0 / 32.0;
+    const double tile_us = (NU * unit + tile_over) / ghz * 1e-3;
+    SplitSchedule a, b;
+    const int64_t total = tiles * NU;
+    a.nblocks = (int)(total < n_cu ? total : n_cu);
+    a.own = (int)(tiles / a.nblocks);
+    const int64_t left = tiles - (int64_t)a.own * a.nblocks;
+    a.us = (double)tiles * tile_us / a.nblocks + (left ? 6.0 + (double)a.nblocks * TK * TQ * 8.0 / 4.0e6 + tile_over / ghz * 1e-3 : 0.0);
+    b.own = (int)((tiles + n_cu - 1) / n_cu);
+    b.nblocks = (int)(tiles / b.own);
+    if (b.nblocks > 64) b.nblocks &= ~7;
+    b.us = b.own * tile_us;
+    if ((int64_t)b.own * b.nblocks != tiles) b.us += 8.0 + (double)b.nblocks * TK * TQ * 2.0 / 4.0e6;
+    return b.us <= a.us ? b : a;
+}
+
 // wino: `v` is the stride-2, four-tap view of pairs of output rows (wino_view) and wino_Ho the real number of rows
 inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf16, int fixed, bool two = false,
-                            int wino_Ho = 0, int planes = 1) {
+                            int wino_Ho = 0, int planes = 1, int split = 0) {
     const int T = v.Hf * v.Wf;
     const bool wino = wino_Ho > 0;
     const IgemmFixed FX = wino ? IGEMM_WINO : IGEMM_FIXED[fixed];
@@ -233,7 +275,9 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     // at its barrier or writes a tile, the other keeps the matrix cores busy
     const size_t lds_limit = two ? IGEMM_LDS_LIMIT / 2 : IGEMM_LDS_LIMIT;
     const int resident = two ? 2 * n_cu : n_cu;
-    if (wino && v.Kg > 64) { shape = IG_W128x128; WK = 2; WP = 4; MK = 2; MP = 1; }
+    const SplitShape &SS = SPLIT_SHAPES[split];
+    if (planes == 3) { shape = SS.shape; WK = SS.WK; WP = SS.WP; MK = SS.MK; MP = SS.MP; }
+    else if (wino && v.Kg > 64) { shape = IG_W128x128; WK = 2; WP = 4; MK = 2; MP = 1; }
     else if (wino) { shape = IG_W64x256; WK = 1; WP = 8; MK = 2; MP = 1; }
     else if (two && v.Kg > 32) { shape = IG_64x256; WK = 1; WP = 4; MK = 2; MP = 2; }
     else if (!bf16 && v.Kg > 64 && v.Kg <= 96) { shape = IG_96x256; WK = 1; WP = 8; MK = 3; MP = 1; }
@@ -241,7 +285,8 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     else if (v.Kg > 32) { shape = IG_64x512; WK = 1; WP = 8; MK = 2; MP = 2; }
     else { shape = IG_32x256; WK = 1; WP = 4; MK = 1; MP = 2; }
     const int TK = WK * MK * 32, TQ = WP * MP * 32, NT = 64 * WK * WP;
-    const int NL = 64 * IGEMM_LOADER_WAVES;      // threads of the fetching (bf16: staging) waves
+    // threads of the fetching (bf16: staging) waves
+    const int NL = 64 * (planes == 3 ? SPLIT_STAGE_WAVES : IGEMM_LOADER_WAVES);
     const int Wp = (v.Wo - 1) * v.Sw + v.Wf;
     // candidates for the row-block height
     int cand[48];
@@ -262,13 +307,13 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         if ((int64_t)TI * v.Wo * v.N >= ((int64_t)1 << 30)) continue;
         const int SC = slab_columns(v, TI, TQ, Wp);
         const int64_t CP = (SR * SC + 63) / 64 * 64;
-        if (CP > (bf16 ? bf_ept_max(NL) : 32) * NL) continue;
+        if (CP > (planes == 3 ? SPLIT_EPT_MAX : bf16 ? bf_ept_max(NL) : 32) * NL) continue;
         // an image crossing inside a tile moves the window by whole images: keep offsets in range
         const int64_t span = (int64_t)SC / Wp + 2;
         if ((double)span * v.Ctot * v.H * v.W * 4.0 >= 2147483647.0) continue;
         if ((double)(span + 1) * v.Ktot * v.OH * v.OW * 4.0 >= 2147483647.0) continue;   // and inside its output window
         const int EPT = (int)((CP + NL - 1) / NL);
-        const size_t fixed_lds = ((size_t)EPT * NL + 2 * TK + 4) * 4;
+        const size_t fixed_lds = ((planes == 3 ? 0 : (size_t)EPT * NL) + (planes == 3 ? SPLIT_BIASES : 2) * TK + 4) * 4;
         UnitCut uc;
         if (bf16) {
             if (fixed_lds + 64 > lds_limit) continue;
@@ -299,6 +344,9 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         // (measured with split operands, same box: layer 4a with one tap range 0.41 against 0.50 ms with three;
         // 4b with two 0.378 against 0.40 with three)
         if (bf16) score *= 1.0 + 0.5 * (uc.NTR - 1);
+        if (planes == 3)     // microseconds; short slab rows and short column runs of results as above
+            score = split_schedule((int64_t)v.G * RB * PT * ((v.Kg + TK - 1) / TK), NCG * uc.NTR, uc.NS, CP * 64 / uc.NTR, SS, n_cu).us *
+                    (input_streams ? 1.0 + 1.0 / (double)SR : 1.0) * (1.0 + 0.5 / (double)TI);
         if (wino) {
             // The row-pair kernels issue fewer MFMAs per staged byte and per stored line, and what was measured on
             // them weighs differently: short slab rows cost little, column runs of results (2*TI samples) that are
@@ -335,7 +383,11 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     // whole tiles first, one share of the left-over tiles after (see IgemmParams::own): fewer tiles go through
     // the workspace and the fix-up pass than when everything is shared
     P.own = (int)(tiles / P.nblocks);
-    if (!bf16 && 2 * tiles >= resident && tiles < resident) {
+    if (planes == 3) {
+        const SplitSchedule sc = split_schedule(tiles, P.NU, P.NS, (int64_t)P.CP * 64 / P.NTR, SS, n_cu);
+        P.nblocks = sc.nblocks;
+        P.own = sc.own;
+    } else if (!bf16 && 2 * tiles >= resident && tiles < resident) {
         // Somewhat fewer tiles than compute units: sharing every tile keeps all units busy but sends every tile through
         // the workspace and the fix-up pass; one whole tile per block leaves some units idle and needs neither.
         // Times in microseconds: a unit's MFMAs at about 80 % of the matrix core's rate (two waves per SIMD with
@@ -356,6 +408,17 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     P.OH = v.OH; P.OW = v.OW; P.oi0 = v.oi0; P.osi = v.osi; P.oj0 = v.oj0; P.osj = v.osj;
     P.mD = v.mD; P.mPt = v.mPt; P.mPl = v.mPl;
     P.wino_Ho = wino_Ho;
+    {
+        const int area = v.HfA * v.WfA;
+        if (v.pack_mode == 0) {
+            P.wo = 0; P.wg = area * v.DfA * v.Kg; P.wk = area * v.DfA; P.wc = area; P.wi = 1; P.wj = v.HfA;
+        } else if (v.pack_mode == 1) {
+            P.wo = v.pi + v.pSh * (v.Hf - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
+            P.wg = area * v.DfA * v.Cg; P.wk = area; P.wc = area * v.DfA; P.wi = -v.pSh; P.wj = -v.HfA * v.pSw;
+        } else if (planes == 3) {
+            return false;       // the fully-connected and merged-phase views stay on the fp32 kernels
+        }
+    }
     P.dTI = make_div32(P.TI); P.dWo = make_div32(P.Wo); P.dWp = make_div32(P.Wp); P.dSRP = make_div32(P.SRP);
     P.dKT = make_div32(P.KT); P.dRB = make_div32(P.RB); P.dPT = make_div32(P.PT);
     // packed weights per unit, in 32-bit words: bf16 steps hold 2 octets x TK filters x 16 bytes
@@ -368,7 +431,9 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     pl->partial_floats = P.nblocks > 1 && (int64_t)P.own * P.nblocks != tiles ? (size_t)2 * P.nblocks * TK * TQ * (wino ? 2 : 1) : 0;
     pl->shape = shape; pl->bf16 = bf16; pl->planes = bf16 ? planes : 1; pl->fixed = fixed; pl->TK = TK; pl->TQ = TQ; pl->NT = NT;
     pl->score = best_score;
-    if (bf16)
+    if (planes == 3)
+        pl->lds_bytes = ((size_t)SPLIT_BIASES * TK + (size_t)SPLIT_SLABS * 6 * P.CP * 4 + 4) * sizeof(float);
+    else if (bf16)
         pl->lds_bytes = (2 * wsz + 2 * (size_t)planes * 2 * P.CP * 4 + (size_t)P.EPT * NL + 2 * TK + 4) *
                         sizeof(float);
     else
@@ -408,12 +473,31 @@ inline bool wino_enabled() {
     return !off;
 }
 
+// Whether an fp32 view takes the three-plane kernel (kern_igemm_split.h).  Not the views of row pairs, and not 1x1 filters: a
+// unit is then one step (768 cycles of MFMAs), and its staging (loads, split, barrier) takes longer (28x28x512, 1x1x512x128,
+// 64 images: forward 93 us against 78 on the fp32 kernel).
+inline bool split_pays(const ConvView &v) {
+    ConvView pv;
+    if (v.mD || v.pack_mode > 1 || v.Cg < BF_DC || v.Hf * v.Wf < 2) return false;
+    return !(wino_enabled() && wino_view(v, &pv));
+}
+
 // The instantiation with this view's filter size if there is one, its channels divide into the
 // fixed units and a plan fits; the general kernel otherwise.
 // row_pairs: 3x3 stride-1 views may take the kernels that compute two output rows from four products per
 // filter column (the caller asks for the plain order of summation with MCN_PREC_FP32_PLAIN).
 // planes (bf16 only): 2 = split operands (kern_igemm_bf16.h)
 inline bool plan_igemm(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf16 = false, bool row_pairs = true, int planes = 1) {
+    if (bf16 && planes == 3) {
+        bool ok = false;
+        for (int f = 0; f < SPLIT_N_SHAPES; ++f) {
+            const int TK = SPLIT_SHAPES[f].WK * SPLIT_SHAPES[f].MK * 32;
+            if (TK == 32 ? v.Kg > 32 : v.Kg <= TK / 2) continue;      // half of the tile would be empty
+            IgemmPlan one;
+            if (plan_igemm_kind(v, n_cu, &one, true, 0, false, 0, 3, f) && (!ok || one.score < pl->score)) { *pl = one; ok = true; }
+        }
+        return ok;
+    }
     if (bf16) return plan_igemm_kind(v, n_cu, pl, true, 0, false, 0, planes);
     ConvView pv;
     if (row_pairs && wino_enabled() && wino_view(v, &pv) && plan_igemm_kind(pv, n_cu, pl, false, 0, false, v.Ho)) return true;

@@ -149,8 +149,35 @@ struct IgemmParams {
     int wino_Ho;
     int wino_pairs;     // WINO: 1 = both rows of a pair go out in one 8-byte store (rows adjacent in memory, every such
                         // address a multiple of 8: output pointer aligned to 8 bytes and an even number of rows per plane)
+    // three-plane kernels only (kern_igemm_split.h): results that are not finite are summed again one by one; where
+    // weight (group g, filter k, channel c, tap (ti, tj)) of the view is in the caller's array:
+    // wo + g*wg + k*wk + c*wc + ti*wi + tj*wj
+    int wo, wg, wk, wc, wi, wj;
     Div32 dTI, dWo, dWp, dSRP, dKT, dRB, dPT;   // reciprocals of the fields of these names
 };
+
+__device__ inline bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
+
+// One result of the view, summed as Sec. 4.1 writes it: what the results that are not finite are taken from.  w: the
+// caller's filter array.
+__device__ inline float plain_result(const IgemmParams &P, const float *in, const float *w, const float *bias, int g,
+                                                        int kl, int io, int jo, int n) {
+    float s = bias ? bias[g * P.Kg + kl] : 0.f;
+    for (int c = 0; c < P.Cg; ++c) {
+        const float *xc = in + (size_t)P.H * P.W * (g * P.Cg + c + (size_t)P.Ctot * n);
+        for (int tj = 0; tj < P.Wf; ++tj) {
+            const int j = P.Sw * jo + tj - P.Pl;
+            if (j < 0 || j >= P.W) continue;
+            for (int ti = 0; ti < P.Hf; ++ti) {
+                const int i = P.Sh * io + ti - P.Pt;
+                if (i < 0 || i >= P.H) continue;
+                const long long wx = P.wo + (long long)g * P.wg + (long long)kl * P.wk + (long long)c * P.wc + ti * P.wi + tj * P.wj;
+                s = fmaf(w[wx], xc[i + (size_t)P.H * j], s);
+            }
+        }
+    }
+    return P.relu ? fmaxf(s, 0.f) : s;
+}
 
 // Merged phases: channel, and placement of output pixel (0,0), of merged filter kl
 struct MergedFilter {
@@ -864,9 +891,10 @@ __global__ __launch_bounds__(64 * (WK * WP + LW), WPE) void igemm_sk_kernel(Igem
 
 // Sum the pieces of every tile that was shared between blocks, in block order, add the bias,
 // and write the tile.  Grid: (left-over tiles, slices of a tile).
-template <int TK, int TQ>
+template <int TK, int TQ, bool REPAIR = false>
 __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const float *__restrict__ part,
-                                                          const float *__restrict__ bias, float *__restrict__ out) {
+                                                          const float *__restrict__ bias, float *__restrict__ out,
+                                                          const float *__restrict__ in, const float *__restrict__ w) {
     const int ts = blockIdx.x;                       // shared tile (the grid has one row of blocks per shared tile)
     const int tile_s0 = P.own * P.nblocks;           // the shared tiles start here; unit numbers are relative to them
     const int t = tile_s0 + ts;
@@ -930,7 +958,8 @@ __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const f
             const int oi = P.oi0 + P.osi * io + fi0, oj = P.oj0 + P.osj * jo + fj0;
             if (P.mD && (oi >= P.OH || oj >= P.OW)) continue;
             float v = vv[j];
-            if (P.relu) v = fmaxf(v, 0.f);
+            if (REPAIR && not_finite(v)) v = plain_result(P, in, w, bias, g, kl, io, jo, n);      // see kern_igemm_split.h
+            else if (P.relu) v = fmaxf(v, 0.f);
             out[(size_t)(oi + P.OH * (oj + P.OW * (P.Ktot * n))) + (size_t)OHW * och] = v;
         }
     }

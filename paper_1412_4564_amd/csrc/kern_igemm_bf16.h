@@ -54,8 +54,18 @@ __device__ inline void split_bf16x2(float v0, float v1, unsigned *hi, unsigned *
     *lo = pack_bf16x2(v0 - __uint_as_float(h << 16), v1 - __uint_as_float(h & 0xffff0000u));
 }
 
+// three planes of a pair: hi = bf16(v), mid = bf16(v - hi), lo = v - hi - mid.  Both differences are exact in fp32 and the
+// last one has at most 8 significant bits left, so the three planes together are v itself (while lo stays above the
+// smallest bf16 number: |v| from about 1e-35 on; below that lo loses its last bits).
+__device__ inline void split_bf16x3(float v0, float v1, unsigned *hi, unsigned *mid, unsigned *lo) {
+    const unsigned h = pack_bf16x2(v0, v1);
+    const float r0 = v0 - __uint_as_float(h << 16), r1 = v1 - __uint_as_float(h & 0xffff0000u);
+    *hi = h;
+    split_bf16x2(r0, r1, mid, lo);
+}
+
 // packed[g][kt][unit][step][plane][octet][kk][8 channels] as bf16 (Q.planes = 1: the values rounded to bf16;
-// 2: their hi and lo planes); one thread writes one pair of channels (a 32-bit word).  Modes as in
+// 2: their hi and lo planes; 3: hi, mid and lo, for kern_igemm_split.h); one thread writes one pair of channels (a 32-bit word).  Modes as in
 // igemm_pack_weights_kernel.
 __global__ __launch_bounds__(256) void igemm_pack_weights_bf16_kernel(const float *__restrict__ w,
                                                                       unsigned *__restrict__ packed, PackParams Q) {
@@ -90,9 +100,9 @@ __global__ __launch_bounds__(256) void igemm_pack_weights_bf16_kernel(const floa
             }
         }
     }
-    unsigned hi, lo;
-    split_bf16x2(v[0], v[1], &hi, &lo);
-    packed[p] = plane ? lo : hi;
+    unsigned hi, mid, lo;
+    split_bf16x3(v[0], v[1], &hi, &mid, &lo);
+    packed[p] = plane == 0 ? hi : plane == 1 ? mid : lo;      // of two planes the second is bf16(v - hi) as well
 }
 
 // WK x WP waves; each wave owns MK x MP tiles of 32 filters x 32 pixels.

@@ -1,0 +1,391 @@
+// Implicit-GEMM convolution of fp32 operands on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16).
+//
+// The sum is that of kern_igemm.h (MatConvNet manual, arXiv 1412.4564, Sec. 4.1), in fp32 precision: every operand v is
+// held on chip as three bf16 planes, v = hi + mid + lo exactly (split_bf16x3), and a product is formed as
+//   w_lo*x_hi + w_mid*x_hi + w_hi*x_hi + w_mid*x_mid + w_hi*x_mid + w_hi*x_lo
+// with fp32 accumulation.  Each product of two bf16 numbers is exact in fp32 and what is left out (w_mid*x_lo and
+// smaller) is below 2^-26 of |w||x|, less than the rounding of one fp32 multiply-add.  The five small products have
+// accumulators of their own, added at the end: an MFMA rounds its sum four times on the way through its 16 elements, and
+// with all six products in one sum the results are 1.2 times as far from sums in 64 bits as those of the fp32
+// instructions (24 roundings per 16 elements against 16); the roundings of the small sum cost nothing.  Six products on a matrix core that multiplies 16 times as fast as in fp32 cost 6/16 of the fp32 kernel's matrix time.
+//
+// Tiling, pixel numbering, schedule and fix-up pass: kern_igemm.h.  One MFMA takes 16 channels of one tap, a lane's operand
+// is 16 consecutive bytes: slab [plane][octet][column][row][8 channels] in LDS, weights
+// [channel group][tap][plane][octet][filter][8 channels] in memory (igemm_pack_weights_bf16_kernel, three planes).  A unit
+// is 16 channels x all taps.
+//
+// What bounds it: the matrix core's power (random data: 1.85 PFLOP/s sustained from registers, 2.45 with zeros) as long as
+// no wave waits.  Hence
+//  * the weights go from the L2 straight into the registers of the waves that use them (waves of one block read the same
+//    ones through the L1: 32 bytes a cycle) and not through LDS: staged there, 12 KB per tap, they forced a barrier every
+//    tap or two, and with eight waves in step the scalar work, the LDS latency and the skew at each barrier cost as much
+//    as half a tap's MFMAs (27x27x96 plane, 5x5x48x256 filters, 128 images: 318 us).  The LDS then holds three slabs and
+//    its reads are halved.
+//  * slabs are published one barrier before they are computed, so the last step of a unit reads the next unit's first
+//    operands and no wave starts a unit with empty registers.
+//  * every plane has one set of registers, read anew for the next step as soon as its last product is issued; the order
+//    of the products leaves 12 MFMAs (weights) or 8 (pixels) between that and the next use.
+#pragma once
+#include "kern_igemm_bf16.h"
+
+namespace mcn {
+
+constexpr int SPLIT_SLABS = 3;         // slab buffers: computed, next (being read ahead), written
+constexpr int SPLIT_BIASES = 4;        // bias buffers: a bias is written at most two tiles ahead
+constexpr int SPLIT_STAGE_WAVES = 4;   // waves that fetch and split the input
+constexpr int SPLIT_EPT_MAX = 2;       // slab samples a thread stages per unit, at most (16 registers each)
+
+// WK x WP computing waves; each owns MK x MP tiles of 32 filters x 32 pixels.  wsrc: the caller's filter array.
+template <int WK, int WP, int MK, int MP>
+__global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 3 : 2) void igemm_split_kernel(
+    IgemmParams P, const float *__restrict__ in, const float *__restrict__ wpk, const float *__restrict__ bias, float *out,
+    float *__restrict__ part, const float *__restrict__ wsrc) {
+    constexpr int NT = 64 * WK * WP;               // computing threads
+    constexpr int NL = 64 * SPLIT_STAGE_WAVES;     // staging threads
+    constexpr int TK = WK * MK * 32;
+    constexpr int TQ = WP * MP * 32;
+    const int NU = P.NU;
+    const int CP = P.CP, SRP = P.SRP;
+    const int XSZ = 3 * 2 * CP * 4;      // 32-bit words of slab per buffer: 3 planes x 2 octets x CP samples x 16 bytes
+
+    extern __shared__ __align__(16) float lds[];
+    float *xbuf = lds;                                              // [SLABS][XSZ]
+    float *blds = xbuf + SPLIT_SLABS * XSZ;        // [BIASES][TK] bias of the tile, slots used in turn
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int HW = P.H * P.W;
+    const int OHW = P.OH * P.OW;
+
+    // ---- the block's range of units (see igemm_sk_kernel) ---------------------------------
+    const int vb = sk_virtual_block(blockIdx.x, P.nblocks);
+    const int tile_s0 = P.own * P.nblocks;                          // first shared tile
+    const long long total = (long long)(P.tiles - tile_s0) * NU;    // units of the shared tiles
+    const int rank = sk_share_rank(P.nblocks, P.nshare, vb);
+    const long long ub = rank < 0 ? 0 : sk_begin(total, P.nshare, rank), ue = rank < 0 ? 0 : sk_begin(total, P.nshare, rank + 1);
+    const int n_own = P.own * NU;                                    // units of this block's own tiles
+    const int nunits = n_own + (int)(ue - ub);
+    if (nunits == 0) return;
+    const int t_s = tile_s0 + (int)(ub / NU), uu_s = (int)(ub - (ub / NU) * NU);
+    auto tile_of = [&](int t) __attribute__((always_inline)) {                    // dealt among the blocks of an XCD, as in igemm_sk_kernel
+        if (t >= tile_s0 || (P.nblocks & 7) != 0) return t;
+        const int b = t / P.own, j = t - b * P.own;
+        const int G = P.nblocks >> 3, x = b / G, i = b - x * G;
+        return (x * G) * P.own + j * G + i;
+    };
+
+    if (wave >= WK * WP) {
+        // ---- the waves that fetch the input and split it ----------------------------------
+        // The samples of three units are on their way at a time, in three sets of registers: a unit of few taps is
+        // computed in less time than a sample takes from memory.  What a unit does not have is requested
+        // out of range and reads as zero: no divergent branches, so that the waits for a set leave younger ones in flight.
+        struct Samples {
+            float v[SPLIT_EPT_MAX][BF_DC];
+            int uu, kt, g, seq;
+        };
+        Samples set[3];
+        const int ltid = tid - NT, lwave = wave - WK * WP;
+        int t = n_own ? vb * P.own : t_s, uu = n_own ? 0 : uu_s, n = 0;      // next unit to request, units before it
+        int kt = 0, g = 0, seq = -1;
+        unsigned go[SPLIT_EPT_MAX];                 // byte offset of the thread's samples in channel 0, or SLAB_INVALID
+        __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void *)in, 0, 0, BUFFER_FLAGS);
+        auto set_tile = [&](int tile) __attribute__((always_inline)) {
+            ++seq;
+            int pt, rb;
+            decode_tile(P, tile, &kt, &pt, &rb, &g);
+            const int q0 = pt * TQ;
+            const int c_first = div32(q0, P.dTI);
+            const int n_first = div32(c_first, P.dWo);
+            const int u0 = (c_first - n_first * P.Wo) * P.Sw;   // chained column of the slab's first column
+            const int row0 = rb * P.TI * P.Sh - P.Pt;           // input row of slab row 0
+            const size_t in_base = ((size_t)n_first * P.Ctot + (size_t)g * P.Cg) * HW;
+            size_t in_left = ((size_t)P.N * P.Ctot * HW - in_base) * 4;
+            if (in_left > 0x7fffffffull) in_left = 0x7fffffffull;
+            xrs = __builtin_amdgcn_make_buffer_rsrc((void *)(in + in_base), 0, (int)in_left, BUFFER_FLAGS);
+#pragma unroll
+            for (int s = 0; s < SPLIT_EPT_MAX; ++s) {
+                const int e = ltid + NL * s;
+                const int col = div32(e, P.dSRP);
+                const int r = e - col * SRP;
+                const int U = u0 + col;
+                const int ni = div32(U, P.dWp);          // image relative to n_first
+                const int j = U - ni * P.Wp - P.Pl;
+                const int i = row0 + r;
+                const bool ok = e < CP && r < P.SR && i >= 0 && i < P.H && j >= 0 && j < P.W && (n_first + ni) < P.N;
+                go[s] = ok ? 4u * (unsigned)(i + P.H * j + ni * P.Ctot * HW) : SLAB_INVALID;
+            }
+        };
+        auto request = [&](Samples &q) __attribute__((always_inline)) {
+            const int c0 = uu * BF_DC, c_end = n < nunits ? P.Cg : 0;
+            q.uu = uu; q.kt = kt; q.g = g; q.seq = seq;
+#pragma unroll
+            for (int s = 0; s < SPLIT_EPT_MAX; ++s) {
+                if (s * NL >= CP) continue;
+#pragma unroll
+                for (int d = 0; d < BF_DC; ++d)
+                    // channels past the group's last one read as zero (their weights are zero too)
+                    q.v[s][d] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        xrs, c0 + d < c_end ? go[s] : SLAB_INVALID, (unsigned)(c0 + d) * (unsigned)HW * 4u, 0));
+            }
+            // on to the next unit
+            ++n;
+            const int t_old = t;
+            if (n == n_own) { t = t_s; uu = uu_s; }
+            else if (++uu == NU) { uu = 0; ++t; }
+            if (t != t_old && n < nunits) set_tile(tile_of(t));
+        };
+        int slab = 0;
+        auto write = [&](Samples &q) __attribute__((always_inline)) {
+            if (q.uu == 0 && bias && ltid < TK) {    // start value of a tile this block owns entirely
+                const int kl = q.kt * TK + ltid;
+                blds[(q.seq & (SPLIT_BIASES - 1)) * TK + ltid] = kl < P.Kg ? bias[q.g * P.Kg + kl] : 0.f;
+            }
+            float *xb = xbuf + slab * XSZ;
+            slab = slab + 1 == SPLIT_SLABS ? 0 : slab + 1;
+#pragma unroll
+            for (int s = 0; s < SPLIT_EPT_MAX; ++s) {
+                const int e = ltid + NL * s;
+                if (lwave * 64 + NL * s >= CP) continue;         // CP is a multiple of 64
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    unsigned hi[4], mid[4], lo[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        split_bf16x3(q.v[s][8 * o + 2 * j], q.v[s][8 * o + 2 * j + 1], &hi[j], &mid[j], &lo[j]);
+                    const uintx4 h = {hi[0], hi[1], hi[2], hi[3]}, m = {mid[0], mid[1], mid[2], mid[3]}, l = {lo[0], lo[1], lo[2], lo[3]};
+                    *reinterpret_cast<uintx4 *>(xb + (size_t)((0 + o) * CP + e) * 4) = h;
+                    *reinterpret_cast<uintx4 *>(xb + (size_t)((2 + o) * CP + e) * 4) = m;
+                    *reinterpret_cast<uintx4 *>(xb + (size_t)((4 + o) * CP + e) * 4) = l;
+                }
+            }
+        };
+        set_tile(tile_of(t));
+#pragma unroll
+        for (int j = 0; j < 3; ++j) request(set[j]);
+        for (int it = -2; it < nunits; it += 3) {    // unit it + 2 is written after the barrier of unit it
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                if (it + j >= 0 && it + j < nunits) lds_barrier();
+                if (it + j + 2 < nunits) {
+                    write(set[j]);
+                    request(set[j]);
+                }
+            }
+        }
+        return;
+    }
+
+    // ---- the computing waves --------------------------------------------------------------
+    const int wk = wave % WK, wp = wave / WK;
+    int bbase[MP];       // slab byte offset of the pixel's window origin, octet of this half-wave
+    unsigned ooff[MP];   // byte offset of the lane's first result relative to the tile's output window, or SLAB_INVALID
+    __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc((void *)out, 0, 0, BUFFER_FLAGS);
+    int c_kt = 0, c_g = 0, c_seq = -1;
+    floatx16 acc[MK][MP], small[MK][MP];            // sums of the hi x hi products, and of the five others
+    auto set_tile = [&](int t) __attribute__((always_inline)) {
+        ++c_seq;
+        int kt, pt, rb, g;
+        decode_tile(P, t, &kt, &pt, &rb, &g);
+        c_kt = kt; c_g = g;
+        const int q0 = pt * TQ;
+        const int qend = min(q0 + TQ, P.QN);
+        const int c_first = div32(q0, P.dTI);
+        const int n_first = div32(c_first, P.dWo);
+        const int u0 = (c_first - n_first * P.Wo) * P.Sw;
+#pragma unroll
+        for (int mp = 0; mp < MP; ++mp) {
+            const int q = q0 + (wp * MP + mp) * 32 + (lane & 31);
+            const int c = div32(q, P.dTI);
+            const int ii = q - c * P.TI;
+            const int n = div32(c, P.dWo);
+            const int jo = c - n * P.Wo;
+            const int io = rb * P.TI + ii;
+            const bool ok = q < qend && io < P.Ho;
+            const int ucol = jo * P.Sw + (n - n_first) * P.Wp - u0;
+            bbase[mp] = 16 * ((ok ? ii * P.Sh + SRP * ucol : 0) + half * CP);
+            ooff[mp] = ok ? 4u * (unsigned)((P.oi0 + P.osi * io) + P.OH * (P.oj0 + P.osj * jo) +
+                                            OHW * (P.Ktot * (n - n_first) + 4 * half))
+                          : SLAB_INVALID;
+        }
+        const size_t out_base = (size_t)n_first * P.Ktot * OHW;
+        size_t out_left = ((size_t)P.N * P.Ktot * OHW - out_base) * 4;
+        if (out_left > 0x7fffffffull) out_left = 0x7fffffffull;
+        ors = __builtin_amdgcn_make_buffer_rsrc((void *)(out + out_base), 0, (int)out_left, BUFFER_FLAGS);
+    };
+    auto init_acc = [&](bool with_bias) __attribute__((always_inline)) {
+        const float *bl = blds + (c_seq & (SPLIT_BIASES - 1)) * TK;
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int kloc = (wk * MK + mk) * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
+                const float bv = with_bias ? bl[kloc] : 0.f;
+#pragma unroll
+                for (int mp = 0; mp < MP; ++mp) { acc[mk][mp][v] = bv; small[mk][mp][v] = 0.f; }
+            }
+    };
+    const int aoff = 16 * (half * TK + wk * MK * 32 + (lane & 31));   // bytes
+    const int T = P.Hf * P.Wf;
+    const int xplane = 2 * CP * 16;                  // bytes from a slab plane to the next
+    // where the next operands are read: weights of the step (steps follow one another in memory through all units of a
+    // tile), slab and offset of its tap.  All scalar but the two lane offsets.
+    const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void *)wpk, 0, (int)P.packed_bytes, BUFFER_FLAGS);
+    constexpr int WPLANE = 2 * TK * 16, WSTEP = 3 * WPLANE;
+    unsigned wo = 0;
+    int xo = 0, xslab = 0, fi = 0, so = 0;
+    const int xbytes = 4 * XSZ;
+    const char *const xlane = reinterpret_cast<const char *>(xbuf);
+    auto next_tap = [&]() __attribute__((always_inline)) {
+        const bool wrap = ++fi == P.Hf;
+        so += wrap ? 16 * (SRP - P.Hf + 1) : 16;
+        if (wrap) fi = 0;
+    };
+    auto next_slab = [&]() __attribute__((always_inline)) {
+        xslab = xslab + xbytes == SPLIT_SLABS * xbytes ? 0 : xslab + xbytes;
+    };
+    typedef bf16x8 OpA[MK];
+    typedef bf16x8 OpB[MP];
+    OpA ah, am, al;
+    OpB bh, bm, bl;
+    auto load_a = [&](OpA &a, int pl) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk) a[mk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wrs, (unsigned)aoff + mk * 512u, wo + (unsigned)(pl * WPLANE), 0));
+    };
+    auto load_b = [&](OpB &b, int pl) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mp = 0; mp < MP; ++mp) b[mp] = *reinterpret_cast<const bf16x8 *>(xlane + bbase[mp] + (xo + so + pl * xplane));
+    };
+    auto mma = [&](floatx16 (&sum)[MK][MP], const OpA &a, const OpB &b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+            for (int mp = 0; mp < MP; ++mp)
+                sum[mk][mp] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mk], b[mp], sum[mk][mp], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto prime = [&]() __attribute__((always_inline)) {
+        load_a(ah, 0); load_b(bl, 2); load_b(bm, 1); load_b(bh, 0); load_a(am, 1); load_a(al, 2);
+    };
+    // one step; wo, xo, so are the next step's when it begins
+    auto step = [&]() __attribute__((always_inline)) {
+        mma(small, ah, bl);
+        load_b(bl, 2);
+        mma(small, ah, bm);
+        mma(acc, ah, bh);
+        load_a(ah, 0);
+        mma(small, am, bm);
+        load_b(bm, 1);
+        mma(small, am, bh);
+        load_a(am, 1);
+        mma(small, al, bh);
+        load_b(bh, 0);
+        load_a(al, 2);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // An operand that is infinite splits into (inf, nan, nan), so every result that it enters comes out as NaN where the
+    // plain sum may say +-inf (and one within 2^-9 of the largest float rounds to inf in its hi plane).  A tile with a
+    // result that is not finite is gone over again once it is stored: such results are summed one by one from the arrays
+    // in memory (plain_result).  The ReLU must not hide them before: they are stored as NaN.
+    bool odd_results = false;
+    auto repair_tile = [&](int t) __attribute__((always_inline)) {
+        int kt, pt, rb, g;
+        decode_tile(P, t, &kt, &pt, &rb, &g);
+        __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);       // this wave reads back what it stored
+#pragma unroll 1
+        for (int mp = 0; mp < MP; ++mp) {
+            const int q = pt * TQ + (wp * MP + mp) * 32 + (lane & 31);
+            const int c = div32(q, P.dTI);
+            const int n = div32(c, P.dWo);
+            const int jo = c - n * P.Wo, io = rb * P.TI + q - c * P.TI;
+            if (q >= P.QN || io >= P.Ho) continue;
+#pragma unroll 1
+            for (int v = 0; v < MK * 16; ++v) {
+                const int kl = kt * TK + (wk * MK + (v >> 4)) * 32 + ((v & 15) >> 2) * 8 + half * 4 + (v & 3);
+                if (kl >= P.Kg) continue;
+                float *o = out + (size_t)(P.oi0 + P.osi * io) + (size_t)P.OH * (P.oj0 + P.osj * jo) +
+                           (size_t)OHW * (g * P.Kg + kl + (size_t)P.Ktot * n);
+                if (not_finite(*(volatile float *)o)) *o = plain_result(P, in, wsrc, bias, g, kl, io, jo, n);
+            }
+        }
+    };
+    auto store_tile = [&]() __attribute__((always_inline)) {
+        odd_results = false;
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int kl0 = c_kt * TK + (wk * MK + mk) * 32 + (v >> 2) * 8 + (v & 3);   // filter of the lower half-wave
+                const int left = P.Kg - kl0;
+                if (left <= 0) continue;
+                const unsigned soff = (unsigned)(c_g * P.Kg + kl0) * (unsigned)OHW * 4u;
+#pragma unroll
+                for (int mp = 0; mp < MP; ++mp) {
+                    const unsigned vo = (left > 4 || half == 0) ? ooff[mp] : SLAB_INVALID;   // the upper half-wave holds filter kl0 + 4
+                    float val = acc[mk][mp][v];
+                    const bool odd = not_finite(val);
+                    odd_results |= odd;
+                    if (P.relu) val = odd ? __uint_as_float(0x7fc00000u) : fmaxf(val, 0.f);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), ors, vo, soff, 0);
+                }
+            }
+        }
+    };
+    auto store_partial = [&](int slot) __attribute__((always_inline)) {
+        float *dst = part + (size_t)slot * (TK * TQ);
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int kloc = (wk * MK + mk) * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
+#pragma unroll
+                for (int mp = 0; mp < MP; ++mp)
+                    dst[kloc * TQ + (wp * MP + mp) * 32 + (lane & 31)] = acc[mk][mp][v];
+            }
+    };
+    // One segment = the units of one tile in a row.
+    int t = n_own ? vb * P.own : t_s, uu = n_own ? 0 : uu_s;
+    bool first_segment = true;
+    for (int done = 0; done < nunits;) {
+        const bool own = done < n_own;
+        const int left = nunits - done, m = NU - uu < left ? NU - uu : left;
+        // the segment covers its tile iff the tile is the block's own, or it starts at 0 and reaches the tile's end
+        const bool whole = m == NU;
+        set_tile(tile_of(t));
+        wo = (unsigned)(((c_g * P.KT + c_kt) * NU + uu) * T) * (unsigned)WSTEP;
+        fi = 0; so = 0; xo = xslab;
+        for (int u = 0; u < m; ++u) {
+            // This unit's slab and the next one's are in place.  The reads still in flight are of this unit's slab, which
+            // is written again two barriers later: nothing to wait for.
+            asm volatile("s_barrier" ::: "memory");
+            if (u == 0) { init_acc(whole && bias != nullptr); prime(); }
+            __builtin_amdgcn_sched_barrier(0);
+            for (int s = 1; s < T; ++s) {
+                wo += WSTEP;
+                next_tap();
+                step();
+            }
+            next_slab();
+            if (u + 1 < m) { wo += WSTEP; fi = 0; so = 0; xo = xslab; }
+            step();                                // the segment's last one reads its own operands again, for nothing
+        }
+        done += m;
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+            for (int mp = 0; mp < MP; ++mp) acc[mk][mp] += small[mk][mp];
+        if (whole) {
+            store_tile();
+            if (__any(odd_results)) repair_tile(tile_of(t));
+        } else {
+            store_partial(2 * vb + (first_segment ? 0 : 1));
+        }
+        first_segment = done == n_own;             // the shared range starts with a "first" segment again
+        if (own && done == n_own) { t = t_s; uu = uu_s; }
+        else { ++t; uu = 0; }
+    }
+}
+
+}  // namespace mcn

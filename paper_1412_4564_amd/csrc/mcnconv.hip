@@ -133,6 +133,9 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
     const bool pairs = d->precision != MCN_PREC_FP32_PLAIN;     // the row-pair kernels for 3x3 stride-1 layers
     auto plan_view = [&](const ConvView &v, IgemmPlan *pl) {
         if (bf && !v.mD && v.Cg >= BF_DC && plan_igemm(v, ncu, pl, true, true, planes)) return true;    // merged phases: fp32 kernel only
+        // fp32: the same sum on the bf16 matrix core, operands in three planes, where the row pairs do not apply
+        // (merged phases, fewer channels than one MFMA takes: fp32 kernel only)
+        if (d->precision == MCN_PREC_FP32 && split_pays(v) && plan_igemm(v, ncu, pl, true, true, 3)) return true;
         return plan_igemm(v, ncu, pl, false, pairs);
     };
     e.fwd_ok = on && plan_view(forward_view(g), &e.fwd);
@@ -185,7 +188,7 @@ int launch_igemm_inst(const IgemmPlan &pl, const float *in, const float *wpk, co
     // no tile is shared; tiles of a single unit cannot be cut, so every block's range holds whole tiles
     if (st || P.nblocks < 2 || P.own * P.nblocks == P.tiles || P.NU == 1) return st;
     constexpr int TK = WK * MK * 32, TQ = WP * MP * 32;
-    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out);
+    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, nullptr, nullptr);
     return check_launch();
 }
 
@@ -211,7 +214,7 @@ int launch_igemm_wino(const IgemmPlan &pl, const float *in, const float *wpk, co
     IgemmParams F = P;
     F.TI = 2 * P.TI; F.QN = 2 * P.QN; F.Ho = P.wino_Ho; F.osi = P.osi / 2;
     F.dTI = make_div32(F.TI);
-    hipLaunchKernelGGL((igemm_fixup_kernel<TK, 2 * TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, F, part, bias, out);
+    hipLaunchKernelGGL((igemm_fixup_kernel<TK, 2 * TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, F, part, bias, out, nullptr, nullptr);
     return check_launch();
 }
 
@@ -239,7 +242,27 @@ int launch_igemm_bf16_inst(const IgemmPlan &pl, const float *in, const float *wp
     // no tile is shared; tiles of a single unit cannot be cut, so every block's range holds whole tiles
     if (st || P.nblocks < 2 || P.own * P.nblocks == P.tiles || P.NU == 1) return st;
     constexpr int TK = WK * MK * 32, TQ = WP * MP * 32;
-    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out);
+    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, nullptr, nullptr);
+    return check_launch();
+}
+
+// fp32 operands in three bf16 planes (kern_igemm_split.h)
+template <int WK, int WP, int MK, int MP>
+int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, const float *bias, float *out,
+                       float *part, hipStream_t s, int relu, const float *w) {
+    IgemmParams P = pl.P;
+    P.relu = relu;
+    auto kern = igemm_split_kernel<WK, WP, MK, MP>;
+    if (pl.lds_bytes > 48 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)pl.lds_bytes);
+        if (e != hipSuccess) { g_last_hip_error = (int)e; return MCN_HIP_ERROR; }
+    }
+    hipLaunchKernelGGL(kern, dim3(P.nblocks), dim3(64 * (WK * WP + SPLIT_STAGE_WAVES)), pl.lds_bytes, s, P, in, wpk, bias, out, part, w);
+    int st = check_launch();
+    if (st || P.nblocks < 2 || P.own * P.nblocks == P.tiles || P.NU == 1) return st;      // no tile is shared
+    constexpr int TK = WK * MK * 32, TQ = WP * MP * 32;
+    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ, true>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, in, w);
     return check_launch();
 }
 
@@ -269,6 +292,15 @@ int launch_igemm(const IgemmPlan &pl, const float *in, const float *w, const flo
                            (unsigned *)packed, pl.Q);
         int st = check_launch();
         if (st) return st;
+        if (pl.planes == 3) {
+            switch (pl.shape) {
+                case IG_S64x256: return launch_igemm_split<2, 4, 1, 2>(pl, in, packed, bias, out, part, s, relu, w);
+                case IG_S128x128: return launch_igemm_split<4, 2, 1, 2>(pl, in, packed, bias, out, part, s, relu, w);
+                case IG_S128x64: return launch_igemm_split<4, 2, 1, 1>(pl, in, packed, bias, out, part, s, relu, w);
+                case IG_32x256: return launch_igemm_split<1, 8, 1, 1>(pl, in, packed, bias, out, part, s, relu, w);
+                default: return MCN_BAD_ARG;
+            }
+        }
         switch (pl.shape) {
             case IG_128x256: return launch_igemm_bf16_inst<2, 4, 2, 2>(pl, in, packed, bias, out, part, s, relu);
             case IG_64x512: return launch_igemm_bf16_inst<1, 8, 2, 2>(pl, in, packed, bias, out, part, s, relu);
@@ -619,7 +651,7 @@ int mcn_conv_workspace_size(const mcn_conv_desc *desc, int op, size_t *bytes) {
 }
 
 static const char *igemm_name(const IgemmPlan &pl) {
-    return pl.bf16 ? (pl.planes == 2 ? "igemm_bf16x3" : "igemm_bf16") : pl.P.wino_Ho ? "igemm_f23" : "igemm";
+    return pl.bf16 && pl.planes < 3 ? (pl.planes == 2 ? "igemm_bf16x3" : "igemm_bf16") : pl.P.wino_Ho ? "igemm_f23" : "igemm";
 }
 
 const char *mcn_conv_kernel_name(const mcn_conv_desc *desc, int op) {

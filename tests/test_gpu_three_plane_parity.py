@@ -1,0 +1,72 @@
+"""fp32 convolutions on the bf16 matrix core with operands in three bf16 planes (kern_igemm_split.h): every element
+against the oracle at the edges of tiles, units and channel groups, and the values that a split operand cannot carry."""
+import numpy as np
+import pytest
+import torch
+
+import parity_util as U
+from paper_1412_4564_amd import binding as B
+from paper_1412_4564_amd import synth
+from test_gpu_parity import custom_layer
+
+pytestmark = pytest.mark.gpu
+
+# The sum of n products in fp32 is off by at most n * 2^-24 of the sum of |w||x|, and by about sqrt(n) of that with random
+# signs; the largest n here is 16 * 25 = 400 channels x taps (6 MFMA roundings per 16 of them): 3e-6 leaves a factor 2 on
+# the random-sign figure 20 * 2^-24 = 1.2e-6.
+BOUND = 3e-6
+
+CASES = [  # H, W, D, N, Hf, Wf, Df, K, stride, pad
+    (12, 11, 16, 3, 5, 5, 16, 64, (1, 1), (2, 2, 2, 2)),      # one unit per tap range, tile of 64 filters
+    (11, 14, 40, 3, 5, 3, 40, 72, (1, 1), (2, 0, 1, 2)),      # channels ragged against 16, filters against 128
+    (9, 10, 17, 2, 2, 2, 17, 33, (1, 1), (0, 1, 1, 0)),       # one channel and one filter past a unit and a tile
+    (13, 12, 48, 4, 1, 2, 48, 130, (1, 1), (0, 0, 0, 0)),     # two taps
+    (20, 18, 64, 2, 3, 3, 32, 24, (2, 1), (1, 1, 1, 1)),      # two groups of 12 filters, vertical stride: phases of dzdx
+    (30, 30, 128, 6, 4, 4, 128, 200, (2, 2), (1, 1, 1, 1)),   # four phases, tiles shared between blocks
+    (27, 27, 96, 8, 5, 5, 48, 256, (1, 1), (2, 2, 2, 2)),     # two groups, 25 taps in several ranges
+    (7, 7, 32, 1, 7, 7, 32, 40, (1, 1), (3, 3, 3, 3)),        # one image, filter as large as the plane
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+@pytest.mark.parametrize("misalign", [0, 1])
+def test_every_element(case, misalign):
+    H, W, D, N, Hf, Wf, Df, K, st, pad = CASES[case]
+    L = custom_layer(H, W, D, N, Hf, Wf, Df, K, st, pad, idx=800 + case)
+    e = U.run_layer_full(L, with_bias=bool(case % 2), seed=case, misalign=misalign)
+    U.assert_errors(e, label="three planes %d" % case)
+    print("three planes, case", case, e, flush=True)
+    assert e["forward"] <= BOUND and e["backward_data"] <= BOUND, e
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("shape", [(9, 10, 20, 2, 48), (40, 40, 32, 16, 70)])      # shared tiles; whole tiles
+def test_values_that_are_not_finite_or_nearly_so(relu, shape):
+    """An infinite operand gives +-inf (or NaN) where the plain sum does, one near the largest float stays finite."""
+    H, W, D, N, K = shape
+    L = custom_layer(H, W, D, N, 5, 5, D, K, (1, 1), (2, 2, 2, 2), idx=830)
+    x, w, b = synth.make_x(L), synth.make_w(L), synth.make_b(L)
+    x[0, 3, 4, 5], x[1, 7, 2, 2], x[N - 1, 0, W - 1, H - 1], x[1, 1, 7, 7] = float("inf"), float("-inf"), float("nan"), 3.4e38
+    w[:, 1] *= 1e-4
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), b.double(), padding=2)
+    xg, wg, bg = x.cuda(), w.cuda(), b.cuda()
+    y = (B.conv_relu_forward if relu else B.conv_forward)(xg, wg, bg, (1, 1), (2, 2, 2, 2)).cpu()
+    if relu:
+        ref = torch.where(torch.isnan(ref), torch.zeros_like(ref), ref.clamp(min=0))       # fmax(NaN, 0) = 0, as in the other kernels
+    assert torch.equal(torch.isnan(y), torch.isnan(ref)) and torch.equal(torch.isinf(y), torch.isinf(ref))
+    inf = torch.isinf(ref)
+    assert int(inf.sum()) > 0 and torch.equal(y[inf].double(), ref[inf])
+    ok = torch.isfinite(ref)
+    den = torch.nn.functional.conv2d(torch.nan_to_num(x, 0, 0, 0).double().abs(), w.double().abs(), b.double().abs(), padding=2)
+    assert float(((y.double() - ref)[ok].abs() / den[ok]).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("scale", [1e30, 1e-20, 1e-30])
+def test_scales(scale):
+    """Powers of the fp32 range that a plane of half the width would lose: the error does not depend on the scale."""
+    L = custom_layer(14, 13, 32, 2, 5, 5, 32, 64, (1, 1), (2, 2, 2, 2), idx=840)
+    x, w = synth.make_x(L) * scale, synth.make_w(L)
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), padding=2)
+    den = torch.nn.functional.conv2d(x.double().abs(), w.double().abs(), padding=2)
+    y = B.conv_forward(x.cuda(), w.cuda(), None, (1, 1), (2, 2, 2, 2)).cpu().double()
+    assert float(((y - ref).abs() / den).max()) <= BOUND

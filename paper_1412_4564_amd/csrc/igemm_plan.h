@@ -237,9 +237,9 @@ constexpr int SPLIT_N_SHAPES = 4;
 // traffic.  Either every block gets the same number of units (left-over tiles shared, fix-up pass), or whole tiles only
 // (up to a handful shared, so that the number of blocks stays a multiple of 8).
 struct SplitSchedule { int nblocks, own; double us; };
-inline SplitSchedule split_schedule(int64_t tiles, int NU, int NS, int64_t slab_bytes, const SplitShape &S, int n_cu) {
+inline SplitSchedule split_schedule(int64_t tiles, int NU, int NS, int64_t slab_bytes, const SplitShape &S, int n_cu, int rows) {
     const double ghz = 2.2;
-    const int TK = S.WK * S.MK * 32, TQ = S.WP * S.MP * 32, waves = S.WK * S.WP;
+    const int TK = S.WK * S.MK * 32, TQ = S.WP * S.MP * 32 * rows, waves = S.WK * S.WP;      // TQ: results per filter
     const double mfma = S.MK * S.MP * 6 * 32.0 * waves / 4, lds = waves * 3072.0 * S.MP / 128, l1 = waves * 3072.0 * S.MK / 64;
     double step = mfma;
     if (step < 1.2 * lds) step = 1.2 * lds;
@@ -268,7 +268,7 @@ inline SplitSchedule split_schedule(int64_t tiles, int NU, int NS, int64_t slab_
 inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf16, int fixed, bool two = false,
                             int wino_Ho = 0, int planes = 1, int split = 0) {
     const int T = v.Hf * v.Wf;
-    const bool wino = wino_Ho > 0;
+    const bool wino = wino_Ho > 0, f23s = wino && planes == 3;
     const IgemmFixed FX = wino ? IGEMM_WINO : IGEMM_FIXED[fixed];
     int shape, WK, WP, MK, MP;
     // `two`: blocks of four waves, two of them resident per compute unit (half the LDS each): while one is
@@ -302,7 +302,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     for (int a = 0; a < nc; ++a) {
         const int TI = cand[a];
         if (TI < 1 || TI > v.Ho) continue;
-        const int64_t SR = (int64_t)(TI - 1) * v.Sh + v.Hf;
+        const int64_t SR = f23s ? TI : (int64_t)(TI - 1) * v.Sh + v.Hf;     // row combinations: one slab sample per pair
         if (SR > 8192) continue;
         if ((int64_t)TI * v.Wo * v.N >= ((int64_t)1 << 30)) continue;
         const int SC = slab_columns(v, TI, TQ, Wp);
@@ -315,7 +315,10 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         const int EPT = (int)((CP + NL - 1) / NL);
         const size_t fixed_lds = ((planes == 3 ? 0 : (size_t)EPT * NL) + (planes == 3 ? SPLIT_BIASES : 2) * TK + 4) * 4;
         UnitCut uc;
-        if (bf16) {
+        if (f23s) {
+            uc.pair_mode = 0; uc.DC = BF_DC; uc.TC = 3; uc.NTR = 1; uc.NS = 3;
+            if (fixed_lds + 64 + SPLIT_SLABS * 6 * (size_t)CP * 16 > lds_limit) continue;
+        } else if (bf16) {
             if (fixed_lds + 64 > lds_limit) continue;
             if (!cut_units_bf16(v, TK, CP, lds_limit - fixed_lds - 64, &uc, planes)) continue;
         } else if (fixed || wino) {
@@ -333,7 +336,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         // rows of pixel tiles and of filter tiles that compute nothing
         const double mfma_waste = (double)RB * PT * TQ / ((double)v.Ho * v.Wo * v.N) *
                                   (double)((v.Kg + TK - 1) / TK * TK) / (double)v.Kg;
-        const int NCG = (v.Cg + uc.DC - 1) / uc.DC;
+        const int NCG = (v.Cg + uc.DC - 1) / uc.DC * (f23s ? 4 : 1);
         const double red_waste = (double)NCG * uc.NTR * uc.NS * (bf16 ? BF_DC : 2) / ((double)v.Cg * T);
         // when the input streams from memory, short slab rows waste most of every 128-byte line they touch
         // results are stored in column runs of TI samples: short runs are partial memory lines
@@ -345,9 +348,9 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         // 4b with two 0.378 against 0.40 with three)
         if (bf16) score *= 1.0 + 0.5 * (uc.NTR - 1);
         if (planes == 3)     // microseconds; short slab rows and short column runs of results as above
-            score = split_schedule((int64_t)v.G * RB * PT * ((v.Kg + TK - 1) / TK), NCG * uc.NTR, uc.NS, CP * 64 / uc.NTR, SS, n_cu).us *
+            score = split_schedule((int64_t)v.G * RB * PT * ((v.Kg + TK - 1) / TK), NCG * uc.NTR, uc.NS, CP * (f23s ? 128 : 64), SS, n_cu, f23s ? 2 : 1).us *
                     (input_streams ? 1.0 + 1.0 / (double)SR : 1.0) * (1.0 + 0.5 / (double)TI);
-        if (wino) {
+        if (wino && !f23s) {
             // The row-pair kernels issue fewer MFMAs per staged byte and per stored line, and what was measured on
             // them weighs differently: short slab rows cost little, column runs of results (2*TI samples) that are
             // whole 128-byte lines are worth some 5 % (layer 4a: 32-row runs 0.74 ms, 112-row runs 0.78, 28-row 0.80).
@@ -367,14 +370,14 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     P.Hf = v.Hf; P.Wf = v.Wf; P.Sh = v.Sh; P.Sw = v.Sw; P.Pt = v.Pt; P.Pl = v.Pl;
     P.TI = bestTI; P.RB = (v.Ho + bestTI - 1) / bestTI;
     P.Wp = Wp;
-    P.SR = (bestTI - 1) * v.Sh + v.Hf; P.SRP = P.SR;
+    P.SR = f23s ? bestTI : (bestTI - 1) * v.Sh + v.Hf; P.SRP = P.SR;
     P.CP = (P.SRP * bestSC + 63) / 64 * 64;
     P.EPT = (P.CP + NL - 1) / NL;
     P.KT = (v.Kg + TK - 1) / TK;
     P.QN = bestTI * v.Wo * v.N;
     P.PT = (P.QN + TQ - 1) / TQ;
     P.DC = best_uc.DC; P.TC = best_uc.TC; P.NTR = best_uc.NTR; P.NS = best_uc.NS; P.pair_mode = best_uc.pair_mode;
-    P.NU = ((v.Cg + P.DC - 1) / P.DC) * P.NTR;
+    P.NU = ((v.Cg + P.DC - 1) / P.DC) * P.NTR * (f23s ? 4 : 1);
     const int64_t tiles = (int64_t)v.G * P.RB * P.PT * P.KT;
     if (tiles >= ((int64_t)1 << 30)) return false;
     P.tiles = (int)tiles;
@@ -384,7 +387,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     // the workspace and the fix-up pass than when everything is shared
     P.own = (int)(tiles / P.nblocks);
     if (planes == 3) {
-        const SplitSchedule sc = split_schedule(tiles, P.NU, P.NS, (int64_t)P.CP * 64 / P.NTR, SS, n_cu);
+        const SplitSchedule sc = split_schedule(tiles, P.NU, P.NS, (int64_t)P.CP * (f23s ? 128 : 64), SS, n_cu, f23s ? 2 : 1);
         P.nblocks = sc.nblocks;
         P.own = sc.own;
     } else if (!bf16 && 2 * tiles >= resident && tiles < resident) {
@@ -413,7 +416,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         if (v.pack_mode == 0) {
             P.wo = 0; P.wg = area * v.DfA * v.Kg; P.wk = area * v.DfA; P.wc = area; P.wi = 1; P.wj = v.HfA;
         } else if (v.pack_mode == 1) {
-            P.wo = v.pi + v.pSh * (v.Hf - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
+            P.wo = v.pi + v.pSh * ((wino ? 3 : v.Hf) - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
             P.wg = area * v.DfA * v.Cg; P.wk = area; P.wc = area * v.DfA; P.wi = -v.pSh; P.wj = -v.HfA * v.pSw;
         } else if (planes == 3) {
             return false;       // the fully-connected and merged-phase views stay on the fp32 kernels
@@ -473,13 +476,20 @@ inline bool wino_enabled() {
     return !off;
 }
 
-// Whether an fp32 view takes the three-plane kernel (kern_igemm_split.h).  Not the views of row pairs, and not 1x1 filters: a
+// Whether an fp32 view takes the three-plane kernel (kern_igemm_split.h).  Not 1x1 filters: a
 // unit is then one step (768 cycles of MFMAs), and its staging (loads, split, barrier) takes longer (28x28x512, 1x1x512x128,
 // 64 images: forward 93 us against 78 on the fp32 kernel).
 inline bool split_pays(const ConvView &v) {
-    ConvView pv;
-    if (v.mD || v.pack_mode > 1 || v.Cg < BF_DC || v.Hf * v.Wf < 2) return false;
-    return !(wino_enabled() && wino_view(v, &pv));
+    return !v.mD && v.pack_mode <= 1 && v.Cg >= BF_DC && v.Hf * v.Wf >= 2;
+}
+
+// Row pairs in three planes (kern_igemm_split.h, F23): deep layers whose plane and batch give at most half as many tiles of
+// 128 filters x 128 pairs as there are compute units.  Measured against the fp32 row-pair kernel (forward): 14x14, 512 -> 512 channels,
+// 32 images (98 tiles) 190 -> 152 us, one image 57 -> 41 us, 256 -> 256, 8 images 47 -> 40 us; 28x28, 256 -> 512, 32 images
+// (392 tiles) 319 -> 340 us, 512 -> 256 (196 tiles) 315 -> 343 us; under 256 channels no gain (28x28, 128 -> 128, 2 images 33 us both).
+inline bool split_pairs_pay(const ConvView &pv, int n_cu) {
+    const int64_t tiles = (((int64_t)pv.Ho * pv.Wo * pv.N + 127) / 128) * ((pv.Kg + 127) / 128) * pv.G;
+    return pv.Cg >= 256 && pv.Kg > 64 && 2 * tiles <= n_cu;
 }
 
 // The instantiation with this view's filter size if there is one, its channels divide into the
@@ -490,11 +500,15 @@ inline bool split_pays(const ConvView &v) {
 inline bool plan_igemm(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf16 = false, bool row_pairs = true, int planes = 1) {
     if (bf16 && planes == 3) {
         bool ok = false;
+        ConvView pv;
+        const bool pairs = wino_enabled() && wino_view(v, &pv);
+        if (pairs && !split_pairs_pay(pv, n_cu)) return false;
         for (int f = 0; f < SPLIT_N_SHAPES; ++f) {
             const int TK = SPLIT_SHAPES[f].WK * SPLIT_SHAPES[f].MK * 32;
             if (TK == 32 ? v.Kg > 32 : v.Kg <= TK / 2) continue;      // half of the tile would be empty
+            if (pairs && TK != 128) continue;
             IgemmPlan one;
-            if (plan_igemm_kind(v, n_cu, &one, true, 0, false, 0, 3, f) && (!ok || one.score < pl->score)) { *pl = one; ok = true; }
+            if (plan_igemm_kind(pairs ? pv : v, n_cu, &one, true, 0, false, pairs ? v.Ho : 0, 3, f) && (!ok || one.score < pl->score)) { *pl = one; ok = true; }
         }
         return ok;
     }

@@ -159,8 +159,8 @@ struct IgemmParams {
 __device__ inline bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
 
 // One result of the view, summed as Sec. 4.1 writes it: what the results that are not finite are taken from.  w: the
-// caller's filter array.
-__device__ inline float plain_result(const IgemmParams &P, const float *in, const float *w, const float *bias, int g,
+// caller's filter array.  Hf, Sh: the view's own (those of P describe pairs of rows in a view of row pairs).
+__device__ inline float plain_result(const IgemmParams &P, int Hf, int Sh, const float *in, const float *w, const float *bias, int g,
                                                         int kl, int io, int jo, int n) {
     float s = bias ? bias[g * P.Kg + kl] : 0.f;
     for (int c = 0; c < P.Cg; ++c) {
@@ -168,8 +168,8 @@ __device__ inline float plain_result(const IgemmParams &P, const float *in, cons
         for (int tj = 0; tj < P.Wf; ++tj) {
             const int j = P.Sw * jo + tj - P.Pl;
             if (j < 0 || j >= P.W) continue;
-            for (int ti = 0; ti < P.Hf; ++ti) {
-                const int i = P.Sh * io + ti - P.Pt;
+            for (int ti = 0; ti < Hf; ++ti) {
+                const int i = Sh * io + ti - P.Pt;
                 if (i < 0 || i >= P.H) continue;
                 const long long wx = P.wo + (long long)g * P.wg + (long long)kl * P.wk + (long long)c * P.wc + ti * P.wi + tj * P.wj;
                 s = fmaf(w[wx], xc[i + (size_t)P.H * j], s);
@@ -958,7 +958,7 @@ __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const f
             const int oi = P.oi0 + P.osi * io + fi0, oj = P.oj0 + P.osj * jo + fj0;
             if (P.mD && (oi >= P.OH || oj >= P.OW)) continue;
             float v = vv[j];
-            if (REPAIR && not_finite(v)) v = plain_result(P, in, w, bias, g, kl, io, jo, n);      // see kern_igemm_split.h
+            if (REPAIR && not_finite(v)) v = plain_result(P, P.Hf, P.Sh, in, w, bias, g, kl, io, jo, n);      // see kern_igemm_split.h
             else if (P.relu) v = fmaxf(v, 0.f);
             out[(size_t)(oi + P.OH * (oj + P.OW * (P.Ktot * n))) + (size_t)OHW * och] = v;
         }

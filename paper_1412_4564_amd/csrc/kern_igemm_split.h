@@ -25,6 +25,17 @@
 //    operands and no wave starts a unit with empty registers.
 //  * every plane has one set of registers, read anew for the next step as soon as its last product is issued; the order
 //    of the products leaves 12 MFMAs (weights) or 8 (pixels) between that and the next use.
+//
+// Row pairs (template flag F23): 3x3 filters at stride 1 through the identity F(2,3) of kern_igemm.h, two thirds of the
+// MFMAs.  A "pixel" is a pair of output rows.  Each of the four sums m0..m3 is a convolution of its own with a filter of
+// three columns and one row, of a row combination of the input (d0-d2, d1+d2, d2-d1, d1-d3, formed in fp32 before the
+// split) with a row combination of the weights, so the waves compute them one after the other with one set of
+// accumulators, and add each unit's to the pair's two rows (y0 += m0 + m1 + m2, y1 += m1 - m2 - m3): the sums that the
+// MFMAs round are short.  A unit is 16 channels of one combination, the four of a group follow one another.
+// It takes fewer MFMAs than the other kernel and more staging (two loads per pair, combination and column for three taps,
+// against one per pixel for nine), and that bounds it on all but planes too small to fill the chip's tiles, where the
+// split of the reduction counts: 14x14x512, 3x3x512x512: 32 images 190 -> 152 us, one image 57 -> 41 us against the fp32
+// row-pair kernel, but 56x56x256, 32 images 596 -> 663 us, 224x224x64 663 -> 822 us (split_pairs_pay in igemm_plan.h).
 #pragma once
 #include "kern_igemm_bf16.h"
 
@@ -35,8 +46,43 @@ constexpr int SPLIT_BIASES = 4;        // bias buffers: a bias is written at mos
 constexpr int SPLIT_STAGE_WAVES = 4;   // waves that fetch and split the input
 constexpr int SPLIT_EPT_MAX = 2;       // slab samples a thread stages per unit, at most (16 registers each)
 
+// Weights for F23: [g][kt][unit][filter column][plane][octet][kk][8 channels]; a thread reads the three rows of one filter
+// column for two channels and writes all planes of their four combinations.
+__global__ __launch_bounds__(256) void igemm_pack_f23_split_kernel(const float *__restrict__ w, unsigned *__restrict__ packed, PackParams Q) {
+    const int NCG = Q.NU / 4;
+    int p = blockIdx.x * 256 + threadIdx.x;
+    const int j2 = p & 3; p >>= 2;
+    const int kk = p % Q.TK; p /= Q.TK;
+    const int oct = p & 1; p >>= 1;
+    const int fj = p % 3; p /= 3;
+    const int cg = p % NCG; p /= NCG;
+    const int kt = p % Q.KT;
+    const int g = p / Q.KT;
+    if (g >= Q.G) return;
+    const int k = kt * Q.TK + kk;
+    float v[2][4] = {};
+    for (int e = 0; e < 2; ++e) {
+        const int c = cg * BF_DC + oct * 8 + 2 * j2 + e;
+        if (k >= Q.Kg || c >= Q.Cg) continue;
+        const float *src = Q.mode == 0 ? w + 3 * (fj + 3 * (c + (size_t)Q.DfA * (g * Q.Kg + k)))
+                                       : w + 3 * ((2 - fj) + 3 * (k + (size_t)Q.DfA * (g * Q.Cg + c)));
+        const float g0 = Q.mode == 0 ? src[0] : src[2], g1 = src[1], g2 = Q.mode == 0 ? src[2] : src[0];   // dzdx: the flipped filter
+        v[e][0] = g0;
+        v[e][1] = 0.5f * (g0 + g1 + g2);
+        v[e][2] = 0.5f * (g0 - g1 + g2);
+        v[e][3] = g2;
+    }
+    for (int combo = 0; combo < 4; ++combo) {
+        const int uu = 4 * cg + combo;
+        unsigned *dst = packed + ((size_t)(g * Q.KT + kt) * Q.NU + uu) * Q.WSZ + (fj * 6 + oct) * Q.TK * 4 + kk * 4 + j2;
+        unsigned hi, mid, lo;
+        split_bf16x3(v[0][combo], v[1][combo], &hi, &mid, &lo);
+        dst[0] = hi; dst[2 * Q.TK * 4] = mid; dst[4 * Q.TK * 4] = lo;
+    }
+}
+
 // WK x WP computing waves; each owns MK x MP tiles of 32 filters x 32 pixels.  wsrc: the caller's filter array.
-template <int WK, int WP, int MK, int MP>
+template <int WK, int WP, int MK, int MP, bool F23>
 __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 3 : 2) void igemm_split_kernel(
     IgemmParams P, const float *__restrict__ in, const float *__restrict__ wpk, const float *__restrict__ bias, float *out,
     float *__restrict__ part, const float *__restrict__ wsrc) {
@@ -44,6 +90,8 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     constexpr int NL = 64 * SPLIT_STAGE_WAVES;     // staging threads
     constexpr int TK = WK * MK * 32;
     constexpr int TQ = WP * MP * 32;
+    constexpr int ROWS = F23 ? 2 : 1;              // input rows of a slab sample; output rows of a pixel
+    constexpr int SETS = F23 ? 2 : 3;
     const int NU = P.NU;
     const int CP = P.CP, SRP = P.SRP;
     const int XSZ = 3 * 2 * CP * 4;      // 32-bit words of slab per buffer: 3 planes x 2 octets x CP samples x 16 bytes
@@ -62,9 +110,12 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     // ---- the block's range of units (see igemm_sk_kernel) ---------------------------------
     const int vb = sk_virtual_block(blockIdx.x, P.nblocks);
     const int tile_s0 = P.own * P.nblocks;                          // first shared tile
-    const long long total = (long long)(P.tiles - tile_s0) * NU;    // units of the shared tiles
+    // units of the shared tiles; F23: cut between channel groups, whose four combinations then meet in one piece (a piece
+    // of fewer holds sums that the other pieces cancel, and rounds them)
+    constexpr int CUT = F23 ? 4 : 1;
+    const long long total = (long long)(P.tiles - tile_s0) * (NU / CUT);
     const int rank = sk_share_rank(P.nblocks, P.nshare, vb);
-    const long long ub = rank < 0 ? 0 : sk_begin(total, P.nshare, rank), ue = rank < 0 ? 0 : sk_begin(total, P.nshare, rank + 1);
+    const long long ub = rank < 0 ? 0 : CUT * sk_begin(total, P.nshare, rank), ue = rank < 0 ? 0 : CUT * sk_begin(total, P.nshare, rank + 1);
     const int n_own = P.own * NU;                                    // units of this block's own tiles
     const int nunits = n_own + (int)(ue - ub);
     if (nunits == 0) return;
@@ -78,18 +129,18 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
 
     if (wave >= WK * WP) {
         // ---- the waves that fetch the input and split it ----------------------------------
-        // The samples of three units are on their way at a time, in three sets of registers: a unit of few taps is
+        // The samples of three (F23: two) units are on their way at a time, in as many sets of registers: a unit of few taps is
         // computed in less time than a sample takes from memory.  What a unit does not have is requested
         // out of range and reads as zero: no divergent branches, so that the waits for a set leave younger ones in flight.
         struct Samples {
-            float v[SPLIT_EPT_MAX][BF_DC];
-            int uu, kt, g, seq;
+            float v[SPLIT_EPT_MAX][ROWS][BF_DC];
+            int uu, kt, g, seq, combo;
         };
-        Samples set[3];
+        Samples set[SETS];
         const int ltid = tid - NT, lwave = wave - WK * WP;
         int t = n_own ? vb * P.own : t_s, uu = n_own ? 0 : uu_s, n = 0;      // next unit to request, units before it
         int kt = 0, g = 0, seq = -1;
-        unsigned go[SPLIT_EPT_MAX];                 // byte offset of the thread's samples in channel 0, or SLAB_INVALID
+        unsigned go[SPLIT_EPT_MAX][F23 ? 4 : 1];    // byte offset of the thread's samples in channel 0, or SLAB_INVALID; F23: of the pair's four rows
         __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void *)in, 0, 0, BUFFER_FLAGS);
         auto set_tile = [&](int tile) __attribute__((always_inline)) {
             ++seq;
@@ -112,22 +163,32 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                 const int U = u0 + col;
                 const int ni = div32(U, P.dWp);          // image relative to n_first
                 const int j = U - ni * P.Wp - P.Pl;
-                const int i = row0 + r;
-                const bool ok = e < CP && r < P.SR && i >= 0 && i < P.H && j >= 0 && j < P.W && (n_first + ni) < P.N;
-                go[s] = ok ? 4u * (unsigned)(i + P.H * j + ni * P.Ctot * HW) : SLAB_INVALID;
+                const int i0 = row0 + (F23 ? 2 * r : r);
+                const bool ok = e < CP && r < P.SR && j >= 0 && j < P.W && (n_first + ni) < P.N;
+#pragma unroll
+                for (int a = 0; a < (F23 ? 4 : 1); ++a)
+                    go[s][a] = ok && i0 + a >= 0 && i0 + a < P.H ? 4u * (unsigned)(i0 + a + P.H * j + ni * P.Ctot * HW) : SLAB_INVALID;
             }
         };
         auto request = [&](Samples &q) __attribute__((always_inline)) {
-            const int c0 = uu * BF_DC, c_end = n < nunits ? P.Cg : 0;
-            q.uu = uu; q.kt = kt; q.g = g; q.seq = seq;
+            const int combo = uu & 3, c0 = (F23 ? uu >> 2 : uu) * BF_DC, c_end = n < nunits ? P.Cg : 0;
+            q.uu = uu; q.kt = kt; q.g = g; q.seq = seq; q.combo = combo;
 #pragma unroll
             for (int s = 0; s < SPLIT_EPT_MAX; ++s) {
                 if (s * NL >= CP) continue;
 #pragma unroll
-                for (int d = 0; d < BF_DC; ++d)
-                    // channels past the group's last one read as zero (their weights are zero too)
-                    q.v[s][d] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                        xrs, c0 + d < c_end ? go[s] : SLAB_INVALID, (unsigned)(c0 + d) * (unsigned)HW * 4u, 0));
+                for (int a = 0; a < ROWS; ++a) {
+                    unsigned off = go[s][0];
+                    if constexpr (F23) {           // d0-d2, d1+d2, d2-d1, d1-d3
+                        if (a == 0) off = combo == 0 ? go[s][0] : combo == 2 ? go[s][2] : go[s][1];
+                        else off = combo == 3 ? go[s][3] : combo == 2 ? go[s][1] : go[s][2];
+                    }
+#pragma unroll
+                    for (int d = 0; d < BF_DC; ++d)
+                        // channels past the group's last one read as zero (their weights are zero too)
+                        q.v[s][a][d] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                            xrs, c0 + d < c_end ? off : SLAB_INVALID, (unsigned)(c0 + d) * (unsigned)HW * 4u, 0));
+                }
             }
             // on to the next unit
             ++n;
@@ -148,12 +209,17 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             for (int s = 0; s < SPLIT_EPT_MAX; ++s) {
                 const int e = ltid + NL * s;
                 if (lwave * 64 + NL * s >= CP) continue;         // CP is a multiple of 64
+                if constexpr (F23) {
+                    const float sign = q.combo == 1 ? 1.f : -1.f;
+#pragma unroll
+                    for (int d = 0; d < BF_DC; ++d) q.v[s][0][d] = fmaf(sign, q.v[s][1][d], q.v[s][0][d]);
+                }
 #pragma unroll
                 for (int o = 0; o < 2; ++o) {
                     unsigned hi[4], mid[4], lo[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        split_bf16x3(q.v[s][8 * o + 2 * j], q.v[s][8 * o + 2 * j + 1], &hi[j], &mid[j], &lo[j]);
+                        split_bf16x3(q.v[s][0][8 * o + 2 * j], q.v[s][0][8 * o + 2 * j + 1], &hi[j], &mid[j], &lo[j]);
                     const uintx4 h = {hi[0], hi[1], hi[2], hi[3]}, m = {mid[0], mid[1], mid[2], mid[3]}, l = {lo[0], lo[1], lo[2], lo[3]};
                     *reinterpret_cast<uintx4 *>(xb + (size_t)((0 + o) * CP + e) * 4) = h;
                     *reinterpret_cast<uintx4 *>(xb + (size_t)((2 + o) * CP + e) * 4) = m;
@@ -163,10 +229,10 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         };
         set_tile(tile_of(t));
 #pragma unroll
-        for (int j = 0; j < 3; ++j) request(set[j]);
-        for (int it = -2; it < nunits; it += 3) {    // unit it + 2 is written after the barrier of unit it
+        for (int j = 0; j < SETS; ++j) request(set[j]);
+        for (int it = -2; it < nunits; it += SETS) {    // unit it + 2 is written after the barrier of unit it
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
+            for (int j = 0; j < SETS; ++j) {
                 if (it + j >= 0 && it + j < nunits) lds_barrier();
                 if (it + j + 2 < nunits) {
                     write(set[j]);
@@ -181,9 +247,12 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     const int wk = wave % WK, wp = wave / WK;
     int bbase[MP];       // slab byte offset of the pixel's window origin, octet of this half-wave
     unsigned ooff[MP];   // byte offset of the lane's first result relative to the tile's output window, or SLAB_INVALID
+    unsigned ooff1[MP];  // F23: the same for the second row of the pair
     __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc((void *)out, 0, 0, BUFFER_FLAGS);
     int c_kt = 0, c_g = 0, c_seq = -1;
-    floatx16 acc[MK][MP], small[MK][MP];            // sums of the hi x hi products, and of the five others
+    // F23 = false: sums of the hi x hi products, and of the five others; F23: the current combination's sum, and the rows'
+    floatx16 acc[MK][MP], small[MK][MP], row1[F23 ? MK : 1][MP];
+    floatx16 (&row0)[MK][MP] = small;
     auto set_tile = [&](int t) __attribute__((always_inline)) {
         ++c_seq;
         int kt, pt, rb, g;
@@ -204,11 +273,14 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             const int io = rb * P.TI + ii;
             const bool ok = q < qend && io < P.Ho;
             const int ucol = jo * P.Sw + (n - n_first) * P.Wp - u0;
-            bbase[mp] = 16 * ((ok ? ii * P.Sh + SRP * ucol : 0) + half * CP);
+            bbase[mp] = 16 * ((ok ? ii * (F23 ? 1 : P.Sh) + SRP * ucol : 0) + half * CP);
             ooff[mp] = ok ? 4u * (unsigned)((P.oi0 + P.osi * io) + P.OH * (P.oj0 + P.osj * jo) +
                                             OHW * (P.Ktot * (n - n_first) + 4 * half))
                           : SLAB_INVALID;
+            if constexpr (F23)
+                ooff1[mp] = ok && 2 * io + 1 < P.wino_Ho ? ooff[mp] + 4u * (unsigned)(P.osi >> 1) : SLAB_INVALID;
         }
+        (void)ooff1;
         const size_t out_base = (size_t)n_first * P.Ktot * OHW;
         size_t out_left = ((size_t)P.N * P.Ktot * OHW - out_base) * 4;
         if (out_left > 0x7fffffffull) out_left = 0x7fffffffull;
@@ -223,11 +295,28 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                 const int kloc = (wk * MK + mk) * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
                 const float bv = with_bias ? bl[kloc] : 0.f;
 #pragma unroll
-                for (int mp = 0; mp < MP; ++mp) { acc[mk][mp][v] = bv; small[mk][mp][v] = 0.f; }
+                for (int mp = 0; mp < MP; ++mp) {
+                    if constexpr (F23) { acc[mk][mp][v] = 0.f; row0[mk][mp][v] = bv; row1[mk][mp][v] = bv; }
+                    else { acc[mk][mp][v] = bv; small[mk][mp][v] = 0.f; }
+                }
             }
     };
+    // F23: the finished sum of a run of units goes to the two rows
+    auto fold = [&](int combo) __attribute__((always_inline)) {
+        const float s0 = combo < 3 ? 1.f : 0.f, s1 = combo == 0 ? 0.f : combo == 1 ? 1.f : -1.f;
+#pragma unroll
+        for (int mk = 0; mk < (F23 ? MK : 0); ++mk)
+#pragma unroll
+            for (int mp = 0; mp < MP; ++mp)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    row0[mk][mp][v] = fmaf(s0, acc[mk][mp][v], row0[mk][mp][v]);
+                    row1[mk][mp][v] = fmaf(s1, acc[mk][mp][v], row1[mk][mp][v]);
+                    acc[mk][mp][v] = 0.f;
+                }
+    };
     const int aoff = 16 * (half * TK + wk * MK * 32 + (lane & 31));   // bytes
-    const int T = P.Hf * P.Wf;
+    const int T = F23 ? 3 : P.Hf * P.Wf;
     const int xplane = 2 * CP * 16;                  // bytes from a slab plane to the next
     // where the next operands are read: weights of the step (steps follow one another in memory through all units of a
     // tile), slab and offset of its tap.  All scalar but the two lane offsets.
@@ -238,9 +327,13 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     const int xbytes = 4 * XSZ;
     const char *const xlane = reinterpret_cast<const char *>(xbuf);
     auto next_tap = [&]() __attribute__((always_inline)) {
-        const bool wrap = ++fi == P.Hf;
-        so += wrap ? 16 * (SRP - P.Hf + 1) : 16;
-        if (wrap) fi = 0;
+        if constexpr (F23) {
+            so += 16 * SRP;
+        } else {
+            const bool wrap = ++fi == P.Hf;
+            so += wrap ? 16 * (SRP - P.Hf + 1) : 16;
+            if (wrap) fi = 0;
+        }
     };
     auto next_slab = [&]() __attribute__((always_inline)) {
         xslab = xslab + xbytes == SPLIT_SLABS * xbytes ? 0 : xslab + xbytes;
@@ -268,18 +361,19 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     auto prime = [&]() __attribute__((always_inline)) {
         load_a(ah, 0); load_b(bl, 2); load_b(bm, 1); load_b(bh, 0); load_a(am, 1); load_a(al, 2);
     };
+    floatx16 (&lesser)[MK][MP] = F23 ? acc : small;
     // one step; wo, xo, so are the next step's when it begins
     auto step = [&]() __attribute__((always_inline)) {
-        mma(small, ah, bl);
+        mma(lesser, ah, bl);
         load_b(bl, 2);
-        mma(small, ah, bm);
+        mma(lesser, ah, bm);
         mma(acc, ah, bh);
         load_a(ah, 0);
-        mma(small, am, bm);
+        mma(lesser, am, bm);
         load_b(bm, 1);
-        mma(small, am, bh);
+        mma(lesser, am, bh);
         load_a(am, 1);
-        mma(small, al, bh);
+        mma(lesser, al, bh);
         load_b(bh, 0);
         load_a(al, 2);
         __builtin_amdgcn_sched_barrier(0);
@@ -305,9 +399,14 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             for (int v = 0; v < MK * 16; ++v) {
                 const int kl = kt * TK + (wk * MK + (v >> 4)) * 32 + ((v & 15) >> 2) * 8 + half * 4 + (v & 3);
                 if (kl >= P.Kg) continue;
-                float *o = out + (size_t)(P.oi0 + P.osi * io) + (size_t)P.OH * (P.oj0 + P.osj * jo) +
-                           (size_t)OHW * (g * P.Kg + kl + (size_t)P.Ktot * n);
-                if (not_finite(*(volatile float *)o)) *o = plain_result(P, in, wsrc, bias, g, kl, io, jo, n);
+                for (int row = 0; row < ROWS; ++row) {
+                    const int ior = ROWS * io + row;           // row of the view
+                    if (F23 && ior >= P.wino_Ho) continue;
+                    float *o = out + (size_t)(P.oi0 + P.osi / ROWS * ior) + (size_t)P.OH * (P.oj0 + P.osj * jo) +
+                               (size_t)OHW * (g * P.Kg + kl + (size_t)P.Ktot * n);
+                    if (not_finite(*(volatile float *)o))
+                        *o = plain_result(P, F23 ? 3 : P.Hf, F23 ? 1 : P.Sh, in, wsrc, bias, g, kl, ior, jo, n);
+                }
             }
         }
     };
@@ -324,25 +423,47 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
 #pragma unroll
                 for (int mp = 0; mp < MP; ++mp) {
                     const unsigned vo = (left > 4 || half == 0) ? ooff[mp] : SLAB_INVALID;   // the upper half-wave holds filter kl0 + 4
-                    float val = acc[mk][mp][v];
-                    const bool odd = not_finite(val);
-                    odd_results |= odd;
-                    if (P.relu) val = odd ? __uint_as_float(0x7fc00000u) : fmaxf(val, 0.f);
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), ors, vo, soff, 0);
+                    auto finish = [&](float val) __attribute__((always_inline)) {
+                        const bool odd = not_finite(val);
+                        odd_results |= odd;
+                        if (P.relu) val = odd ? __uint_as_float(0x7fc00000u) : fmaxf(val, 0.f);
+                        return __float_as_uint(val);
+                    };
+                    if constexpr (F23) {
+                        const bool both = left > 4 || half == 0, two_rows = ooff1[mp] != SLAB_INVALID;
+                        uintx2 yy;
+                        yy.x = finish(row0[mk][mp][v]);
+                        yy.y = finish(row1[mk][mp][v]);
+                        if (P.wino_pairs) {        // a pair without a second row (odd number of rows) goes alone
+                            __builtin_amdgcn_raw_buffer_store_b64(yy, ors, both && two_rows ? ooff[mp] : SLAB_INVALID, soff, 0);
+                            if (P.wino_Ho & 1)
+                                __builtin_amdgcn_raw_buffer_store_b32(yy.x, ors, both && !two_rows ? ooff[mp] : SLAB_INVALID, soff, 0);
+                        } else {
+                            __builtin_amdgcn_raw_buffer_store_b32(yy.x, ors, both ? ooff[mp] : SLAB_INVALID, soff, 0);
+                            __builtin_amdgcn_raw_buffer_store_b32(yy.y, ors, both ? ooff1[mp] : SLAB_INVALID, soff, 0);
+                        }
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b32(finish(acc[mk][mp][v]), ors, vo, soff, 0);
+                    }
                 }
             }
         }
     };
     auto store_partial = [&](int slot) __attribute__((always_inline)) {
-        float *dst = part + (size_t)slot * (TK * TQ);
+        float *dst = part + (size_t)slot * (TK * TQ * ROWS);
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int kloc = (wk * MK + mk) * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
 #pragma unroll
-                for (int mp = 0; mp < MP; ++mp)
-                    dst[kloc * TQ + (wp * MP + mp) * 32 + (lane & 31)] = acc[mk][mp][v];
+                for (int mp = 0; mp < MP; ++mp) {
+                    const int ql = (wp * MP + mp) * 32 + (lane & 31);
+                    if constexpr (F23)             // in the output domain: pixel = 2 * pair + row
+                        *reinterpret_cast<float2 *>(dst + kloc * (2 * TQ) + 2 * ql) = float2{row0[mk][mp][v], row1[mk][mp][v]};
+                    else
+                        dst[kloc * TQ + ql] = acc[mk][mp][v];
+                }
             }
     };
     // One segment = the units of one tile in a row.
@@ -370,12 +491,13 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             next_slab();
             if (u + 1 < m) { wo += WSTEP; fi = 0; so = 0; xo = xslab; }
             step();                                // the segment's last one reads its own operands again, for nothing
+            if constexpr (F23) fold((uu + u) & 3);
         }
         done += m;
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)
 #pragma unroll
-            for (int mp = 0; mp < MP; ++mp) acc[mk][mp] += small[mk][mp];
+            for (int mp = 0; mp < (F23 ? 0 : MP); ++mp) acc[mk][mp] += small[mk][mp];
         if (whole) {
             store_tile();
             if (__any(odd_results)) repair_tile(tile_of(t));

@@ -133,9 +133,8 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
     const bool pairs = d->precision != MCN_PREC_FP32_PLAIN;     // the row-pair kernels for 3x3 stride-1 layers
     auto plan_view = [&](const ConvView &v, IgemmPlan *pl) {
         if (bf && !v.mD && v.Cg >= BF_DC && plan_igemm(v, ncu, pl, true, true, planes)) return true;    // merged phases: fp32 kernel only
-        // fp32: the same sum on the bf16 matrix core, operands in three planes, where the row pairs do not apply
-        // (merged phases, fewer channels than one MFMA takes: fp32 kernel only)
-        if (d->precision == MCN_PREC_FP32 && split_pays(v) && plan_igemm(v, ncu, pl, true, true, 3)) return true;
+        // fp32: the same sum on the bf16 matrix core, operands in three planes (merged phases, fewer channels than one MFMA takes: fp32 kernel only)
+        if (d->precision == MCN_PREC_FP32 && wino_enabled() && split_pays(v) && plan_igemm(v, ncu, pl, true, true, 3)) return true;
         return plan_igemm(v, ncu, pl, false, pairs);
     };
     e.fwd_ok = on && plan_view(forward_view(g), &e.fwd);
@@ -247,12 +246,15 @@ int launch_igemm_bf16_inst(const IgemmPlan &pl, const float *in, const float *wp
 }
 
 // fp32 operands in three bf16 planes (kern_igemm_split.h)
-template <int WK, int WP, int MK, int MP>
+template <int WK, int WP, int MK, int MP, bool F23 = false>
 int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, const float *bias, float *out,
                        float *part, hipStream_t s, int relu, const float *w) {
+    if constexpr (!F23 && WK * MK == 4)       // row pairs: tiles of 128 filters
+        if (pl.P.wino_Ho) return launch_igemm_split<WK, WP, MK, MP, true>(pl, in, wpk, bias, out, part, s, relu, w);
     IgemmParams P = pl.P;
     P.relu = relu;
-    auto kern = igemm_split_kernel<WK, WP, MK, MP>;
+    P.wino_pairs = F23 && P.osi == 2 && P.OH % 2 == 0 && ((uintptr_t)out & 7) == 0;
+    auto kern = igemm_split_kernel<WK, WP, MK, MP, F23>;
     if (pl.lds_bytes > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)pl.lds_bytes);
@@ -262,7 +264,11 @@ int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, c
     int st = check_launch();
     if (st || P.nblocks < 2 || P.own * P.nblocks == P.tiles || P.NU == 1) return st;      // no tile is shared
     constexpr int TK = WK * MK * 32, TQ = WP * MP * 32;
-    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ, true>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, in, w);
+    if constexpr (F23) {        // the fix-up pass sees rows instead of pairs
+        P.TI *= 2; P.QN *= 2; P.Ho = P.wino_Ho; P.osi /= 2; P.Hf = 3; P.Sh = 1; P.NU /= 4;
+        P.dTI = make_div32(P.TI);
+    }
+    hipLaunchKernelGGL((igemm_fixup_kernel<TK, F23 ? 2 * TQ : TQ, true>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, in, w);
     return check_launch();
 }
 
@@ -288,7 +294,10 @@ int launch_igemm(const IgemmPlan &pl, const float *in, const float *w, const flo
     float *packed = (float *)ws;
     float *part = (float *)((char *)ws + align256(pl.packed_floats * sizeof(float)));
     if (pl.bf16) {
-        hipLaunchKernelGGL(igemm_pack_weights_bf16_kernel, dim3(cdiv(pl.Q.total, 256)), dim3(256), 0, s, w,
+        if (pl.Q.wino)
+            hipLaunchKernelGGL(igemm_pack_f23_split_kernel, dim3(cdiv(pl.Q.total / 12, 256)), dim3(256), 0, s, w, (unsigned *)packed, pl.Q);
+        else
+            hipLaunchKernelGGL(igemm_pack_weights_bf16_kernel, dim3(cdiv(pl.Q.total, 256)), dim3(256), 0, s, w,
                            (unsigned *)packed, pl.Q);
         int st = check_launch();
         if (st) return st;

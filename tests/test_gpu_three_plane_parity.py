@@ -39,25 +39,48 @@ def test_every_element(case, misalign):
     assert e["forward"] <= BOUND and e["backward_data"] <= BOUND, e
 
 
+PAIRS = [  # H, W, D, N, Df, K, pad: 3x3 layers whose row pairs take the kernel (at least 256 channels, few tiles)
+    (14, 14, 256, 2, 256, 256, (1, 1, 1, 1)),      # even plane: both rows of a pair in one store
+    (13, 9, 263, 3, 263, 130, (1, 1, 1, 1)),       # odd plane (a pair without a second row), ragged channels and filters
+    (7, 16, 512, 1, 256, 264, (1, 0, 2, 1)),       # two groups of 132 filters, uneven pads
+    (30, 5, 272, 1, 272, 96, (0, 0, 0, 0)),        # no pads; tile of 128 filters, 96 used
+]
+
+
+@pytest.mark.parametrize("case", range(len(PAIRS)))
+@pytest.mark.parametrize("misalign", [0, 1])
+def test_row_pairs_every_element(case, misalign):
+    H, W, D, N, Df, K, pad = PAIRS[case]
+    L = custom_layer(H, W, D, N, 3, 3, Df, K, (1, 1), pad, idx=820 + case)
+    assert B.mcn_conv_kernel_name(B.make_desc(synth.x_shape(L), synth.w_shape(L), (1, 1), pad), 0) == "igemm_f23"
+    e = U.run_layer_full(L, with_bias=bool(case % 2), seed=case, misalign=misalign)
+    U.assert_errors(e, label="three planes, row pairs %d" % case)
+    print("three planes, row pairs", case, e, flush=True)
+    # the error is bounded by the sums over all pairings of rows, up to three times a result's own: n = 3 * 263 * 3
+    assert e["forward"] <= 2 * BOUND and e["backward_data"] <= 2 * BOUND, e
+
+
 @pytest.mark.parametrize("relu", [False, True])
-@pytest.mark.parametrize("shape", [(9, 10, 20, 2, 48), (40, 40, 32, 16, 70)])      # shared tiles; whole tiles
+@pytest.mark.parametrize("shape", [(9, 10, 20, 2, 48, 5), (40, 40, 32, 16, 70, 5),      # shared tiles; whole tiles
+                                   (14, 13, 256, 2, 96, 3)])                            # row pairs
 def test_values_that_are_not_finite_or_nearly_so(relu, shape):
     """An infinite operand gives +-inf (or NaN) where the plain sum does, one near the largest float stays finite."""
-    H, W, D, N, K = shape
-    L = custom_layer(H, W, D, N, 5, 5, D, K, (1, 1), (2, 2, 2, 2), idx=830)
+    H, W, D, N, K, f = shape
+    P = f // 2
+    L = custom_layer(H, W, D, N, f, f, D, K, (1, 1), (P, P, P, P), idx=830)
     x, w, b = synth.make_x(L), synth.make_w(L), synth.make_b(L)
     x[0, 3, 4, 5], x[1, 7, 2, 2], x[N - 1, 0, W - 1, H - 1], x[1, 1, 7, 7] = float("inf"), float("-inf"), float("nan"), 3.4e38
     w[:, 1] *= 1e-4
-    ref = torch.nn.functional.conv2d(x.double(), w.double(), b.double(), padding=2)
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), b.double(), padding=P)
     xg, wg, bg = x.cuda(), w.cuda(), b.cuda()
-    y = (B.conv_relu_forward if relu else B.conv_forward)(xg, wg, bg, (1, 1), (2, 2, 2, 2)).cpu()
+    y = (B.conv_relu_forward if relu else B.conv_forward)(xg, wg, bg, (1, 1), (P, P, P, P)).cpu()
     if relu:
         ref = torch.where(torch.isnan(ref), torch.zeros_like(ref), ref.clamp(min=0))       # fmax(NaN, 0) = 0, as in the other kernels
     assert torch.equal(torch.isnan(y), torch.isnan(ref)) and torch.equal(torch.isinf(y), torch.isinf(ref))
     inf = torch.isinf(ref)
     assert int(inf.sum()) > 0 and torch.equal(y[inf].double(), ref[inf])
     ok = torch.isfinite(ref)
-    den = torch.nn.functional.conv2d(torch.nan_to_num(x, 0, 0, 0).double().abs(), w.double().abs(), b.double().abs(), padding=2)
+    den = torch.nn.functional.conv2d(torch.nan_to_num(x, 0, 0, 0).double().abs(), w.double().abs(), b.double().abs(), padding=P)
     assert float(((y.double() - ref)[ok].abs() / den[ok]).max()) <= 1e-5
 
 

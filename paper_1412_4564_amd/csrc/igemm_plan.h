@@ -418,8 +418,10 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         } else if (v.pack_mode == 1) {
             P.wo = v.pi + v.pSh * ((wino ? 3 : v.Hf) - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
             P.wg = area * v.DfA * v.Cg; P.wk = area; P.wc = area * v.DfA; P.wi = -v.pSh; P.wj = -v.HfA * v.pSw;
+        } else if (v.pack_mode == 3) {
+            P.HfA = v.HfA; P.WfA = v.WfA; P.DfA = v.DfA; P.B0i = v.B0i; P.B0j = v.B0j;
         } else if (planes == 3) {
-            return false;       // the fully-connected and merged-phase views stay on the fp32 kernels
+            return false;       // the fully-connected views stay on the fp32 kernels
         }
     }
     P.dTI = make_div32(P.TI); P.dWo = make_div32(P.Wo); P.dWp = make_div32(P.Wp); P.dSRP = make_div32(P.SRP);
@@ -480,7 +482,7 @@ inline bool wino_enabled() {
 // unit is then one step (768 cycles of MFMAs), and its staging (loads, split, barrier) takes longer (28x28x512, 1x1x512x128,
 // 64 images: forward 93 us against 78 on the fp32 kernel).
 inline bool split_pays(const ConvView &v) {
-    return !v.mD && v.pack_mode <= 1 && v.Cg >= BF_DC && v.Hf * v.Wf >= 2;
+    return v.pack_mode != 2 && v.Cg >= BF_DC && v.Hf * v.Wf >= 2;
 }
 
 // Row pairs in three planes (kern_igemm_split.h, F23): deep layers whose plane and batch give at most half as many tiles of

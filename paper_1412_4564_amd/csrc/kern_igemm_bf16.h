@@ -95,8 +95,13 @@ __global__ __launch_bounds__(256) void igemm_pack_weights_bf16_kernel(const floa
             } else if (Q.mode == 1) {
                 const int fi = Q.pi + Q.Sh * (Q.Hf - 1 - ti), fj = Q.pj + Q.Sw * (Q.Wf - 1 - tj);
                 v[e] = w[fi + Q.HfA * (fj + Q.WfA * (k + (size_t)Q.DfA * (g * Q.Cg + c)))];
-            } else {
+            } else if (Q.mode == 2) {
                 v[e] = w[k + (size_t)Q.ldk * c];
+            } else {
+                const int ph = k / Q.mD, cch = k - ph * Q.mD;
+                const int pj = ph / Q.Sh, pi = ph - pj * Q.Sh;
+                const int fi = merged_tap(ti, Q.Hf, Q.HfA, Q.Sh, Q.Pt, Q.B0i, pi), fj = merged_tap(tj, Q.Wf, Q.WfA, Q.Sw, Q.Pl, Q.B0j, pj);
+                if (fi >= 0 && fj >= 0) v[e] = w[fi + Q.HfA * (fj + Q.WfA * (cch + (size_t)Q.DfA * (g * Q.Cg + c)))];
             }
         }
     }

@@ -81,8 +81,9 @@ __global__ __launch_bounds__(256) void igemm_pack_f23_split_kernel(const float *
     }
 }
 
+// MERGED: the stride phases of an input derivative side by side in the filter dimension (IgemmParams::mD).
 // WK x WP computing waves; each owns MK x MP tiles of 32 filters x 32 pixels.  wsrc: the caller's filter array.
-template <int WK, int WP, int MK, int MP, bool F23>
+template <int WK, int WP, int MK, int MP, bool F23, bool MERGED>
 __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 3 : 2) void igemm_split_kernel(
     IgemmParams P, const float *__restrict__ in, const float *__restrict__ wpk, const float *__restrict__ bias, float *out,
     float *__restrict__ part, const float *__restrict__ wsrc) {
@@ -201,7 +202,8 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         auto write = [&](Samples &q) __attribute__((always_inline)) {
             if (q.uu == 0 && bias && ltid < TK) {    // start value of a tile this block owns entirely
                 const int kl = q.kt * TK + ltid;
-                blds[(q.seq & (SPLIT_BIASES - 1)) * TK + ltid] = kl < P.Kg ? bias[q.g * P.Kg + kl] : 0.f;
+                const int ch = MERGED ? q.g * P.mD + merged_filter(P, kl).c : q.g * P.Kg + kl;
+                blds[(q.seq & (SPLIT_BIASES - 1)) * TK + ltid] = kl < P.Kg ? bias[ch] : 0.f;
             }
             float *xb = xbuf + slab * XSZ;
             slab = slab + 1 == SPLIT_SLABS ? 0 : slab + 1;
@@ -248,6 +250,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     int bbase[MP];       // slab byte offset of the pixel's window origin, octet of this half-wave
     unsigned ooff[MP];   // byte offset of the lane's first result relative to the tile's output window, or SLAB_INVALID
     unsigned ooff1[MP];  // F23: the same for the second row of the pair
+    int edge[MP];        // merged phases: 1 = last row of the view, 2 = last column
     __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc((void *)out, 0, 0, BUFFER_FLAGS);
     int c_kt = 0, c_g = 0, c_seq = -1;
     // F23 = false: sums of the hi x hi products, and of the five others; F23: the current combination's sum, and the rows'
@@ -275,12 +278,13 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             const int ucol = jo * P.Sw + (n - n_first) * P.Wp - u0;
             bbase[mp] = 16 * ((ok ? ii * (F23 ? 1 : P.Sh) + SRP * ucol : 0) + half * CP);
             ooff[mp] = ok ? 4u * (unsigned)((P.oi0 + P.osi * io) + P.OH * (P.oj0 + P.osj * jo) +
-                                            OHW * (P.Ktot * (n - n_first) + 4 * half))
+                                            OHW * (P.Ktot * (n - n_first) + (MERGED ? 0 : 4 * half)))
                           : SLAB_INVALID;
+            edge[mp] = (io == P.Ho - 1 ? 1 : 0) | (jo == P.Wo - 1 ? 2 : 0);
             if constexpr (F23)
                 ooff1[mp] = ok && 2 * io + 1 < P.wino_Ho ? ooff[mp] + 4u * (unsigned)(P.osi >> 1) : SLAB_INVALID;
         }
-        (void)ooff1;
+        (void)ooff1; (void)edge;
         const size_t out_base = (size_t)n_first * P.Ktot * OHW;
         size_t out_left = ((size_t)P.N * P.Ktot * OHW - out_base) * 4;
         if (out_left > 0x7fffffffull) out_left = 0x7fffffffull;
@@ -399,13 +403,21 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             for (int v = 0; v < MK * 16; ++v) {
                 const int kl = kt * TK + (wk * MK + (v >> 4)) * 32 + ((v & 15) >> 2) * 8 + half * 4 + (v & 3);
                 if (kl >= P.Kg) continue;
+                if constexpr (MERGED) {
+                    const MergedFilter f = merged_filter(P, kl);
+                    const int oi = f.i0 + P.osi * io, oj = f.j0 + P.osj * jo;
+                    if (oi >= P.OH || oj >= P.OW) continue;
+                    float *o = out + (size_t)oi + (size_t)P.OH * oj + (size_t)OHW * (g * P.mD + f.c + (size_t)P.Ktot * n);
+                    if (not_finite(*(volatile float *)o)) *o = plain_result<true>(P, P.Hf, P.Sh, in, wsrc, bias, g, kl, io, jo, n);
+                    continue;
+                }
                 for (int row = 0; row < ROWS; ++row) {
                     const int ior = ROWS * io + row;           // row of the view
                     if (F23 && ior >= P.wino_Ho) continue;
                     float *o = out + (size_t)(P.oi0 + P.osi / ROWS * ior) + (size_t)P.OH * (P.oj0 + P.osj * jo) +
                                (size_t)OHW * (g * P.Kg + kl + (size_t)P.Ktot * n);
                     if (not_finite(*(volatile float *)o))
-                        *o = plain_result(P, F23 ? 3 : P.Hf, F23 ? 1 : P.Sh, in, wsrc, bias, g, kl, ior, jo, n);
+                        *o = plain_result<false>(P, F23 ? 3 : P.Hf, F23 ? 1 : P.Sh, in, wsrc, bias, g, kl, ior, jo, n);
                 }
             }
         }
@@ -448,6 +460,36 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                 }
             }
         }
+    };
+    // Merged phases: the two half-waves hold filters of different phases, so the filter part of the address and the "does
+    // this pixel exist in this phase" test are per half-wave (as in igemm_sk_kernel).
+    auto store_tile_merged = [&]() __attribute__((always_inline)) {
+        odd_results = false;
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int kl0 = c_kt * TK + (wk * MK + mk) * 32 + (v >> 2) * 8 + (v & 3);
+                if (kl0 >= P.Kg) continue;
+                unsigned foff[2];
+                int missing[2];                    // 1: this phase has no last row, 2: no last column, 4: no such filter
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int kl = kl0 + 4 * h;
+                    const MergedFilter f = merged_filter(P, kl < P.Kg ? kl : 0);
+                    foff[h] = 4u * (unsigned)((c_g * P.mD + f.c) * OHW + f.i0 + P.OH * f.j0);
+                    missing[h] = (f.i0 + P.osi * (P.Ho - 1) >= P.OH ? 1 : 0) | (f.j0 + P.osj * (P.Wo - 1) >= P.OW ? 2 : 0) | (kl < P.Kg ? 0 : 4);
+                }
+                const unsigned fo = half ? foff[1] : foff[0];
+                const int miss = half ? missing[1] : missing[0];
+#pragma unroll
+                for (int mp = 0; mp < MP; ++mp) {
+                    const bool drop = (miss & (edge[mp] | 4)) != 0 || ooff[mp] == SLAB_INVALID;
+                    const float val = acc[mk][mp][v];
+                    odd_results |= !drop && not_finite(val);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), ors, drop ? SLAB_INVALID : ooff[mp] + fo, 0, 0);
+                }
+            }
     };
     auto store_partial = [&](int slot) __attribute__((always_inline)) {
         float *dst = part + (size_t)slot * (TK * TQ * ROWS);
@@ -499,7 +541,8 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
 #pragma unroll
             for (int mp = 0; mp < (F23 ? 0 : MP); ++mp) acc[mk][mp] += small[mk][mp];
         if (whole) {
-            store_tile();
+            if constexpr (MERGED) store_tile_merged();
+            else store_tile();
             if (__any(odd_results)) repair_tile(tile_of(t));
         } else {
             store_partial(2 * vb + (first_segment ? 0 : 1));

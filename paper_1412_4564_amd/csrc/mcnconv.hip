@@ -246,15 +246,17 @@ int launch_igemm_bf16_inst(const IgemmPlan &pl, const float *in, const float *wp
 }
 
 // fp32 operands in three bf16 planes (kern_igemm_split.h)
-template <int WK, int WP, int MK, int MP, bool F23 = false>
+template <int WK, int WP, int MK, int MP, bool F23 = false, bool MERGED = false>
 int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, const float *bias, float *out,
                        float *part, hipStream_t s, int relu, const float *w) {
-    if constexpr (!F23 && WK * MK == 4)       // row pairs: tiles of 128 filters
+    if constexpr (!F23 && !MERGED)
+        if (pl.P.mD) return launch_igemm_split<WK, WP, MK, MP, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
+    if constexpr (!F23 && !MERGED && WK * MK == 4)       // row pairs: tiles of 128 filters
         if (pl.P.wino_Ho) return launch_igemm_split<WK, WP, MK, MP, true>(pl, in, wpk, bias, out, part, s, relu, w);
     IgemmParams P = pl.P;
     P.relu = relu;
     P.wino_pairs = F23 && P.osi == 2 && P.OH % 2 == 0 && ((uintptr_t)out & 7) == 0;
-    auto kern = igemm_split_kernel<WK, WP, MK, MP, F23>;
+    auto kern = igemm_split_kernel<WK, WP, MK, MP, F23, MERGED>;
     if (pl.lds_bytes > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)pl.lds_bytes);

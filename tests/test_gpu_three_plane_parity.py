@@ -25,6 +25,9 @@ CASES = [  # H, W, D, N, Hf, Wf, Df, K, stride, pad
     (30, 30, 128, 6, 4, 4, 128, 200, (2, 2), (1, 1, 1, 1)),   # four phases, tiles shared between blocks
     (27, 27, 96, 8, 5, 5, 48, 256, (1, 1), (2, 2, 2, 2)),     # two groups, 25 taps in several ranges
     (7, 7, 32, 1, 7, 7, 32, 40, (1, 1), (3, 3, 3, 3)),        # one image, filter as large as the plane
+    (47, 39, 3, 5, 11, 11, 3, 64, (4, 4), (0, 0, 0, 0)),      # dzdx: 16 phases merged into 48 filters, rows that no window reads
+    (20, 17, 4, 3, 5, 5, 4, 40, (2, 2), (2, 1, 0, 2)),        # dzdx: four phases of four channels, phases without a last row
+    (31, 33, 6, 2, 4, 3, 3, 36, (3, 2), (1, 0, 2, 1)),        # dzdx: two groups of six phases
 ]
 
 
@@ -82,6 +85,23 @@ def test_values_that_are_not_finite_or_nearly_so(relu, shape):
     ok = torch.isfinite(ref)
     den = torch.nn.functional.conv2d(torch.nan_to_num(x, 0, 0, 0).double().abs(), w.double().abs(), b.double().abs(), padding=P)
     assert float(((y.double() - ref)[ok].abs() / den[ok]).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("N", [2, 40])      # shared tiles; whole tiles
+def test_infinite_derivative_in_merged_phases(N):
+    """dzdx of a strided first layer: an infinite dzdy reaches the samples of its window and no others."""
+    w, p = torch.randn(64, 3, 7, 7), torch.randn(N, 64, 30, 31)
+    p[0, 5, 7, 8], p[N - 1, 60, 29, 3] = float("inf"), float("-inf")
+    x_shape = (N, 3, 2 * 29 + 7, 2 * 30 + 7)
+    ref = torch.nn.functional.conv_transpose2d(p.double(), w.double(), stride=2)
+    assert ref.shape == x_shape
+    dx = B.conv_backward_data(x_shape, w.cuda(), p.cuda(), (2, 2), (0, 0, 0, 0)).cpu()
+    assert torch.equal(torch.isnan(dx), torch.isnan(ref)) and torch.equal(torch.isinf(dx), torch.isinf(ref))
+    inf = torch.isinf(ref)
+    assert int(inf.sum()) == 2 * 3 * 49 and torch.equal(dx[inf].double(), ref[inf])
+    den = torch.nn.functional.conv_transpose2d(torch.nan_to_num(p, 0, 0, 0).double().abs(), w.double().abs(), stride=2)
+    ok = torch.isfinite(ref)
+    assert float(((dx.double() - ref)[ok].abs() / den[ok].clamp(min=1e-30)).max()) <= 1e-5
 
 
 @pytest.mark.parametrize("scale", [1e30, 1e-20, 1e-30])

@@ -420,8 +420,8 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
             P.wg = area * v.DfA * v.Cg; P.wk = area; P.wc = area * v.DfA; P.wi = -v.pSh; P.wj = -v.HfA * v.pSw;
         } else if (v.pack_mode == 3) {
             P.HfA = v.HfA; P.WfA = v.WfA; P.DfA = v.DfA; P.B0i = v.B0i; P.B0j = v.B0j;
-        } else if (planes == 3) {
-            return false;       // the fully-connected views stay on the fp32 kernels
+        } else if (bf16) {
+            return false;       // the fully-connected views are packed for the fp32 kernels only
         }
     }
     P.dTI = make_div32(P.TI); P.dWo = make_div32(P.Wo); P.dWp = make_div32(P.Wp); P.dSRP = make_div32(P.SRP);

@@ -64,50 +64,69 @@ __device__ inline void split_bf16x3(float v0, float v1, unsigned *hi, unsigned *
     split_bf16x2(r0, r1, mid, lo);
 }
 
-// packed[g][kt][unit][step][plane][octet][kk][8 channels] as bf16 (Q.planes = 1: the values rounded to bf16;
-// 2: their hi and lo planes; 3: hi, mid and lo, for kern_igemm_split.h); one thread writes one pair of channels (a 32-bit word).  Modes as in
-// igemm_pack_weights_kernel.
+// packed[g][kt][unit][step][plane][octet][kk][8 channels] as bf16 (PLANES = 1: the values rounded to bf16; 2: their hi and
+// lo planes; 3: hi, mid and lo, for kern_igemm_split.h); one thread reads one pair of channels and writes its word of every
+// plane.  Modes as in igemm_pack_weights_kernel; MERGED: mode 3.
+// Bound by the latency of its two loads (a stride apart in memory) and of the index divisions: planes and mode are template
+// arguments so that nothing stands between the two loads.  With both at run time the loads of a pair went one after the other
+// and every value was read once per plane (14x14x512, 3x3x512x512, 32 images: split operands, forward 136.5 us with that, 117.6 us
+// with this; bf16 76.4 and 70.2 us).
+template <int PLANES, bool MERGED>
 __global__ __launch_bounds__(256) void igemm_pack_weights_bf16_kernel(const float *__restrict__ w,
                                                                       unsigned *__restrict__ packed, PackParams Q) {
-    int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= Q.total) return;
-    int t = p / Q.WSZ;
-    int within = p - t * Q.WSZ;
-    const int j2 = within & 3; within >>= 2;
-    const int kk = within % Q.TK; within /= Q.TK;
-    const int oct = within & 1; within >>= 1;
-    const int plane = within % Q.planes;
-    const int s = within / Q.planes;             // tap of the unit's tap range
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= Q.total / PLANES) return;
+    const int words = Q.WSZ / PLANES;            // of one plane, per unit
+    int t = p / words;
+    const int within = p - t * words;
+    unsigned *const unit = packed + (size_t)t * Q.WSZ;
+    const int j2 = within & 3, row = within >> 2;
+    const int so = row / Q.TK, kk = row - so * Q.TK;
+    const int oct = so & 1, s = so >> 1;         // s: tap of the unit's tap range
     const int uu = t % Q.NU; t /= Q.NU;
     const int kt = t % Q.KT;
     const int g = t / Q.KT;
     const int cg = uu / Q.NTR, tr = uu - cg * Q.NTR;
     const int tap = tr * Q.TC + s;
     const int k = kt * Q.TK + kk;
+    const int c = cg * BF_DC + oct * 8 + 2 * j2;
     float v[2] = {0.f, 0.f};
-    if (s < Q.TC && tap < Q.Hf * Q.Wf && k < Q.Kg) {
+    if (s < Q.TC && tap < Q.Hf * Q.Wf && k < Q.Kg && c < Q.Cg) {
         const int ti = tap % Q.Hf, tj = tap / Q.Hf;
-        for (int e = 0; e < 2; ++e) {
-            const int c = cg * BF_DC + oct * 8 + 2 * j2 + e;
-            if (c >= Q.Cg) continue;
-            if (Q.mode == 0) {
-                v[e] = w[ti + Q.HfA * (tj + Q.WfA * (c + (size_t)Q.DfA * (g * Q.Kg + k)))];
-            } else if (Q.mode == 1) {
-                const int fi = Q.pi + Q.Sh * (Q.Hf - 1 - ti), fj = Q.pj + Q.Sw * (Q.Wf - 1 - tj);
-                v[e] = w[fi + Q.HfA * (fj + Q.WfA * (k + (size_t)Q.DfA * (g * Q.Cg + c)))];
-            } else if (Q.mode == 2) {
-                v[e] = w[k + (size_t)Q.ldk * c];
-            } else {
-                const int ph = k / Q.mD, cch = k - ph * Q.mD;
-                const int pj = ph / Q.Sh, pi = ph - pj * Q.Sh;
-                const int fi = merged_tap(ti, Q.Hf, Q.HfA, Q.Sh, Q.Pt, Q.B0i, pi), fj = merged_tap(tj, Q.Wf, Q.WfA, Q.Sw, Q.Pl, Q.B0j, pj);
-                if (fi >= 0 && fj >= 0) v[e] = w[fi + Q.HfA * (fj + Q.WfA * (cch + (size_t)Q.DfA * (g * Q.Cg + c)))];
-            }
+        const float *src = w;
+        size_t step;                             // from a channel to the next
+        bool ok = true;
+        if (MERGED) {
+            const int ph = k / Q.mD, cch = k - ph * Q.mD;
+            const int pj = ph / Q.Sh, pi = ph - pj * Q.Sh;
+            const int fi = merged_tap(ti, Q.Hf, Q.HfA, Q.Sh, Q.Pt, Q.B0i, pi), fj = merged_tap(tj, Q.Wf, Q.WfA, Q.Sw, Q.Pl, Q.B0j, pj);
+            ok = fi >= 0 && fj >= 0;
+            step = (size_t)Q.HfA * Q.WfA * Q.DfA;
+            if (ok) src += fi + Q.HfA * (fj + Q.WfA * (cch + (size_t)Q.DfA * (g * Q.Cg + c)));
+        } else if (Q.mode == 0) {
+            step = (size_t)Q.HfA * Q.WfA;
+            src += ti + Q.HfA * (tj + Q.WfA * (c + (size_t)Q.DfA * (g * Q.Kg + k)));
+        } else {
+            const int fi = Q.pi + Q.Sh * (Q.Hf - 1 - ti), fj = Q.pj + Q.Sw * (Q.Wf - 1 - tj);
+            step = (size_t)Q.HfA * Q.WfA * Q.DfA;
+            src += fi + Q.HfA * (fj + Q.WfA * (k + (size_t)Q.DfA * (g * Q.Cg + c)));
         }
+        const bool two = c + 1 < Q.Cg;
+        const float v0 = *src, v1 = src[two ? step : 0];
+        if (ok) { v[0] = v0; v[1] = two ? v1 : 0.f; }
     }
-    unsigned hi, mid, lo;
-    split_bf16x3(v[0], v[1], &hi, &mid, &lo);
-    packed[p] = plane == 0 ? hi : plane == 1 ? mid : lo;      // of two planes the second is bf16(v - hi) as well
+    unsigned *dst = unit + ((size_t)(s * PLANES) * 2 + oct) * Q.TK * 4 + kk * 4 + j2;
+    if constexpr (PLANES == 1) {
+        dst[0] = pack_bf16x2(v[0], v[1]);
+    } else if constexpr (PLANES == 2) {
+        unsigned hi, lo;
+        split_bf16x2(v[0], v[1], &hi, &lo);
+        dst[0] = hi; dst[2 * Q.TK * 4] = lo;
+    } else {
+        unsigned hi, mid, lo;
+        split_bf16x3(v[0], v[1], &hi, &mid, &lo);
+        dst[0] = hi; dst[2 * Q.TK * 4] = mid; dst[4 * Q.TK * 4] = lo;
+    }
 }
 
 // WK x WP waves; each wave owns MK x MP tiles of 32 filters x 32 pixels.

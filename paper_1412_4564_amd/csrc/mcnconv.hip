@@ -298,9 +298,11 @@ int launch_igemm(const IgemmPlan &pl, const float *in, const float *w, const flo
     if (pl.bf16) {
         if (pl.Q.wino)
             hipLaunchKernelGGL(igemm_pack_f23_split_kernel, dim3(cdiv(pl.Q.total / 12, 256)), dim3(256), 0, s, w, (unsigned *)packed, pl.Q);
-        else
-            hipLaunchKernelGGL(igemm_pack_weights_bf16_kernel, dim3(cdiv(pl.Q.total, 256)), dim3(256), 0, s, w,
-                           (unsigned *)packed, pl.Q);
+        else {
+            auto pack = pl.planes == 1 ? igemm_pack_weights_bf16_kernel<1, false> : pl.planes == 2 ? igemm_pack_weights_bf16_kernel<2, false>
+                        : pl.P.mD ? igemm_pack_weights_bf16_kernel<3, true> : igemm_pack_weights_bf16_kernel<3, false>;
+            hipLaunchKernelGGL(pack, dim3(cdiv(pl.Q.total / pl.planes, 256)), dim3(256), 0, s, w, (unsigned *)packed, pl.Q);
+        }
         int st = check_launch();
         if (st) return st;
         if (pl.planes == 3) {

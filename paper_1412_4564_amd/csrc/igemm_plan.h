@@ -143,6 +143,7 @@ struct IgemmPlan {
     int TK, TQ, NT;
     IgemmParams P;
     PackParams Q;
+    PlainView V;        // three planes
     size_t lds_bytes;
     size_t packed_floats;
     size_t partial_floats;   // 2 slots of TK*TQ per resident block
@@ -307,7 +308,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         if ((int64_t)TI * v.Wo * v.N >= ((int64_t)1 << 30)) continue;
         const int SC = slab_columns(v, TI, TQ, Wp);
         const int64_t CP = (SR * SC + 63) / 64 * 64;
-        if (CP > (planes == 3 ? SPLIT_EPT_MAX : bf16 ? bf_ept_max(NL) : 32) * NL) continue;
+        if (CP > (planes == 3 ? split_ept(f23s) : bf16 ? bf_ept_max(NL) : 32) * NL) continue;
         // an image crossing inside a tile moves the window by whole images: keep offsets in range
         const int64_t span = (int64_t)SC / Wp + 2;
         if ((double)span * v.Ctot * v.H * v.W * 4.0 >= 2147483647.0) continue;
@@ -411,17 +412,19 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     P.OH = v.OH; P.OW = v.OW; P.oi0 = v.oi0; P.osi = v.osi; P.oj0 = v.oj0; P.osj = v.osj;
     P.mD = v.mD; P.mPt = v.mPt; P.mPl = v.mPl;
     P.wino_Ho = wino_Ho;
-    {
+    if (bf16 && v.pack_mode == 2) return false;       // the fully-connected views are packed for the fp32 kernels only
+    if (planes == 3) {
         const int area = v.HfA * v.WfA;
+        PlainView &V = pl->V;
+        V = PlainView{};
+        V.Hf = wino ? 3 : v.Hf; V.Sh = wino ? 1 : v.Sh;
         if (v.pack_mode == 0) {
-            P.wo = 0; P.wg = area * v.DfA * v.Kg; P.wk = area * v.DfA; P.wc = area; P.wi = 1; P.wj = v.HfA;
+            V.wo = 0; V.wg = area * v.DfA * v.Kg; V.wk = area * v.DfA; V.wc = area; V.wi = 1; V.wj = v.HfA;
         } else if (v.pack_mode == 1) {
-            P.wo = v.pi + v.pSh * ((wino ? 3 : v.Hf) - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
-            P.wg = area * v.DfA * v.Cg; P.wk = area; P.wc = area * v.DfA; P.wi = -v.pSh; P.wj = -v.HfA * v.pSw;
-        } else if (v.pack_mode == 3) {
-            P.HfA = v.HfA; P.WfA = v.WfA; P.DfA = v.DfA; P.B0i = v.B0i; P.B0j = v.B0j;
-        } else if (bf16) {
-            return false;       // the fully-connected views are packed for the fp32 kernels only
+            V.wo = v.pi + v.pSh * (V.Hf - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
+            V.wg = area * v.DfA * v.Cg; V.wk = area; V.wc = area * v.DfA; V.wi = -v.pSh; V.wj = -v.HfA * v.pSw;
+        } else {
+            V.HfA = v.HfA; V.WfA = v.WfA; V.DfA = v.DfA; V.B0i = v.B0i; V.B0j = v.B0j;
         }
     }
     P.dTI = make_div32(P.TI); P.dWo = make_div32(P.Wo); P.dWp = make_div32(P.Wp); P.dSRP = make_div32(P.SRP);

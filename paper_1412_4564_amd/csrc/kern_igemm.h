@@ -149,46 +149,8 @@ struct IgemmParams {
     int wino_Ho;
     int wino_pairs;     // WINO: 1 = both rows of a pair go out in one 8-byte store (rows adjacent in memory, every such
                         // address a multiple of 8: output pointer aligned to 8 bytes and an even number of rows per plane)
-    // three-plane kernels only (kern_igemm_split.h): results that are not finite are summed again one by one; where
-    // weight (group g, filter k, channel c, tap (ti, tj)) of the view is in the caller's array:
-    // wo + g*wg + k*wk + c*wc + ti*wi + tj*wj
-    // (merged phases: shape of that array and the largest b0 per direction, see PackParams)
-    int wo, wg, wk, wc, wi, wj;
-    int HfA, WfA, DfA, B0i, B0j;
     Div32 dTI, dWo, dWp, dSRP, dKT, dRB, dPT;   // reciprocals of the fields of these names
 };
-
-__device__ __host__ inline int merged_tap(int ti, int Hfv, int HfA, int S, int Pt, int B0, int pi);
-__device__ inline bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
-
-// One result of the view, summed as Sec. 4.1 writes it: what the results that are not finite are taken from.  w: the
-// caller's filter array.  Hf, Sh: the view's own (those of P describe pairs of rows in a view of row pairs).
-template <bool MERGED>
-__device__ inline float plain_result(const IgemmParams &P, int Hf, int Sh, const float *in, const float *w, const float *bias, int g,
-                                                        int kl, int io, int jo, int n) {
-    const int ph = MERGED ? kl / P.mD : 0, mc = kl - ph * P.mD;      // merged phases: phase and channel of "filter" kl
-    const int pj = MERGED ? ph / P.osi : 0, pi = ph - pj * P.osi;
-    float s = bias ? bias[MERGED ? g * P.mD + mc : g * P.Kg + kl] : 0.f;
-    for (int c = 0; c < P.Cg; ++c) {
-        const float *xc = in + (size_t)P.H * P.W * (g * P.Cg + c + (size_t)P.Ctot * n);
-        for (int tj = 0; tj < P.Wf; ++tj) {
-            const int j = P.Sw * jo + tj - P.Pl;
-            if (j < 0 || j >= P.W) continue;
-            for (int ti = 0; ti < Hf; ++ti) {
-                const int i = Sh * io + ti - P.Pt;
-                if (i < 0 || i >= P.H) continue;
-                long long wx = P.wo + (long long)g * P.wg + (long long)kl * P.wk + (long long)c * P.wc + ti * P.wi + tj * P.wj;
-                if constexpr (MERGED) {
-                    const int fi = merged_tap(ti, Hf, P.HfA, P.osi, P.mPt, P.B0i, pi), fj = merged_tap(tj, P.Wf, P.WfA, P.osj, P.mPl, P.B0j, pj);
-                    if (fi < 0 || fj < 0) continue;
-                    wx = fi + P.HfA * (fj + P.WfA * (mc + (long long)P.DfA * (g * P.Cg + c)));
-                }
-                s = fmaf(w[wx], xc[i + (size_t)P.H * j], s);
-            }
-        }
-    }
-    return P.relu ? fmaxf(s, 0.f) : s;
-}
 
 // Merged phases: channel, and placement of output pixel (0,0), of merged filter kl
 struct MergedFilter {
@@ -900,12 +862,16 @@ __global__ __launch_bounds__(64 * (WK * WP + LW), WPE) void igemm_sk_kernel(Igem
     }
 }
 
+// What the fix-up pass does with results that are not finite: nothing, or (three-plane kernels) see kern_igemm_split.h
+struct KeepResults {
+    static constexpr bool on = false;
+};
+
 // Sum the pieces of every tile that was shared between blocks, in block order, add the bias,
 // and write the tile.  Grid: (left-over tiles, slices of a tile).
-template <int TK, int TQ, bool REPAIR = false>
+template <int TK, int TQ, class Repair = KeepResults>
 __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const float *__restrict__ part,
-                                                          const float *__restrict__ bias, float *__restrict__ out,
-                                                          const float *__restrict__ in, const float *__restrict__ w) {
+                                                          const float *__restrict__ bias, float *__restrict__ out, Repair R) {
     const int ts = blockIdx.x;                       // shared tile (the grid has one row of blocks per shared tile)
     const int tile_s0 = P.own * P.nblocks;           // the shared tiles start here; unit numbers are relative to them
     const int t = tile_s0 + ts;
@@ -956,7 +922,8 @@ __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const f
             const float4 v0 = *reinterpret_cast<const float4 *>(src + (size_t)slots[i] * (TK * TQ));
             acc.x += v0.x; acc.y += v0.y; acc.z += v0.z; acc.w += v0.w;
         }
-        const float vv[4] = {acc.x, acc.y, acc.z, acc.w};
+        float vv[4] = {acc.x, acc.y, acc.z, acc.w};
+        if constexpr (Repair::on) R.pixels(P, bias, g, rb, kl, pt * TQ + ql, vv);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int q = pt * TQ + ql + j;
@@ -969,9 +936,7 @@ __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const f
             const int oi = P.oi0 + P.osi * io + fi0, oj = P.oj0 + P.osj * jo + fj0;
             if (P.mD && (oi >= P.OH || oj >= P.OW)) continue;
             float v = vv[j];
-            if (REPAIR && not_finite(v)) v = P.mD ? plain_result<true>(P, P.Hf, P.Sh, in, w, bias, g, kl, io, jo, n)
-                                                           : plain_result<false>(P, P.Hf, P.Sh, in, w, bias, g, kl, io, jo, n);      // see kern_igemm_split.h
-            else if (P.relu) v = fmaxf(v, 0.f);
+            if (P.relu) v = fmaxf(v, 0.f);
             out[(size_t)(oi + P.OH * (oj + P.OW * (P.Ktot * n))) + (size_t)OHW * och] = v;
         }
     }

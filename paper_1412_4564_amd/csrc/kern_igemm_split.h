@@ -44,7 +44,162 @@ namespace mcn {
 constexpr int SPLIT_SLABS = 3;         // slab buffers: computed, next (being read ahead), written
 constexpr int SPLIT_BIASES = 4;        // bias buffers: a bias is written at most two tiles ahead
 constexpr int SPLIT_STAGE_WAVES = 4;   // waves that fetch and split the input
-constexpr int SPLIT_EPT_MAX = 2;       // slab samples a thread stages per unit, at most (16 registers each)
+// slab samples a thread stages per unit, at most (16 registers each in three sets; F23: 32 each in two)
+__device__ __host__ constexpr int split_ept(bool f23) { return f23 ? 1 : 2; }
+
+// ---- results that are not finite -------------------------------------------------------
+// An operand that is infinite splits into (inf, nan, nan), so every result that it enters comes out as NaN where the plain
+// sum may say +-inf (and one within 2^-9 of the largest float rounds to inf in its hi plane).  Results that are not finite
+// are summed again as Sec. 4.1 writes them, in fp32, from the arrays in memory.
+
+// The view as such a sum sees it: filter size and stride (those of IgemmParams describe pairs of rows in a view of row
+// pairs), and where weight (group g, filter k, channel c, tap (ti, tj)) is in the caller's array:
+// wo + g*wg + k*wk + c*wc + ti*wi + tj*wj (merged phases: shape of that array and the largest b0 per direction, see PackParams)
+struct PlainView {
+    int Hf, Sh;
+    int wo, wg, wk, wc, wi, wj;
+    int HfA, WfA, DfA, B0i, B0j;
+};
+
+__device__ inline bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
+
+// NF results: filters k0 .. k0+NF-1 of pixel (io, jo, n) of group g, those whose bit of `need` is set; s: their bias, then the
+// sum.  A lane whose results are all NaN is done.  Bound by address arithmetic and latency: the x of a tap and channel is read
+// once for all NF filters, the loads of four channels are in flight together.  A diverged batch (NaN) costs little, an infinite
+// operand among ordinary ones a fraction of a millisecond, infinite results everywhere ten times the call and more
+// (27x27x96, 5x5x48x256 in two groups, 128 images, forward, 0.35 ms: one NaN 0.36 ms, one inf 1.6 ms, all NaN 0.75 ms, +inf
+// everywhere 10.7 ms; one result at a time and to the end of its sum 5.2, 5.6, 33.9 and 33.9 ms).
+template <int NF, bool MERGED>
+__device__ inline void plain_results(const IgemmParams &P, const PlainView &V, const float *in, const float *w, int g, int k0, int io, int jo,
+                                     int n, unsigned need, float (&s)[NF]) {
+    const size_t HW = (size_t)P.H * P.W, wc = MERGED ? (size_t)V.HfA * V.WfA * V.DfA : (size_t)V.wc;
+    const float *const xg = in + HW * (g * P.Cg + (size_t)P.Ctot * n);
+    auto more = [&]() __attribute__((always_inline)) {
+        bool m = false;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) m |= (need >> f & 1) && s[f] == s[f];
+        return m;
+    };
+#pragma unroll 1
+    for (int tj = 0; tj < P.Wf; ++tj)
+#pragma unroll 1
+        for (int ti = 0; ti < V.Hf; ++ti) {
+            const int xi = V.Sh * io + ti - P.Pt, xj = P.Sw * jo + tj - P.Pl;
+            if (xi < 0 || xi >= P.H || xj < 0 || xj >= P.W || !more()) continue;
+            const float *xp = xg + xi + (size_t)P.H * xj;
+            const float *wp[NF];
+            bool tap[NF];                              // merged phases: the filter's phase has this tap
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const int k = min(k0 + f, P.Kg - 1);
+                tap[f] = true;
+                if constexpr (MERGED) {
+                    const int ph = k / P.mD, mc = k - ph * P.mD, pj = ph / P.osi, pi = ph - pj * P.osi;
+                    const int fi = merged_tap(ti, V.Hf, V.HfA, P.osi, P.mPt, V.B0i, pi), fj = merged_tap(tj, P.Wf, V.WfA, P.osj, P.mPl, V.B0j, pj);
+                    tap[f] = fi >= 0 && fj >= 0;
+                    wp[f] = w + (tap[f] ? fi + V.HfA * fj : 0) + (size_t)V.HfA * V.WfA * (mc + (size_t)V.DfA * (g * P.Cg));
+                } else {
+                    wp[f] = w + (V.wo + g * V.wg + k * V.wk + ti * V.wi + tj * V.wj);
+                }
+            }
+#pragma unroll 1
+            for (int c0 = 0; c0 < P.Cg; c0 += 4) {
+                const bool full = c0 + 4 <= P.Cg;
+                float xv[4], wv[4][NF];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const size_t c = full ? c0 + u : min(c0 + u, P.Cg - 1);
+                    xv[u] = xp[c * HW];
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) wv[u][f] = wp[f][c * wc];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        const float next = fmaf(wv[u][f], xv[u], s[f]);
+                        s[f] = c0 + u < P.Cg && (!MERGED || tap[f]) ? next : s[f];
+                    }
+                if (!__any(more())) break;
+            }
+        }
+}
+
+// in the fix-up pass: four consecutive pixels from q on, of one filter
+struct PlainPixels {
+    static constexpr bool on = true;
+    PlainView V;
+    const float *in, *w;
+    __device__ void pixels(const IgemmParams &P, const float *bias, int g, int rb, int kl, int q0, float (&v)[4]) const {
+        if (!(not_finite(v[0]) || not_finite(v[1]) || not_finite(v[2]) || not_finite(v[3]))) return;
+        const float b = bias ? bias[P.mD ? g * P.mD + kl % P.mD : g * P.Kg + kl] : 0.f;
+#pragma unroll 1
+        for (int j = 0; j < 4; ++j) {
+            const float was = j == 0 ? v[0] : j == 1 ? v[1] : j == 2 ? v[2] : v[3];
+            const int q = q0 + j, c = div32(q, P.dTI), n = div32(c, P.dWo), jo = c - n * P.Wo, io = rb * P.TI + q - c * P.TI;
+            if (!not_finite(was) || q >= P.QN || io >= P.Ho) continue;
+            float s[1] = {b};
+            if (P.mD) plain_results<1, true>(P, V, in, w, g, kl, io, jo, n, 1u, s);
+            else plain_results<1, false>(P, V, in, w, g, kl, io, jo, n, 1u, s);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = u == j ? s[0] : v[u];
+        }
+    }
+};
+
+// What the main kernel goes by, and (read from the kernel's arguments in memory, where this is the first one) the repair of
+// its tiles.
+struct SplitParams : IgemmParams {
+    PlainView V;
+    const float *in, *w, *bias;
+    float *out;
+};
+
+// A wave's part of a stored tile t: results that are not finite (the ReLU must not hide them: they are stored as NaN) are read
+// back, four filters of the lane's pixel at a time, and replaced.  A function of its own: inside the kernel it would live off the
+// kernel's registers (92 vector registers of the merged form spilled).  params: where the kernel's arguments are in memory.
+template <int TK, int WK, int MK, int MP, int TQ, int ROWS, bool MERGED>
+__device__ __attribute__((noinline)) void repair_tile(unsigned params_lo, unsigned params_hi, int t, int wave) {
+    const size_t at = (size_t)(unsigned)__builtin_amdgcn_readfirstlane(params_hi) << 32 | (unsigned)__builtin_amdgcn_readfirstlane(params_lo);
+    const SplitParams &P = *(const SplitParams *)(const __attribute__((address_space(4))) void *)at;
+    t = __builtin_amdgcn_readfirstlane(t);
+    wave = __builtin_amdgcn_readfirstlane(wave);
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), half = lane >> 5, wk = wave % WK, wp = wave / WK;
+    int kt, pt, rb, g;
+    decode_tile(P, t, &kt, &pt, &rb, &g);
+    const int OHW = P.OH * P.OW;
+    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);           // this wave reads back what it stored
+#pragma unroll 1
+    for (int e = 0; e < MK * MP * ROWS * 4; ++e) {
+        const int row = e % ROWS, v4 = e / ROWS % 4, mk = e / (4 * ROWS) % MK, mp = e / (4 * ROWS * MK);
+        const int q = pt * TQ + (wp * MP + mp) * 32 + (lane & 31);
+        const int c = div32(q, P.dTI);
+        const int n = div32(c, P.dWo);
+        const int jo = c - n * P.Wo, pair = rb * P.TI + q - c * P.TI, io = ROWS * pair + row;      // io: row of the view
+        const bool pixel = q < P.QN && (ROWS == 2 ? io < P.wino_Ho : pair < P.Ho);
+        const int k0 = kt * TK + (wk * MK + mk) * 32 + v4 * 8 + half * 4;
+        unsigned need = 0;
+        float s[4], *o[4];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            bool there = pixel && k0 + f < P.Kg;
+            int oi = P.oi0 + P.osi / ROWS * io, oj = P.oj0 + P.osj * jo, ch = g * P.Kg + k0 + f;
+            if constexpr (MERGED) {
+                const MergedFilter m = merged_filter(P, k0 + f);
+                oi = m.i0 + P.osi * io; oj = m.j0 + P.osj * jo; ch = g * P.mD + m.c;
+                there = there && oi < P.OH && oj < P.OW;
+            }
+            o[f] = P.out + (there ? (size_t)oi + (size_t)P.OH * oj + (size_t)OHW * (ch + (size_t)P.Ktot * n) : 0);
+            if (there && not_finite(*(const volatile float *)o[f])) need |= 1u << f;
+            s[f] = P.bias && there ? P.bias[ch] : 0.f;
+        }
+        if (need == 0) continue;
+        plain_results<4, MERGED>(P, P.V, P.in, P.w, g, k0, io, jo, n, need, s);
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+            if (need >> f & 1) *o[f] = P.relu ? fmaxf(s[f], 0.f) : s[f];
+    }
+}
 
 // Weights for F23: [g][kt][unit][filter column][plane][octet][kk][8 channels]; a thread reads the three rows of one filter
 // column for two channels and writes all planes of their four combinations.
@@ -82,17 +237,17 @@ __global__ __launch_bounds__(256) void igemm_pack_f23_split_kernel(const float *
 }
 
 // MERGED: the stride phases of an input derivative side by side in the filter dimension (IgemmParams::mD).
-// WK x WP computing waves; each owns MK x MP tiles of 32 filters x 32 pixels.  wsrc: the caller's filter array.
+// WK x WP computing waves; each owns MK x MP tiles of 32 filters x 32 pixels.
 template <int WK, int WP, int MK, int MP, bool F23, bool MERGED>
 __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 3 : 2) void igemm_split_kernel(
-    IgemmParams P, const float *__restrict__ in, const float *__restrict__ wpk, const float *__restrict__ bias, float *out,
-    float *__restrict__ part, const float *__restrict__ wsrc) {
+    SplitParams P, const float *__restrict__ in, const float *__restrict__ wpk, const float *__restrict__ bias, float *out,
+    float *__restrict__ part) {
     constexpr int NT = 64 * WK * WP;               // computing threads
     constexpr int NL = 64 * SPLIT_STAGE_WAVES;     // staging threads
     constexpr int TK = WK * MK * 32;
     constexpr int TQ = WP * MP * 32;
     constexpr int ROWS = F23 ? 2 : 1;              // input rows of a slab sample; output rows of a pixel
-    constexpr int SETS = F23 ? 2 : 3;
+    constexpr int EPT = split_ept(F23), SETS = F23 ? 2 : 3;
     const int NU = P.NU;
     const int CP = P.CP, SRP = P.SRP;
     const int XSZ = 3 * 2 * CP * 4;      // 32-bit words of slab per buffer: 3 planes x 2 octets x CP samples x 16 bytes
@@ -134,14 +289,14 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         // computed in less time than a sample takes from memory.  What a unit does not have is requested
         // out of range and reads as zero: no divergent branches, so that the waits for a set leave younger ones in flight.
         struct Samples {
-            float v[SPLIT_EPT_MAX][ROWS][BF_DC];
+            float v[EPT][ROWS][BF_DC];
             int uu, kt, g, seq, combo;
         };
         Samples set[SETS];
         const int ltid = tid - NT, lwave = wave - WK * WP;
         int t = n_own ? vb * P.own : t_s, uu = n_own ? 0 : uu_s, n = 0;      // next unit to request, units before it
         int kt = 0, g = 0, seq = -1;
-        unsigned go[SPLIT_EPT_MAX][F23 ? 4 : 1];    // byte offset of the thread's samples in channel 0, or SLAB_INVALID; F23: of the pair's four rows
+        unsigned go[EPT][F23 ? 4 : 1];    // byte offset of the thread's samples in channel 0, or SLAB_INVALID; F23: of the pair's four rows
         __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void *)in, 0, 0, BUFFER_FLAGS);
         auto set_tile = [&](int tile) __attribute__((always_inline)) {
             ++seq;
@@ -157,7 +312,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             if (in_left > 0x7fffffffull) in_left = 0x7fffffffull;
             xrs = __builtin_amdgcn_make_buffer_rsrc((void *)(in + in_base), 0, (int)in_left, BUFFER_FLAGS);
 #pragma unroll
-            for (int s = 0; s < SPLIT_EPT_MAX; ++s) {
+            for (int s = 0; s < EPT; ++s) {
                 const int e = ltid + NL * s;
                 const int col = div32(e, P.dSRP);
                 const int r = e - col * SRP;
@@ -175,7 +330,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             const int combo = uu & 3, c0 = (F23 ? uu >> 2 : uu) * BF_DC, c_end = n < nunits ? P.Cg : 0;
             q.uu = uu; q.kt = kt; q.g = g; q.seq = seq; q.combo = combo;
 #pragma unroll
-            for (int s = 0; s < SPLIT_EPT_MAX; ++s) {
+            for (int s = 0; s < EPT; ++s) {
                 if (s * NL >= CP) continue;
 #pragma unroll
                 for (int a = 0; a < ROWS; ++a) {
@@ -208,7 +363,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             float *xb = xbuf + slab * XSZ;
             slab = slab + 1 == SPLIT_SLABS ? 0 : slab + 1;
 #pragma unroll
-            for (int s = 0; s < SPLIT_EPT_MAX; ++s) {
+            for (int s = 0; s < EPT; ++s) {
                 const int e = ltid + NL * s;
                 if (lwave * 64 + NL * s >= CP) continue;         // CP is a multiple of 64
                 if constexpr (F23) {
@@ -300,7 +455,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                 const float bv = with_bias ? bl[kloc] : 0.f;
 #pragma unroll
                 for (int mp = 0; mp < MP; ++mp) {
-                    if constexpr (F23) { acc[mk][mp][v] = 0.f; row0[mk][mp][v] = bv; row1[mk][mp][v] = bv; }
+                    if constexpr (F23) { row0[mk][mp][v] = bv; row1[mk][mp][v] = bv; }
                     else { acc[mk][mp][v] = bv; small[mk][mp][v] = 0.f; }
                 }
             }
@@ -314,9 +469,9 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             for (int mp = 0; mp < MP; ++mp)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    row0[mk][mp][v] = fmaf(s0, acc[mk][mp][v], row0[mk][mp][v]);
-                    row1[mk][mp][v] = fmaf(s1, acc[mk][mp][v], row1[mk][mp][v]);
-                    acc[mk][mp][v] = 0.f;
+                    const float m = acc[mk][mp][v];
+                    row0[mk][mp][v] = fmaf(s0, m, row0[mk][mp][v]);
+                    row1[mk][mp][v] = fmaf(s1, m, row1[mk][mp][v]);
                 }
     };
     const int aoff = 16 * (half * TK + wk * MK * 32 + (lane & 31));   // bytes
@@ -354,21 +509,21 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
 #pragma unroll
         for (int mp = 0; mp < MP; ++mp) b[mp] = *reinterpret_cast<const bf16x8 *>(xlane + bbase[mp] + (xo + so + pl * xplane));
     };
-    auto mma = [&](floatx16 (&sum)[MK][MP], const OpA &a, const OpB &b) __attribute__((always_inline)) {
+    auto mma = [&](floatx16 (&sum)[MK][MP], const OpA &a, const OpB &b, bool from_zero = false) __attribute__((always_inline)) {
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)
 #pragma unroll
             for (int mp = 0; mp < MP; ++mp)
-                sum[mk][mp] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mk], b[mp], sum[mk][mp], 0, 0, 0);
+                sum[mk][mp] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mk], b[mp], from_zero ? floatx16{} : sum[mk][mp], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto prime = [&]() __attribute__((always_inline)) {
         load_a(ah, 0); load_b(bl, 2); load_b(bm, 1); load_b(bh, 0); load_a(am, 1); load_a(al, 2);
     };
     floatx16 (&lesser)[MK][MP] = F23 ? acc : small;
-    // one step; wo, xo, so are the next step's when it begins
-    auto step = [&]() __attribute__((always_inline)) {
-        mma(lesser, ah, bl);
+    // one step; wo, xo, so are the next step's when it begins; first: the first one of a combination's sums (F23)
+    auto step = [&](bool first) __attribute__((always_inline)) {
+        mma(lesser, ah, bl, F23 && first);
         load_b(bl, 2);
         mma(lesser, ah, bm);
         mma(acc, ah, bh);
@@ -383,45 +538,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // An operand that is infinite splits into (inf, nan, nan), so every result that it enters comes out as NaN where the
-    // plain sum may say +-inf (and one within 2^-9 of the largest float rounds to inf in its hi plane).  A tile with a
-    // result that is not finite is gone over again once it is stored: such results are summed one by one from the arrays
-    // in memory (plain_result).  The ReLU must not hide them before: they are stored as NaN.
-    bool odd_results = false;
-    auto repair_tile = [&](int t) __attribute__((always_inline)) {
-        int kt, pt, rb, g;
-        decode_tile(P, t, &kt, &pt, &rb, &g);
-        __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);       // this wave reads back what it stored
-#pragma unroll 1
-        for (int mp = 0; mp < MP; ++mp) {
-            const int q = pt * TQ + (wp * MP + mp) * 32 + (lane & 31);
-            const int c = div32(q, P.dTI);
-            const int n = div32(c, P.dWo);
-            const int jo = c - n * P.Wo, io = rb * P.TI + q - c * P.TI;
-            if (q >= P.QN || io >= P.Ho) continue;
-#pragma unroll 1
-            for (int v = 0; v < MK * 16; ++v) {
-                const int kl = kt * TK + (wk * MK + (v >> 4)) * 32 + ((v & 15) >> 2) * 8 + half * 4 + (v & 3);
-                if (kl >= P.Kg) continue;
-                if constexpr (MERGED) {
-                    const MergedFilter f = merged_filter(P, kl);
-                    const int oi = f.i0 + P.osi * io, oj = f.j0 + P.osj * jo;
-                    if (oi >= P.OH || oj >= P.OW) continue;
-                    float *o = out + (size_t)oi + (size_t)P.OH * oj + (size_t)OHW * (g * P.mD + f.c + (size_t)P.Ktot * n);
-                    if (not_finite(*(volatile float *)o)) *o = plain_result<true>(P, P.Hf, P.Sh, in, wsrc, bias, g, kl, io, jo, n);
-                    continue;
-                }
-                for (int row = 0; row < ROWS; ++row) {
-                    const int ior = ROWS * io + row;           // row of the view
-                    if (F23 && ior >= P.wino_Ho) continue;
-                    float *o = out + (size_t)(P.oi0 + P.osi / ROWS * ior) + (size_t)P.OH * (P.oj0 + P.osj * jo) +
-                               (size_t)OHW * (g * P.Kg + kl + (size_t)P.Ktot * n);
-                    if (not_finite(*(volatile float *)o))
-                        *o = plain_result<false>(P, F23 ? 3 : P.Hf, F23 ? 1 : P.Sh, in, wsrc, bias, g, kl, ior, jo, n);
-                }
-            }
-        }
-    };
+    bool odd_results = false;        // of the lane in the tile just stored: some are not finite (repair_tile)
     auto store_tile = [&]() __attribute__((always_inline)) {
         odd_results = false;
 #pragma unroll
@@ -519,22 +636,38 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         set_tile(tile_of(t));
         wo = (unsigned)(((c_g * P.KT + c_kt) * NU + uu) * T) * (unsigned)WSTEP;
         fi = 0; so = 0; xo = xslab;
-        for (int u = 0; u < m; ++u) {
-            // This unit's slab and the next one's are in place.  The reads still in flight are of this unit's slab, which
-            // is written again two barriers later: nothing to wait for.
-            asm volatile("s_barrier" ::: "memory");
-            if (u == 0) { init_acc(whole && bias != nullptr); prime(); }
+        // This unit's slab and the next one's are in place.  The reads still in flight are of this unit's slab, which
+        // is written again two barriers later: nothing to wait for.
+        asm volatile("s_barrier" ::: "memory");
+        // not inside the loop: no sum is then alive (in registers) between two segments
+        init_acc(whole && bias != nullptr);
+        prime();
+        for (int u = 0;;) {
             __builtin_amdgcn_sched_barrier(0);
             for (int s = 1; s < T; ++s) {
                 wo += WSTEP;
                 next_tap();
-                step();
+                step(s == 1);
             }
             next_slab();
             if (u + 1 < m) { wo += WSTEP; fi = 0; so = 0; xo = xslab; }
-            step();                                // the segment's last one reads its own operands again, for nothing
-            if constexpr (F23) fold((uu + u) & 3);
+            step(false);                           // the segment's last one reads its own operands again, for nothing
+            if constexpr (F23) {
+                fold((uu + u) & 3);
+                // before the barrier, where waves wait for one another anyway: the compiler would move it behind (14x14x512,
+                // 3x3x512x512, 32 images: 209 against 189 us)
+#pragma unroll
+                for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+                    for (int mp = 0; mp < MP; ++mp) asm volatile("" : "+v"(row0[mk][mp]), "+v"(row1[mk][mp]));
+            }
+            if (++u == m) break;
+            asm volatile("s_barrier" ::: "memory");
         }
+        // a use of what the last step read for nothing: without one the compiler moves the weights' loads of every unit's last step
+        // behind its products, where their latency is not hidden
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk) asm volatile("" ::"v"(ah[mk]), "v"(am[mk]), "v"(al[mk]));
         done += m;
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)
@@ -543,7 +676,10 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         if (whole) {
             if constexpr (MERGED) store_tile_merged();
             else store_tile();
-            if (__any(odd_results)) repair_tile(tile_of(t));
+            if (__any(odd_results)) {
+                const size_t params = (size_t)__builtin_amdgcn_kernarg_segment_ptr();
+                repair_tile<TK, WK, MK, MP, TQ, ROWS, MERGED>((unsigned)params, (unsigned)(params >> 32), tile_of(t), wave);
+            }
         } else {
             store_partial(2 * vb + (first_segment ? 0 : 1));
         }

@@ -187,7 +187,7 @@ int launch_igemm_inst(const IgemmPlan &pl, const float *in, const float *wpk, co
     // no tile is shared; tiles of a single unit cannot be cut, so every block's range holds whole tiles
     if (st || P.nblocks < 2 || P.own * P.nblocks == P.tiles || P.NU == 1) return st;
     constexpr int TK = WK * MK * 32, TQ = WP * MP * 32;
-    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, nullptr, nullptr);
+    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, KeepResults());
     return check_launch();
 }
 
@@ -213,7 +213,7 @@ int launch_igemm_wino(const IgemmPlan &pl, const float *in, const float *wpk, co
     IgemmParams F = P;
     F.TI = 2 * P.TI; F.QN = 2 * P.QN; F.Ho = P.wino_Ho; F.osi = P.osi / 2;
     F.dTI = make_div32(F.TI);
-    hipLaunchKernelGGL((igemm_fixup_kernel<TK, 2 * TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, F, part, bias, out, nullptr, nullptr);
+    hipLaunchKernelGGL((igemm_fixup_kernel<TK, 2 * TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, F, part, bias, out, KeepResults());
     return check_launch();
 }
 
@@ -241,7 +241,7 @@ int launch_igemm_bf16_inst(const IgemmPlan &pl, const float *in, const float *wp
     // no tile is shared; tiles of a single unit cannot be cut, so every block's range holds whole tiles
     if (st || P.nblocks < 2 || P.own * P.nblocks == P.tiles || P.NU == 1) return st;
     constexpr int TK = WK * MK * 32, TQ = WP * MP * 32;
-    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, nullptr, nullptr);
+    hipLaunchKernelGGL((igemm_fixup_kernel<TK, TQ>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, KeepResults());
     return check_launch();
 }
 
@@ -253,7 +253,9 @@ int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, c
         if (pl.P.mD) return launch_igemm_split<WK, WP, MK, MP, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
     if constexpr (!F23 && !MERGED && WK * MK == 4)       // row pairs: tiles of 128 filters
         if (pl.P.wino_Ho) return launch_igemm_split<WK, WP, MK, MP, true>(pl, in, wpk, bias, out, part, s, relu, w);
-    IgemmParams P = pl.P;
+    SplitParams P;
+    (IgemmParams &)P = pl.P;
+    P.V = pl.V; P.in = in; P.w = w; P.bias = bias; P.out = out;
     P.relu = relu;
     P.wino_pairs = F23 && P.osi == 2 && P.OH % 2 == 0 && ((uintptr_t)out & 7) == 0;
     auto kern = igemm_split_kernel<WK, WP, MK, MP, F23, MERGED>;
@@ -262,15 +264,16 @@ int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, c
                                            (int)pl.lds_bytes);
         if (e != hipSuccess) { g_last_hip_error = (int)e; return MCN_HIP_ERROR; }
     }
-    hipLaunchKernelGGL(kern, dim3(P.nblocks), dim3(64 * (WK * WP + SPLIT_STAGE_WAVES)), pl.lds_bytes, s, P, in, wpk, bias, out, part, w);
+    hipLaunchKernelGGL(kern, dim3(P.nblocks), dim3(64 * (WK * WP + SPLIT_STAGE_WAVES)), pl.lds_bytes, s, P, in, wpk, bias, out, part);
     int st = check_launch();
     if (st || P.nblocks < 2 || P.own * P.nblocks == P.tiles || P.NU == 1) return st;      // no tile is shared
     constexpr int TK = WK * MK * 32, TQ = WP * MP * 32;
     if constexpr (F23) {        // the fix-up pass sees rows instead of pairs
-        P.TI *= 2; P.QN *= 2; P.Ho = P.wino_Ho; P.osi /= 2; P.Hf = 3; P.Sh = 1; P.NU /= 4;
+        P.TI *= 2; P.QN *= 2; P.Ho = P.wino_Ho; P.osi /= 2; P.NU /= 4;
         P.dTI = make_div32(P.TI);
     }
-    hipLaunchKernelGGL((igemm_fixup_kernel<TK, F23 ? 2 * TQ : TQ, true>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, P, part, bias, out, in, w);
+    hipLaunchKernelGGL((igemm_fixup_kernel<TK, F23 ? 2 * TQ : TQ, PlainPixels>), dim3(P.tiles - P.own * P.nblocks, IGEMM_FIXUP_SLICES), dim3(256), 0, s, (const IgemmParams &)P, part, bias, out,
+                       (PlainPixels{P.V, in, w}));
     return check_launch();
 }
 

@@ -87,6 +87,50 @@ def test_values_that_are_not_finite_or_nearly_so(relu, shape):
     assert float(((y.double() - ref)[ok].abs() / den[ok]).max()) <= 1e-5
 
 
+@pytest.mark.parametrize("where", ["weight", "bias"])
+@pytest.mark.parametrize("shape", [(9, 10, 20, 2, 48, 5), (40, 40, 32, 16, 70, 5), (14, 13, 256, 2, 96, 3)])      # as above
+def test_weights_and_biases_that_are_not_finite(where, shape):
+    """An infinite weight or bias reaches every result of its filter (no pads: each meets all of the filter) and no other."""
+    H, W, D, N, K, f = shape
+    L = custom_layer(H, W, D, N, f, f, D, K, (1, 1), (0, 0, 0, 0), idx=831)
+    x, w, b = synth.make_x(L), synth.make_w(L), synth.make_b(L)
+    if where == "weight":
+        w[3, 2, 1, 0], w[K - 1, D - 1, f - 1, f - 1], w[5, 0, 0, 0] = float("inf"), float("-inf"), float("nan")
+    else:
+        b[3], b[K - 1], b[5] = float("inf"), float("-inf"), float("nan")
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), b.double())
+    y = B.conv_forward(x.cuda(), w.cuda(), b.cuda()).cpu()
+    assert torch.equal(torch.isnan(y), torch.isnan(ref)) and torch.equal(torch.isinf(y), torch.isinf(ref))
+    inf = torch.isinf(ref)
+    assert int(inf.sum()) == 2 * N * ref.shape[2] * ref.shape[3] and torch.equal(y[inf].double(), ref[inf])
+
+
+def test_results_that_are_not_finite_do_not_hold_up_the_call():
+    """27x27x96, 5x5x48x256 in two groups, 128 images.  Measured: 3.8, 5.1 and 2.4 times an ordinary call; one result after another,
+    each to the end of its sum, 15, 16 and 97 times.  Bounds between the two."""
+    x, w = torch.randn(128, 96, 27, 27, device="cuda"), torch.randn(256, 48, 5, 5, device="cuda") * 0.03
+    out = torch.empty(128, 256, 27, 27, device="cuda")
+
+    def best():
+        t = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record(); B.conv_forward(x, w, None, (1, 1), (2, 2, 2, 2), out=out); b.record(); b.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t)
+
+    ordinary, got = best(), {}
+    kept = float(x[0, 0, 3, 3])
+    for name, bound in (("nan", 10), ("inf", 12)):
+        x[0, 0, 3, 3] = float(name)
+        got[name] = (best() / ordinary, bound)
+    x[0, 0, 3, 3] = kept
+    x.fill_(float("nan"))
+    got["all nan"] = (best() / ordinary, 12)
+    print("three planes, not finite:", got, flush=True)
+    assert all(t <= bound for t, bound in got.values()), got
+
+
 @pytest.mark.parametrize("N", [2, 40])      # shared tiles; whole tiles
 def test_infinite_derivative_in_merged_phases(N):
     """dzdx of a strided first layer: an infinite dzdy reaches the samples of its window and no others."""

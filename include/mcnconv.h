@@ -77,9 +77,11 @@ typedef struct mcn_conv_desc {
  *   Forward and dzdx of other filter sizes (two taps or more, at least 16 channels per group), and of
  *   3x3 layers with at least 256 channels and few tiles, run on the bf16 matrix core with every operand
  *   held as THREE bf16 values whose sum it is exactly, and six products accumulated in fp32 (what is left
- *   out is below 2^-26 of |w||x|): the error measures as on the fp32 matrix core or less.  Operands
- *   below about 1e-35 lose their last bits.  Results that are not finite there are summed again one by one
- *   in fp32, so infinities and NaN come out as the plain sum gives them, but slowly.
+ *   out is below 2^-26 of |w||x|): the error measures as on the fp32 matrix core or less, for operands of every
+ *   size (a product with an operand below the smallest normal number, 1.2e-38, may be off by 2^-150 of the
+ *   other one, half of the smallest fp32 number).  Results that are not finite there are summed again in
+ *   fp32, so infinities and NaN come out as the plain sum gives them: NaN at little cost, an infinite operand
+ *   in about a millisecond, infinite results everywhere at some thirty times the time of an ordinary call.
  * MCN_PREC_FP32_PLAIN: fp32 operands and accumulation, every product of the sum of Sec. 4.1
  *   formed as written, in fp32, and added one by one ("igemm" / "wgrad_igemm"): error bound n * 2^-24
  *   of the result's own sum of |w||x|; 3x3 stride-1 layers run about 1.3 times slower.

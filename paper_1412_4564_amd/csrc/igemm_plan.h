@@ -511,7 +511,7 @@ inline bool plan_igemm(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf16 = f
         for (int f = 0; f < SPLIT_N_SHAPES; ++f) {
             const int TK = SPLIT_SHAPES[f].WK * SPLIT_SHAPES[f].MK * 32;
             if (TK == 32 ? v.Kg > 32 : v.Kg <= TK / 2) continue;      // half of the tile would be empty
-            if (pairs && TK != 128) continue;
+            if (pairs && SPLIT_SHAPES[f].shape != IG_S128x64) continue;     // three sums and two rows per pair: registers for no larger tile
             IgemmPlan one;
             if (plan_igemm_kind(pairs ? pv : v, n_cu, &one, true, 0, false, pairs ? v.Ho : 0, 3, f) && (!ok || one.score < pl->score)) { *pl = one; ok = true; }
         }

@@ -54,14 +54,18 @@ __device__ inline void split_bf16x2(float v0, float v1, unsigned *hi, unsigned *
     *lo = pack_bf16x2(v0 - __uint_as_float(h << 16), v1 - __uint_as_float(h & 0xffff0000u));
 }
 
-// three planes of a pair: hi = bf16(v), mid = bf16(v - hi), lo = v - hi - mid.  Both differences are exact in fp32 and the
-// last one has at most 8 significant bits left, so the three planes together are v itself (while lo stays above the
-// smallest bf16 number: |v| from about 1e-35 on; below that lo loses its last bits).
+// three planes of a pair, v = hi + mid / 2^8 + lo / 2^16: hi = bf16(v), mid = bf16(2^8 (v - hi)), lo = 2^8 (2^8 (v - hi) - mid).
+// The differences are exact in fp32 and the last one has at most 8 significant bits left, so the three planes together are v
+// itself.  The powers of two bring mid and lo back to the size of v: bf16 has the exponents of fp32 and no smaller numbers, so
+// unscaled they would lose the last bits of every |v| below 2^-110; scaled they are exact for every finite v down to 2^-149
+// (multiples of 2^-133, the smallest number of bf16).
 __device__ inline void split_bf16x3(float v0, float v1, unsigned *hi, unsigned *mid, unsigned *lo) {
     const unsigned h = pack_bf16x2(v0, v1);
-    const float r0 = v0 - __uint_as_float(h << 16), r1 = v1 - __uint_as_float(h & 0xffff0000u);
+    const float r0 = (v0 - __uint_as_float(h << 16)) * 256.f, r1 = (v1 - __uint_as_float(h & 0xffff0000u)) * 256.f;
     *hi = h;
-    split_bf16x2(r0, r1, mid, lo);
+    const unsigned m = pack_bf16x2(r0, r1);
+    *mid = m;
+    *lo = pack_bf16x2((r0 - __uint_as_float(m << 16)) * 256.f, (r1 - __uint_as_float(m & 0xffff0000u)) * 256.f);
 }
 
 // packed[g][kt][unit][step][plane][octet][kk][8 channels] as bf16 (PLANES = 1: the values rounded to bf16; 2: their hi and

@@ -1,13 +1,15 @@
 // Implicit-GEMM convolution of fp32 operands on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16).
 //
 // The sum is that of kern_igemm.h (MatConvNet manual, arXiv 1412.4564, Sec. 4.1), in fp32 precision: every operand v is
-// held on chip as three bf16 planes, v = hi + mid + lo exactly (split_bf16x3), and a product is formed as
-//   w_lo*x_hi + w_mid*x_hi + w_hi*x_hi + w_mid*x_mid + w_hi*x_mid + w_hi*x_lo
+// held on chip as three bf16 planes, v = hi + mid / 2^8 + lo / 2^16 exactly (split_bf16x3), and a product is formed as
+//   w_hi*x_hi + (w_hi*x_mid + w_mid*x_hi) / 2^8 + (w_mid*x_mid + w_lo*x_hi + w_hi*x_lo) / 2^16
 // with fp32 accumulation.  Each product of two bf16 numbers is exact in fp32 and what is left out (w_mid*x_lo and
-// smaller) is below 2^-26 of |w||x|, less than the rounding of one fp32 multiply-add.  The five small products have
-// accumulators of their own, added at the end: an MFMA rounds its sum four times on the way through its 16 elements, and
-// with all six products in one sum the results are 1.2 times as far from sums in 64 bits as those of the fp32
-// instructions (24 roundings per 16 elements against 16); the roundings of the small sum cost nothing.  Six products on a matrix core that multiplies 16 times as fast as in fp32 cost 6/16 of the fp32 kernel's matrix time.
+// smaller) is below 2^-26 of |w||x|, less than the rounding of one fp32 multiply-add.  The three scales have accumulators of
+// their own, put together at the end: the planes can then carry operands of every size (split_bf16x3), and an MFMA rounds its
+// sum four times on the way through its 16 elements: with all six products in one sum the results are 1.2 times as far from
+// sums in 64 bits as those of the fp32 instructions (24 roundings per 16 elements against 16); the roundings of the scaled
+// sums cost nothing.  Six products on a matrix core that multiplies 16 times as fast as in fp32 cost 6/16 of the fp32 kernel's
+// matrix time.
 //
 // Tiling, pixel numbering, schedule and fix-up pass: kern_igemm.h.  One MFMA takes 16 channels of one tap, a lane's operand
 // is 16 consecutive bytes: slab [plane][octet][column][row][8 channels] in LDS, weights
@@ -408,9 +410,11 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     int edge[MP];        // merged phases: 1 = last row of the view, 2 = last column
     __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc((void *)out, 0, 0, BUFFER_FLAGS);
     int c_kt = 0, c_g = 0, c_seq = -1;
-    // F23 = false: sums of the hi x hi products, and of the five others; F23: the current combination's sum, and the rows'
-    floatx16 acc[MK][MP], small[MK][MP], row1[F23 ? MK : 1][MP];
-    floatx16 (&row0)[MK][MP] = small;
+    // sums of the products of the three scales (F23: of the current combination), and F23: the rows'
+    floatx16 acc[MK][MP], sum8[MK][MP], sum16[MK][MP], row0[F23 ? MK : 1][MP], row1[F23 ? MK : 1][MP];
+    auto whole_sum = [&](int mk, int mp, int v) __attribute__((always_inline)) {
+        return fmaf(fmaf(sum16[mk][mp][v], 0x1p-8f, sum8[mk][mp][v]), 0x1p-8f, acc[mk][mp][v]);
+    };
     auto set_tile = [&](int t) __attribute__((always_inline)) {
         ++c_seq;
         int kt, pt, rb, g;
@@ -456,7 +460,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
 #pragma unroll
                 for (int mp = 0; mp < MP; ++mp) {
                     if constexpr (F23) { row0[mk][mp][v] = bv; row1[mk][mp][v] = bv; }
-                    else { acc[mk][mp][v] = bv; small[mk][mp][v] = 0.f; }
+                    else { acc[mk][mp][v] = bv; sum8[mk][mp][v] = sum16[mk][mp][v] = 0.f; }
                 }
             }
     };
@@ -469,7 +473,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             for (int mp = 0; mp < MP; ++mp)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const float m = acc[mk][mp][v];
+                    const float m = whole_sum(mk, mp, v);
                     row0[mk][mp][v] = fmaf(s0, m, row0[mk][mp][v]);
                     row1[mk][mp][v] = fmaf(s1, m, row1[mk][mp][v]);
                 }
@@ -520,19 +524,18 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     auto prime = [&]() __attribute__((always_inline)) {
         load_a(ah, 0); load_b(bl, 2); load_b(bm, 1); load_b(bh, 0); load_a(am, 1); load_a(al, 2);
     };
-    floatx16 (&lesser)[MK][MP] = F23 ? acc : small;
     // one step; wo, xo, so are the next step's when it begins; first: the first one of a combination's sums (F23)
     auto step = [&](bool first) __attribute__((always_inline)) {
-        mma(lesser, ah, bl, F23 && first);
+        mma(sum16, ah, bl, F23 && first);
         load_b(bl, 2);
-        mma(lesser, ah, bm);
-        mma(acc, ah, bh);
+        mma(sum8, ah, bm, F23 && first);
+        mma(acc, ah, bh, F23 && first);
         load_a(ah, 0);
-        mma(lesser, am, bm);
+        mma(sum16, am, bm);
         load_b(bm, 1);
-        mma(lesser, am, bh);
+        mma(sum8, am, bh);
         load_a(am, 1);
-        mma(lesser, al, bh);
+        mma(sum16, al, bh);
         load_b(bh, 0);
         load_a(al, 2);
         __builtin_amdgcn_sched_barrier(0);
@@ -672,7 +675,9 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)
 #pragma unroll
-            for (int mp = 0; mp < (F23 ? 0 : MP); ++mp) acc[mk][mp] += small[mk][mp];
+            for (int mp = 0; mp < (F23 ? 0 : MP); ++mp)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[mk][mp][v] = whole_sum(mk, mp, v);
         if (whole) {
             if constexpr (MERGED) store_tile_merged();
             else store_tile();

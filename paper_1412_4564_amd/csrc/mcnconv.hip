@@ -251,8 +251,8 @@ int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, c
                        float *part, hipStream_t s, int relu, const float *w) {
     if constexpr (!F23 && !MERGED)
         if (pl.P.mD) return launch_igemm_split<WK, WP, MK, MP, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
-    if constexpr (!F23 && !MERGED && WK * MK == 4)       // row pairs: tiles of 128 filters
-        if (pl.P.wino_Ho) return launch_igemm_split<WK, WP, MK, MP, true>(pl, in, wpk, bias, out, part, s, relu, w);
+    if constexpr (!F23 && !MERGED && WK * MK == 4 && MP == 1)       // row pairs: the same tile on half the waves, twice as much each
+        if (pl.P.wino_Ho) return launch_igemm_split<WK, WP / 2, MK, 2 * MP, true>(pl, in, wpk, bias, out, part, s, relu, w);
     SplitParams P;
     (IgemmParams &)P = pl.P;
     P.V = pl.V; P.in = in; P.w = w; P.bias = bias; P.out = out;

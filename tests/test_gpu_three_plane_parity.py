@@ -157,3 +157,19 @@ def test_scales(scale):
     den = torch.nn.functional.conv2d(x.double().abs(), w.double().abs(), padding=2)
     y = B.conv_forward(x.cuda(), w.cuda(), None, (1, 1), (2, 2, 2, 2)).cpu().double()
     assert float(((y - ref).abs() / den).max()) <= BOUND
+
+
+@pytest.mark.parametrize("sx,sw", [(1e-34, 1), (1e-36, 1), (1e-37, 1), (1, 1e-37), (1e-37, 1e30), (1e30, 1e-37)])
+@pytest.mark.parametrize("shape", [(14, 13, 32, 2, 64, 5), (14, 14, 256, 2, 96, 3)])       # any filter; row pairs
+def test_operands_down_to_the_smallest_normal_number(sx, sw, shape):
+    """The planes are scaled (split_bf16x3): operands of every size are held exactly.  Unscaled the last plane of an operand of
+    1e-36 loses its bits (error 1e-5)."""
+    H, W, D, N, K, f = shape
+    L = custom_layer(H, W, D, N, f, f, D, K, (1, 1), (f // 2,) * 4, idx=841)
+    x, w = synth.make_x(L) * sx, synth.make_w(L) * sw
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), padding=f // 2)
+    den = torch.nn.functional.conv2d(x.double().abs(), w.double().abs(), padding=f // 2)
+    y = B.conv_forward(x.cuda(), w.cuda(), None, (1, 1), (f // 2,) * 4).cpu().double()
+    err = float(((y - ref).abs() / den).max())
+    print("three planes, small operands:", shape, sx, sw, err, flush=True)
+    assert err <= BOUND

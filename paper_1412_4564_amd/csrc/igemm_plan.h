@@ -314,7 +314,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         if ((double)span * v.Ctot * v.H * v.W * 4.0 >= 2147483647.0) continue;
         if ((double)(span + 1) * v.Ktot * v.OH * v.OW * 4.0 >= 2147483647.0) continue;   // and inside its output window
         const int EPT = (int)((CP + NL - 1) / NL);
-        const size_t fixed_lds = ((planes == 3 ? 0 : (size_t)EPT * NL) + (planes == 3 ? SPLIT_BIASES : 2) * TK + 4) * 4;
+        const size_t fixed_lds = ((planes == 3 ? 0 : (size_t)EPT * NL) + (planes == 3 ? (v.mD ? 3 : 1) * SPLIT_BIASES : 2) * TK + 4) * 4;
         UnitCut uc;
         if (f23s) {
             uc.pair_mode = 0; uc.DC = BF_DC; uc.TC = 3; uc.NTR = 1; uc.NS = 3;
@@ -440,7 +440,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     pl->shape = shape; pl->bf16 = bf16; pl->planes = bf16 ? planes : 1; pl->fixed = fixed; pl->TK = TK; pl->TQ = TQ; pl->NT = NT;
     pl->score = best_score;
     if (planes == 3)
-        pl->lds_bytes = ((size_t)SPLIT_BIASES * TK + (size_t)SPLIT_SLABS * 6 * P.CP * 4 + 4) * sizeof(float);
+        pl->lds_bytes = ((size_t)(v.mD ? 3 : 1) * SPLIT_BIASES * TK + (size_t)SPLIT_SLABS * 6 * P.CP * 4 + 4) * sizeof(float);
     else if (bf16)
         pl->lds_bytes = (2 * wsz + 2 * (size_t)planes * 2 * P.CP * 4 + (size_t)P.EPT * NL + 2 * TK + 4) *
                         sizeof(float);

@@ -257,6 +257,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     extern __shared__ __align__(16) float lds[];
     float *xbuf = lds;                                              // [SLABS][XSZ]
     float *blds = xbuf + SPLIT_SLABS * XSZ;        // [BIASES][TK] bias of the tile, slots used in turn
+    int2 *mlds = reinterpret_cast<int2 *>(blds + SPLIT_BIASES * TK);      // MERGED: [BIASES][TK] where the tile's filters go, see store_tile_merged
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -357,10 +358,17 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         };
         int slab = 0;
         auto write = [&](Samples &q) __attribute__((always_inline)) {
-            if (q.uu == 0 && bias && ltid < TK) {    // start value of a tile this block owns entirely
-                const int kl = q.kt * TK + ltid;
-                const int ch = MERGED ? q.g * P.mD + merged_filter(P, kl).c : q.g * P.Kg + kl;
-                blds[(q.seq & (SPLIT_BIASES - 1)) * TK + ltid] = kl < P.Kg ? bias[ch] : 0.f;
+            if (q.uu == 0 && (MERGED || bias) && ltid < TK) {    // of a tile this block may own entirely: start values, and where filters go
+                const int kl = q.kt * TK + ltid, at = (q.seq & (SPLIT_BIASES - 1)) * TK + ltid;
+                int ch = q.g * P.Kg + kl;
+                if constexpr (MERGED) {
+                    const MergedFilter f = merged_filter(P, kl < P.Kg ? kl : 0);
+                    ch = q.g * P.mD + f.c;
+                    // 1: this phase has no last row, 2: no last column, 4: no such filter
+                    const int missing = (f.i0 + P.osi * (P.Ho - 1) >= P.OH ? 1 : 0) | (f.j0 + P.osj * (P.Wo - 1) >= P.OW ? 2 : 0) | (kl < P.Kg ? 0 : 4);
+                    mlds[at] = int2{4 * (ch * OHW + f.i0 + P.OH * f.j0), missing};
+                }
+                if (bias) blds[at] = kl < P.Kg ? bias[ch] : 0.f;
             }
             float *xb = xbuf + slab * XSZ;
             slab = slab + 1 == SPLIT_SLABS ? 0 : slab + 1;
@@ -582,32 +590,24 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         }
     };
     // Merged phases: the two half-waves hold filters of different phases, so the filter part of the address and the "does
-    // this pixel exist in this phase" test are per half-wave (as in igemm_sk_kernel).
+    // this pixel exist in this phase" test are per half-wave.  Both come from a table that the staging waves write, one filter a
+    // thread: found here, by each wave for all of its filters, they were thousands of instructions of divisions a tile (dzdx of
+    // 37x53x16, 3x5x16x24 at stride 2x3, four images: 26.1 -> 14.0 us; of 227x227x3, 11x11x3x96 at stride 4, 128 images: 293 -> 235).
     auto store_tile_merged = [&]() __attribute__((always_inline)) {
         odd_results = false;
+        const int2 *table = mlds + (c_seq & (SPLIT_BIASES - 1)) * TK + wk * MK * 32 + half * 4;
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int kl0 = c_kt * TK + (wk * MK + mk) * 32 + (v >> 2) * 8 + (v & 3);
-                if (kl0 >= P.Kg) continue;
-                unsigned foff[2];
-                int missing[2];                    // 1: this phase has no last row, 2: no last column, 4: no such filter
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int kl = kl0 + 4 * h;
-                    const MergedFilter f = merged_filter(P, kl < P.Kg ? kl : 0);
-                    foff[h] = 4u * (unsigned)((c_g * P.mD + f.c) * OHW + f.i0 + P.OH * f.j0);
-                    missing[h] = (f.i0 + P.osi * (P.Ho - 1) >= P.OH ? 1 : 0) | (f.j0 + P.osj * (P.Wo - 1) >= P.OW ? 2 : 0) | (kl < P.Kg ? 0 : 4);
-                }
-                const unsigned fo = half ? foff[1] : foff[0];
-                const int miss = half ? missing[1] : missing[0];
+                if (c_kt * TK + (wk * MK + mk) * 32 + (v >> 2) * 8 + (v & 3) >= P.Kg) continue;
+                const int2 f = table[mk * 32 + (v >> 2) * 8 + (v & 3)];
 #pragma unroll
                 for (int mp = 0; mp < MP; ++mp) {
-                    const bool drop = (miss & (edge[mp] | 4)) != 0 || ooff[mp] == SLAB_INVALID;
+                    const bool drop = (f.y & (edge[mp] | 4)) != 0 || ooff[mp] == SLAB_INVALID;
                     const float val = acc[mk][mp][v];
                     odd_results |= !drop && not_finite(val);
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), ors, drop ? SLAB_INVALID : ooff[mp] + fo, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(val), ors, drop ? SLAB_INVALID : ooff[mp] + (unsigned)f.x, 0, 0);
                 }
             }
     };

@@ -1,0 +1,59 @@
+"""Forward and dzdx in the default precision take no longer than on the fp32 matrix core (the same calls under
+MCN_PREC_FP32_PLAIN, which differ in nothing else where there are no row pairs): the smallest layers, where a tile is all
+there is.  GPU time of graph replays, the two in turn."""
+import statistics
+
+import pytest
+import torch
+
+from paper_1412_4564_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def replay_time(call, reps=20):
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(reps):
+            call()
+
+    def once():
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record(); g.replay(); b.record(); b.synchronize()
+        return a.elapsed_time(b) * 1e3 / reps
+    return once
+
+
+def both_precisions(layer, op):
+    """Microseconds under the default and under the plain order of summation."""
+    H, W, D, N, Hf, Wf, Df, K, stride, pad = layer
+    x, w = torch.randn(N, D, W, H, device="cuda"), torch.randn(K, Df, Wf, Hf, device="cuda")
+    y, ws = B.conv_forward(x, w, None, stride, pad), B.Workspace()
+    out = y if op == "forward" else torch.empty_like(x)
+    timers = []
+    for precision in (B.MCN_PREC_FP32, B.MCN_PREC_FP32_PLAIN):
+        def call(precision=precision):
+            if op == "forward":
+                B.conv_forward(x, w, None, stride, pad, precision, out=out, workspace=ws)
+            else:
+                B.conv_backward_data(x.shape, w, y, stride, pad, precision, out=out, workspace=ws)
+        call()                                   # the workspace grows to the larger of the two before any graph holds it
+        timers.append(call)
+    timers = [replay_time(c) for c in timers]
+    t = [[f() for f in timers] for _ in range(9)]
+    return statistics.median(a for a, _ in t), statistics.median(b for _, b in t)
+
+
+MERGED = [  # dzdx in one launch of all stride phases
+    (37, 53, 16, 4, 3, 5, 16, 24, (2, 3), (1, 0, 2, 1)),
+    (13, 33, 5, 5, 3, 4, 5, 32, (3, 2), (1, 1, 1, 1)),
+]
+
+
+@pytest.mark.parametrize("case", range(len(MERGED)))
+def test_merged_phases(case):
+    t = both_precisions(MERGED[case], "dzdx")
+    print("merged phases, default and plain: %.1f %.1f us" % t, flush=True)
+    assert t[0] <= 1.15 * t[1], t                # 1.3 to 1.7 with the addresses of the filters found tile by tile

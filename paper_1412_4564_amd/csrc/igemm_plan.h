@@ -481,20 +481,53 @@ inline bool wino_enabled() {
     return !off;
 }
 
-// Whether an fp32 view takes the three-plane kernel (kern_igemm_split.h).  Not 1x1 filters: a
+// Views the three-plane kernel (kern_igemm_split.h) can take.  Not 1x1 filters: a
 // unit is then one step (768 cycles of MFMAs), and its staging (loads, split, barrier) takes longer (28x28x512, 1x1x512x128,
 // 64 images: forward 93 us against 78 on the fp32 kernel).
-inline bool split_pays(const ConvView &v) {
+inline bool split_possible(const ConvView &v) {
     return v.pack_mode != 2 && v.Cg >= BF_DC && v.Hf * v.Wf >= 2;
 }
 
-// Row pairs in three planes (kern_igemm_split.h, F23): deep layers whose plane and batch give at most half as many tiles of
-// 128 filters x 128 pairs as there are compute units.  Measured against the fp32 row-pair kernel (forward): 14x14, 512 -> 512 channels,
-// 32 images (98 tiles) 190 -> 152 us, one image 57 -> 41 us, 256 -> 256, 8 images 47 -> 40 us; 28x28, 256 -> 512, 32 images
-// (392 tiles) 319 -> 340 us, 512 -> 256 (196 tiles) 315 -> 343 us; under 256 channels no gain (28x28, 128 -> 128, 2 images 33 us both).
-inline bool split_pairs_pay(const ConvView &pv, int n_cu) {
+// Row pairs in three planes (F23): deep layers whose plane and batch give at most as many tiles of 128 filters x 64 pairs as
+// there are compute units.
+inline bool split_pairs_possible(const ConvView &pv, int n_cu) {
     const int64_t tiles = (((int64_t)pv.Ho * pv.Wo * pv.N + 127) / 128) * ((pv.Kg + 127) / 128) * pv.G;
     return pv.Cg >= 256 && pv.Kg > 64 && 2 * tiles <= n_cu;
+}
+
+// Estimated microseconds of a whole call (packing, main kernel, fix-up pass), for the choice between the two kernels only.  The
+// constants are a fit to 568 forward and dzdx calls of random layers on 256 compute units, both kernels timed in turn (5 to 230
+// samples a side, 1 to 128 images, 8 to 384 channels and filters, 2 to 121 taps, strides 1 to 4): the estimate is off by 9 %
+// (three planes) and 16 % (fp32) of a call, 1 standard deviation.
+inline double call_us(const ConvView &v, const IgemmPlan &pl, int n_cu) {
+    const IgemmParams &P = pl.P;
+    const double out_mb = 4e-6 * v.Ho * v.Wo * (double)v.Kg * v.G * v.N, pack_mb = 4e-6 * (double)pl.packed_floats;
+    const int64_t left = P.tiles - (int64_t)P.own * P.nblocks;         // tiles that are shared
+    const double shared = left ? (double)((left * P.NU + P.nblocks - 1) / P.nblocks) : 0.0;      // units of them per block
+    const double part_mb = left && P.NU > 1 ? 4e-6 * (double)pl.partial_floats : 0.0;
+    if (pl.planes == 3) {
+        const double step = pl.shape == IG_32x256 ? 0.25 : pl.shape == IG_S64x256 ? 0.42 : pl.shape == IG_S128x128 ? 0.44 : 0.265;
+        const double unit = 0.70 + P.NS * step;
+        return 10.7 + 0.95 * pack_mb + P.own * P.NU * unit + (left ? 4.7 + shared * unit + 0.29 * part_mb : 0.0) + 0.37 * out_mb;
+    }
+    const int resident = (P.nblocks + n_cu - 1) / n_cu;                // blocks that share a compute unit
+    const double mfma_us = pl.TK * pl.TQ / 1024 / 4.0 * P.NS * 64.0 / 2400.0;      // a unit's MFMAs at full rate
+    const double slow = pl.shape == IG_64x512 ? 1.31 : pl.shape == IG_32x256 ? 0.92 : pl.shape == IG_64x256 ? 0.89 : pl.shape == IG_96x256 ? 1.10 : 0.98;
+    const double unit = resident * (0.64 + mfma_us * slow);
+    return 10.4 + 2.8 * pack_mb + P.own * P.NU * unit + (left ? 3.5 + shared * unit + 0.22 * part_mb : 0.0) + 0.126 * out_mb;
+}
+
+// Whether the three-plane kernel is the faster one for view v; split, fp32: the two plans.
+// Over those 568 calls: always three planes 27.8 ms, always fp32 36.4 ms, by this rule 27.55 ms, the faster of the two each time
+// 27.1 ms.  Small layers are what it keeps on the fp32 kernel, which cuts a tile's reduction finer: 32x32x32 -> 3, 5x5,
+// eight images 16.4 us against 25.1, 16x16x32, 5x5x32x32, one image 15.3 against 25.6.
+// Row pairs: the fp32 kernel where the slab is large beside its 64 pairs (58x58x280, 160 filters, three images: 91 us against 111;
+// 52x52x424, 121 filters, nine images 143 against 173), since staging bounds the three-plane one, or where the call has less than
+// about 0.4 groups of units per compute unit, since its short pieces then cost more than they save (13x14x264, 112 filters, one
+// image 31.7 against 34.3; 14x14x512 -> 512, one image, 4 groups per compute unit, 56.9 against 40.0).
+inline bool split_faster(const ConvView &v, const IgemmPlan &split, const IgemmPlan &fp32, int n_cu) {
+    if (split.P.wino_Ho) return split.P.CP <= 128 && 10 * (int64_t)split.P.tiles * split.P.NU >= 16 * (int64_t)n_cu;
+    return call_us(v, split, n_cu) < 0.97 * call_us(v, fp32, n_cu);
 }
 
 // The instantiation with this view's filter size if there is one, its channels divide into the
@@ -507,7 +540,7 @@ inline bool plan_igemm(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf16 = f
         bool ok = false;
         ConvView pv;
         const bool pairs = wino_enabled() && wino_view(v, &pv);
-        if (pairs && !split_pairs_pay(pv, n_cu)) return false;
+        if (pairs && !split_pairs_possible(pv, n_cu)) return false;
         for (int f = 0; f < SPLIT_N_SHAPES; ++f) {
             const int TK = SPLIT_SHAPES[f].WK * SPLIT_SHAPES[f].MK * 32;
             if (TK == 32 ? v.Kg > 32 : v.Kg <= TK / 2) continue;      // half of the tile would be empty

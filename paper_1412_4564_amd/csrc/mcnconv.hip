@@ -133,8 +133,13 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
     const bool pairs = d->precision != MCN_PREC_FP32_PLAIN;     // the row-pair kernels for 3x3 stride-1 layers
     auto plan_view = [&](const ConvView &v, IgemmPlan *pl) {
         if (bf && !v.mD && v.Cg >= BF_DC && plan_igemm(v, ncu, pl, true, true, planes)) return true;    // merged phases: fp32 kernel only
-        // fp32: the same sum on the bf16 matrix core, operands in three planes (merged phases, fewer channels than one MFMA takes: fp32 kernel only)
-        if (d->precision == MCN_PREC_FP32 && wino_enabled() && split_pays(v) && plan_igemm(v, ncu, pl, true, true, 3)) return true;
+        // fp32: the same sum on the bf16 matrix core, operands in three planes, where that is faster
+        if (d->precision == MCN_PREC_FP32 && wino_enabled() && split_possible(v)) {
+            IgemmPlan split;
+            const bool ok = plan_igemm(v, ncu, pl, false, pairs);
+            if (plan_igemm(v, ncu, &split, true, true, 3) && (!ok || split_faster(v, split, *pl, ncu))) { *pl = split; return true; }
+            return ok;
+        }
         return plan_igemm(v, ncu, pl, false, pairs);
     };
     e.fwd_ok = on && plan_view(forward_view(g), &e.fwd);

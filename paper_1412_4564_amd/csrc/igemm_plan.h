@@ -391,6 +391,10 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         const SplitSchedule sc = split_schedule(tiles, P.NU, P.NS, (int64_t)P.CP * (f23s ? 128 : 64), SS, n_cu, f23s ? 2 : 1);
         P.nblocks = sc.nblocks;
         P.own = sc.own;
+        // Row pairs: a tile in at most 32 pieces.  With 64 or more the fix-up pass, which adds them one after another, costs more
+        // than the shorter pieces save (14x13x256, 96 filters, two images: 34.1 us on 256 blocks, 29.0 on 128; 7x7x512 -> 512, one
+        // image 43.3 and 38.0; 16 pieces at most: 26.3 and 38.1, but 7x9x309, 336 filters, four images 37.9 against 35.7).
+        if (f23s && P.own == 0 && P.nblocks > 32 * (int)tiles) P.nblocks = 32 * (int)tiles;
     } else if (!bf16 && 2 * tiles >= resident && tiles < resident) {
         // Somewhat fewer tiles than compute units: sharing every tile keeps all units busy but sends every tile through
         // the workspace and the fix-up pass; one whole tile per block leaves some units idle and needs neither.
@@ -522,11 +526,9 @@ inline double call_us(const ConvView &v, const IgemmPlan &pl, int n_cu) {
 // 27.1 ms.  Small layers are what it keeps on the fp32 kernel, which cuts a tile's reduction finer: 32x32x32 -> 3, 5x5,
 // eight images 16.4 us against 25.1, 16x16x32, 5x5x32x32, one image 15.3 against 25.6.
 // Row pairs: the fp32 kernel where the slab is large beside its 64 pairs (58x58x280, 160 filters, three images: 91 us against 111;
-// 52x52x424, 121 filters, nine images 143 against 173), since staging bounds the three-plane one, or where the call has less than
-// about 0.4 groups of units per compute unit, since its short pieces then cost more than they save (13x14x264, 112 filters, one
-// image 31.7 against 34.3; 14x14x512 -> 512, one image, 4 groups per compute unit, 56.9 against 40.0).
+// 52x52x424, 121 filters, nine images 143 against 173), since staging bounds the three-plane one.
 inline bool split_faster(const ConvView &v, const IgemmPlan &split, const IgemmPlan &fp32, int n_cu) {
-    if (split.P.wino_Ho) return split.P.CP <= 128 && 10 * (int64_t)split.P.tiles * split.P.NU >= 16 * (int64_t)n_cu;
+    if (split.P.wino_Ho) return split.P.CP <= 128;
     return call_us(v, split, n_cu) < 0.97 * call_us(v, fp32, n_cu);
 }
 

@@ -57,3 +57,21 @@ def test_merged_phases(case):
     t = both_precisions(MERGED[case], "dzdx")
     print("merged phases, default and plain: %.1f %.1f us" % t, flush=True)
     assert t[0] <= 1.15 * t[1], t                # 1.3 to 1.7 with the addresses of the filters found tile by tile
+
+
+SMALL = [  # layer, pass: few tiles, or a few more than compute units; what the three-plane kernel takes of the same call, in plain calls
+    ((32, 32, 3, 8, 5, 5, 3, 32, (1, 1), (2, 2, 2, 2)), "dzdx"),           # 1.53
+    ((16, 16, 32, 1, 5, 5, 32, 32, (1, 1), (2, 2, 2, 2)), "forward"),      # 1.67
+    ((12, 12, 20, 2, 5, 5, 20, 50, (1, 1), (2, 2, 2, 2)), "forward"),      # 1.34
+    ((27, 27, 32, 76, 5, 5, 32, 27, (1, 1), (2, 2, 2, 2)), "forward"),     # 1.56
+    ((22, 22, 16, 3, 4, 4, 16, 24, (2, 2), (1, 1, 1, 1)), "dzdx"),         # 1.27
+    ((20, 20, 40, 8, 4, 4, 40, 72, (2, 2), (1, 1, 1, 1)), "dzdx"),         # 1.26
+]
+
+
+@pytest.mark.parametrize("case", range(len(SMALL)))
+def test_small_layers(case):
+    t = both_precisions(*SMALL[case])
+    print("small layers, default and plain: %.1f %.1f us" % t, flush=True)
+    assert t[0] <= 1.12 * t[1], t
+

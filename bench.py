@@ -67,12 +67,21 @@ def profile_lines(path):
     return lines
 
 
-def issued_share(kernel):
+def on_bf16_core(Ls, op):
+    """Whether the call's products run on the bf16 matrix core: the bf16 kernels, and fp32 operands in three planes."""
+    return op < 3 and Ls.planes[op] > 0
+
+
+def matrix_peak(Ls, op):
+    return BF16_MFMA_PEAK_TFLOPS if on_bf16_core(Ls, op) else FP32_MFMA_PEAK_TFLOPS
+
+
+def issued_share(kernel, planes=0):
     """Flops the matrix core executes per flop of the plain sum, by arithmetic: the *_f23 kernels take the three
     row taps of a 3x3 filter for two output rows with four products instead of six; the bf16x3 kernels form every
-    product from three bf16 products.  (Padding of channel and filter counts to tile sizes comes on top; the
+    product from three bf16 products, those with fp32 operands in three planes from six.  (Padding of channel and filter counts to tile sizes comes on top; the
     counter summary, where there is one, has the measured figure.)"""
-    return 2.0 / 3.0 if "_f23" in kernel else 3.0 if "bf16x3" in kernel else 1.0
+    return (2.0 / 3.0 if "_f23" in kernel else 1.0) * (6.0 if planes == 3 else 3.0 if "bf16x3" in kernel else 1.0)
 
 
 def measured_mfma(call):
@@ -130,6 +139,7 @@ class LayerState:
         self.turn = 0
         self.macs = layer_macs(L, self.ho, self.wo)
         self.kernels = [B.mcn_conv_kernel_name(desc, op) for op in range(4)]
+        self.planes = [B.mcn_conv_operand_planes(desc, op) for op in range(4)]
         # dzdw and dzdb from one kernel where the library has one (the backward mode returns both): the step then
         # calls mcn_conv_backward_filter_bias for the two, and the bias derivative's own call is not made
         self.fused_bias = B.mcn_conv_kernel_name(desc, B.MCN_OP_BACKWARD_FILTER_BIAS) == "wgrad_f23+bias"
@@ -152,6 +162,7 @@ class LayerState:
         o.prec = precision
         o.desc = B.make_desc(self.x.shape, self.w.shape, self.st, self.pad, precision)
         o.kernels = [B.mcn_conv_kernel_name(o.desc, op) for op in range(4)]
+        o.planes = [B.mcn_conv_operand_planes(o.desc, op) for op in range(4)]
         o.fused_bias = B.mcn_conv_kernel_name(o.desc, B.MCN_OP_BACKWARD_FILTER_BIAS) == "wgrad_f23+bias"
         if o.fused_bias:
             o.kernels[2], o.kernels[3] = "wgrad_f23+bias", FUSED_AWAY
@@ -201,6 +212,7 @@ class ConvtLayerState:
         # every input sample meets every filter tap once per output channel of its group
         self.macs = L["H"] * L["W"] * L["D"] * L["N"] * L["Hf"] * L["Wf"] * L["Kf"]
         self.kernels = [B.mcn_convt_kernel_name(desc, op) for op in range(4)]
+        self.planes = [B.mcn_convt_operand_planes(desc, op) for op in range(4)]
         ws = max(B.mcn_convt_workspace_size(desc, op) for op in range(4))
         self.ws = torch.empty(max(ws, 16), dtype=torch.uint8, device="cuda")
         nx, nw, ny = self.x.numel(), self.w.numel(), self.p.numel()
@@ -452,11 +464,13 @@ def call_report(Ls, op, ms):
     if matrix_pass:
         tf = 2.0 * Ls.macs / ms / 1e9
         e["TFLOPs"] = round(tf, 2)
-        e["issued_TFLOPs"] = round(issued_share(kernel) * tf, 2)
+        e["issued_TFLOPs"] = round(issued_share(kernel, Ls.planes[op]) * tf, 2)
+        if Ls.planes[op] == 3:
+            e["planes"] = 3          # fp32 operands on the bf16 matrix core: issued_TFLOPs are bf16
     bound = "mfma" if matrix_pass and BOUND.get(Ls.name, "mfma") == "mfma" else "hbm"
     e["bound"] = bound
     if bound == "mfma":
-        peak = BF16_MFMA_PEAK_TFLOPS if "bf16" in kernel else FP32_MFMA_PEAK_TFLOPS
+        peak = matrix_peak(Ls, op)
         e["frac"] = round(e["issued_TFLOPs"] / peak, 4)
     else:
         e["frac"] = round(e["GBps"] / HBM_PEAK_GBS, 4)
@@ -550,19 +564,22 @@ def main():
     dom = layers[li]
     detail = {}
     issued_step = 0.0        # flops the matrix core executes per step (see issued_share)
+    at_peak = 0.0            # seconds they take at the peak of the core they run on
     for i, Ls in enumerate(layers):
         for o in range(len(Ls.op_names)):
             detail["%s.%s" % (Ls.name, Ls.op_names[o])] = call_report(Ls, o, per[i, o])
             if o < 3 and Ls.macs and Ls.kernels[o] != FUSED_AWAY:
-                issued_step += issued_share(Ls.kernels[o]) * 2.0 * Ls.macs
+                issued = issued_share(Ls.kernels[o], Ls.planes[o]) * 2.0 * Ls.macs
+                issued_step += issued
+                at_peak += issued / matrix_peak(Ls, o) / 1e12
     dom_call = "%s.%s" % (dom.name, dom.op_names[op])
     traffic = measured_traffic(dom_call) if headline and prec == B.MCN_PREC_FP32 else None
     if op < 3 and dom.macs:
         # 'achieved' = the flops the matrix core executes for the call (what its peak bounds); 'algorithmic_equiv' =
         # the flops of the sum as the paper writes it, 2 * MACs (the *_f23 kernels execute two thirds of them)
         equiv = 2.0 * dom.macs / per[li, op] / 1e9
-        peak = BF16_MFMA_PEAK_TFLOPS if "bf16" in dom.kernels[op] else FP32_MFMA_PEAK_TFLOPS
-        ach, source = issued_share(dom.kernels[op]) * equiv, "arithmetic (2/3 of 2*MACs for *_f23 kernels, else all)"
+        peak = matrix_peak(dom, op)
+        ach, source = issued_share(dom.kernels[op], dom.planes[op]) * equiv, "arithmetic (2/3 of 2*MACs for *_f23 kernels, else all)"
         counters = measured_mfma(dom_call) if headline and prec == B.MCN_PREC_FP32 else None
         if counters:
             ach, source = counters[0] / per[li, op] / 1e9, "profiles/vgg3x3_mfma_counters.txt (SQ_INSTS_VALU_MFMA_MOPS_F32)"
@@ -590,7 +607,7 @@ def main():
                    "layers": {Ls.name: Ls.shape_info() for Ls in layers}},
         # 'value' counts 2 * MACs of the plain sum; the matrix core executes fewer flops for it in the *_f23 kernels:
         "mfma_issued_TFLOPs": round(issued_tflops, 3),
-        "mfma_issued_frac_of_peak": round(issued_tflops / (FP32_MFMA_PEAK_TFLOPS if fp32 else BF16_MFMA_PEAK_TFLOPS), 4),
+        "mfma_issued_frac_of_peak": round(at_peak / sec_per_step, 4),       # each call against the core it runs on
         "roofline": roof,
         "calls": detail,
     }

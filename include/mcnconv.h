@@ -315,6 +315,13 @@ int mcn_last_hip_error(void);
  * column, ...); for reports and tests.  Returns NULL on a bad descriptor.  Host only. */
 const char *mcn_conv_kernel_name(const mcn_conv_desc *desc, int op);
 
+/* How that kernel holds the operands of its products on chip: 3 = fp32 in three bf16 planes (six products
+ * each on the bf16 matrix core), 2 = hi and lo planes (three products), 1 = rounded to bf16, 0 = fp32 (or no
+ * product at all).  Where an input derivative takes several launches (stride phases), the first one's.
+ * -1 on a bad descriptor or operation.  For reports and tests.  Host only. */
+int mcn_conv_operand_planes(const mcn_conv_desc *desc, int op);
+int mcn_convt_operand_planes(const mcn_convt_desc *desc, int op);
+
 /* ---- Measurement aids (no part of the paper's blocks) ---------------------------------
  * The rates this GPU sustains on the two resources the kernels above are priced against,
  * so that a benchmark can quote a fraction of the measured ceiling beside the fraction

@@ -35,7 +35,7 @@ EXPORTS = (
     "mcn_convt_output_size", "mcn_convt_workspace_size", "mcn_convt_forward", "mcn_convt_backward_data",
     "mcn_convt_backward_filter", "mcn_convt_backward_bias", "mcn_convt_kernel_name",
     "mcn_pool_output_size", "mcn_pool_workspace_size", "mcn_pool_forward", "mcn_pool_backward",
-    "mcn_probe_mfma", "mcn_probe_copy", "mcn_conv_backward_bias_static",
+    "mcn_probe_mfma", "mcn_probe_copy", "mcn_conv_backward_bias_static", "mcn_conv_operand_planes", "mcn_convt_operand_planes",
 )
 MCN_PROBE_SINK_FLOATS = 2048 * 256
 
@@ -98,6 +98,7 @@ def lib():
         L.mcn_last_hip_error.restype = ctypes.c_int
         L.mcn_conv_kernel_name.argtypes = [D, ctypes.c_int]
         L.mcn_conv_kernel_name.restype = ctypes.c_char_p
+        L.mcn_conv_operand_planes.argtypes = [D, ctypes.c_int]
         L.mcn_conv_relu_forward.argtypes = [D, P, P, P, P, P, SZ, P]
         L.mcn_conv_relu_backward_bias.argtypes = [D, P, P, P, P, P, SZ, P]
         L.mcn_conv_relu_forward.restype = ctypes.c_int
@@ -121,6 +122,7 @@ def lib():
         L.mcn_convt_backward_bias.argtypes = [T, P, P, P, SZ, P]
         L.mcn_convt_kernel_name.argtypes = [T, ctypes.c_int]
         L.mcn_convt_kernel_name.restype = ctypes.c_char_p
+        L.mcn_convt_operand_planes.argtypes = [T, ctypes.c_int]
         for f in ("mcn_conv_output_size", "mcn_conv_workspace_size", "mcn_conv_forward",
                   "mcn_conv_backward_data", "mcn_conv_backward_filter", "mcn_conv_backward_bias",
                   "mcn_convt_output_size", "mcn_convt_workspace_size", "mcn_convt_forward",
@@ -158,6 +160,10 @@ def mcn_conv_workspace_size(desc, op):
 def mcn_conv_kernel_name(desc, op):
     s = lib().mcn_conv_kernel_name(ctypes.byref(desc), int(op))
     return None if s is None else s.decode()
+
+
+def mcn_conv_operand_planes(desc, op):
+    return lib().mcn_conv_operand_planes(ctypes.byref(desc), int(op))
 
 
 def mcn_conv_forward(desc, x, w, b, y, ws, ws_bytes, stream):
@@ -263,6 +269,10 @@ def mcn_convt_workspace_size(desc, op):
 def mcn_convt_kernel_name(desc, op):
     s = lib().mcn_convt_kernel_name(ctypes.byref(desc), int(op))
     return None if s is None else s.decode()
+
+
+def mcn_convt_operand_planes(desc, op):
+    return lib().mcn_convt_operand_planes(ctypes.byref(desc), int(op))
 
 
 def mcn_convt_forward(desc, x, f, b, y, ws, ws_bytes, stream):

@@ -698,6 +698,16 @@ const char *mcn_conv_kernel_name(const mcn_conv_desc *desc, int op) {
     }
 }
 
+int mcn_conv_operand_planes(const mcn_conv_desc *desc, int op) {
+    Geom g;
+    if (make_geom(desc, &g) || op < MCN_OP_FORWARD || op > MCN_OP_BACKWARD_FILTER_BIAS) return -1;
+    const PlanEntry *e = plans_for(desc, g);
+    if (e->fc) return 0;
+    const IgemmPlan *pl = op == MCN_OP_FORWARD && e->fwd_ok ? &e->fwd : op == MCN_OP_BACKWARD_DATA && e->bwd_ok && e->n_bwd ? &e->bwd[0] : nullptr;
+    if (pl) return pl->bf16 ? pl->planes : 0;
+    return (op == MCN_OP_BACKWARD_FILTER || op == MCN_OP_BACKWARD_FILTER_BIAS) && e->wgb_ok ? 1 : 0;
+}
+
 int mcn_conv_forward(const mcn_conv_desc *desc, const float *x, const float *w, const float *b, float *y,
                      void *ws, size_t ws_bytes, void *stream) {
     Geom g;
@@ -834,6 +844,19 @@ const char *mcn_convt_kernel_name(const mcn_convt_desc *desc, int op) {
         case MCN_OP_BACKWARD_FILTER: return mcn_conv_kernel_name(&c, MCN_OP_BACKWARD_FILTER);
         case MCN_OP_BACKWARD_BIAS: return plan_bias((int64_t)g.H * g.W, g.D, g.N).rows ? "reduce_rows" : "reduce2";
         default: return NULL;
+    }
+}
+
+int mcn_convt_operand_planes(const mcn_convt_desc *desc, int op) {
+    mcn_conv_desc c;
+    Geom g;
+    if (conjugate_convolution(desc, &c, &g)) return -1;
+    switch (op) {
+        case MCN_OP_FORWARD: return mcn_conv_operand_planes(&c, MCN_OP_BACKWARD_DATA);
+        case MCN_OP_BACKWARD_DATA: return mcn_conv_operand_planes(&c, MCN_OP_FORWARD);
+        case MCN_OP_BACKWARD_FILTER: return mcn_conv_operand_planes(&c, MCN_OP_BACKWARD_FILTER);
+        case MCN_OP_BACKWARD_BIAS: return 0;
+        default: return -1;
     }
 }
 

@@ -241,20 +241,18 @@ __global__ __launch_bounds__(256) void pool_backward_max_disjoint_kernel(PoolGeo
         for (int i = max(oi, 0); i < i_end; ++i) dp[i + g.H * j] = 0.f;
 }
 
-// Max pooling whose windows overlap, 2x2 or 3x3: one pass as well.  A block takes whole planes (as many as fit POOL_XS
-// samples) or, of larger planes, a strip of columns and the columns that its windows reach beyond it.  It brings the
-// samples into LDS (they are contiguous), finds every window's maximum there, keeps position and derivative in LDS, and
-// gathers from them.  Bound by memory: x, dzdy and dzdx move once (and the strips' shared columns twice), coalesced,
-// where finding the maxima in one kernel (pool_argmax_kernel, nine strided loads per window) and gathering through a
-// byte per window in another moved x and dzdy through twice as many instructions (55x55x96, 128 images, 3x3 at stride 2:
-// 178 -> 82 us, 4.1 TB/s).
+// ---- overlapping windows through LDS ---------------------------------------------------
+// Two kernels that bring the samples of a block into LDS (they are contiguous: whole planes, as many as fit POOL_XS samples, or, of
+// larger planes, a strip of columns and the columns that its windows reach beyond it), where the others read every window's
+// samples from memory through the caches.
 struct PoolTiles {
     int planes, strips, cols;      // planes per block (strips = 1), or strips per plane and columns per strip
     int wcols;                     // forward pass: window columns per strip
     int xs, ws;                    // samples and windows that the LDS arrays hold
     Div32 dna;                     // 3x3 at stride 2: by the pairs of rows of a plane
 };
-constexpr int POOL_XS = 4096;      // 16 KB of samples and 5 bytes per window: at least six blocks per compute unit
+constexpr int POOL_XS = 4096;      // 16 KB of samples; the derivative's five bytes per window come to 5 KB, at most 20 (planes of one column)
+inline int64_t pool_blocks(const PoolGeom &g, const PoolTiles &t) { return ((int64_t)g.D * g.N + t.planes - 1) / t.planes * t.strips; }
 // false: planes too tall for strips that are wide beside what they share
 inline bool pool_tiles(const PoolGeom &g, PoolTiles *t) {
     const int64_t plane = (int64_t)g.H * g.W;
@@ -282,6 +280,29 @@ inline bool pool_tiles(const PoolGeom &g, PoolTiles *t) {
     return true;
 }
 
+// Where the forward pass goes through LDS: overlapping 2x2 and 3x3 windows over inputs beyond 128 MiB.  Smaller inputs are in the
+// caches when the network comes to them, and the nine loads of a window then cost less than the way through LDS (us, loads
+// from memory -> through LDS, inputs rotated / the same again; 3x3 at stride 2: 55x55, 96 planes 3.3 -> 5.5 / 3.0 -> 4.8, 28x28, 8192
+// planes 13.8 -> 15.8 / 10.6 -> 11.4, 27x27, 32768 planes 39.6 -> 36.4 / 27.8 -> 29.1; 3x3 at stride 1: 12x12, 18960 planes
+// 15.3 -> 21.5 / 13.6 -> 18.5); beyond, the memory's accesses count (55x55, 12288 planes 65.6 -> 53.4 / 54.2 -> 41.8; 3x3 at stride 1,
+// 56x56, 12288 planes 154 -> 139 / 130 -> 116; 2x2 at stride 1, 112x112, 4096 planes 158 -> 111 / 152 -> 108).  At stride 2 not in strips
+// (284x284, 564 planes 75.3 -> 68.7 / 54.1 -> 55.8).
+inline bool pool_forward_in_lds(const PoolGeom &g, PoolTiles *t) {
+    if (g.Hp != g.Wp || (g.Hp != 2 && g.Hp != 3) || g.Sh >= g.Hp || g.Sw >= g.Wp) return false;
+    if ((int64_t)g.H * g.W * g.D * g.N < ((int64_t)1 << 25) || !pool_tiles(g, t)) return false;
+    return t->strips == 1 || (g.Sh == 1 && g.Sw == 1 && g.H * (g.Sw * (t->wcols - 1) + g.Wp) <= t->xs);
+}
+
+// Where the derivative does: max pooling, 3x3 at stride 2, with enough blocks for the chip, or small ones.  Fewer, large blocks take longer
+// than the two passes of the other form (us, two passes -> through LDS, inputs rotated / the same again: 55x55, 96 planes
+// 6.4 -> 7.5 / 5.8 -> 6.3, 60x60, 200 planes 8.9 -> 9.7 / 7.3 -> 7.1, but 400 planes 12.9 -> 12.0 / 10.4 -> 8.4, 55x55, 12288 planes
+// 191 -> 94 / 166 -> 87; blocks of 32x32 samples, 12 planes 4.2 -> 3.2 / 4.5 -> 3.4).  2x2 at stride 1, with a derivative for every
+// sample in four windows, was slower as often as not (12x12, 25405 planes 22.2 -> 27.8, 224x224, 512 planes 156 -> 167).
+inline bool pool_derivative_in_lds(const PoolGeom &g, PoolTiles *t) {
+    if (g.method != 0 || g.Hp != 3 || g.Wp != 3 || g.Sh != 2 || g.Sw != 2 || !pool_tiles(g, t)) return false;
+    return pool_blocks(g, *t) >= 320 || t->xs <= 2048;
+}
+
 // n contiguous samples into LDS, eight loads in flight per thread
 __device__ inline void pool_stage(float *xs, const float *__restrict__ src, int n) {
     for (int e0 = threadIdx.x; e0 < n; e0 += 8 * 256) {
@@ -294,8 +315,8 @@ __device__ inline void pool_stage(float *xs, const float *__restrict__ src, int 
     }
 }
 
-// The forward pass with overlapping 2x2 or 3x3 windows, through the same blocks (strips of window columns here): the samples
-// enter LDS once, coalesced, instead of nine strided loads per window (55x55x96, 128 images, 3x3 at stride 2: 58 -> 46 us).
+// The forward pass (strips of window columns): the samples enter LDS once, coalesced, instead of nine strided loads per window
+// (pool_forward_in_lds has the figures).
 template <int HP, int WP>
 __global__ __launch_bounds__(256) void pool_forward_overlap_kernel(PoolGeom g, PoolTiles t, const float *__restrict__ x, float *__restrict__ y) {
     extern __shared__ float xs[];                                          // [t.xs] samples
@@ -337,10 +358,14 @@ __global__ __launch_bounds__(256) void pool_forward_overlap_kernel(PoolGeom g, P
     }
 }
 
-// NH x NW: at most so many windows hold one sample; S2: 3x3 windows at stride 2 both ways
-template <int HP, int WP, int NH, int NW, bool S2 = false>
+// The derivative of max pooling, 3x3 at stride 2, in one pass: every window's maximum is found in LDS, its position and derivative are
+// kept there, and the samples gather from them.  Bound by memory: x, dzdy and dzdx move once (and the strips' shared columns
+// twice), coalesced, where finding the maxima in one kernel (pool_argmax_kernel, nine strided loads per window) and gathering
+// through a byte per window in another move x and dzdy through twice as many instructions (55x55x96, 128 images: 178 -> 82 us,
+// 4.1 TB/s).
 __global__ __launch_bounds__(256) void pool_backward_max_overlap_kernel(PoolGeom g, PoolTiles t, const float *__restrict__ x,
                                                                         const float *__restrict__ dzdy, float *__restrict__ dzdx) {
+    constexpr int HP = 3, WP = 3;
     extern __shared__ float xs[];                                          // [t.xs] samples
     float *ps = xs + t.xs;                                                 // [t.ws] derivatives of the windows
     unsigned char *cs = reinterpret_cast<unsigned char *>(ps + t.ws);      // [t.ws] positions of their maxima
@@ -359,7 +384,7 @@ __global__ __launch_bounds__(256) void pool_backward_max_overlap_kernel(PoolGeom
         c1 = w1 > w0 ? min(g.Sw * (w1 - 1) - g.Pl + WP, g.W) : 0;
     }
     // all three ranges are contiguous in memory: whole columns of one plane, or whole planes
-    const int nx = np * g.H * (c1 - c0), nw1 = g.Ho * (w1 - w0), nw = np * nw1, no1 = g.H * (s1 - s0), no = np * no1;
+    const int nx = np * g.H * (c1 - c0), nw1 = g.Ho * (w1 - w0), nw = np * nw1, no1 = g.H * (s1 - s0);
     const float *xsrc = x + (size_t)plane0 * HW + (size_t)g.H * c0;
     const float *psrc = dzdy + (size_t)plane0 * g.Ho * g.Wo + (size_t)g.Ho * w0;
     float *dst = dzdx + (size_t)plane0 * HW + (size_t)g.H * s0;
@@ -388,59 +413,39 @@ __global__ __launch_bounds__(256) void pool_backward_max_overlap_kernel(PoolGeom
         cs[e] = (unsigned char)best;
     }
     __syncthreads();
-    if constexpr (S2) {
-        // 3x3 at stride 2: the samples (2a, 2b) .. (2a+1, 2b+1), counted from the first window's uncropped origin, lie in the
-        // windows (a-1, a) x (b-1, b) only, each at a fixed position: a thread gathers four samples from four windows,
-        // nine comparisons instead of sixteen with an address each (55x55x96, 128 images: 123 -> 82 us)
-        const int a0 = g.Pt >> 1, na = ((g.H - 1 + g.Pt) >> 1) - a0 + 1;                   // pairs of rows
-        const int b0 = (s0 + g.Pl) >> 1, nb = ((s1 - 1 + g.Pl) >> 1) - b0 + 1;             // pairs of columns
-        const Div32 dna = t.dna;
-        for (int e = tid; e < np * na * nb; e += 256) {
-            const int q = div32(e, dna), a = a0 + e - q * na;
-            const int pl = np == 1 ? 0 : q / nb, b = b0 + q - pl * nb;
-            const bool ua = a >= 1 && a - 1 < g.Ho, la = a < g.Ho, ub = b - 1 >= w0 && b - 1 < w1, lb = b >= w0 && b < w1;
-            const int at = pl * nw1 + a + g.Ho * (b - w0);
-            int c[2][2];
-            float p[2][2];                         // [column][row], 0: the window before
-            c[0][0] = ua && ub ? cs[at - 1 - g.Ho] : 255; p[0][0] = ua && ub ? ps[at - 1 - g.Ho] : 0.f;
-            c[0][1] = la && ub ? cs[at - g.Ho] : 255;     p[0][1] = la && ub ? ps[at - g.Ho] : 0.f;
-            c[1][0] = ua && lb ? cs[at - 1] : 255;        p[1][0] = ua && lb ? ps[at - 1] : 0.f;
-            c[1][1] = la && lb ? cs[at] : 255;            p[1][1] = la && lb ? ps[at] : 0.f;
-            // in the order of the windows: columns, then rows
-            const float v00 = (((c[0][0] == 8 ? p[0][0] : 0.f) + (c[0][1] == 6 ? p[0][1] : 0.f)) + (c[1][0] == 2 ? p[1][0] : 0.f)) + (c[1][1] == 0 ? p[1][1] : 0.f);
-            const float v10 = (c[0][1] == 7 ? p[0][1] : 0.f) + (c[1][1] == 1 ? p[1][1] : 0.f);
-            const float v01 = (c[1][0] == 5 ? p[1][0] : 0.f) + (c[1][1] == 3 ? p[1][1] : 0.f);
-            const float v11 = c[1][1] == 4 ? p[1][1] : 0.f;
-            const int i = 2 * a - g.Pt, j = 2 * b - g.Pl;
-            float *d = dst + pl * no1 + i + g.H * (j - s0);
-            const bool r0 = i >= 0, r1 = i + 1 < g.H;
-            if (j >= s0) {
-                if (r0) d[0] = v00;
-                if (r1) d[1] = v10;
-            }
-            if (j + 1 < s1) {
-                if (r0) d[g.H] = v01;
-                if (r1) d[g.H + 1] = v11;
-            }
+    // 3x3 at stride 2: the samples (2a, 2b) .. (2a+1, 2b+1), counted from the first window's uncropped origin, lie in the
+    // windows (a-1, a) x (b-1, b) only, each at a fixed position: a thread gathers four samples from four windows,
+    // nine comparisons instead of sixteen with an address each (55x55x96, 128 images: 123 -> 82 us)
+    const int a0 = g.Pt >> 1, na = ((g.H - 1 + g.Pt) >> 1) - a0 + 1;                   // pairs of rows
+    const int b0 = (s0 + g.Pl) >> 1, nb = ((s1 - 1 + g.Pl) >> 1) - b0 + 1;             // pairs of columns
+    const Div32 dna = t.dna;
+    for (int e = tid; e < np * na * nb; e += 256) {
+        const int q = div32(e, dna), a = a0 + e - q * na;
+        const int pl = np == 1 ? 0 : q / nb, b = b0 + q - pl * nb;
+        const bool ua = a >= 1 && a - 1 < g.Ho, la = a < g.Ho, ub = b - 1 >= w0 && b - 1 < w1, lb = b >= w0 && b < w1;
+        const int at = pl * nw1 + a + g.Ho * (b - w0);
+        int c[2][2];
+        float p[2][2];                         // [column][row], 0: the window before
+        c[0][0] = ua && ub ? cs[at - 1 - g.Ho] : 255; p[0][0] = ua && ub ? ps[at - 1 - g.Ho] : 0.f;
+        c[0][1] = la && ub ? cs[at - g.Ho] : 255;     p[0][1] = la && ub ? ps[at - g.Ho] : 0.f;
+        c[1][0] = ua && lb ? cs[at - 1] : 255;        p[1][0] = ua && lb ? ps[at - 1] : 0.f;
+        c[1][1] = la && lb ? cs[at] : 255;            p[1][1] = la && lb ? ps[at] : 0.f;
+        // in the order of the windows: columns, then rows
+        const float v00 = (((c[0][0] == 8 ? p[0][0] : 0.f) + (c[0][1] == 6 ? p[0][1] : 0.f)) + (c[1][0] == 2 ? p[1][0] : 0.f)) + (c[1][1] == 0 ? p[1][1] : 0.f);
+        const float v10 = (c[0][1] == 7 ? p[0][1] : 0.f) + (c[1][1] == 1 ? p[1][1] : 0.f);
+        const float v01 = (c[1][0] == 5 ? p[1][0] : 0.f) + (c[1][1] == 3 ? p[1][1] : 0.f);
+        const float v11 = c[1][1] == 4 ? p[1][1] : 0.f;
+        const int i = 2 * a - g.Pt, j = 2 * b - g.Pl;
+        float *d = dst + pl * no1 + i + g.H * (j - s0);
+        const bool r0 = i >= 0, r1 = i + 1 < g.H;
+        if (j >= s0) {
+            if (r0) d[0] = v00;
+            if (r1) d[1] = v10;
         }
-        return;
-    }
-    for (int e = tid; e < no; e += 256) {
-        const int pl = np == 1 ? 0 : (int)div64((unsigned)e, g.dIn), rem = e - pl * no1;
-        const int jl = div32(rem, g.dH), i = rem - jl * g.H, j = s0 + jl;
-        const WindowRange r = windows_of(g, i, j);
-        float acc = 0.f;
-#pragma unroll
-        for (int b = 0; b < NW; ++b)
-#pragma unroll
-            for (int a = 0; a < NH; ++a) {
-                const int io = r.io_lo + a, jo = r.jo_lo + b;
-                if (io > r.io_hi || jo > r.jo_hi) continue;
-                const int at = pl * nw1 + io + g.Ho * (jo - w0);
-                const int fi = i - (g.Sh * io - g.Pt), fj = j - (g.Sw * jo - g.Pl);
-                if (cs[at] == fi + HP * fj) acc += ps[at];
-            }
-        dst[e] = acc;
+        if (j + 1 < s1) {
+            if (r0) d[g.H] = v01;
+            if (r1) d[g.H + 1] = v11;
+        }
     }
 }
 

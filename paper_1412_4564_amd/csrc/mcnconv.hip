@@ -943,9 +943,8 @@ int mcn_pool_forward(const mcn_pool_desc *desc, const float *x, float *y, void *
     const unsigned total = (unsigned)g.Ho * g.Wo * g.D * g.N;
     const dim3 grid(cdiv(total, 256));
     PoolTiles t;
-    if (g.Hp == g.Wp && (g.Hp == 2 || g.Hp == 3) && g.Sh < g.Hp && g.Sw < g.Wp && pool_tiles(g, &t) &&
-        (t.strips == 1 || g.H * (g.Sw * (t.wcols - 1) + g.Wp) <= t.xs)) {
-        const dim3 tiles(cdiv((int64_t)g.D * g.N, t.planes) * (unsigned)t.strips);
+    if (pool_forward_in_lds(g, &t)) {
+        const dim3 tiles((unsigned)pool_blocks(g, t));
         if (g.Hp == 2)
             hipLaunchKernelGGL((pool_forward_overlap_kernel<2, 2>), tiles, dim3(256), (size_t)t.xs * 4, (hipStream_t)stream, g, t, x, y);
         else
@@ -963,7 +962,8 @@ int mcn_pool_forward(const mcn_pool_desc *desc, const float *x, float *y, void *
 static bool pool_disjoint(const PoolGeom &g) {
     return g.method == MCN_POOL_MAX && g.Sh == g.Hp && g.Sw == g.Wp && g.Hp == g.Wp && (g.Hp == 2 || g.Hp == 3);
 }
-// one byte per window for the position of its maximum, if a byte can hold it and the two-pass form is used
+// one byte per window for the position of its maximum, if a byte can hold it; asked for whether the two-pass form runs or the one in LDS,
+// which has no use for it
 static size_t pool_ws_bytes(const PoolGeom &g) {
     return (g.method == MCN_POOL_MAX && g.Hp * g.Wp <= 256 && !pool_disjoint(g)) ? (size_t)g.Ho * g.Wo * g.D * g.N : 0;
 }
@@ -994,19 +994,9 @@ int mcn_pool_backward(const mcn_pool_desc *desc, const float *x, const float *dz
             hipLaunchKernelGGL((pool_backward_max_disjoint_kernel<3, 3>), dim3(cdiv(n_out, 256)), dim3(256), 0, s, g, x, dzdy, dzdx, n_out);
         return check_launch();
     }
-    // windows that can hold one sample, per direction
-    const int nh = (g.Hp + g.Sh - 1) / g.Sh, nw = (g.Wp + g.Sw - 1) / g.Sw;
-    const int nmax = nh > nw ? nh : nw;
     PoolTiles t;
-    if (need && g.Hp == g.Wp && (g.Hp == 2 || g.Hp == 3) && nmax <= 2 && pool_tiles(g, &t)) {
-        const dim3 grid(cdiv((int64_t)g.D * g.N, t.planes) * (unsigned)t.strips);
-        const size_t lds = (size_t)t.xs * 4 + (size_t)t.ws * 5;
-        if (g.Hp == 2)
-            hipLaunchKernelGGL((pool_backward_max_overlap_kernel<2, 2, 2, 2>), grid, dim3(256), lds, s, g, t, x, dzdy, dzdx);
-        else if (g.Sh == 2 && g.Sw == 2)
-            hipLaunchKernelGGL((pool_backward_max_overlap_kernel<3, 3, 2, 2, true>), grid, dim3(256), lds, s, g, t, x, dzdy, dzdx);
-        else
-            hipLaunchKernelGGL((pool_backward_max_overlap_kernel<3, 3, 2, 2>), grid, dim3(256), lds, s, g, t, x, dzdy, dzdx);
+    if (pool_derivative_in_lds(g, &t)) {
+        hipLaunchKernelGGL(pool_backward_max_overlap_kernel, dim3((unsigned)pool_blocks(g, t)), dim3(256), (size_t)t.xs * 4 + (size_t)t.ws * 5, s, g, t, x, dzdy, dzdx);
         return check_launch();
     }
     if (need) {
@@ -1019,6 +1009,9 @@ int mcn_pool_backward(const mcn_pool_desc *desc, const float *x, const float *dz
             hipLaunchKernelGGL((pool_argmax_kernel<0, 0>), go, dim3(256), 0, s, g, x, (unsigned char *)ws, n_out);
         st = check_launch();
         if (st) return st;
+        // windows that can hold one sample, per direction
+        const int nh = (g.Hp + g.Sh - 1) / g.Sh, nw = (g.Wp + g.Sw - 1) / g.Sw;
+        const int nmax = nh > nw ? nh : nw;
         const dim3 gi(cdiv(n_in, 256));
         const unsigned char *code = (const unsigned char *)ws;
         if (nmax == 1)

@@ -75,7 +75,8 @@ typedef struct mcn_conv_desc {
  *   stay exact).  For inputs of one scale (the workloads here) the error equals that of the
  *   plain order, about 1e-7 of the sum of |w||x|.
  *   Forward and dzdx of other filter sizes (two taps or more, at least 16 channels per group), and of
- *   3x3 layers with at least 256 channels and few tiles, run on the bf16 matrix core with every operand
+ *   3x3 layers with at least 256 channels and few tiles, run, where that is estimated to be the faster way
+ *   (mcn_conv_operand_planes says 3; small layers stay on the fp32 matrix core), on the bf16 matrix core with every operand
  *   held as THREE bf16 values whose sum it is exactly, and six products accumulated in fp32 (what is left
  *   out is below 2^-26 of |w||x|): the error measures as on the fp32 matrix core or less, for operands of every
  *   size (a product with an operand below the smallest normal number, 1.2e-38, may be off by 2^-150 of the
@@ -89,13 +90,15 @@ typedef struct mcn_conv_desc {
  *   products accumulated in fp32; arrays in memory stay fp32.  Normalised error <= 1e-2.
  *   Geometries the bf16 kernels do not cover (fewer than 16 channels per group,
  *   fully-connected layers, the filter derivative with a vertical stride, more than 5 filter
- *   rows or at most 32 filters per group) compute in fp32, which meets the same bound.
+ *   rows or at most 32 filters per group) compute in fp32, which meets the same bound.  dzdx of a strided layer
+ *   with at most 16 channels per group (first layers) does too, on the fp32 matrix core: the default is faster
+ *   there (227x227x3, 11x11 at stride 4, 128 images: 390 us against 240).
  * MCN_PREC_FP32_BF16X3: fp32 arrays, fp32 accumulation, and every operand of the forward pass and of
  *   dzdx held on chip as TWO bf16 values, hi = bf16(v) and lo = bf16(v - hi) (16 bits of v's
  *   significand), with each product formed as w_hi*x_hi + w_hi*x_lo + w_lo*x_hi on the bf16 matrix core
  *   ("igemm_bf16x3").  Error per product below 1.2e-5 of |w||x| in the worst case, so the normalised
  *   error stays under the fp32 bars (1e-4 forward, 1e-3 backward) with a margin of eight or more, and
- *   measures 5e-7 to 6e-6; the two passes run 1.5 to 1.8 times as fast as under MCN_PREC_FP32 on the
+ *   measures 5e-7 to 6e-6; the two passes run 1.6 to 1.8 times as fast as under MCN_PREC_FP32 on the
  *   3x3 layers of the benchmark (staging, not the matrix core, bounds them).  For callers who would otherwise trade fp32 for
  *   bf16 operands: this keeps 16 instead of 8 significant bits.  dzdw, dzdb and the geometries the bf16
  *   kernels do not cover compute as under MCN_PREC_FP32.

@@ -16,17 +16,18 @@
 // [channel group][tap][plane][octet][filter][8 channels] in memory (igemm_pack_weights_bf16_kernel, three planes).  A unit
 // is 16 channels x all taps.
 //
-// What bounds it: the matrix core's power (random data: 1.85 PFLOP/s sustained from registers, 2.45 with zeros) as long as
-// no wave waits.  Hence
+// What bounds it: the matrix core, at the clock that its power leaves, and the waits between its products (two groups of 5x5, 128
+// images: 0.68 to 0.73 of the active cycles execute products, at 1.86 GHz of 2.4; a loop of products alone reaches 1.85 PFLOP/s on
+// random data and 2.45 on zeros, this kernel 1.3).  Hence
 //  * the weights go from the L2 straight into the registers of the waves that use them (waves of one block read the same
 //    ones through the L1: 32 bytes a cycle) and not through LDS: staged there, 12 KB per tap, they forced a barrier every
 //    tap or two, and with eight waves in step the scalar work, the LDS latency and the skew at each barrier cost as much
-//    as half a tap's MFMAs (27x27x96 plane, 5x5x48x256 filters, 128 images: 318 us, now 272, 1.26 PFLOP/s of bf16
+//    as half a tap's MFMAs (27x27x96 plane, 5x5x48x256 filters, 128 images: 318 us, now 262, 1.31 PFLOP/s of bf16
 //    products; the fp32 kernel 440).  The LDS then holds three slabs and its reads are halved.
 //  * slabs are published one barrier before they are computed, so the last step of a unit reads the next unit's first
 //    operands and no wave starts a unit with empty registers.
 //  * every plane has one set of registers, read anew for the next step as soon as its last product is issued; the order
-//    of the products leaves 12 MFMAs (weights) or 8 (pixels) between that and the next use.
+//    of the products leaves 3 to 5 products (weights) or 2 to 5 (pixels), of MK*MP MFMAs each, between that and the next use.
 //
 // Row pairs (template flag F23): 3x3 filters at stride 1 through the identity F(2,3) of kern_igemm.h, two thirds of the
 // MFMAs.  A "pixel" is a pair of output rows.  Each of the four sums m0..m3 is a convolution of its own with a filter of
@@ -34,10 +35,13 @@
 // split) with a row combination of the weights, so the waves compute them one after the other with one set of
 // accumulators, and add each unit's to the pair's two rows (y0 += m0 + m1 + m2, y1 += m1 - m2 - m3): the sums that the
 // MFMAs round are short.  A unit is 16 channels of one combination, the four of a group follow one another.
+// Three sums and two rows a result: registers for tiles of 128 filters x 64 pairs, on four computing waves (one a SIMD, 112
+// vector registers and the accumulators; eight waves of half as much each take 1 to 3 % longer).
 // It takes fewer MFMAs than the other kernel and more staging (two loads per pair, combination and column for three taps,
 // against one per pixel for nine), and that bounds it on all but planes too small to fill the chip's tiles, where the
-// split of the reduction counts: 14x14x512, 3x3x512x512: 32 images 190 -> 152 us, one image 57 -> 41 us against the fp32
-// row-pair kernel, but 56x56x256, 32 images 596 -> 663 us, 224x224x64 663 -> 822 us (split_pairs_pay in igemm_plan.h).
+// split of the reduction counts: 14x14x512, 3x3x512x512: 32 images 188 -> 181 us, one image 57 -> 40 us against the fp32
+// row-pair kernel (split_faster in igemm_plan.h; on tiles of 128 pairs, with operands held less exactly, 56x56x256, 32 images
+// 596 -> 663 us, 224x224x64 663 -> 822 us).
 #pragma once
 #include "kern_igemm_bf16.h"
 

@@ -162,10 +162,11 @@ struct SplitParams : IgemmParams {
 };
 
 // A wave's part of a stored tile t: results that are not finite (the ReLU must not hide them: they are stored as NaN) are read
-// back, four filters of the lane's pixel at a time, and replaced.  A function of its own: inside the kernel it would live off the
-// kernel's registers (92 vector registers of the merged form spilled).  params: where the kernel's arguments are in memory.
+// back, four filters of the lane's pixel at a time, and replaced.  params_lo, params_hi: where the kernel's arguments are in memory.
+// What it needs it reads from there anew: taken from the kernel's own copies, with the kernel's sums still alive around it, it
+// cost the kernel up to 240 spilled vector registers.
 template <int TK, int WK, int MK, int MP, int TQ, int ROWS, bool MERGED>
-__device__ __attribute__((noinline)) void repair_tile(unsigned params_lo, unsigned params_hi, int t, int wave) {
+__device__ __attribute__((always_inline)) inline void repair_tile(unsigned params_lo, unsigned params_hi, int t, int wave) {
     const size_t at = (size_t)(unsigned)__builtin_amdgcn_readfirstlane(params_hi) << 32 | (unsigned)__builtin_amdgcn_readfirstlane(params_lo);
     const SplitParams &P = *(const SplitParams *)(const __attribute__((address_space(4))) void *)at;
     t = __builtin_amdgcn_readfirstlane(t);
@@ -205,6 +206,14 @@ __device__ __attribute__((noinline)) void repair_tile(unsigned params_lo, unsign
         for (int f = 0; f < 4; ++f)
             if (need >> f & 1) *o[f] = P.relu ? fmaxf(s[f], 0.f) : s[f];
     }
+}
+
+// Row pairs: as a function, which the kernel's sums, in more registers there, stay clear of (14x14x512, 3x3x512x512, 32 images: 186 us,
+// 190 with it inside).  The others keep it inside: a call takes stack in memory, up to 180 bytes a lane for merged phases, which the
+// runtime sets aside for every wave that fits the chip (94 MB).
+template <int TK, int WK, int MK, int MP, int TQ>
+__device__ __attribute__((noinline)) void repair_pairs(unsigned params_lo, unsigned params_hi, int t, int wave) {
+    repair_tile<TK, WK, MK, MP, TQ, 2, false>(params_lo, params_hi, t, wave);
 }
 
 // Weights for F23: [g][kt][unit][filter column][plane][octet][kk][8 channels]; a thread reads the three rows of one filter
@@ -687,7 +696,8 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             else store_tile();
             if (__any(odd_results)) {
                 const size_t params = (size_t)__builtin_amdgcn_kernarg_segment_ptr();
-                repair_tile<TK, WK, MK, MP, TQ, ROWS, MERGED>((unsigned)params, (unsigned)(params >> 32), tile_of(t), wave);
+                if constexpr (F23) repair_pairs<TK, WK, MK, MP, TQ>((unsigned)params, (unsigned)(params >> 32), tile_of(t), wave);
+                else repair_tile<TK, WK, MK, MP, TQ, ROWS, MERGED>((unsigned)params, (unsigned)(params >> 32), tile_of(t), wave);
             }
         } else {
             store_partial(2 * vb + (first_segment ? 0 : 1));

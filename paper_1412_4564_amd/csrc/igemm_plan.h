@@ -308,7 +308,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         if ((int64_t)TI * v.Wo * v.N >= ((int64_t)1 << 30)) continue;
         const int SC = slab_columns(v, TI, TQ, Wp);
         const int64_t CP = (SR * SC + 63) / 64 * 64;
-        if (CP > (planes == 3 ? split_ept(f23s) : bf16 ? bf_ept_max(NL) : 32) * NL) continue;
+        if (CP > (planes == 3 ? split_samples(f23s) : (bf16 ? bf_ept_max(NL) : 32) * NL)) continue;
         // an image crossing inside a tile moves the window by whole images: keep offsets in range
         const int64_t span = (int64_t)SC / Wp + 2;
         if ((double)span * v.Ctot * v.H * v.W * 4.0 >= 2147483647.0) continue;
@@ -525,10 +525,11 @@ inline double call_us(const ConvView &v, const IgemmPlan &pl, int n_cu) {
 // Over those 568 calls: always three planes 27.8 ms, always fp32 36.4 ms, by this rule 27.55 ms, the faster of the two each time
 // 27.1 ms.  Small layers are what it keeps on the fp32 kernel, which cuts a tile's reduction finer: 32x32x32 -> 3, 5x5,
 // eight images 16.4 us against 25.1, 16x16x32, 5x5x32x32, one image 15.3 against 25.6.
-// Row pairs: the fp32 kernel where the slab is large beside its 64 pairs (58x58x280, 160 filters, three images: 91 us against 111;
-// 52x52x424, 121 filters, nine images 143 against 173), since staging bounds the three-plane one.
+// Row pairs, whose slab the planner keeps within 128 samples (split_samples), always: of 222 calls one is slower than on the fp32
+// kernel by more than 1 % (52x52x424, 121 filters, nine images 145 -> 149 us), half of them by 14 % or more faster.  With slabs of up to 256
+// samples beside the 64 pairs, staging bound them (58x58x280, 160 filters, three images 91 -> 111 us).
 inline bool split_faster(const ConvView &v, const IgemmPlan &split, const IgemmPlan &fp32, int n_cu) {
-    if (split.P.wino_Ho) return split.P.CP <= 128;
+    if (split.P.wino_Ho) return true;
     return call_us(v, split, n_cu) < 0.97 * call_us(v, fp32, n_cu);
 }
 

@@ -35,12 +35,12 @@
 // split) with a row combination of the weights, so the waves compute them one after the other with one set of
 // accumulators, and add each unit's to the pair's two rows (y0 += m0 + m1 + m2, y1 += m1 - m2 - m3): the sums that the
 // MFMAs round are short.  A unit is 16 channels of one combination, the four of a group follow one another.
-// Three sums and two rows a result: registers for tiles of 128 filters x 64 pairs, on four computing waves (one a SIMD, 112
-// vector registers and the accumulators; eight waves of half as much each take 1 to 3 % longer).
+// Three sums and two rows a result: registers for tiles of 128 filters x 64 pairs, on four computing waves (one a SIMD; eight waves of
+// half as much each take 1 to 3 % longer), which hold the weights of a whole unit.
 // It takes fewer MFMAs than the other kernel and more staging (two loads per pair, combination and column for three taps,
 // against one per pixel for nine), and that bounds it on all but planes too small to fill the chip's tiles, where the
-// split of the reduction counts: 14x14x512, 3x3x512x512: 32 images 188 -> 181 us, one image 57 -> 40 us against the fp32
-// row-pair kernel (split_faster in igemm_plan.h; on tiles of 128 pairs, with operands held less exactly, 56x56x256, 32 images
+// split of the reduction counts: 14x14x512, 3x3x512x512: 32 images 195 -> 173 us, one image 57 -> 39 us against the fp32
+// row-pair kernel (split_pairs_possible in igemm_plan.h; on tiles of 128 pairs, with operands held less exactly, 56x56x256, 32 images
 // 596 -> 663 us, 224x224x64 663 -> 822 us).
 #pragma once
 #include "kern_igemm_bf16.h"
@@ -50,8 +50,10 @@ namespace mcn {
 constexpr int SPLIT_SLABS = 3;         // slab buffers: computed, next (being read ahead), written
 constexpr int SPLIT_BIASES = 4;        // bias buffers: a bias is written at most two tiles ahead
 constexpr int SPLIT_STAGE_WAVES = 4;   // waves that fetch and split the input
-// slab samples a thread stages per unit, at most (16 registers each in three sets; F23: 32 each in two)
-__device__ __host__ constexpr int split_ept(bool f23) { return f23 ? 1 : 2; }
+// Slab samples of a unit, at most: a staging thread brings two of them (16 channels, as many registers, in three sets), or, of
+// row pairs, half a one (8 channels of two rows each, in two sets; whole ones on half of the threads: 14x14x512, 3x3x512x512, one image
+// 39.9 -> 38.7 us, eight images 69 -> 67 us).
+__device__ __host__ constexpr int split_samples(bool f23) { return 64 * SPLIT_STAGE_WAVES * (f23 ? 1 : 4) / 2; }
 
 // ---- results that are not finite -------------------------------------------------------
 // An operand that is infinite splits into (inf, nan, nan), so every result that it enters comes out as NaN where the plain
@@ -262,7 +264,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     constexpr int TK = WK * MK * 32;
     constexpr int TQ = WP * MP * 32;
     constexpr int ROWS = F23 ? 2 : 1;              // input rows of a slab sample; output rows of a pixel
-    constexpr int EPT = split_ept(F23), SETS = F23 ? 2 : 3;
+    constexpr int EPT = F23 ? 1 : 2, CH = F23 ? 8 : BF_DC, SETS = F23 ? 2 : 3;      // samples, channels a staging thread brings; units on their way
     const int NU = P.NU;
     const int CP = P.CP, SRP = P.SRP;
     const int XSZ = 3 * 2 * CP * 4;      // 32-bit words of slab per buffer: 3 planes x 2 octets x CP samples x 16 bytes
@@ -305,11 +307,13 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         // computed in less time than a sample takes from memory.  What a unit does not have is requested
         // out of range and reads as zero: no divergent branches, so that the waits for a set leave younger ones in flight.
         struct Samples {
-            float v[EPT][ROWS][BF_DC];
+            float v[EPT][ROWS][CH];
             int uu, kt, g, seq, combo;
         };
         Samples set[SETS];
         const int ltid = tid - NT, lwave = wave - WK * WP;
+        // F23: the first two waves bring the first octet of channels, the others the second
+        const int e0 = F23 ? ltid & (NL / 2 - 1) : ltid, wave0 = 64 * (F23 ? lwave & (SPLIT_STAGE_WAVES / 2 - 1) : lwave), oct0 = F23 ? lwave / (SPLIT_STAGE_WAVES / 2) : 0;
         int t = n_own ? vb * P.own : t_s, uu = n_own ? 0 : uu_s, n = 0;      // next unit to request, units before it
         int kt = 0, g = 0, seq = -1;
         unsigned go[EPT][F23 ? 4 : 1];    // byte offset of the thread's samples in channel 0, or SLAB_INVALID; F23: of the pair's four rows
@@ -329,7 +333,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             xrs = __builtin_amdgcn_make_buffer_rsrc((void *)(in + in_base), 0, (int)in_left, BUFFER_FLAGS);
 #pragma unroll
             for (int s = 0; s < EPT; ++s) {
-                const int e = ltid + NL * s;
+                const int e = e0 + NL * s;
                 const int col = div32(e, P.dSRP);
                 const int r = e - col * SRP;
                 const int U = u0 + col;
@@ -343,7 +347,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             }
         };
         auto request = [&](Samples &q) __attribute__((always_inline)) {
-            const int combo = uu & 3, c0 = (F23 ? uu >> 2 : uu) * BF_DC, c_end = n < nunits ? P.Cg : 0;
+            const int combo = uu & 3, c0 = (F23 ? uu >> 2 : uu) * BF_DC + 8 * oct0, c_end = n < nunits ? P.Cg : 0;
             q.uu = uu; q.kt = kt; q.g = g; q.seq = seq; q.combo = combo;
 #pragma unroll
             for (int s = 0; s < EPT; ++s) {
@@ -356,7 +360,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                         else off = combo == 3 ? go[s][3] : combo == 2 ? go[s][1] : go[s][2];
                     }
 #pragma unroll
-                    for (int d = 0; d < BF_DC; ++d)
+                    for (int d = 0; d < CH; ++d)
                         // channels past the group's last one read as zero (their weights are zero too)
                         q.v[s][a][d] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
                             xrs, c0 + d < c_end ? off : SLAB_INVALID, (unsigned)(c0 + d) * (unsigned)HW * 4u, 0));
@@ -387,19 +391,20 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             slab = slab + 1 == SPLIT_SLABS ? 0 : slab + 1;
 #pragma unroll
             for (int s = 0; s < EPT; ++s) {
-                const int e = ltid + NL * s;
-                if (lwave * 64 + NL * s >= CP) continue;         // CP is a multiple of 64
+                const int e = e0 + NL * s;
+                if (wave0 + NL * s >= CP) continue;              // CP is a multiple of 64
                 if constexpr (F23) {
                     const float sign = q.combo == 1 ? 1.f : -1.f;
 #pragma unroll
-                    for (int d = 0; d < BF_DC; ++d) q.v[s][0][d] = fmaf(sign, q.v[s][1][d], q.v[s][0][d]);
+                    for (int d = 0; d < CH; ++d) q.v[s][0][d] = fmaf(sign, q.v[s][1][d], q.v[s][0][d]);
                 }
 #pragma unroll
-                for (int o = 0; o < 2; ++o) {
+                for (int i = 0; i < CH / 8; ++i) {
+                    const int o = oct0 + i;
                     unsigned hi[4], mid[4], lo[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        split_bf16x3(q.v[s][0][8 * o + 2 * j], q.v[s][0][8 * o + 2 * j + 1], &hi[j], &mid[j], &lo[j]);
+                        split_bf16x3(q.v[s][0][8 * i + 2 * j], q.v[s][0][8 * i + 2 * j + 1], &hi[j], &mid[j], &lo[j]);
                     const uintx4 h = {hi[0], hi[1], hi[2], hi[3]}, m = {mid[0], mid[1], mid[2], mid[3]}, l = {lo[0], lo[1], lo[2], lo[3]};
                     *reinterpret_cast<uintx4 *>(xb + (size_t)((0 + o) * CP + e) * 4) = h;
                     *reinterpret_cast<uintx4 *>(xb + (size_t)((2 + o) * CP + e) * 4) = m;
@@ -524,7 +529,8 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     };
     typedef bf16x8 OpA[MK];
     typedef bf16x8 OpB[MP];
-    OpA ah, am, al;
+    OpA wreg[F23 ? 3 : 1][3];                  // [tap (F23)][plane]
+    OpA (&ah) = wreg[0][0], (&am) = wreg[0][1], (&al) = wreg[0][2];
     OpB bh, bm, bl;
     auto load_a = [&](OpA &a, int pl) __attribute__((always_inline)) {
 #pragma unroll
@@ -544,21 +550,29 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     };
     auto prime = [&]() __attribute__((always_inline)) {
         load_a(ah, 0); load_b(bl, 2); load_b(bm, 1); load_b(bh, 0); load_a(am, 1); load_a(al, 2);
+        if constexpr (F23) {
+#pragma unroll
+            for (int s = 1; s < 3; ++s) {
+                wo += WSTEP;
+                load_a(wreg[s][0], 0); load_a(wreg[s][1], 1); load_a(wreg[s][2], 2);
+            }
+        }
     };
-    // one step; wo, xo, so are the next step's when it begins; first: the first one of a combination's sums (F23)
-    auto step = [&](bool first) __attribute__((always_inline)) {
-        mma(sum16, ah, bl, F23 && first);
+    // one step; xo, so are the next step's when it begins, wo is where the weights are that h, m, l hold next: the next step's, or
+    // (F23) the same tap's of the next unit; first: the first one of a combination's sums (F23)
+    auto step = [&](OpA &h, OpA &m, OpA &l, bool first) __attribute__((always_inline)) {
+        mma(sum16, h, bl, F23 && first);
         load_b(bl, 2);
-        mma(sum8, ah, bm, F23 && first);
-        mma(acc, ah, bh, F23 && first);
-        load_a(ah, 0);
-        mma(sum16, am, bm);
+        mma(sum8, h, bm, F23 && first);
+        mma(acc, h, bh, F23 && first);
+        load_a(h, 0);
+        mma(sum16, m, bm);
         load_b(bm, 1);
-        mma(sum8, am, bh);
-        load_a(am, 1);
-        mma(sum16, al, bh);
+        mma(sum8, m, bh);
+        load_a(m, 1);
+        mma(sum16, l, bh);
         load_b(bh, 0);
-        load_a(al, 2);
+        load_a(l, 2);
         __builtin_amdgcn_sched_barrier(0);
     };
 
@@ -660,14 +674,27 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         prime();
         for (int u = 0;;) {
             __builtin_amdgcn_sched_barrier(0);
-            for (int s = 1; s < T; ++s) {
-                wo += WSTEP;
-                next_tap();
-                step(s == 1);
+            if constexpr (F23) {
+                // One wave a SIMD: the weights of a step are requested a whole unit ahead, since nothing else covers their way from
+                // the L2 (14x14x512, 3x3x512x512, 32 images: 187 us with one step ahead, now 173).  Past the last unit they read what follows,
+                // or zero, for nothing.
+                wo += WSTEP; next_tap();
+                step(wreg[0][0], wreg[0][1], wreg[0][2], true);
+                wo += WSTEP; next_tap();
+                step(wreg[1][0], wreg[1][1], wreg[1][2], false);
+                wo += WSTEP; next_slab();
+                if (u + 1 < m) { so = 0; xo = xslab; }
+                step(wreg[2][0], wreg[2][1], wreg[2][2], false);
+            } else {
+                for (int s = 1; s < T; ++s) {
+                    wo += WSTEP;
+                    next_tap();
+                    step(ah, am, al, false);
+                }
+                next_slab();
+                if (u + 1 < m) { wo += WSTEP; fi = 0; so = 0; xo = xslab; }
+                step(ah, am, al, false);           // the segment's last one reads its own operands again, for nothing
             }
-            next_slab();
-            if (u + 1 < m) { wo += WSTEP; fi = 0; so = 0; xo = xslab; }
-            step(false);                           // the segment's last one reads its own operands again, for nothing
             if constexpr (F23) {
                 fold((uu + u) & 3);
                 // before the barrier, where waves wait for one another anyway: the compiler would move it behind (14x14x512,
@@ -683,7 +710,9 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         // a use of what the last step read for nothing: without one the compiler moves the weights' loads of every unit's last step
         // behind its products, where their latency is not hidden
 #pragma unroll
-        for (int mk = 0; mk < MK; ++mk) asm volatile("" ::"v"(ah[mk]), "v"(am[mk]), "v"(al[mk]));
+        for (int s = 0; s < (F23 ? 3 : 1); ++s)
+#pragma unroll
+            for (int mk = 0; mk < MK; ++mk) asm volatile("" ::"v"(wreg[s][0][mk]), "v"(wreg[s][1][mk]), "v"(wreg[s][2][mk]));
         done += m;
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)

@@ -83,6 +83,11 @@ typedef struct mcn_conv_desc {
  *   other one, half of the smallest fp32 number).  Results that are not finite there are summed again in
  *   fp32, so infinities and NaN come out as the plain sum gives them: NaN at little cost, an infinite operand
  *   in about a millisecond, infinite results everywhere at some thirty times the time of an ordinary call.
+ *   dzdw of layers that the row-pair kernel does not take runs the same way where that is estimated to be faster
+ *   (mcn_conv_operand_planes says 3): the same planes, products and error, half of the fp32 matrix core's on the
+ *   workloads.  A coefficient that is not finite there is summed again over the samples inside the array (a zero
+ *   of the padding times an infinity counts as zero): one NaN or infinity costs a few milliseconds, infinite
+ *   coefficients everywhere some seventy times the time of an ordinary call.
  * MCN_PREC_FP32_PLAIN: fp32 operands and accumulation, every product of the sum of Sec. 4.1
  *   formed as written, in fp32, and added one by one ("igemm" / "wgrad_igemm"): error bound n * 2^-24
  *   of the result's own sum of |w||x|; 3x3 stride-1 layers run about 1.3 times slower.

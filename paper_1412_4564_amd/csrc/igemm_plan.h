@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stddef.h>
 #include <stdlib.h>
+#include <math.h>
 #include "geom.h"
 #include "kern_igemm.h"
 #include "kern_igemm_bf16.h"
@@ -870,6 +871,197 @@ inline bool plan_wgrad_bf16(const ConvView &v, int n_cu, WgradBfPlan *pl) {
     pl->lds_bytes = 2 * ((size_t)TK * P.PYW + (size_t)NCH * P.CPC) * 16;
     pl->partial_floats = P.nchunks > 1 ? (size_t)P.nblocks * TK * TR : 0;
     return true;
+}
+
+}  // namespace mcn
+
+// ---- filter derivative, fp32 operands in three bf16 planes (kern_wgrad_split.h) -----------------
+#include "kern_wgrad_split.h"
+namespace mcn {
+
+enum WgradSplitShape { WGS_128x128 = 0, WGS_64x256 = 1, WGS_32x256 = 2 };
+
+struct WgradSplitPlan {
+    int shape;
+    int TK, TR;
+    bool linear;
+    WgradSplitParams P;
+    size_t lds_bytes;
+    size_t partial_floats;   // 2 slots of TK*TR per block
+    double us;               // estimated microseconds of the call
+};
+
+// Slab pitches in 32-bit words: lane r of an operand read is at word phase*PHP + fj*COLP + c*CHP + (row of the phase), and
+// 32 lanes should fall into 32 banks.  The pitches with the fewest collisions of at most `limit` words a plane, smallest first.
+inline void wgs_pitches(const ConvView &v, int NCH, int limit, WgradSplitParams *P) {
+    const int T = v.Hf * v.Wf;
+    const int lanes = 32 * 4 < T * v.Cg ? 32 * 4 : (T * v.Cg + 31) / 32 * 32;
+    const int b0 = P->COLP, c0 = P->CHP - P->NP * P->RC * b0;
+    long best = -1;
+    WgradSplitParams B = *P;
+    for (int b = 0; b < 16; ++b)
+        for (int c = 0; c < 32; ++c) {
+            const int colp = b0 + b, chp = P->NP * P->RC * colp + c0 + c;
+            if (NCH * chp > limit) break;
+            int extra = 0;                             // reads beyond the first, over the fullest bank of each half-wave
+            for (int r0 = 0; r0 < lanes; r0 += 32) {
+                unsigned char count[32] = {};
+                int most = 0;
+                for (int r = r0, ch = r0 / T, fj = r0 % T / v.Hf, fi = r0 % v.Hf; r < r0 + 32; ++r) {
+                    const int n = ++count[(fi % v.Sh * P->PHP + fi / v.Sh + fj * colp + ch * chp) & 31];
+                    if (n > most) most = n;
+                    if (++fi == v.Hf) { fi = 0; if (++fj == v.Wf) { fj = 0; ++ch; } }
+                }
+                extra += most - 1;
+            }
+            const long cost = (long)extra * 4096 * 32 / lanes + chp;
+            if (best < 0 || cost < best) { best = cost; B.COLP = colp; B.MPP = P->RC * colp; B.CHP = chp; }
+        }
+    *P = B;
+}
+
+// max(a, b, c), rounded where two of them are close, and a part of what the largest one hides
+inline double overlapped(double a, double b, double c, double part) {
+    const double most = a > b ? (a > c ? a : c) : (b > c ? b : c);
+    const double x = a * a, y = b * b, z = c * c;
+    return sqrt(sqrt(x * x + y * y + z * z)) + part * (a + b + c - most);
+}
+
+inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool streams, WgradSplitPlan *pl) {
+    const int TK = shape == WGS_128x128 ? 128 : shape == WGS_64x256 ? 64 : 32, TR = shape == WGS_128x128 ? 128 : 256;
+    const int T = v.Hf * v.Wf;
+    const int64_t R64 = (int64_t)T * v.Cg;
+    if (R64 >= ((int64_t)1 << 30)) return false;
+    const int R = (int)R64, RT = (R + TR - 1) / TR, KT = (v.Kg + TK - 1) / TK;
+    int NCH = 0;
+    for (int rt = 0; rt < RT && rt <= T; ++rt) {       // the pattern repeats after T tiles
+        const int lo = rt * TR, hi = lo + TR < R ? lo + TR : R, n = (hi - 1) / T - lo / T + 1;
+        if (n > NCH) NCH = n;
+    }
+    const int64_t tiles = (int64_t)v.G * KT * RT;
+    if (tiles >= ((int64_t)1 << 20)) return false;
+    const int NPH = v.Hf < v.Sh ? v.Hf : v.Sh;
+    const int threads = 64 * WGS_STAGE_WAVES;
+    const bool linear = T == 1 && v.Sh == 1 && v.Sw == 1 && v.Pt == 0 && v.Pl == 0;
+    // octets per staging thread of the instantiations there are (launch_wgrad_split)
+    const int most_y = linear ? (TK == 128 ? 3 : 1) : TK == 32 ? 2 : 4, most_x = linear ? (TK == 128 ? 3 : 4) : 2;
+    double best = 1e300;
+    WgradSplitParams B = {};
+    for (int TIQ = 1; TIQ <= 32; ++TIQ) {
+        const int RB = (v.Ho + 4 * TIQ - 1) / (4 * TIQ);
+        if (TIQ > 1 && (v.Ho + 4 * TIQ - 5) / (4 * TIQ - 4) == RB) continue;          // fewer rows give the same row blocks
+        for (int NP = 1; NP <= 4; NP *= 2)
+            for (int MC = 1; MC <= v.Wo && TIQ * MC * NP <= 32; ++MC) {
+                const int NO = TIQ * MC * NP;
+                if (NO & 1) continue;
+                if (NP > 1 && NP > (v.N + 1) / 2) continue;
+                const int TI = (v.Ho + RB - 1) / RB < 4 * TIQ ? (v.Ho + RB - 1) / RB : 4 * TIQ;      // rows shared out evenly
+                const int YW = TK * NO;
+                if (YW > most_y * threads) break;
+                const int SC = (MC - 1) * v.Sw + v.Wf;
+                const int XQ = (4 * TIQ + (v.Hf - 1) / v.Sh + 3) / 4;        // quads of a phase
+                const int64_t XW1 = (int64_t)NCH * NP * NPH * XQ;
+                const int step = MC * v.Sw < SC ? MC * v.Sw : SC, RC = 2 * SC;
+                if (XW1 * step > most_x * threads || XW1 * (SC - step) > 2 * threads) break;
+                const int PHP = 4 * XQ, COLP = NPH * PHP, MPP = RC * COLP, CHP = NP * MPP;
+                const int PYW = NO | 1, XPL = NCH * (CHP + NP * RC * 4 + 8);         // room for pitches: wgs_pitches
+                const size_t lds = 2 * (size_t)TK * PYW * 48 + (size_t)3 * XPL * 4 + 16;
+                if (lds > IGEMM_LDS_LIMIT) break;
+                const int CC = (v.Wo + MC - 1) / MC, IB = (v.N + 2 * NP - 1) / (2 * NP);
+                // Microseconds of a unit: its MFMAs, splitting what it stages, fetching that (memory lines of 128 bytes), and of the
+                // whole call.  The constants are a fit to 31000 timed calls of 13400 random layers (several tiles and patches of each;
+                // the estimate is off by 8 %, 1 standard deviation).
+                const int64_t NU = (int64_t)RB * CC * IB, total = tiles * NU;
+                const int kn = v.Kg < TK ? v.Kg : TK, images = 2 * NP < v.N ? 2 * NP : v.N;
+                const double extra = (double)(SC - step) / CC, columns = step + extra;
+                const double lines = (double)kn * images * (TI == v.Ho ? MC * TI / 32.0 + 1.0 : MC * (TI / 32.0 + 1.0)) +
+                                     (double)NCH * images * columns * (((TI - 1) * v.Sh + v.Hf) / 32.0 + 1.0);
+                const double mfma = NO / 2 * (TK == 32 ? 0.245 : 0.47);
+                const double split = 0.865 + 0.228 * ((YW + threads - 1) / threads) + (linear ? 0.222 : 0.308) * (double)((XW1 * step + threads - 1) / threads) +
+                                     0.67 * XW1 * extra / threads;
+                const double unit = overlapped(mfma, split, lines * (streams ? 1.84e-3 : 1.09e-3), 0.225);
+                double us = unit * (double)((total + n_cu - 1) / n_cu);
+                // The two schedules of kern_wgrad.h; chunks for arrays that stream from memory, at most one to a compute unit, if they are
+                // estimated to be faster or keep the compute units about as busy (they read the arrays fewer times).
+                int nchunks = 0;
+                if (streams && tiles <= n_cu) {
+                    const int64_t nch = n_cu / tiles < NU ? n_cu / tiles : NU;
+                    const double chunked = overlapped(mfma, split, lines * 1.48e-3, 0.225) * (double)((NU + nch - 1) / nch);
+                    if (chunked < us || (double)total >= 0.95 * n_cu * (double)((NU + nch - 1) / nch)) { us = chunked; nchunks = (int)nch; }
+                }
+                if (us < best) {
+                    best = us;
+                    B.TI = TI; B.RB = RB; B.MC = MC; B.CC = CC; B.SC = SC; B.NP = NP; B.IB = IB; B.TIQ = TIQ; B.NO = NO; B.PYW = PYW; B.nchunks = nchunks;
+                    B.NPH = NPH; B.XQ = XQ; B.PHP = PHP; B.COLP = COLP; B.MPP = MPP; B.CHP = CHP; B.YW = YW; B.XW1 = (int)XW1; B.RC = RC; B.step = step;
+                }
+            }
+    }
+    if (best >= 1e300) return false;
+    WgradSplitParams &P = pl->P;
+    P = B;
+    wgs_pitches(v, NCH, (int)(IGEMM_LDS_LIMIT - 2 * (size_t)TK * P.PYW * 48 - 16) / 12, &P);
+    P.XPL = NCH * P.CHP;
+    P.counts = 2 * TK * P.PYW * 48 + 3 * P.XPL * 4;
+    P.H = v.H; P.W = v.W; P.N = v.N; P.Ctot = v.Ctot; P.Cg = v.Cg;
+    P.Ho = v.Ho; P.Wo = v.Wo; P.Ktot = v.Ktot; P.Kg = v.Kg; P.G = v.G;
+    P.Hf = v.Hf; P.Wf = v.Wf; P.Sh = v.Sh; P.Sw = v.Sw; P.Pt = v.Pt; P.Pl = v.Pl;
+    P.xsj = v.H; P.xsc = v.H * v.W; P.xsn = v.H * v.W * v.Ctot; P.xtot = (long long)P.xsn * v.N;
+    P.ysj = v.Ho; P.ysc = v.Ho * v.Wo; P.ysn = v.Ho * v.Wo * v.Ktot; P.ytot = (long long)P.ysn * v.N;
+    // 32-bit byte offsets inside a unit's images
+    if ((double)v.H * v.W * v.Ctot * 8 * P.NP >= 2147483647.0 || (double)v.Ho * v.Wo * v.Ktot * 8 * P.NP >= 2147483647.0) return false;
+    P.KT = KT; P.RT = RT; P.R = R; P.tiles = (int)tiles;
+    const int64_t NU = (int64_t)P.RB * P.CC * P.IB;
+    if (NU >= ((int64_t)1 << 30)) return false;
+    P.NU = (int)NU;
+    P.dRB = make_div32(P.RB); P.dCC = make_div32(P.CC);
+    P.dXW1 = make_div32(P.XW1); P.dXQ = make_div32(P.XQ); P.dNPH = make_div32(P.NPH); P.dNP = make_div32(P.NP);
+    const int64_t total = tiles * NU;
+    P.nblocks = P.nchunks > 0 ? (int)tiles * P.nchunks : (int)(total < n_cu ? total : n_cu);
+    pl->shape = shape; pl->TK = TK; pl->TR = TR;
+    pl->linear = linear;
+    pl->lds_bytes = (size_t)P.counts + 16;
+    pl->partial_floats = P.nblocks > 1 && P.nchunks != 1 ? (size_t)2 * P.nblocks * TK * TR : 0;
+    const double filled = (v.Kg < TK ? (double)v.Kg / TK : 1.0) * (R < TR ? (double)R / TR : 1.0);        // of a tile
+    pl->us = 12.7 + best + (pl->partial_floats ? 0.298 * 8e-6 * filled * P.nblocks * TK * TR : 0.0);
+    return true;
+}
+
+// Estimated microseconds of a call on the fp32 kernel, from the same calls: off by 14 %.
+inline double wgrad_fp32_us(const ConvView &v, const WgradPlan &pl, int n_cu) {
+    const WgradParams &P = pl.P;
+    const int lanes = pl.wino ? pl.TR / 3 : pl.TR, R = pl.wino ? v.Wf * v.Cg : P.R;
+    const double rate = pl.shape == WG_64x192 ? 1.2023 : pl.shape == WG_32x256 ? 1.0474 : pl.shape == WG_96x128 ? 0.9502 : pl.shape == WG_96x384 ? 1.2412 : 1.1706;
+    const double resident = P.nblocks > n_cu && pl.occupancy > 1 ? 2.0 : 1.0, rounds = ceil((double)P.nblocks / (n_cu * pl.occupancy));
+    const int kn = v.Kg < pl.TK ? v.Kg : pl.TK, SRC = P.SRP * P.SC;
+    const double lines = (double)kn * P.MC * (P.TI / 32.0 + 1.0) + (double)P.XS / SRC * (SRC / 32.0 + P.MC);
+    const double mfma = pl.TK * lanes / 1024 / 4.0 * P.PCH / 2 * 64.0 / 2400.0 * rate * resident, fetch = 1.631 + resident * lines * 1.3143e-3;
+    const double unit = overlapped(mfma, fetch, 0.0, 0.421);
+    const double filled = (v.Kg < pl.TK ? (double)v.Kg / pl.TK : 1.0) * (R < lanes ? (double)R / lanes : 1.0);
+    return 13.1 + rounds * ceil((double)P.tiles * P.NU / P.nblocks) * unit + 0.2884 * 4e-6 * (double)pl.partial_floats * filled;
+}
+
+// Whether the three-plane kernel is the faster one; split, fp32: the two plans.  Over 15600 other random layers: always fp32 1.437 s,
+// by this rule 1.031 s, the faster of the two each time 1.019 s; of the 10687 that it sends to three planes 87 are slower there by more
+// than 2 %, 44 by more than 5 %.  The 4 us: calls of 15 to 20 us are launches, and the estimates do not tell their kernels apart.
+inline bool wgrad_split_faster(const ConvView &v, const WgradSplitPlan &split, const WgradPlan &fp32, int n_cu) {
+    return split.us < wgrad_fp32_us(v, fp32, n_cu) - 4.0;
+}
+
+inline bool plan_wgrad_split(const ConvView &view, int n_cu, WgradSplitPlan *pl) {
+    ConvView v = view;
+    if (v.Hf == 1 && v.Wf == 1 && v.Sh == 1 && v.Sw == 1 && v.Pt == 0 && v.Pl == 0 && v.H == v.Ho && v.W == v.Wo) {
+        v.H = v.Ho = v.H * v.W;          // a plane is one column
+        v.W = v.Wo = 1;
+    }
+    const bool streams = 4.0 * ((double)v.H * v.W * v.Ctot + (double)v.Ho * v.Wo * v.Ktot) * v.N > 64.0 * 1024 * 1024;
+    bool ok = false;
+    for (int shape = 0; shape < 3; ++shape) {
+        if (shape == WGS_32x256 ? v.Kg > 32 : v.Kg <= 32) continue;
+        if (shape == WGS_128x128 && v.Kg <= 64) continue;
+        WgradSplitPlan one;
+        if (plan_wgrad_split_shape(v, n_cu, shape, streams, &one) && (!ok || one.us < pl->us)) { *pl = one; ok = true; }
+    }
+    return ok;
 }
 
 }  // namespace mcn

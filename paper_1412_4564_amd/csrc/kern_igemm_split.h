@@ -69,8 +69,6 @@ struct PlainView {
     int HfA, WfA, DfA, B0i, B0j;
 };
 
-__device__ inline bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
-
 // NF results: filters k0 .. k0+NF-1 of pixel (io, jo, n) of group g, those whose bit of `need` is set; s: their bias, then the
 // sum.  A lane whose results are all NaN is done.  Bound by address arithmetic and latency: the x of a tap and channel is read
 // once for all NF filters, the loads of four channels are in flight together.  A diverged batch (NaN) costs little, an infinite

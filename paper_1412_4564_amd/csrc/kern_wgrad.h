@@ -554,10 +554,14 @@ __global__ __launch_bounds__(64 * (WK * WR + WGRAD_LOADER_WAVES), WPE) void wgra
 // fraction of every piece.
 // CHUNKED: the pieces of tile t are the first slots of blocks t + tiles*i, i < nchunks; else those of the blocks
 // whose equal ranges of units overlap the tile.
-template <int TK, int TR, bool CHUNKED>
-__global__ __launch_bounds__(512) void wgrad_fixup_kernel(WgradParams P, const float *__restrict__ part,
+// Repair: what becomes of sums that are not finite (kern_wgrad_split.h).
+struct KeepSums {
+    static constexpr bool on = false;
+};
+template <int TK, int TR, bool CHUNKED, class Repair = KeepSums>
+__global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, const float *__restrict__ part,
                                                           const float *__restrict__ rbias, float *__restrict__ out,
-                                                          int G) {
+                                                          int G, Repair repair) {
     const int t = blockIdx.x;
     int npieces, slot0 = 0, b0 = 0;
     if constexpr (CHUNKED) {
@@ -597,6 +601,7 @@ __global__ __launch_bounds__(512) void wgrad_fixup_kernel(WgradParams P, const f
     const int Q = 512 / G;                              // words per block and pass
     const int q = threadIdx.x % Q, pg = threadIdx.x / Q;
     __shared__ float4 red[512];
+    bool odd = false;                                   // one of the thread's results is not finite
     for (int w0 = blockIdx.y * Q; w0 < nwords; w0 += gridDim.y * Q) {
         const int w = w0 + q;
         const bool valid = w < nwords;
@@ -639,13 +644,27 @@ __global__ __launch_bounds__(512) void wgrad_fixup_kernel(WgradParams P, const f
                 const int rl = 4 * c4 + j;
                 if (rl < rlim) {
                     float v = vv[j];
+                    const bool bad = Repair::on && not_finite(v);
+                    odd |= bad;
                     if (rbias) v += rbias[rt * TR + rl];
-                    if (P.relu) v = fmaxf(v, 0.f);
+                    if (P.relu) v = bad ? __uint_as_float(0x7fc00000u) : fmaxf(v, 0.f);      // the ReLU must not hide it
                     o[rl] = v;
                 }
             }
         }
         __syncthreads();
+    }
+    (void)odd;
+    if constexpr (Repair::on) {
+        if (__syncthreads_or(odd)) {
+            // all threads of the block sum again what is not finite of its slice, in the passes above
+            for (int w0 = blockIdx.y * Q; w0 < nwords; w0 += gridDim.y * Q)
+                repair(g, 4 * Q, [&](int at, int *k, int *r) {
+                    const int w = w0 + at / 4, kloc = w / C4, rl = 4 * (w - kloc * C4) + at % 4;
+                    *k = kt * TK + kloc; *r = rt * TR + rl;
+                    return w < nwords && rl < rlim;
+                }, rbias, P.relu, out);
+        }
     }
 }
 

@@ -106,6 +106,8 @@ struct PlanEntry {
     WgradPlan wg;
     bool wgb_ok;               // filter derivative on the bf16 kernel
     WgradBfPlan wgb;
+    bool wgs_ok;               // filter derivative on the three-plane kernel
+    WgradSplitPlan wgs;
     bool fc;                   // fully-connected layer: the three passes run as plain matrix products
     WgradPlan fc_fwd;
     IgemmPlan fc_bwd, fc_wg;
@@ -165,6 +167,8 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
     e.wg_ok = on && ((pairs && wino_enabled() && plan_wgrad(forward_view(g), ncu, &e.wg, true)) ||
                      plan_wgrad(forward_view(g), ncu, &e.wg));
     e.wgb_ok = on && d->precision == MCN_PREC_BF16 && plan_wgrad_bf16(forward_view(g), ncu, &e.wgb);
+    e.wgs_ok = on && !e.wgb_ok && pairs && wino_enabled() && !(e.wg_ok && e.wg.wino) && plan_wgrad_split(forward_view(g), ncu, &e.wgs) &&
+               (!e.wg_ok || wgrad_split_faster(forward_view(g), e.wgs, e.wg, ncu));
     e.fc = on && is_fully_connected(g) && (int64_t)g.H * g.W * g.D < ((int64_t)1 << 30) &&
            plan_wgrad(fc_forward_view(g), ncu, &e.fc_fwd) && plan_igemm(fc_backward_data_view(g), ncu, &e.fc_bwd) &&
            plan_igemm(fc_backward_filter_view(g), ncu, &e.fc_wg);
@@ -350,8 +354,8 @@ int launch_igemm(const IgemmPlan &pl, const float *in, const float *w, const flo
 
 // The pass that adds the pieces of the tiles shared between blocks (kern_wgrad.h).  G partial sums per result: about
 // the number of pieces per tile, at most 32; about 1024 blocks in all, none without work.
-template <int TK, int TR>
-int launch_wgrad_fixup(const WgradParams &P, const float *part, const float *rbias, float *out, hipStream_t s) {
+template <int TK, int TR, class Repair = KeepSums>
+int launch_wgrad_fixup(const WgradParams &P, const float *part, const float *rbias, float *out, hipStream_t s, Repair repair = Repair()) {
     const bool chunked = P.nchunks > 0;
     const long long pieces = chunked ? P.nchunks : ((long long)P.nblocks + P.tiles - 1) / P.tiles + 1;
     int G = 2;
@@ -363,9 +367,9 @@ int launch_wgrad_fixup(const WgradParams &P, const float *part, const float *rbi
     if (fy < 1) fy = 1;
     if (fy > passes) fy = passes;
     if (chunked)
-        hipLaunchKernelGGL((wgrad_fixup_kernel<TK, TR, true>), dim3(P.tiles, fy), dim3(512), 0, s, P, part, rbias, out, G);
+        hipLaunchKernelGGL((wgrad_fixup_kernel<TK, TR, true, Repair>), dim3(P.tiles, fy), dim3(512), 0, s, P, part, rbias, out, G, repair);
     else
-        hipLaunchKernelGGL((wgrad_fixup_kernel<TK, TR, false>), dim3(P.tiles, fy), dim3(512), 0, s, P, part, rbias, out, G);
+        hipLaunchKernelGGL((wgrad_fixup_kernel<TK, TR, false, Repair>), dim3(P.tiles, fy), dim3(512), 0, s, P, part, rbias, out, G, repair);
     return check_launch();
 }
 
@@ -433,6 +437,44 @@ int launch_wgrad(const WgradPlan &pl, const float *x, const float *dzdy, const f
     }
 }
 
+// fp32 operands in three bf16 planes (kern_wgrad_split.h)
+template <int WK, int WR, int MK, int YT, int XT, bool LINEAR>
+int launch_wgrad_split_inst(const WgradSplitPlan &pl, const float *x, const float *dzdy, const float *rbias, float *out, float *part,
+                            hipStream_t s, int relu) {
+    WgradSplitParams P = pl.P;
+    P.relu = relu;
+    auto kern = wgrad_split_kernel<WK, WR, MK, YT, XT, LINEAR>;
+    if (pl.lds_bytes > 48 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)pl.lds_bytes);
+        if (e != hipSuccess) { g_last_hip_error = (int)e; return MCN_HIP_ERROR; }
+    }
+    hipLaunchKernelGGL(kern, dim3(P.nchunks > 0 ? wg_chunk_grid(P.nblocks) : P.nblocks), dim3(64 * (WK * WR + WGS_STAGE_WAVES)), pl.lds_bytes, s, P,
+                       x, dzdy, rbias, out, part);
+    int st = check_launch();
+    if (st || P.nblocks < 2 || P.nchunks == 1) return st;
+    return launch_wgrad_fixup<WK * MK * 32, WR * 32>(P, part, rbias, out, s, RepairSums{P, x, dzdy});
+}
+
+template <int WK, int WR, int MK, int YT, int YTL, int XTL>
+int launch_wgrad_split_shape(const WgradSplitPlan &pl, const float *x, const float *dzdy, const float *rbias, float *out, float *part,
+                             hipStream_t s, int relu) {
+    if (pl.linear) return launch_wgrad_split_inst<WK, WR, MK, YTL, XTL, true>(pl, x, dzdy, rbias, out, part, s, relu);
+    return pl.P.step * pl.P.XW1 <= 64 * WGS_STAGE_WAVES ? launch_wgrad_split_inst<WK, WR, MK, YT, 1, false>(pl, x, dzdy, rbias, out, part, s, relu)
+                                                        : launch_wgrad_split_inst<WK, WR, MK, YT, 2, false>(pl, x, dzdy, rbias, out, part, s, relu);
+}
+
+int launch_wgrad_split(const WgradSplitPlan &pl, const float *x, const float *dzdy, const float *rbias, float *out, void *ws,
+                       hipStream_t s, int relu = 0) {
+    float *part = (float *)ws;
+    switch (pl.shape) {
+        case WGS_128x128: return launch_wgrad_split_shape<2, 4, 2, 4, 3, 3>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGS_64x256: return launch_wgrad_split_shape<1, 8, 2, 4, 1, 4>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGS_32x256: return launch_wgrad_split_shape<1, 8, 1, 2, 1, 4>(pl, x, dzdy, rbias, out, part, s, relu);
+        default: return MCN_BAD_ARG;
+    }
+}
+
 template <int WK, int WR, int MK, int MR, int HF>
 int launch_wgrad_bf16_inst(const WgradBfPlan &pl, const float *x, const float *dzdy, float *out, float *part,
                            hipStream_t s) {
@@ -495,6 +537,7 @@ size_t workspace_bytes(const mcn_conv_desc *d, const Geom &g, int op) {
         case MCN_OP_BACKWARD_FILTER:
             if (e->fc) return igemm_ws_bytes(e->fc_wg);
             if (e->wgb_ok) return e->wgb.partial_floats * sizeof(float);
+            if (e->wgs_ok) return e->wgs.partial_floats * sizeof(float);
             return e->wg_ok ? e->wg.partial_floats * sizeof(float) : 0;
         case MCN_OP_BACKWARD_FILTER_BIAS: {
             // fused: the filter derivative's scratch and the partial bias sums; otherwise the two passes one
@@ -567,6 +610,7 @@ int run_backward_filter(const mcn_conv_desc *desc, const Geom &g, const float *x
     const PlanEntry *pe = plans_for(desc, g);
     if (pe->fc) return launch_igemm(pe->fc_wg, x, dzdy, nullptr, dzdw, ws, s);
     if (pe->wgb_ok) return launch_wgrad_bf16(pe->wgb, x, dzdy, dzdw, ws, s);
+    if (pe->wgs_ok) return launch_wgrad_split(pe->wgs, x, dzdy, nullptr, dzdw, ws, s);
     if (pe->wg_ok) return launch_wgrad(pe->wg, x, dzdy, nullptr, dzdw, ws, s);
     const int total = (int)numel_w(g);
     hipLaunchKernelGGL(direct_backward_filter_kernel, dim3(cdiv(total, 4)), dim3(256), 0, s, g, x, dzdy, dzdw, total);
@@ -687,6 +731,7 @@ const char *mcn_conv_kernel_name(const mcn_conv_desc *desc, int op) {
         case MCN_OP_BACKWARD_FILTER:
             if (e->fc) return "fc_gemm";
             if (e->wgb_ok) return "wgrad_bf16";
+            if (e->wgs_ok) return e->wgs.P.nchunks > 0 ? "wgrad_igemm_chunked" : "wgrad_igemm";
             if (!e->wg_ok) return "direct";
             // "_chunked": the schedule for arrays that stream from memory (kern_wgrad.h, WgradParams::nchunks)
             if (e->wg.P.nchunks > 0) return e->wg.wino ? "wgrad_f23_chunked" : "wgrad_igemm_chunked";
@@ -705,7 +750,7 @@ int mcn_conv_operand_planes(const mcn_conv_desc *desc, int op) {
     if (e->fc) return 0;
     const IgemmPlan *pl = op == MCN_OP_FORWARD && e->fwd_ok ? &e->fwd : op == MCN_OP_BACKWARD_DATA && e->bwd_ok && e->n_bwd ? &e->bwd[0] : nullptr;
     if (pl) return pl->bf16 ? pl->planes : 0;
-    return (op == MCN_OP_BACKWARD_FILTER || op == MCN_OP_BACKWARD_FILTER_BIAS) && e->wgb_ok ? 1 : 0;
+    return op != MCN_OP_BACKWARD_FILTER && op != MCN_OP_BACKWARD_FILTER_BIAS ? 0 : e->wgb_ok ? 1 : e->wgs_ok ? 3 : 0;
 }
 
 int mcn_conv_forward(const mcn_conv_desc *desc, const float *x, const float *w, const float *b, float *y,

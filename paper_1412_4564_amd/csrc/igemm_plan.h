@@ -1064,4 +1064,19 @@ inline bool plan_wgrad_split(const ConvView &view, int n_cu, WgradSplitPlan *pl)
     return ok;
 }
 
+// Fully-connected forward (fc_forward_view): a lane's octet takes rows of a pair of images and there is one image only, so the R terms of a
+// result go as two images of R/2.  Odd R: false.  6x6x256 -> 4096, 256 images: 233 us on the fp32 kernel, 198 here; of 49 layers of 1x1 to
+// 7x7 inputs, 128 to 4096 channels, 16 to 256 images, 500 to 4096 filters the rule (wgrad_split_faster) sends 29 here, which are 1.12 to 1.58 times
+// as fast (median 1.35), with half of the error against 64 bits; none is slower.
+inline bool plan_fc_forward_split(const Geom &g, int n_cu, WgradSplitPlan *pl) {
+    ConvView v = fc_forward_view(g);
+    const int R = v.H;
+    if (R % 2) return false;
+    v.H = v.Ho = R / 2; v.N = 2;
+    if (!plan_wgrad_split(v, n_cu, pl)) return false;
+    WgradSplitParams &P = pl->P;
+    P.xsn = P.ysn = R / 2; P.xsc = P.ysc = R;          // offsets inside a unit stay below those that plan_wgrad_split has checked
+    return true;
+}
+
 }  // namespace mcn

@@ -110,6 +110,8 @@ struct PlanEntry {
     WgradSplitPlan wgs;
     bool fc;                   // fully-connected layer: the three passes run as plain matrix products
     WgradPlan fc_fwd;
+    bool fcs_ok;               // its forward pass on the three-plane kernel
+    WgradSplitPlan fcs;
     IgemmPlan fc_bwd, fc_wg;
 };
 constexpr int PLAN_CACHE = 8;
@@ -172,6 +174,7 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
     e.fc = on && is_fully_connected(g) && (int64_t)g.H * g.W * g.D < ((int64_t)1 << 30) &&
            plan_wgrad(fc_forward_view(g), ncu, &e.fc_fwd) && plan_igemm(fc_backward_data_view(g), ncu, &e.fc_bwd) &&
            plan_igemm(fc_backward_filter_view(g), ncu, &e.fc_wg);
+    e.fcs_ok = e.fc && pairs && wino_enabled() && plan_fc_forward_split(g, ncu, &e.fcs) && wgrad_split_faster(fc_forward_view(g), e.fcs, e.fc_fwd, ncu);
     return &e;
 }
 
@@ -524,7 +527,7 @@ size_t workspace_bytes(const mcn_conv_desc *d, const Geom &g, int op) {
             return plan_bias(g).ws_floats * sizeof(float);
         }
         case MCN_OP_FORWARD:
-            if (e->fc) return e->fc_fwd.partial_floats * sizeof(float);
+            if (e->fc) return (e->fcs_ok ? e->fcs.partial_floats : e->fc_fwd.partial_floats) * sizeof(float);
             return e->fwd_ok ? igemm_ws_bytes(e->fwd) : 0;
         case MCN_OP_BACKWARD_DATA: {
             if (e->fc) return igemm_ws_bytes(e->fc_bwd);
@@ -559,6 +562,7 @@ int run_forward(const mcn_conv_desc *desc, const Geom &g, const float *x, const 
     const size_t need = workspace_bytes(desc, g, MCN_OP_FORWARD);
     if (ws_bytes < need || (!ws && need)) return MCN_WORKSPACE_TOO_SMALL;
     const PlanEntry *pe = plans_for(desc, g);
+    if (pe->fcs_ok) return launch_wgrad_split(pe->fcs, w, x, b, y, ws, s, relu);
     if (pe->fc) return launch_wgrad(pe->fc_fwd, w, x, b, y, ws, s, relu);
     if (pe->fwd_ok) return launch_igemm(pe->fwd, x, w, b, y, ws, s, relu);
     const int total = (int)numel_y(g);
@@ -747,7 +751,7 @@ int mcn_conv_operand_planes(const mcn_conv_desc *desc, int op) {
     Geom g;
     if (make_geom(desc, &g) || op < MCN_OP_FORWARD || op > MCN_OP_BACKWARD_FILTER_BIAS) return -1;
     const PlanEntry *e = plans_for(desc, g);
-    if (e->fc) return 0;
+    if (e->fc) return op == MCN_OP_FORWARD && e->fcs_ok ? 3 : 0;
     const IgemmPlan *pl = op == MCN_OP_FORWARD && e->fwd_ok ? &e->fwd : op == MCN_OP_BACKWARD_DATA && e->bwd_ok && e->n_bwd ? &e->bwd[0] : nullptr;
     if (pl) return pl->bf16 ? pl->planes : 0;
     return op != MCN_OP_BACKWARD_FILTER && op != MCN_OP_BACKWARD_FILTER_BIAS ? 0 : e->wgb_ok ? 1 : e->wgs_ok ? 3 : 0;

@@ -105,3 +105,38 @@ def test_values_that_are_not_finite(case):
     assert torch.equal(got[inf].double(), want[inf])
     ok = touched & fits & torch.isfinite(want)
     assert torch.isfinite(got[ok]).all()
+
+
+# Fully-connected forward passes: the R terms of a result as two images of R/2, in the same kernel.  n = R here: below 3600.
+FC_CASES = [  # H, W, D, N, K
+    (4, 4, 96, 130, 1100),       # two images and 76 filters past a tile
+    (1, 1, 282, 162, 2771),      # halves of 141 rows: the last quad holds one
+    (7, 6, 61, 70, 900),         # halves of 1281 rows
+    (3, 3, 394, 60, 1011),       # fewer than 64 images
+]
+
+
+@pytest.mark.parametrize("case", range(len(FC_CASES)))
+@pytest.mark.parametrize("misalign", [0, 1])
+def test_fully_connected_forward(case, misalign):
+    h, w_, d, n, k = FC_CASES[case]
+    L = custom_layer(h, w_, d, n, h, w_, d, k, idx=900 + case)
+    make = lambda precision: B.make_desc(synth.x_shape(L), synth.w_shape(L), L["stride"], L["pad"], precision)
+    assert [B.mcn_conv_operand_planes(make(p), B.MCN_OP_FORWARD) for p in (B.MCN_PREC_FP32, B.MCN_PREC_BF16, B.MCN_PREC_FP32_PLAIN)] == [3, 3, 0]
+    x, w, b = synth.make_x(L, case), synth.make_w(L, case), synth.make_b(L, case)
+    xd, wd, bd = U.np64(x), U.np64(w), U.np64(b)
+    xg, wg, bg = U.gpu(x, misalign), U.gpu(w, misalign), U.gpu(b, misalign)
+    y = B.conv_forward(xg, wg, bg)
+    e = U.norm_err(y.cpu().numpy(), oracle.forward(xd, wd, bd), oracle.forward(np.abs(xd), np.abs(wd), np.abs(bd)))
+    print("fully-connected forward in three planes", case, misalign, e, flush=True)
+    assert e <= BOUND
+    assert torch.equal(y, B.conv_forward(xg, wg, bg, (1, 1), (0, 0, 0, 0), B.MCN_PREC_BF16))
+    assert torch.equal(B.conv_relu_forward(xg, wg, bg), y.clamp(min=0.0))
+    e0 = U.norm_err(B.conv_forward(xg, wg, None).cpu().numpy(), oracle.forward(xd, wd, None), oracle.forward(np.abs(xd), np.abs(wd), None))
+    assert e0 <= BOUND
+    # an infinity in the last term of an image, a NaN in the last weight of a filter: results that meet neither are as without them
+    xg[n - 1, d - 1, w_ - 1, h - 1], wg[k - 2, d - 1, w_ - 1, h - 1] = float("inf"), float("nan")
+    z = B.conv_forward(xg, wg, bg).reshape(n, k)
+    assert torch.equal(z[:n - 1, :k - 2], y.reshape(n, k)[:n - 1, :k - 2]) and torch.isnan(z[:, k - 2]).all()
+    others = [i for i in range(k) if i != k - 2]
+    assert torch.equal(z[n - 1, others], torch.where(w[others, d - 1, w_ - 1, h - 1] > 0, float("inf"), float("-inf")).cuda())

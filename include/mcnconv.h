@@ -89,7 +89,8 @@ typedef struct mcn_conv_desc {
  *   of the padding times an infinity counts as zero): one NaN or infinity costs a few milliseconds, infinite
  *   coefficients everywhere some seventy times the time of an ordinary call.
  *   The forward pass of fully-connected layers with an even number of coefficients per filter runs on the same kernel
- *   where that is estimated to be faster, under every precision but MCN_PREC_FP32_PLAIN.
+ *   where that is estimated to be faster, their derivatives likewise on that of the forward pass, under every
+ *   precision but MCN_PREC_FP32_PLAIN.
  * MCN_PREC_FP32_PLAIN: fp32 operands and accumulation, every product of the sum of Sec. 4.1
  *   formed as written, in fp32, and added one by one ("igemm" / "wgrad_igemm"): error bound n * 2^-24
  *   of the result's own sum of |w||x|; 3x3 stride-1 layers run about 1.3 times slower.

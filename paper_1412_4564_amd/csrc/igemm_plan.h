@@ -239,7 +239,7 @@ constexpr int SPLIT_N_SHAPES = 4;
 // traffic.  Either every block gets the same number of units (left-over tiles shared, fix-up pass), or whole tiles only
 // (up to a handful shared, so that the number of blocks stays a multiple of 8).
 struct SplitSchedule { int nblocks, own; double us; };
-inline SplitSchedule split_schedule(int64_t tiles, int NU, int NS, int64_t slab_bytes, const SplitShape &S, int n_cu, int rows) {
+inline SplitSchedule split_schedule(int64_t tiles, int NU, int NS, int64_t slab_bytes, const SplitShape &S, int n_cu, int rows, bool grouped) {
     const double ghz = 2.2;
     const int TK = S.WK * S.MK * 32, TQ = S.WP * S.MP * 32 * rows, waves = S.WK * S.WP;      // TQ: results per filter
     const double mfma = S.MK * S.MP * 6 * 32.0 * waves / 4, lds = waves * 3072.0 * S.MP / 128, l1 = waves * 3072.0 * S.MK / 64;
@@ -260,7 +260,9 @@ inline SplitSchedule split_schedule(int64_t tiles, int NU, int NS, int64_t slab_
     a.us = (double)tiles * tile_us / a.nblocks + (left ? 6.0 + (double)a.nblocks * TK * TQ * 8.0 / 4.0e6 + tile_over / ghz * 1e-3 : 0.0);
     b.own = (int)((tiles + n_cu - 1) / n_cu);
     b.nblocks = (int)(tiles / b.own);
-    if (b.nblocks > 64) b.nblocks &= ~7;
+    // 1x1 filters: their tiles are short, and a few left over cost more than what blocks of one XCD share (24x40x344, 1x1x144x344, five images,
+    // dzdx: 225 tiles on 224 blocks 50.8 us, on 225 blocks 18.5)
+    if (b.nblocks > 64 && !(grouped && (int64_t)b.own * b.nblocks == tiles)) b.nblocks &= ~7;
     b.us = b.own * tile_us;
     if ((int64_t)b.own * b.nblocks != tiles) b.us += 8.0 + (double)b.nblocks * TK * TQ * 2.0 / 4.0e6;
     return b.us <= a.us ? b : a;
@@ -290,6 +292,13 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     // threads of the fetching (bf16: staging) waves
     const int NL = 64 * (planes == 3 ? SPLIT_STAGE_WAVES : IGEMM_LOADER_WAVES);
     const int Wp = (v.Wo - 1) * v.Sw + v.Wf;
+    // 1x1 filters in three planes: 16-channel groups per unit, as many as the slab holds, shared out evenly
+    const bool grouped = planes == 3 && T == 1;
+    int GR = 1;
+    if (grouped) {
+        const int groups = (v.Cg + BF_DC - 1) / BF_DC, most = split_samples(false) / TQ, units = (groups + most - 1) / most;
+        GR = (groups + units - 1) / units;
+    }
     // candidates for the row-block height
     int cand[48];
     int nc = 0;
@@ -297,6 +306,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     for (int parts = 2; parts <= 16; ++parts) cand[nc++] = (v.Ho + parts - 1) / parts;
     for (int t = 32; t <= 256; t += 32) cand[nc++] = t;
     for (int t = 1; t <= 16; t *= 2) cand[nc++] = t;
+    if (grouped) nc = 1;               // no slab rows: whole columns
     const bool input_streams = 4.0 * v.H * v.W * (double)v.Ctot * v.N > 32.0 * 1024 * 1024;
     double best_score = 1e30;
     int bestTI = 0, bestSC = 0;
@@ -305,10 +315,10 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         const int TI = cand[a];
         if (TI < 1 || TI > v.Ho) continue;
         const int64_t SR = f23s ? TI : (int64_t)(TI - 1) * v.Sh + v.Hf;     // row combinations: one slab sample per pair
-        if (SR > 8192) continue;
+        if (SR > 8192 && !grouped) continue;
         if ((int64_t)TI * v.Wo * v.N >= ((int64_t)1 << 30)) continue;
         const int SC = slab_columns(v, TI, TQ, Wp);
-        const int64_t CP = (SR * SC + 63) / 64 * 64;
+        const int64_t CP = grouped ? (int64_t)GR * TQ : (SR * SC + 63) / 64 * 64;
         if (CP > (planes == 3 ? split_samples(f23s) : (bf16 ? bf_ept_max(NL) : 32) * NL)) continue;
         // an image crossing inside a tile moves the window by whole images: keep offsets in range
         const int64_t span = (int64_t)SC / Wp + 2;
@@ -323,6 +333,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         } else if (bf16) {
             if (fixed_lds + 64 > lds_limit) continue;
             if (!cut_units_bf16(v, TK, CP, lds_limit - fixed_lds - 64, &uc, planes)) continue;
+            if (grouped) { uc.DC = BF_DC * GR; uc.NS = GR; }
         } else if (fixed || wino) {
             uc.pair_mode = 0; uc.DC = FX.DC; uc.TC = T; uc.NTR = 1; uc.NS = (FX.DC / 2) * T;
             if ((2 * ((size_t)uc.NS * 2 * TK + 255) + 2 * (size_t)uc.DC * CP) * 4 + fixed_lds > lds_limit) continue;
@@ -350,7 +361,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         // 4b with two 0.378 against 0.40 with three)
         if (bf16) score *= 1.0 + 0.5 * (uc.NTR - 1);
         if (planes == 3)     // microseconds; short slab rows and short column runs of results as above
-            score = split_schedule((int64_t)v.G * RB * PT * ((v.Kg + TK - 1) / TK), NCG * uc.NTR, uc.NS, CP * (f23s ? 128 : 64), SS, n_cu, f23s ? 2 : 1).us *
+            score = split_schedule((int64_t)v.G * RB * PT * ((v.Kg + TK - 1) / TK), NCG * uc.NTR, uc.NS, CP * (f23s ? 128 : 64), SS, n_cu, f23s ? 2 : 1, grouped).us *
                     (input_streams ? 1.0 + 1.0 / (double)SR : 1.0) * (1.0 + 0.5 / (double)TI);
         if (wino && !f23s) {
             // The row-pair kernels issue fewer MFMAs per staged byte and per stored line, and what was measured on
@@ -373,7 +384,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     P.TI = bestTI; P.RB = (v.Ho + bestTI - 1) / bestTI;
     P.Wp = Wp;
     P.SR = f23s ? bestTI : (bestTI - 1) * v.Sh + v.Hf; P.SRP = P.SR;
-    P.CP = (P.SRP * bestSC + 63) / 64 * 64;
+    P.CP = grouped ? GR * TQ : (P.SRP * bestSC + 63) / 64 * 64;
     P.EPT = (P.CP + NL - 1) / NL;
     P.KT = (v.Kg + TK - 1) / TK;
     P.QN = bestTI * v.Wo * v.N;
@@ -389,7 +400,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     // the workspace and the fix-up pass than when everything is shared
     P.own = (int)(tiles / P.nblocks);
     if (planes == 3) {
-        const SplitSchedule sc = split_schedule(tiles, P.NU, P.NS, (int64_t)P.CP * (f23s ? 128 : 64), SS, n_cu, f23s ? 2 : 1);
+        const SplitSchedule sc = split_schedule(tiles, P.NU, P.NS, (int64_t)P.CP * (f23s ? 128 : 64), SS, n_cu, f23s ? 2 : 1, grouped);
         P.nblocks = sc.nblocks;
         P.own = sc.own;
         // Row pairs: a tile in at most 32 pieces.  With 64 or more the fix-up pass, which adds them one after another, costs more
@@ -417,7 +428,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     P.OH = v.OH; P.OW = v.OW; P.oi0 = v.oi0; P.osi = v.osi; P.oj0 = v.oj0; P.osj = v.osj;
     P.mD = v.mD; P.mPt = v.mPt; P.mPl = v.mPl;
     P.wino_Ho = wino_Ho;
-    if (bf16 && v.pack_mode == 2) return false;       // the fully-connected views are packed for the fp32 kernels only
+    if (bf16 && planes < 3 && v.pack_mode == 2) return false;       // the fully-connected views compute in fp32
     if (planes == 3) {
         const int area = v.HfA * v.WfA;
         PlainView &V = pl->V;
@@ -428,6 +439,8 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
         } else if (v.pack_mode == 1) {
             V.wo = v.pi + v.pSh * (V.Hf - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
             V.wg = area * v.DfA * v.Cg; V.wk = area; V.wc = area * v.DfA; V.wi = -v.pSh; V.wj = -v.HfA * v.pSw;
+        } else if (v.pack_mode == 2) {
+            V.wk = 1; V.wc = v.ldk;
         } else {
             V.HfA = v.HfA; V.WfA = v.WfA; V.DfA = v.DfA; V.B0i = v.B0i; V.B0j = v.B0j;
         }
@@ -464,6 +477,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     Q.wino = wino ? 1 : 0;
     Q.planes = bf16 ? planes : 1;
     Q.total = (int)pl->packed_floats;
+    if (grouped) { Q.NU *= GR; Q.NS = 1; Q.WSZ /= GR; }       // groups follow one another in memory, as units of one
     return true;
 }
 
@@ -486,11 +500,11 @@ inline bool wino_enabled() {
     return !off;
 }
 
-// Views the three-plane kernel (kern_igemm_split.h) can take.  Not 1x1 filters: a
-// unit is then one step (768 cycles of MFMAs), and its staging (loads, split, barrier) takes longer (28x28x512, 1x1x512x128,
-// 64 images: forward 93 us against 78 on the fp32 kernel).
+// Views the three-plane kernel (kern_igemm_split.h) can take.  1x1 filters (fully-connected layers' products among them) in units of several
+// groups of 16 channels: with one, a unit was one step (768 cycles of MFMAs), and its staging (loads, split, barrier) took longer (28x28x512,
+// 1x1x512x128, 64 images: forward 93 us, now 60, 83 on the fp32 kernel).  Not merged phases of them.
 inline bool split_possible(const ConvView &v) {
-    return v.pack_mode != 2 && v.Cg >= BF_DC && v.Hf * v.Wf >= 2;
+    return v.Cg >= BF_DC && (!v.mD || v.Hf * v.Wf >= 2);
 }
 
 // Row pairs in three planes (F23): deep layers whose plane and batch give at most as many tiles of 128 filters x 64 pairs as
@@ -529,6 +543,8 @@ inline double call_us(const ConvView &v, const IgemmPlan &pl, int n_cu) {
 // Row pairs, whose slab the planner keeps within 128 samples (split_samples), always: of 222 calls one is slower than on the fp32
 // kernel by more than 1 % (52x52x424, 121 filters, nine images 145 -> 149 us), half of them by 14 % or more faster.  With slabs of up to 256
 // samples beside the 64 pairs, staging bound them (58x58x280, 160 filters, three images 91 -> 111 us).
+// 1x1 filters (49 random layers, 98 calls): always fp32 3.11 ms, by this rule 2.49; products of 31 fully-connected layers (62 calls) 2.84 and 2.02;
+// none of either that it sends here is slower by more than 2 %.
 inline bool split_faster(const ConvView &v, const IgemmPlan &split, const IgemmPlan &fp32, int n_cu) {
     if (split.P.wino_Ho) return true;
     return call_us(v, split, n_cu) < 0.97 * call_us(v, fp32, n_cu);

@@ -110,6 +110,9 @@ __global__ __launch_bounds__(256) void igemm_pack_weights_bf16_kernel(const floa
         } else if (Q.mode == 0) {
             step = (size_t)Q.HfA * Q.WfA;
             src += ti + Q.HfA * (tj + Q.WfA * (c + (size_t)Q.DfA * (g * Q.Kg + k)));
+        } else if (Q.mode == 2) {
+            step = Q.ldk;
+            src += k + (size_t)Q.ldk * c;
         } else {
             const int fi = Q.pi + Q.Sh * (Q.Hf - 1 - ti), fj = Q.pj + Q.Sw * (Q.Wf - 1 - tj);
             step = (size_t)Q.HfA * Q.WfA * Q.DfA;

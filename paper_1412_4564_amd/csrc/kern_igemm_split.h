@@ -252,8 +252,10 @@ __global__ __launch_bounds__(256) void igemm_pack_f23_split_kernel(const float *
 }
 
 // MERGED: the stride phases of an input derivative side by side in the filter dimension (IgemmParams::mD).
+// GROUPED: 1x1 filters.  A unit of one group of 16 channels is a single step, and its barrier and staging take longer than that, so a unit is P.NS
+// groups.  They stand in the slab as taps do, TQ samples from one to the next, and a sample is that of one pixel: no window, no halo.
 // WK x WP computing waves; each owns MK x MP tiles of 32 filters x 32 pixels.
-template <int WK, int WP, int MK, int MP, bool F23, bool MERGED>
+template <int WK, int WP, int MK, int MP, bool F23, bool MERGED, bool GROUPED>
 __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 3 : 2) void igemm_split_kernel(
     SplitParams P, const float *__restrict__ in, const float *__restrict__ wpk, const float *__restrict__ bias, float *out,
     float *__restrict__ part) {
@@ -314,6 +316,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         const int e0 = F23 ? ltid & (NL / 2 - 1) : ltid, wave0 = 64 * (F23 ? lwave & (SPLIT_STAGE_WAVES / 2 - 1) : lwave), oct0 = F23 ? lwave / (SPLIT_STAGE_WAVES / 2) : 0;
         int t = n_own ? vb * P.own : t_s, uu = n_own ? 0 : uu_s, n = 0;      // next unit to request, units before it
         int kt = 0, g = 0, seq = -1;
+        const int sample_dc = GROUPED ? BF_DC * (ltid / TQ) : 0, set_dc = GROUPED ? BF_DC * (NL / TQ) : 0;       // first channel of the thread's samples, in the unit
         unsigned go[EPT][F23 ? 4 : 1];    // byte offset of the thread's samples in channel 0, or SLAB_INVALID; F23: of the pair's four rows
         __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void *)in, 0, 0, BUFFER_FLAGS);
         auto set_tile = [&](int tile) __attribute__((always_inline)) {
@@ -332,6 +335,12 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
 #pragma unroll
             for (int s = 0; s < EPT; ++s) {
                 const int e = e0 + NL * s;
+                if constexpr (GROUPED) {
+                    const int q = q0 + (e & (TQ - 1)), c = div32(q, P.dTI), n = div32(c, P.dWo), j = (c - n * P.Wo) * P.Sw - P.Pl, i = row0 + (q - c * P.TI) * P.Sh;
+                    const bool ok = e < CP && q < P.QN && rb * P.TI + q - c * P.TI < P.Ho && j >= 0 && j < P.W && i >= 0 && i < P.H;
+                    go[s][0] = ok ? 4u * (unsigned)(i + P.H * j + (n - n_first) * P.Ctot * HW + (sample_dc + set_dc * s) * HW) : SLAB_INVALID;
+                    continue;
+                }
                 const int col = div32(e, P.dSRP);
                 const int r = e - col * SRP;
                 const int U = u0 + col;
@@ -345,7 +354,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             }
         };
         auto request = [&](Samples &q) __attribute__((always_inline)) {
-            const int combo = uu & 3, c0 = (F23 ? uu >> 2 : uu) * BF_DC + 8 * oct0, c_end = n < nunits ? P.Cg : 0;
+            const int combo = uu & 3, c0 = (F23 ? uu >> 2 : GROUPED ? uu * P.NS : uu) * BF_DC + 8 * oct0, c_end = n < nunits ? P.Cg : 0;
             q.uu = uu; q.kt = kt; q.g = g; q.seq = seq; q.combo = combo;
 #pragma unroll
             for (int s = 0; s < EPT; ++s) {
@@ -361,7 +370,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                     for (int d = 0; d < CH; ++d)
                         // channels past the group's last one read as zero (their weights are zero too)
                         q.v[s][a][d] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                            xrs, c0 + d < c_end ? off : SLAB_INVALID, (unsigned)(c0 + d) * (unsigned)HW * 4u, 0));
+                            xrs, c0 + d + (GROUPED ? sample_dc + set_dc * s : 0) < c_end ? off : SLAB_INVALID, (unsigned)(c0 + d) * (unsigned)HW * 4u, 0));
                 }
             }
             // on to the next unit
@@ -459,7 +468,8 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             const int io = rb * P.TI + ii;
             const bool ok = q < qend && io < P.Ho;
             const int ucol = jo * P.Sw + (n - n_first) * P.Wp - u0;
-            bbase[mp] = 16 * ((ok ? ii * (F23 ? 1 : P.Sh) + SRP * ucol : 0) + half * CP);
+            if constexpr (GROUPED) bbase[mp] = 16 * ((wp * MP + mp) * 32 + (lane & 31) + half * CP);
+            else bbase[mp] = 16 * ((ok ? ii * (F23 ? 1 : P.Sh) + SRP * ucol : 0) + half * CP);
             ooff[mp] = ok ? 4u * (unsigned)((P.oi0 + P.osi * io) + P.OH * (P.oj0 + P.osj * jo) +
                                             OHW * (P.Ktot * (n - n_first) + (MERGED ? 0 : 4 * half)))
                           : SLAB_INVALID;
@@ -503,7 +513,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                 }
     };
     const int aoff = 16 * (half * TK + wk * MK * 32 + (lane & 31));   // bytes
-    const int T = F23 ? 3 : P.Hf * P.Wf;
+    const int T = F23 ? 3 : GROUPED ? P.NS : P.Hf * P.Wf;
     const int xplane = 2 * CP * 16;                  // bytes from a slab plane to the next
     // where the next operands are read: weights of the step (steps follow one another in memory through all units of a
     // tile), slab and offset of its tap.  All scalar but the two lane offsets.
@@ -516,6 +526,8 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     auto next_tap = [&]() __attribute__((always_inline)) {
         if constexpr (F23) {
             so += 16 * SRP;
+        } else if constexpr (GROUPED) {
+            so += 16 * TQ;
         } else {
             const bool wrap = ++fi == P.Hf;
             so += wrap ? 16 * (SRP - P.Hf + 1) : 16;

@@ -171,9 +171,15 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
     e.wgb_ok = on && d->precision == MCN_PREC_BF16 && plan_wgrad_bf16(forward_view(g), ncu, &e.wgb);
     e.wgs_ok = on && !e.wgb_ok && pairs && wino_enabled() && !(e.wg_ok && e.wg.wino) && plan_wgrad_split(forward_view(g), ncu, &e.wgs) &&
                (!e.wg_ok || wgrad_split_faster(forward_view(g), e.wgs, e.wg, ncu));
+    auto plan_product = [&](const ConvView &v, IgemmPlan *pl) {
+        IgemmPlan split;
+        if (!plan_igemm(v, ncu, pl)) return false;
+        if (pairs && wino_enabled() && split_possible(v) && plan_igemm(v, ncu, &split, true, true, 3) && split_faster(v, split, *pl, ncu)) *pl = split;
+        return true;
+    };
     e.fc = on && is_fully_connected(g) && (int64_t)g.H * g.W * g.D < ((int64_t)1 << 30) &&
-           plan_wgrad(fc_forward_view(g), ncu, &e.fc_fwd) && plan_igemm(fc_backward_data_view(g), ncu, &e.fc_bwd) &&
-           plan_igemm(fc_backward_filter_view(g), ncu, &e.fc_wg);
+           plan_wgrad(fc_forward_view(g), ncu, &e.fc_fwd) && plan_product(fc_backward_data_view(g), &e.fc_bwd) &&
+           plan_product(fc_backward_filter_view(g), &e.fc_wg);
     e.fcs_ok = e.fc && pairs && wino_enabled() && plan_fc_forward_split(g, ncu, &e.fcs) && wgrad_split_faster(fc_forward_view(g), e.fcs, e.fc_fwd, ncu);
     return &e;
 }
@@ -258,19 +264,21 @@ int launch_igemm_bf16_inst(const IgemmPlan &pl, const float *in, const float *wp
 }
 
 // fp32 operands in three bf16 planes (kern_igemm_split.h)
-template <int WK, int WP, int MK, int MP, bool F23 = false, bool MERGED = false>
+template <int WK, int WP, int MK, int MP, bool F23 = false, bool MERGED = false, bool GROUPED = false>
 int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, const float *bias, float *out,
                        float *part, hipStream_t s, int relu, const float *w) {
-    if constexpr (!F23 && !MERGED)
+    if constexpr (!F23 && !MERGED && !GROUPED)
+        if (pl.P.Hf * pl.P.Wf == 1) return launch_igemm_split<WK, WP, MK, MP, false, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
+    if constexpr (!F23 && !MERGED && !GROUPED)
         if (pl.P.mD) return launch_igemm_split<WK, WP, MK, MP, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
-    if constexpr (!F23 && !MERGED && WK * MK == 4 && MP == 1)       // row pairs: the same tile on half the waves, twice as much each
+    if constexpr (!F23 && !MERGED && !GROUPED && WK * MK == 4 && MP == 1)       // row pairs: the same tile on half the waves, twice as much each
         if (pl.P.wino_Ho) return launch_igemm_split<WK, WP / 2, MK, 2 * MP, true>(pl, in, wpk, bias, out, part, s, relu, w);
     SplitParams P;
     (IgemmParams &)P = pl.P;
     P.V = pl.V; P.in = in; P.w = w; P.bias = bias; P.out = out;
     P.relu = relu;
     P.wino_pairs = F23 && P.osi == 2 && P.OH % 2 == 0 && ((uintptr_t)out & 7) == 0;
-    auto kern = igemm_split_kernel<WK, WP, MK, MP, F23, MERGED>;
+    auto kern = igemm_split_kernel<WK, WP, MK, MP, F23, MERGED, GROUPED>;
     if (pl.lds_bytes > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)pl.lds_bytes);
@@ -751,7 +759,10 @@ int mcn_conv_operand_planes(const mcn_conv_desc *desc, int op) {
     Geom g;
     if (make_geom(desc, &g) || op < MCN_OP_FORWARD || op > MCN_OP_BACKWARD_FILTER_BIAS) return -1;
     const PlanEntry *e = plans_for(desc, g);
-    if (e->fc) return op == MCN_OP_FORWARD && e->fcs_ok ? 3 : 0;
+    if (e->fc) {
+        const IgemmPlan &pl = op == MCN_OP_BACKWARD_DATA ? e->fc_bwd : e->fc_wg;
+        return op == MCN_OP_BACKWARD_BIAS ? 0 : op == MCN_OP_FORWARD ? (e->fcs_ok ? 3 : 0) : pl.bf16 ? pl.planes : 0;
+    }
     const IgemmPlan *pl = op == MCN_OP_FORWARD && e->fwd_ok ? &e->fwd : op == MCN_OP_BACKWARD_DATA && e->bwd_ok && e->n_bwd ? &e->bwd[0] : nullptr;
     if (pl) return pl->bf16 ? pl->planes : 0;
     return op != MCN_OP_BACKWARD_FILTER && op != MCN_OP_BACKWARD_FILTER_BIAS ? 0 : e->wgb_ok ? 1 : e->wgs_ok ? 3 : 0;

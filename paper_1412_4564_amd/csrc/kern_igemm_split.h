@@ -14,7 +14,7 @@
 // Tiling, pixel numbering, schedule and fix-up pass: kern_igemm.h.  One MFMA takes 16 channels of one tap, a lane's operand
 // is 16 consecutive bytes: slab [plane][octet][column][row][8 channels] in LDS, weights
 // [channel group][tap][plane][octet][filter][8 channels] in memory (igemm_pack_weights_bf16_kernel, three planes).  A unit
-// is 16 channels x all taps.
+// is 16 channels x all taps, of 1x1 filters several groups of 16 channels (GROUPED).
 //
 // What bounds it: the matrix core, at the clock that its power leaves, and the waits between its products (two groups of 5x5, 128
 // images: 0.68 to 0.73 of the active cycles execute products, at 1.86 GHz of 2.4; a loop of products alone reaches 1.85 PFLOP/s on
@@ -254,6 +254,8 @@ __global__ __launch_bounds__(256) void igemm_pack_f23_split_kernel(const float *
 // MERGED: the stride phases of an input derivative side by side in the filter dimension (IgemmParams::mD).
 // GROUPED: 1x1 filters.  A unit of one group of 16 channels is a single step, and its barrier and staging take longer than that, so a unit is P.NS
 // groups.  They stand in the slab as taps do, TQ samples from one to the next, and a sample is that of one pixel: no window, no halo.
+// Bound by staging (a split sample meets 128 filters).  Forward of 28x28x512 -> 128, 64 images: 93 us with one group a unit, now 60, fp32 kernel 83; dzdw of
+// 6x6x256 -> 4096, 256 images: 207 us on the fp32 kernel, now 155, its dzdx 187 and 134.
 // WK x WP computing waves; each owns MK x MP tiles of 32 filters x 32 pixels.
 template <int WK, int WP, int MK, int MP, bool F23, bool MERGED, bool GROUPED>
 __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 3 : 2) void igemm_split_kernel(

@@ -68,8 +68,13 @@ __device__ inline float wgrad_plain_sum(const WgradSplitParams &P, const float *
             const int xj = jo * P.Sw + fj - P.Pl;
             if (!on || xj < 0 || xj >= P.W) continue;
             const float *xc = xp + (ptrdiff_t)xj * P.xsj, *yc = yp + (size_t)jo * P.ysj;
+            // a sum that is NaN stays so (columns of thousands of rows: 1x1 filters, fully-connected layers)
+#pragma unroll 1
+            for (int io = i0; io < i1 && s == s;) {
+                const int stop = min(io + 64, i1);
 #pragma unroll 4
-            for (int io = i0; io < i1; ++io) s = fmaf(xc[(ptrdiff_t)io * P.Sh], yc[io], s);
+                for (; io < stop; ++io) s = fmaf(xc[(ptrdiff_t)io * P.Sh], yc[io], s);
+            }
         }
         if (!__any(on && s == s)) break;
     }

@@ -958,7 +958,8 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
     if (tiles >= ((int64_t)1 << 20)) return false;
     const int NPH = v.Hf < v.Sh ? v.Hf : v.Sh;
     const int threads = 64 * WGS_STAGE_WAVES;
-    const bool linear = T == 1 && v.Sh == 1 && v.Sw == 1 && v.Pt == 0 && v.Pl == 0;
+    // octets of x limited by rows of dzdy, columns by x itself: no output row may lie past the last row of x
+    const bool linear = T == 1 && v.Sh == 1 && v.Sw == 1 && v.Pt == 0 && v.Pl == 0 && v.Ho == v.H;
     // octets per staging thread of the instantiations there are (launch_wgrad_split)
     const int most_y = linear ? (TK == 128 ? 3 : 1) : TK == 32 ? 2 : 4, most_x = linear ? (TK == 128 ? 3 : 4) : 2;
     double best = 1e300;

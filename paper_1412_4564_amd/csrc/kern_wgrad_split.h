@@ -113,7 +113,7 @@ struct RepairSums {
 };
 
 // YT, XT: 16-byte words (octets) of dzdy and of new slab columns that a staging thread brings per unit, at most.
-// LINEAR: 1x1 filters at stride 1 without pads: octets of x lie in memory like those of dzdy
+// LINEAR: 1x1 filters at stride 1 whose output has the rows of x: octets of x lie in memory like those of dzdy
 template <int WK, int WR, int MK, int YT, int XT, bool LINEAR>
 __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_split_kernel(WgradSplitParams P, const float *__restrict__ x,
                                                                                        const float *__restrict__ dzdy,

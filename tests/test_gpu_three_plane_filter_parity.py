@@ -59,6 +59,22 @@ def test_every_coefficient(case, misalign):
     assert torch.equal(got, derivative(L, xg, pg)) and torch.equal(got, derivative(L, xg, pg, B.MCN_PREC_FP32_BF16X3))
 
 
+# 1x1 filters at stride 1 whose windows run past the last row or column: those rows and columns of the output read nothing
+@pytest.mark.parametrize("shape", [(28, 28, 160, 24, 128), (27, 14, 300, 33, 70), (9, 7, 300, 77, 260), (26, 25, 96, 24, 64)])
+@pytest.mark.parametrize("pad", [(0, 1, 0, 0), (0, 2, 0, 1), (0, 0, 0, 1), (0, 5, 0, 2)])
+def test_pointwise_with_pads_below_and_to_the_right(shape, pad):
+    h, w_, d, n, k = shape
+    L = custom_layer(h, w_, d, n, 1, 1, d, k, pad=pad, idx=870)
+    assert planes(L) == 3
+    x, w = synth.make_x(L, 4), synth.make_w(L, 4)
+    p = synth.make_dzdy(L, h + pad[1], w_ + pad[3], 4)
+    xd, pd = U.np64(x), U.np64(p)
+    got = derivative(L, x.cuda(), p.cuda()).cpu().numpy()
+    e = U.norm_err(got, oracle.backward_filter(xd, w.shape, pd, (1, 1), pad), oracle.backward_filter(np.abs(xd), w.shape, np.abs(pd), (1, 1), pad))
+    print("pointwise filter derivative, pads", shape, pad, e, flush=True)
+    assert e <= BOUND
+
+
 @pytest.mark.parametrize("exponent", [-126, -118, -100, 0, 96])
 def test_operands_of_every_size(exponent):
     """x scaled by a power of two: the planes hold it exactly, so the error stays that of ordinary operands (down to the rounding of

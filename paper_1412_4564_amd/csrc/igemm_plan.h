@@ -901,6 +901,7 @@ struct WgradSplitPlan {
     int shape;
     int TK, TR;
     bool linear;
+    int NCH;                 // channels of the slab
     WgradSplitParams P;
     size_t lds_bytes;
     size_t partial_floats;   // 2 slots of TK*TR per block
@@ -908,26 +909,45 @@ struct WgradSplitPlan {
 };
 
 // Slab pitches in 32-bit words: lane r of an operand read is at word phase*PHP + fj*COLP + c*CHP + (row of the phase), and
-// 32 lanes should fall into 32 banks.  The pitches with the fewest collisions of at most `limit` words a plane, smallest first.
-inline void wgs_pitches(const ConvView &v, int NCH, int limit, WgradSplitParams *P) {
-    const int T = v.Hf * v.Wf;
-    const int lanes = 32 * 4 < T * v.Cg ? 32 * 4 : (T * v.Cg + 31) / 32 * 32;
+// 32 lanes should fall into 32 banks.  The pitches with the fewest collisions of at most `limit` words a plane, smallest first.  For the
+// plan that a call will use and for no other: lane by lane, for every shape tried, the 512 pairs of pitches took 0.2 ms of host time, longer
+// than many a call.  The lanes of a filter column keep their distances whatever the pitches: their banks are one mask, turned.
+inline void wgs_pitches(int NCH, int limit, WgradSplitParams *P) {
+    struct Column { int col, chan; unsigned banks; };  // lanes of one column in different banks, from bank 0 on
+    Column at[128];
+    int first[5] = {}, groups = 0, n = 0;              // half-wave h: columns first[h] .. first[h + 1] - 1
+    const int lanes = 32 * 4 < P->R ? 32 * 4 : (P->R + 31) / 32 * 32;
+    for (int r = 0, ch = 0, fj = 0, fi = 0; r < lanes; ++r) {
+        if (r % 32 == 0) first[groups++] = n;
+        const unsigned bank = 1u << ((fi % P->Sh * P->PHP + fi / P->Sh) & 31);
+        int a = first[groups - 1];
+        while (a < n && (at[a].col != fj || at[a].chan != ch || (at[a].banks & bank))) ++a;
+        if (a == n) at[n++] = Column{fj, ch, 0};
+        at[a].banks |= bank;
+        if (++fi == P->Hf) { fi = 0; if (++fj == P->Wf) { fj = 0; ++ch; } }
+    }
+    first[groups] = n;
     const int b0 = P->COLP, c0 = P->CHP - P->NP * P->RC * b0;
     long best = -1;
     WgradSplitParams B = *P;
     for (int b = 0; b < 16; ++b)
         for (int c = 0; c < 32; ++c) {
             const int colp = b0 + b, chp = P->NP * P->RC * colp + c0 + c;
-            if (NCH * chp > limit) break;
-            int extra = 0;                             // reads beyond the first, over the fullest bank of each half-wave
-            for (int r0 = 0; r0 < lanes; r0 += 32) {
-                unsigned char count[32] = {};
-                int most = 0;
-                for (int r = r0, ch = r0 / T, fj = r0 % T / v.Hf, fi = r0 % v.Hf; r < r0 + 32; ++r) {
-                    const int n = ++count[(fi % v.Sh * P->PHP + fi / v.Sh + fj * colp + ch * chp) & 31];
-                    if (n > most) most = n;
-                    if (++fi == v.Hf) { fi = 0; if (++fj == v.Wf) { fj = 0; ++ch; } }
+            if (NCH * chp > limit || (best >= 0 && chp >= best)) break;
+            // reads beyond the first, over the fullest bank of each half-wave; from `enough` on they cost more than the best pair so far
+            int extra = 0;
+            const int enough = best < 0 ? 128 : (int)((best - chp) * lanes / (4096 * 32)) + 1;
+            for (int h = 0; h < groups && extra < enough; ++h) {
+                unsigned bit[6] = {};                  // reads of each bank, as binary digits
+                for (int a = first[h]; a < first[h + 1]; ++a) {
+                    const unsigned turn = (unsigned)(at[a].col * colp + at[a].chan * chp) & 31;
+                    unsigned carry = at[a].banks << turn | at[a].banks >> (-turn & 31);
+                    for (int d = 0; carry; ++d) { const unsigned both = bit[d] & carry; bit[d] ^= carry; carry = both; }
                 }
+                unsigned fullest = ~0u;
+                int most = 0;
+                for (int d = 5; d >= 0; --d)
+                    if (fullest & bit[d]) { fullest &= bit[d]; most |= 1 << d; }
                 extra += most - 1;
             }
             const long cost = (long)extra * 4096 * 32 / lanes + chp;
@@ -1016,9 +1036,6 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
     if (best >= 1e300) return false;
     WgradSplitParams &P = pl->P;
     P = B;
-    wgs_pitches(v, NCH, (int)(IGEMM_LDS_LIMIT - 2 * (size_t)TK * P.PYW * 48 - 16) / 12, &P);
-    P.XPL = NCH * P.CHP;
-    P.counts = 2 * TK * P.PYW * 48 + 3 * P.XPL * 4;
     P.H = v.H; P.W = v.W; P.N = v.N; P.Ctot = v.Ctot; P.Cg = v.Cg;
     P.Ho = v.Ho; P.Wo = v.Wo; P.Ktot = v.Ktot; P.Kg = v.Kg; P.G = v.G;
     P.Hf = v.Hf; P.Wf = v.Wf; P.Sh = v.Sh; P.Sw = v.Sw; P.Pt = v.Pt; P.Pl = v.Pl;
@@ -1036,7 +1053,7 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
     P.nblocks = P.nchunks > 0 ? (int)tiles * P.nchunks : (int)(total < n_cu ? total : n_cu);
     pl->shape = shape; pl->TK = TK; pl->TR = TR;
     pl->linear = linear;
-    pl->lds_bytes = (size_t)P.counts + 16;
+    pl->NCH = NCH;
     pl->partial_floats = P.nblocks > 1 && P.nchunks != 1 ? (size_t)2 * P.nblocks * TK * TR : 0;
     const double filled = (v.Kg < TK ? (double)v.Kg / TK : 1.0) * (R < TR ? (double)R / TR : 1.0);        // of a tile
     pl->us = 12.7 + best + (pl->partial_floats ? 0.298 * 8e-6 * filled * P.nblocks * TK * TR : 0.0);
@@ -1057,14 +1074,11 @@ inline double wgrad_fp32_us(const ConvView &v, const WgradPlan &pl, int n_cu) {
     return 13.1 + rounds * ceil((double)P.tiles * P.NU / P.nblocks) * unit + 0.2884 * 4e-6 * (double)pl.partial_floats * filled;
 }
 
-// Whether the three-plane kernel is the faster one; split, fp32: the two plans.  Over 15600 other random layers: always fp32 1.437 s,
-// by this rule 1.031 s, the faster of the two each time 1.019 s; of the 10687 that it sends to three planes 87 are slower there by more
-// than 2 %, 44 by more than 5 %.  The 4 us: calls of 15 to 20 us are launches, and the estimates do not tell their kernels apart.
-inline bool wgrad_split_faster(const ConvView &v, const WgradSplitPlan &split, const WgradPlan &fp32, int n_cu) {
-    return split.us < wgrad_fp32_us(v, fp32, n_cu) - 4.0;
-}
-
-inline bool plan_wgrad_split(const ConvView &view, int n_cu, WgradSplitPlan *pl) {
+// The filter derivative of `view` on the three-plane kernel; fp32: its plan on the fp32 kernel, or NULL if there is none.  False where the
+// fp32 kernel is the faster one.  Over 15600 other random layers: always fp32 1.437 s, by this rule 1.031 s, the faster of the two each time
+// 1.019 s; of the 10687 that it sends to three planes 87 are slower there by more than 2 %, 44 by more than 5 %.  The 4 us: calls of 15 to
+// 20 us are launches, and the estimates do not tell their kernels apart.
+inline bool plan_wgrad_split(const ConvView &view, int n_cu, const WgradPlan *fp32, WgradSplitPlan *pl) {
     ConvView v = view;
     if (v.Hf == 1 && v.Wf == 1 && v.Sh == 1 && v.Sw == 1 && v.Pt == 0 && v.Pl == 0 && v.H == v.Ho && v.W == v.Wo) {
         v.H = v.Ho = v.H * v.W;          // a plane is one column
@@ -1078,19 +1092,25 @@ inline bool plan_wgrad_split(const ConvView &view, int n_cu, WgradSplitPlan *pl)
         WgradSplitPlan one;
         if (plan_wgrad_split_shape(v, n_cu, shape, streams, &one) && (!ok || one.us < pl->us)) { *pl = one; ok = true; }
     }
-    return ok;
+    if (!ok || (fp32 && pl->us >= wgrad_fp32_us(view, *fp32, n_cu) - 4.0)) return false;
+    WgradSplitParams &P = pl->P;
+    wgs_pitches(pl->NCH, (int)(IGEMM_LDS_LIMIT - 2 * (size_t)pl->TK * P.PYW * 48 - 16) / 12, &P);
+    P.XPL = pl->NCH * P.CHP;
+    P.counts = 2 * pl->TK * P.PYW * 48 + 3 * P.XPL * 4;
+    pl->lds_bytes = (size_t)P.counts + 16;
+    return true;
 }
 
 // Fully-connected forward (fc_forward_view): a lane's octet takes rows of a pair of images and there is one image only, so the R terms of a
 // result go as two images of R/2.  Odd R: false.  6x6x256 -> 4096, 256 images: 233 us on the fp32 kernel, 198 here; of 49 layers of 1x1 to
-// 7x7 inputs, 128 to 4096 channels, 16 to 256 images, 500 to 4096 filters the rule (wgrad_split_faster) sends 29 here, which are 1.12 to 1.58 times
+// 7x7 inputs, 128 to 4096 channels, 16 to 256 images, 500 to 4096 filters the rule of plan_wgrad_split sends 29 here, which are 1.12 to 1.58 times
 // as fast (median 1.35), with half of the error against 64 bits; none is slower.
-inline bool plan_fc_forward_split(const Geom &g, int n_cu, WgradSplitPlan *pl) {
+inline bool plan_fc_forward_split(const Geom &g, int n_cu, const WgradPlan *fp32, WgradSplitPlan *pl) {
     ConvView v = fc_forward_view(g);
     const int R = v.H;
     if (R % 2) return false;
     v.H = v.Ho = R / 2; v.N = 2;
-    if (!plan_wgrad_split(v, n_cu, pl)) return false;
+    if (!plan_wgrad_split(v, n_cu, fp32, pl)) return false;
     WgradSplitParams &P = pl->P;
     P.xsn = P.ysn = R / 2; P.xsc = P.ysc = R;          // offsets inside a unit stay below those that plan_wgrad_split has checked
     return true;

@@ -169,8 +169,8 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
     e.wg_ok = on && ((pairs && wino_enabled() && plan_wgrad(forward_view(g), ncu, &e.wg, true)) ||
                      plan_wgrad(forward_view(g), ncu, &e.wg));
     e.wgb_ok = on && d->precision == MCN_PREC_BF16 && plan_wgrad_bf16(forward_view(g), ncu, &e.wgb);
-    e.wgs_ok = on && !e.wgb_ok && pairs && wino_enabled() && !(e.wg_ok && e.wg.wino) && plan_wgrad_split(forward_view(g), ncu, &e.wgs) &&
-               (!e.wg_ok || wgrad_split_faster(forward_view(g), e.wgs, e.wg, ncu));
+    e.wgs_ok = on && !e.wgb_ok && pairs && wino_enabled() && !(e.wg_ok && e.wg.wino) &&
+               plan_wgrad_split(forward_view(g), ncu, e.wg_ok ? &e.wg : nullptr, &e.wgs);
     auto plan_product = [&](const ConvView &v, IgemmPlan *pl) {
         IgemmPlan split;
         if (!plan_igemm(v, ncu, pl)) return false;
@@ -180,7 +180,7 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
     e.fc = on && is_fully_connected(g) && (int64_t)g.H * g.W * g.D < ((int64_t)1 << 30) &&
            plan_wgrad(fc_forward_view(g), ncu, &e.fc_fwd) && plan_product(fc_backward_data_view(g), &e.fc_bwd) &&
            plan_product(fc_backward_filter_view(g), &e.fc_wg);
-    e.fcs_ok = e.fc && pairs && wino_enabled() && plan_fc_forward_split(g, ncu, &e.fcs) && wgrad_split_faster(fc_forward_view(g), e.fcs, e.fc_fwd, ncu);
+    e.fcs_ok = e.fc && pairs && wino_enabled() && plan_fc_forward_split(g, ncu, &e.fc_fwd, &e.fcs);
     return &e;
 }
 

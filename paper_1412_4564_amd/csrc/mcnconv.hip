@@ -12,6 +12,7 @@
 #include "kern_direct.h"
 #include "kern_igemm.h"
 #include "igemm_plan.h"
+#include "plan_cache.h"
 #include "kern_pool.h"
 #include "kern_probe.h"
 
@@ -95,39 +96,36 @@ constexpr int IGEMM_FIXUP_SLICES = 16;
 
 // Plans depend only on the descriptor; planning walks candidate tilings, so the last few
 // descriptors' plans are remembered per host thread (host memory only, no device state).
+// Passes: MCN_OP_FORWARD, MCN_OP_BACKWARD_DATA and MCN_OP_BACKWARD_FILTER; what belongs to a pass not asked for yet is zero.
 struct PlanEntry {
-    mcn_conv_desc d;
-    bool used;
-    bool fwd_ok, bwd_ok, wg_ok;
+    bool fc;                   // fully-connected layer: the three passes run as plain matrix products
+    // forward
+    bool fwd_ok;
     IgemmPlan fwd;
-    int n_bwd;                 // stride phases of the input derivative that have work
+    // input derivative
+    bool bwd_ok;
+    int n_bwd;                 // stride phases that have work
     bool bwd_fill;             // some samples of dzdx belong to no phase with work: zero-fill first
     IgemmPlan bwd[MAX_PHASES];
+    // filter derivative
+    bool wg_ok;
     WgradPlan wg;
-    bool wgb_ok;               // filter derivative on the bf16 kernel
+    bool wgb_ok;               // on the bf16 kernel (wg is then not set)
     WgradBfPlan wgb;
-    bool wgs_ok;               // filter derivative on the three-plane kernel
+    bool wgs_ok;               // on the three-plane kernel
     WgradSplitPlan wgs;
-    bool fc;                   // fully-connected layer: the three passes run as plain matrix products
+    // fc
     WgradPlan fc_fwd;
-    bool fcs_ok;               // its forward pass on the three-plane kernel
+    bool fcs_ok;               // forward on the three-plane kernel
     WgradSplitPlan fcs;
     IgemmPlan fc_bwd, fc_wg;
 };
 constexpr int PLAN_CACHE = 8;
-thread_local PlanEntry g_plans[PLAN_CACHE];
-thread_local int g_plan_next = 0;
+thread_local PlanCache<PlanEntry, PLAN_CACHE> g_plans;
 
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
-    for (int i = 0; i < PLAN_CACHE; ++i)
-        if (g_plans[i].used && memcmp(&g_plans[i].d, d, sizeof(*d)) == 0) return &g_plans[i];
-    PlanEntry &e = g_plans[g_plan_next];
-    g_plan_next = (g_plan_next + 1) % PLAN_CACHE;
-    e.d = *d;
-    e.used = true;
-    const bool on = igemm_enabled();
+bool plan_view(const mcn_conv_desc *d, const ConvView &v, IgemmPlan *pl) {
     const int ncu = compute_units();
     // bf16 operands: the bf16 kernel where a view has at least one full MFMA depth of channels;
     // other views (and the filter derivative) compute in fp32, which meets the same error bound
@@ -135,53 +133,78 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g) {
     const bool bf = d->precision == MCN_PREC_BF16 || d->precision == MCN_PREC_FP32_BF16X3;
     const int planes = d->precision == MCN_PREC_FP32_BF16X3 ? 2 : 1;
     const bool pairs = d->precision != MCN_PREC_FP32_PLAIN;     // the row-pair kernels for 3x3 stride-1 layers
-    auto plan_view = [&](const ConvView &v, IgemmPlan *pl) {
-        if (bf && !v.mD && v.Cg >= BF_DC && plan_igemm(v, ncu, pl, true, true, planes)) return true;    // merged phases: fp32 kernel only
-        // fp32: the same sum on the bf16 matrix core, operands in three planes, where that is faster
-        if (d->precision == MCN_PREC_FP32 && wino_enabled() && split_possible(v)) {
-            IgemmPlan split;
-            const bool ok = plan_igemm(v, ncu, pl, false, pairs);
-            if (plan_igemm(v, ncu, &split, true, true, 3) && (!ok || split_faster(v, split, *pl, ncu))) { *pl = split; return true; }
-            return ok;
-        }
-        return plan_igemm(v, ncu, pl, false, pairs);
-    };
-    e.fwd_ok = on && plan_view(forward_view(g), &e.fwd);
+    if (bf && !v.mD && v.Cg >= BF_DC && plan_igemm(v, ncu, pl, true, true, planes)) return true;    // merged phases: fp32 kernel only
+    // fp32: the same sum on the bf16 matrix core, operands in three planes, where that is faster
+    if (d->precision == MCN_PREC_FP32 && wino_enabled() && split_possible(v)) {
+        IgemmPlan split;
+        const bool ok = plan_igemm(v, ncu, pl, false, pairs);
+        if (plan_igemm(v, ncu, &split, true, true, 3) && (!ok || split_faster(v, split, *pl, ncu))) { *pl = split; return true; }
+        return ok;
+    }
+    return plan_igemm(v, ncu, pl, false, pairs);
+}
+
+void plan_backward_data(PlanEntry &e, const mcn_conv_desc *d, const Geom &g) {
+    const bool on = igemm_enabled();
     e.bwd_ok = on && g.Sh * g.Sw <= MAX_PHASES;
     e.n_bwd = 0;
     e.bwd_fill = false;
-    ConvView mv;
-    if (on && merged_backward_data_view(g, &mv) && plan_view(mv, &e.bwd[0])) {
+    ConvView v;
+    if (on && merged_backward_data_view(g, &v) && plan_view(d, v, &e.bwd[0])) {
         e.bwd_ok = true;       // one launch computes every stride phase
         e.n_bwd = 1;
-    } else if (e.bwd_ok) {
-        for (int pj = 0; pj < g.Sw && e.bwd_ok; ++pj)
-            for (int pi = 0; pi < g.Sh && e.bwd_ok; ++pi) {
-                ConvView v;
-                if (!backward_data_view(g, pi, pj, &v)) {
-                    // no taps in this phase: its samples (if it has any) are zero
-                    e.bwd_fill = true;
-                    continue;
-                }
-                e.bwd_ok = plan_view(v, &e.bwd[e.n_bwd++]);
-            }
+        return;
     }
-    e.wg_ok = on && ((pairs && wino_enabled() && plan_wgrad(forward_view(g), ncu, &e.wg, true)) ||
-                     plan_wgrad(forward_view(g), ncu, &e.wg));
-    e.wgb_ok = on && d->precision == MCN_PREC_BF16 && plan_wgrad_bf16(forward_view(g), ncu, &e.wgb);
-    e.wgs_ok = on && !e.wgb_ok && pairs && wino_enabled() && !(e.wg_ok && e.wg.wino) &&
-               plan_wgrad_split(forward_view(g), ncu, e.wg_ok ? &e.wg : nullptr, &e.wgs);
-    auto plan_product = [&](const ConvView &v, IgemmPlan *pl) {
-        IgemmPlan split;
-        if (!plan_igemm(v, ncu, pl)) return false;
-        if (pairs && wino_enabled() && split_possible(v) && plan_igemm(v, ncu, &split, true, true, 3) && split_faster(v, split, *pl, ncu)) *pl = split;
-        return true;
+    if (!e.bwd_ok) return;
+    for (int pj = 0; pj < g.Sw && e.bwd_ok; ++pj)
+        for (int pi = 0; pi < g.Sh && e.bwd_ok; ++pi) {
+            if (!backward_data_view(g, pi, pj, &v)) {
+                // no taps in this phase: its samples (if it has any) are zero
+                e.bwd_fill = true;
+                continue;
+            }
+            e.bwd_ok = plan_view(d, v, &e.bwd[e.n_bwd++]);
+        }
+}
+
+void plan_backward_filter(PlanEntry &e, const mcn_conv_desc *d, const Geom &g) {
+    const bool on = igemm_enabled(), pairs = d->precision != MCN_PREC_FP32_PLAIN && wino_enabled();
+    const int ncu = compute_units();
+    const ConvView v = forward_view(g);
+    e.wg_ok = e.wgs_ok = false;
+    e.wgb_ok = on && d->precision == MCN_PREC_BF16 && plan_wgrad_bf16(v, ncu, &e.wgb);
+    if (!on || e.wgb_ok) return;
+    e.wg_ok = (pairs && plan_wgrad(v, ncu, &e.wg, true)) || plan_wgrad(v, ncu, &e.wg);
+    e.wgs_ok = pairs && !(e.wg_ok && e.wg.wino) && plan_wgrad_split(v, ncu, e.wg_ok ? &e.wg : nullptr, &e.wgs);
+}
+
+// The plans of a descriptor; those of `pass` (a matrix-core pass, MCN_OP_*) are set.
+const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g, int pass) {
+    auto begin = [&](PlanEntry &e) {
+        const int ncu = compute_units();
+        e.fc = igemm_enabled() && is_fully_connected(g) && (int64_t)g.H * g.W * g.D < ((int64_t)1 << 30) &&
+               plan_wgrad(fc_forward_view(g), ncu, &e.fc_fwd) && plan_igemm(fc_backward_data_view(g), ncu, &e.fc_bwd) &&
+               plan_igemm(fc_backward_filter_view(g), ncu, &e.fc_wg);
     };
-    e.fc = on && is_fully_connected(g) && (int64_t)g.H * g.W * g.D < ((int64_t)1 << 30) &&
-           plan_wgrad(fc_forward_view(g), ncu, &e.fc_fwd) && plan_product(fc_backward_data_view(g), &e.fc_bwd) &&
-           plan_product(fc_backward_filter_view(g), &e.fc_wg);
-    e.fcs_ok = e.fc && pairs && wino_enabled() && plan_fc_forward_split(g, ncu, &e.fc_fwd, &e.fcs);
-    return &e;
+    auto make = [&](PlanEntry &e, int pass) {
+        if (!e.fc) {
+            if (pass == MCN_OP_FORWARD) e.fwd_ok = igemm_enabled() && plan_view(d, forward_view(g), &e.fwd);
+            else if (pass == MCN_OP_BACKWARD_DATA) plan_backward_data(e, d, g);
+            else plan_backward_filter(e, d, g);
+            return;
+        }
+        const bool three = d->precision != MCN_PREC_FP32_PLAIN && wino_enabled();
+        const int ncu = compute_units();
+        if (pass == MCN_OP_FORWARD) {
+            e.fcs_ok = three && plan_fc_forward_split(g, ncu, &e.fc_fwd, &e.fcs);
+            return;
+        }
+        const ConvView v = pass == MCN_OP_BACKWARD_DATA ? fc_backward_data_view(g) : fc_backward_filter_view(g);
+        IgemmPlan &pl = pass == MCN_OP_BACKWARD_DATA ? e.fc_bwd : e.fc_wg;
+        IgemmPlan split;
+        if (three && split_possible(v) && plan_igemm(v, ncu, &split, true, true, 3) && split_faster(v, split, pl, ncu)) pl = split;
+    };
+    return g_plans.get(*d, pass, begin, make);
 }
 
 // every block has four more waves that only fetch; blocks of four computing waves (IG_64x256) run two to a
@@ -528,12 +551,13 @@ int launch_wgrad_bf16(const WgradBfPlan &pl, const float *x, const float *dzdy, 
     }
 }
 
+// the pass whose plans tell about operation `op` (not the bias derivative)
+int planned_pass(int op) { return op == MCN_OP_BACKWARD_FILTER_BIAS ? MCN_OP_BACKWARD_FILTER : op; }
+
 size_t workspace_bytes(const mcn_conv_desc *d, const Geom &g, int op) {
-    const PlanEntry *e = plans_for(d, g);
+    if (op == MCN_OP_BACKWARD_BIAS) return plan_bias(g).ws_floats * sizeof(float);
+    const PlanEntry *e = plans_for(d, g, planned_pass(op));
     switch (op) {
-        case MCN_OP_BACKWARD_BIAS: {
-            return plan_bias(g).ws_floats * sizeof(float);
-        }
         case MCN_OP_FORWARD:
             if (e->fc) return (e->fcs_ok ? e->fcs.partial_floats : e->fc_fwd.partial_floats) * sizeof(float);
             return e->fwd_ok ? igemm_ws_bytes(e->fwd) : 0;
@@ -569,9 +593,8 @@ int run_forward(const mcn_conv_desc *desc, const Geom &g, const float *x, const 
     if (!x || !w || !y) return MCN_BAD_ARG;
     const size_t need = workspace_bytes(desc, g, MCN_OP_FORWARD);
     if (ws_bytes < need || (!ws && need)) return MCN_WORKSPACE_TOO_SMALL;
-    const PlanEntry *pe = plans_for(desc, g);
-    if (pe->fcs_ok) return launch_wgrad_split(pe->fcs, w, x, b, y, ws, s, relu);
-    if (pe->fc) return launch_wgrad(pe->fc_fwd, w, x, b, y, ws, s, relu);
+    const PlanEntry *pe = plans_for(desc, g, MCN_OP_FORWARD);
+    if (pe->fc) return pe->fcs_ok ? launch_wgrad_split(pe->fcs, w, x, b, y, ws, s, relu) : launch_wgrad(pe->fc_fwd, w, x, b, y, ws, s, relu);
     if (pe->fwd_ok) return launch_igemm(pe->fwd, x, w, b, y, ws, s, relu);
     const int total = (int)numel_y(g);
     hipLaunchKernelGGL(direct_forward_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, g, x, w, b, y, total, relu);
@@ -585,7 +608,7 @@ int run_backward_data(const mcn_conv_desc *desc, const Geom &g, const float *w, 
     if (!w || !dzdy || !dzdx) return MCN_BAD_ARG;
     const size_t need = workspace_bytes(desc, g, MCN_OP_BACKWARD_DATA);
     if (ws_bytes < need || (!ws && need)) return MCN_WORKSPACE_TOO_SMALL;
-    const PlanEntry *pe = plans_for(desc, g);
+    const PlanEntry *pe = plans_for(desc, g, MCN_OP_BACKWARD_DATA);
     const int total = (int)numel_x(g);
     int st;
     if (pe->bwd_ok && !pe->fc) {
@@ -619,7 +642,7 @@ int run_backward_filter(const mcn_conv_desc *desc, const Geom &g, const float *x
     if (!x || !dzdy || !dzdw) return MCN_BAD_ARG;
     const size_t need = workspace_bytes(desc, g, MCN_OP_BACKWARD_FILTER);
     if (ws_bytes < need || (!ws && need)) return MCN_WORKSPACE_TOO_SMALL;
-    const PlanEntry *pe = plans_for(desc, g);
+    const PlanEntry *pe = plans_for(desc, g, MCN_OP_BACKWARD_FILTER);
     if (pe->fc) return launch_igemm(pe->fc_wg, x, dzdy, nullptr, dzdw, ws, s);
     if (pe->wgb_ok) return launch_wgrad_bf16(pe->wgb, x, dzdy, dzdw, ws, s);
     if (pe->wgs_ok) return launch_wgrad_split(pe->wgs, x, dzdy, nullptr, dzdw, ws, s);
@@ -638,7 +661,7 @@ int run_backward_filter_bias(const mcn_conv_desc *desc, const Geom &g, const flo
     if (!x || !dzdy || !dzdw || !dzdb) return MCN_BAD_ARG;
     const size_t need = workspace_bytes(desc, g, MCN_OP_BACKWARD_FILTER_BIAS);
     if (ws_bytes < need || (!ws && need)) return MCN_WORKSPACE_TOO_SMALL;
-    const PlanEntry *pe = plans_for(desc, g);
+    const PlanEntry *pe = plans_for(desc, g, MCN_OP_BACKWARD_FILTER);
     if (!pe->fc && !pe->wgb_ok && pe->wg_ok && wgrad_gives_bias(pe->wg))
         return launch_wgrad(pe->wg, x, dzdy, nullptr, dzdw, ws, s, 0, dzdb);
     const int st = run_backward_filter(desc, g, x, dzdy, dzdw, ws, ws_bytes, s);
@@ -733,8 +756,9 @@ static const char *igemm_name(const IgemmPlan &pl) {
 
 const char *mcn_conv_kernel_name(const mcn_conv_desc *desc, int op) {
     Geom g;
-    if (make_geom(desc, &g)) return NULL;
-    const PlanEntry *e = plans_for(desc, g);
+    if (make_geom(desc, &g) || op < MCN_OP_FORWARD || op > MCN_OP_BACKWARD_FILTER_BIAS) return NULL;
+    if (op == MCN_OP_BACKWARD_BIAS) return plan_bias(g).rows ? "reduce_rows" : "reduce2";
+    const PlanEntry *e = plans_for(desc, g, planned_pass(op));
     switch (op) {
         case MCN_OP_FORWARD:
             return e->fc ? "fc_gemm" : e->fwd_ok ? igemm_name(e->fwd) : "direct";
@@ -748,7 +772,6 @@ const char *mcn_conv_kernel_name(const mcn_conv_desc *desc, int op) {
             // "_chunked": the schedule for arrays that stream from memory (kern_wgrad.h, WgradParams::nchunks)
             if (e->wg.P.nchunks > 0) return e->wg.wino ? "wgrad_f23_chunked" : "wgrad_igemm_chunked";
             return e->wg.wino ? "wgrad_f23" : "wgrad_igemm";
-        case MCN_OP_BACKWARD_BIAS: return plan_bias(g).rows ? "reduce_rows" : "reduce2";
         case MCN_OP_BACKWARD_FILTER_BIAS:
             return !e->fc && !e->wgb_ok && e->wg_ok && wgrad_gives_bias(e->wg) ? "wgrad_f23+bias" : "two passes";
         default: return NULL;
@@ -758,14 +781,20 @@ const char *mcn_conv_kernel_name(const mcn_conv_desc *desc, int op) {
 int mcn_conv_operand_planes(const mcn_conv_desc *desc, int op) {
     Geom g;
     if (make_geom(desc, &g) || op < MCN_OP_FORWARD || op > MCN_OP_BACKWARD_FILTER_BIAS) return -1;
-    const PlanEntry *e = plans_for(desc, g);
-    if (e->fc) {
-        const IgemmPlan &pl = op == MCN_OP_BACKWARD_DATA ? e->fc_bwd : e->fc_wg;
-        return op == MCN_OP_BACKWARD_BIAS ? 0 : op == MCN_OP_FORWARD ? (e->fcs_ok ? 3 : 0) : pl.bf16 ? pl.planes : 0;
+    if (op == MCN_OP_BACKWARD_BIAS) return 0;
+    const PlanEntry *e = plans_for(desc, g, planned_pass(op));
+    const IgemmPlan *pl = nullptr;
+    if (op == MCN_OP_FORWARD) {
+        if (e->fc) return e->fcs_ok ? 3 : 0;
+        if (e->fwd_ok) pl = &e->fwd;
+    } else if (op == MCN_OP_BACKWARD_DATA) {
+        if (e->fc) pl = &e->fc_bwd;
+        else if (e->bwd_ok && e->n_bwd) pl = &e->bwd[0];
+    } else {
+        if (!e->fc) return e->wgb_ok ? 1 : e->wgs_ok ? 3 : 0;
+        pl = &e->fc_wg;
     }
-    const IgemmPlan *pl = op == MCN_OP_FORWARD && e->fwd_ok ? &e->fwd : op == MCN_OP_BACKWARD_DATA && e->bwd_ok && e->n_bwd ? &e->bwd[0] : nullptr;
-    if (pl) return pl->bf16 ? pl->planes : 0;
-    return op != MCN_OP_BACKWARD_FILTER && op != MCN_OP_BACKWARD_FILTER_BIAS ? 0 : e->wgb_ok ? 1 : e->wgs_ok ? 3 : 0;
+    return pl && pl->bf16 ? pl->planes : 0;
 }
 
 int mcn_conv_forward(const mcn_conv_desc *desc, const float *x, const float *w, const float *b, float *y,

@@ -1,20 +1,25 @@
 """Host time of planning (no GPU): what a call on a new layer waits for before its kernels."""
 import ctypes
+import os
+import subprocess
 import time
 
 from paper_1412_4564_amd import binding as B
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
 
 def layers(precision, shapes, batch):
     return [B.make_desc((batch, d, w, h), (k, d, f, f), (s, s), (f // 2,) * 4, precision) for h, w, d, f, k, s in shapes]
 
 
-def query(descs, op):
-    """Microseconds that one size query of every descriptor takes, one after another."""
+def query(descs, ops=(B.MCN_OP_FORWARD, B.MCN_OP_BACKWARD_DATA, B.MCN_OP_BACKWARD_FILTER)):
+    """Microseconds that size queries of every descriptor take, one after another."""
     refs, size = [ctypes.byref(d) for d in descs], ctypes.c_size_t()
     out, fn = ctypes.byref(size), B.lib().mcn_conv_workspace_size
     start = time.perf_counter()
     for r in refs:
-        fn(r, op, out)
+        for op in ops:
+            fn(r, op, out)
     return 1e6 * (time.perf_counter() - start)
 
 
@@ -29,6 +34,23 @@ def test_planning_in_three_planes_is_not_much_longer_than_in_fp32():
     best = {0: 1e9, 2: 1e9}
     for batch in range(1, 13):                 # other descriptors every time: none is remembered
         for precision in best:
-            best[precision] = min(best[precision], query(layers(precision, SHAPES, batch), 2))
+            best[precision] = min(best[precision], query(layers(precision, SHAPES, batch)))
     print("planning of %d layers: %.0f us, fp32 only %.0f" % (len(SHAPES), best[0], best[2]))
     assert best[0] <= 2.5 * best[2]
+
+
+def test_a_pass_does_not_wait_for_the_plans_of_another():
+    best = {"forward": 1e9, "all": 1e9}
+    for batch in range(13, 33, 2):
+        best["forward"] = min(best["forward"], query(layers(0, SHAPES, batch), (B.MCN_OP_FORWARD,)))
+        best["all"] = min(best["all"], query(layers(0, SHAPES, batch + 1)))
+    print("planning of %d layers: forward %.0f us, all passes %.0f" % (len(SHAPES), best["forward"], best["all"]))
+    assert best["forward"] <= 0.75 * best["all"]
+
+
+def test_every_pass_is_planned_once_when_first_asked_for(tmp_path):
+    exe = str(tmp_path / "plan_cache_check")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "paper_1412_4564_amd", "csrc"),
+                           "-o", exe, os.path.join(ROOT, "tests", "plan_cache_check.cpp")])
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.startswith("OK"), r.stdout[-500:] + r.stderr[-500:]

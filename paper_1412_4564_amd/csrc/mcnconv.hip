@@ -94,8 +94,9 @@ constexpr int MAX_PHASES = 64;
 // blocks per shared tile in igemm_fixup_kernel (8 to 32 take the same time: the pass moves the pieces once)
 constexpr int IGEMM_FIXUP_SLICES = 16;
 
-// Plans depend only on the descriptor; planning walks candidate tilings, so the last few
-// descriptors' plans are remembered per host thread (host memory only, no device state).
+// Plans depend only on the descriptor; planning walks candidate tilings, so the plans of the last PLAN_CACHE descriptors, as many as a
+// network has different layers, are remembered per host thread (0.5 MB of host memory, no device state).  With eight places, a
+// network of more layers planned all of them on every pass (fourteen layers, 32 images: 0.4 ms a forward pass).
 // Passes: MCN_OP_FORWARD, MCN_OP_BACKWARD_DATA and MCN_OP_BACKWARD_FILTER; what belongs to a pass not asked for yet is zero.
 struct PlanEntry {
     bool fc;                   // fully-connected layer: the three passes run as plain matrix products
@@ -106,7 +107,8 @@ struct PlanEntry {
     bool bwd_ok;
     int n_bwd;                 // stride phases that have work
     bool bwd_fill;             // some samples of dzdx belong to no phase with work: zero-fill first
-    IgemmPlan bwd[MAX_PHASES];
+    IgemmPlan bwd;             // of the only phase with work
+    unsigned long long phases; // of several: where they begin in g_phases
     // filter derivative
     bool wg_ok;
     WgradPlan wg;
@@ -120,8 +122,16 @@ struct PlanEntry {
     WgradSplitPlan fcs;
     IgemmPlan fc_bwd, fc_wg;
 };
-constexpr int PLAN_CACHE = 8;
+constexpr int PLAN_CACHE = 64;
 thread_local PlanCache<PlanEntry, PLAN_CACHE> g_plans;
+
+// The plans of the layers with several stride phases, in a ring: the last PHASE_PLANS that were made (g_phases_made in all).
+constexpr int PHASE_PLANS = 512;
+thread_local IgemmPlan g_phases[PHASE_PLANS];
+thread_local unsigned long long g_phases_made;
+IgemmPlan &phase_plan(unsigned long long phases, int i) { return g_phases[(phases + i) % PHASE_PLANS]; }
+const IgemmPlan &phase_plan(const PlanEntry &e, int i) { return e.n_bwd > 1 ? phase_plan(e.phases, i) : e.bwd; }
+bool phases_kept(const PlanEntry &e) { return e.n_bwd < 2 || g_phases_made - e.phases <= PHASE_PLANS; }
 
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
@@ -150,12 +160,16 @@ void plan_backward_data(PlanEntry &e, const mcn_conv_desc *d, const Geom &g) {
     e.n_bwd = 0;
     e.bwd_fill = false;
     ConvView v;
-    if (on && merged_backward_data_view(g, &v) && plan_view(d, v, &e.bwd[0])) {
+    if (on && merged_backward_data_view(g, &v) && plan_view(d, v, &e.bwd)) {
         e.bwd_ok = true;       // one launch computes every stride phase
         e.n_bwd = 1;
         return;
     }
     if (!e.bwd_ok) return;
+    int n = 0;
+    for (int p = 0; p < g.Sh * g.Sw; ++p) n += backward_data_view(g, p % g.Sh, p / g.Sh, &v);
+    e.phases = g_phases_made;
+    if (n > 1) g_phases_made += n;
     for (int pj = 0; pj < g.Sw && e.bwd_ok; ++pj)
         for (int pi = 0; pi < g.Sh && e.bwd_ok; ++pi) {
             if (!backward_data_view(g, pi, pj, &v)) {
@@ -163,7 +177,8 @@ void plan_backward_data(PlanEntry &e, const mcn_conv_desc *d, const Geom &g) {
                 e.bwd_fill = true;
                 continue;
             }
-            e.bwd_ok = plan_view(d, v, &e.bwd[e.n_bwd++]);
+            e.bwd_ok = plan_view(d, v, n > 1 ? &phase_plan(e.phases, e.n_bwd) : &e.bwd);
+            ++e.n_bwd;
         }
 }
 
@@ -204,7 +219,9 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g, int pass) {
         IgemmPlan split;
         if (three && split_possible(v) && plan_igemm(v, ncu, &split, true, true, 3) && split_faster(v, split, pl, ncu)) pl = split;
     };
-    return g_plans.get(*d, pass, begin, make);
+    PlanEntry *e = g_plans.get(*d, pass, begin, make);
+    if (!e->fc && pass == MCN_OP_BACKWARD_DATA && !phases_kept(*e)) plan_backward_data(*e, d, g);
+    return e;
 }
 
 // every block has four more waves that only fetch; blocks of four computing waves (IG_64x256) run two to a
@@ -566,7 +583,7 @@ size_t workspace_bytes(const mcn_conv_desc *d, const Geom &g, int op) {
             // the phases run one after the other on the stream and share one region
             size_t m = 0;
             if (e->bwd_ok)
-                for (int i = 0; i < e->n_bwd; ++i) { size_t b = igemm_ws_bytes(e->bwd[i]); if (b > m) m = b; }
+                for (int i = 0; i < e->n_bwd; ++i) { size_t b = igemm_ws_bytes(phase_plan(*e, i)); if (b > m) m = b; }
             return m;
         }
         case MCN_OP_BACKWARD_FILTER:
@@ -621,7 +638,7 @@ int run_backward_data(const mcn_conv_desc *desc, const Geom &g, const float *w, 
             if (st) return st;
         }
         for (int i = 0; i < pe->n_bwd; ++i) {
-            st = launch_igemm(pe->bwd[i], dzdy, w, bias, dzdx, ws, s);
+            st = launch_igemm(phase_plan(*pe, i), dzdy, w, bias, dzdx, ws, s);
             if (st) return st;
         }
         return MCN_OK;
@@ -763,7 +780,7 @@ const char *mcn_conv_kernel_name(const mcn_conv_desc *desc, int op) {
         case MCN_OP_FORWARD:
             return e->fc ? "fc_gemm" : e->fwd_ok ? igemm_name(e->fwd) : "direct";
         case MCN_OP_BACKWARD_DATA:
-            return e->fc ? "fc_gemm" : e->bwd_ok ? (e->n_bwd ? igemm_name(e->bwd[0]) : "igemm") : "direct";
+            return e->fc ? "fc_gemm" : e->bwd_ok ? (e->n_bwd ? igemm_name(phase_plan(*e, 0)) : "igemm") : "direct";
         case MCN_OP_BACKWARD_FILTER:
             if (e->fc) return "fc_gemm";
             if (e->wgb_ok) return "wgrad_bf16";
@@ -789,7 +806,7 @@ int mcn_conv_operand_planes(const mcn_conv_desc *desc, int op) {
         if (e->fwd_ok) pl = &e->fwd;
     } else if (op == MCN_OP_BACKWARD_DATA) {
         if (e->fc) pl = &e->fc_bwd;
-        else if (e->bwd_ok && e->n_bwd) pl = &e->bwd[0];
+        else if (e->bwd_ok && e->n_bwd) pl = &phase_plan(*e, 0);
     } else {
         if (!e->fc) return e->wgb_ok ? 1 : e->wgs_ok ? 3 : 0;
         pl = &e->fc_wg;

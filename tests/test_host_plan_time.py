@@ -54,3 +54,22 @@ def test_every_pass_is_planned_once_when_first_asked_for(tmp_path):
                            "-o", exe, os.path.join(ROOT, "tests", "plan_cache_check.cpp")])
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.startswith("OK"), r.stdout[-500:] + r.stderr[-500:]
+
+
+def test_the_layers_of_a_network_are_remembered():
+    best, again = 1e9, 1e9
+    for batch in range(40, 60, 5):
+        net = [d for b in range(4) for d in layers(0, SHAPES, batch + b)]
+        best = min(best, query(net, (B.MCN_OP_FORWARD,)))
+        again = min(again, query(net, (B.MCN_OP_FORWARD,)))
+    print("forward plans of %d layers: %.0f us, once more %.0f" % (len(net), best, again))
+    assert again <= 0.25 * best
+
+
+def test_stride_phases_of_many_layers():
+    """More stride phases (64 a layer) than there is room for: the plans of a layer whose place was taken are made again."""
+    descs = [B.make_desc((2, 24 + n, 64, 64), (24 + 16 * n, 24 + n, 9, 8 + n % 3), (8, 8), (0, 0, 0, 0)) for n in range(12)]
+    ask = lambda d: (B.mcn_conv_workspace_size(d, B.MCN_OP_BACKWARD_DATA), B.mcn_conv_kernel_name(d, B.MCN_OP_BACKWARD_DATA))
+    first = [ask(d) for d in descs]
+    assert len(set(first)) > 3
+    assert [ask(d) for d in descs] == first and [ask(d) for d in reversed(descs)] == first[::-1]

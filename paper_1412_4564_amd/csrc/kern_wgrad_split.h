@@ -55,36 +55,73 @@ struct WgradSplitParams : WgradParams {
 };
 
 // ---- results that are not finite (see kern_igemm_split.h) --------------------------------
-// A lane's coefficient (g, k, r) over images n0 .. n1-1, summed as Sec. 6.1 writes it, in fp32.
-__device__ inline float wgrad_plain_sum(const WgradSplitParams &P, const float *x, const float *dzdy, int g, int k, int r, int n0, int n1, bool on) {
+// Part `part` of `parts` of a lane's coefficient (g, k, r), summed as Sec. 6.1 writes it, in fp32: the terms of a coefficient go by runs of
+// at most 64 rows of a column, dealt among its parts.  All lanes of a wave call it together; stop(nan), after every run: whether a part of the
+// coefficient is NaN by now, and with it the sum.  Bound by the latency of its loads: 8 rows are on their way at a time.
+template <class Stop>
+__device__ inline float wgrad_plain_part(const WgradSplitParams &P, const float *x, const float *dzdy, int g, int k, int r, int part, int parts, bool on, Stop stop) {
+    typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr int RUN = 64;
     const int T = P.Hf * P.Wf, c = r / T, tap = r - c * T, fj = tap / P.Hf, fi = tap - fj * P.Hf;
+    // rows and columns of dzdy that meet a sample inside the array
     const int i0 = max(0, (P.Pt - fi + P.Sh - 1) / P.Sh), i1 = P.H - 1 + P.Pt < fi ? 0 : min(P.Ho, (P.H - 1 + P.Pt - fi) / P.Sh + 1);
+    const int j0 = max(0, (P.Pl - fj + P.Sw - 1) / P.Sw), j1 = P.W - 1 + P.Pl < fj ? 0 : min(P.Wo, (P.W - 1 + P.Pl - fj) / P.Sw + 1);
+    const int runs = max(0, i1 - i0 + RUN - 1) / RUN, cols = max(0, j1 - j0);
+    const unsigned all = on ? P.N * cols * runs : 0;
+    const float *const x0 = x + (size_t)(g * P.Cg + c) * P.xsc + ((ptrdiff_t)(fj - P.Pl) * P.xsj + (fi - P.Pt)), *const y0 = dzdy + (size_t)(g * P.Kg + k) * P.ysc;
     float s = 0.f;
+    bool done = false;
 #pragma unroll 1
-    for (int n = n0; n < n1; ++n) {
-        const float *xp = x + (size_t)n * P.xsn + (size_t)(g * P.Cg + c) * P.xsc + (fi - P.Pt), *yp = dzdy + (size_t)n * P.ysn + (size_t)(g * P.Kg + k) * P.ysc;
+    for (unsigned q = part;; q += parts) {
+        const bool more = q < all && !done;
+        if (!__any(more)) break;
+        if (more) {
+            const int line = (int)q / runs, n = line / cols, jo = j0 + line - n * cols, io0 = i0 + RUN * ((int)q - line * runs), last = min(io0 + RUN, i1) - 1;
+            const float *const xc = x0 + (size_t)n * P.xsn + (ptrdiff_t)jo * P.Sw * P.xsj, *const yc = y0 + (size_t)n * P.ysn + (size_t)jo * P.ysj;
+            int io = io0;
+            if (P.Sh == 1 && i1 - i0 >= 4) {
+                // two fours of rows that end with the run at the latest: rows that they share count once
 #pragma unroll 1
-        for (int jo = 0; jo < P.Wo; ++jo) {
-            const int xj = jo * P.Sw + fj - P.Pl;
-            if (!on || xj < 0 || xj >= P.W) continue;
-            const float *xc = xp + (ptrdiff_t)xj * P.xsj, *yc = yp + (size_t)jo * P.ysj;
-            // a sum that is NaN stays so (columns of thousands of rows: 1x1 filters, fully-connected layers)
+                for (; io <= last; io += 8) {
+                    const int a[2] = {min(io, last - 3), min(io + 4, last - 3)};
+                    Quad xq[2], yq[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) { xq[e] = *(const Quad *)(xc + a[e]); yq[e] = *(const Quad *)(yc + a[e]); }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float next = fmaf(xq[e / 4][e % 4], yq[e / 4][e % 4], s);
+                        s = a[e / 4] + e % 4 >= io + e / 4 * 4 ? next : s;
+                    }
+                }
+            }
 #pragma unroll 1
-            for (int io = i0; io < i1 && s == s;) {
-                const int stop = min(io + 64, i1);
-#pragma unroll 4
-                for (; io < stop; ++io) s = fmaf(xc[(ptrdiff_t)io * P.Sh], yc[io], s);
+            for (; io <= last; io += 4) {
+                float xv[4], yv[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = min(io + e, last);
+                    xv[e] = xc[i * P.Sh]; yv[e] = yc[i];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float next = fmaf(xv[e], yv[e], s);
+                    s = io + e <= last ? next : s;
+                }
             }
         }
-        if (!__any(on && s == s)) break;
+        done |= stop(s != s);
     }
     return s;
 }
 
+// How many of `threads` (a power of two) sum one of m results together, a power of two.
+__device__ inline int repair_parts(int threads, int m) { return 1 << (31 - __clz(threads / m)); }
+
 // In the fix-up pass: of n stored results, where(i, &k, &r) says which and whether there is one, those that are not finite are summed
-// again by the block's 512 threads, a result each or, of few, a part of its images each.  Bound by the latency of its loads: 27x27x96,
-// 5x5x48x256 in two groups, 128 images (0.31 ms): one NaN 2.4 ms, one inf 3.1, all NaN 0.9, +inf everywhere 22; 16x16x32, 5x5x32x32, 100
-// images (0.03 ms): 0.3, 0.4, 0.1, 0.6.
+// again by the block's 512 threads, shared out evenly.  27x27x96, 5x5x48x256 in two groups, 128 images (0.31 ms): one NaN in x 0.5 ms at most
+// (4.3 with one result a thread), in dzdy 1.7 (4.1), one inf 0.7 and 1.7 (4.6 and 4.3), all NaN 0.3, +inf everywhere 11 (24); 28x28x512,
+// 1x1x512x128, 64 images (0.1 ms): one NaN 0.4 at most (1.5), one inf 0.6 (1.7); 227x227x3, 11x11x3x96 at stride 4, 128 images (0.3 ms), where the
+// results of few blocks meet it: one NaN 3.3 at most (13), one inf 6.4 (13).
 struct RepairSums {
     static constexpr bool on = true;
     WgradSplitParams S;
@@ -92,20 +129,36 @@ struct RepairSums {
     template <class Where>
     __device__ void operator()(int g, int n, Where where, const float *rbias, int relu, float *out) const {
         __shared__ float part[512];
-        const int tid = threadIdx.x, here = n < 512 ? n : 512, parts = 512 / here, p = tid / here;
+        __shared__ int list[512], dead[512], found;
+        const int tid = threadIdx.x;
 #pragma unroll 1
         for (int c0 = 0; c0 < n; c0 += 512) {
             int k = 0, r = 0;
-            const bool there = c0 + tid % here < n && p < parts && where(c0 + tid % here, &k, &r);
-            float *const o = out + (there ? (size_t)(g * S.Kg + k) * S.R + r : 0);
-            const bool again = there && not_finite(*(volatile float *)o);
-            part[tid] = wgrad_plain_sum(S, x, dzdy, g, again ? k : 0, again ? r : 0, (int)((long long)S.N * p / parts), (int)((long long)S.N * (p + 1) / parts), again);
+            if (tid == 0) found = 0;
+            dead[tid] = 0;
             __syncthreads();
-            if (again && p == 0) {
-                float v = part[tid];
-                for (int i = 1; i < parts; ++i) v += part[tid + i * here];
-                if (rbias) v += rbias[r];
-                *o = relu ? fmaxf(v, 0.f) : v;
+            if (c0 + tid < n && where(c0 + tid, &k, &r) && not_finite(*(volatile float *)(out + (size_t)(g * S.Kg + k) * S.R + r))) list[atomicAdd(&found, 1)] = c0 + tid;
+            __syncthreads();
+            const int m = found;
+            if (m > 0) {
+                // neighbours take neighbouring coefficients, whose samples share lines of memory
+                const int parts = repair_parts(512, m), M = 512 / parts, j = tid & (M - 1), p = tid / M;
+                const bool mine = j < m;
+                where(list[mine ? j : 0], &k, &r);
+                part[tid] = wgrad_plain_part(S, x, dzdy, g, k, r, p, parts, mine, [&](bool nan) __attribute__((always_inline)) {
+                    if (nan) dead[j] = 1;
+                    return *(volatile int *)&dead[j] != 0;
+                });
+#pragma unroll 1
+                for (int h = parts >> 1; h > 0; h >>= 1) {
+                    __syncthreads();
+                    if (p < h) part[tid] += part[tid + h * M];
+                }
+                if (mine && p == 0) {
+                    float v = dead[j] ? __uint_as_float(0x7fc00000u) : part[tid];
+                    if (rbias) v += rbias[r];
+                    out[(size_t)(g * S.Kg + k) * S.R + r] = relu ? fmaxf(v, 0.f) : v;
+                }
             }
             __syncthreads();
         }
@@ -437,6 +490,8 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_spl
                 out[(size_t)(c_g * P.Kg + c_kt * TK + kl) * P.R + r] = not_finite(val) ? __uint_as_float(0x7fc00000u) : P.relu ? fmaxf(val + rb, 0.f) : val + rb;
             }
         if (!__any(odd)) return;
+        // The wave sums again what is not finite of its part: 14x14x512, 5x5x512x512, 32 images (0.5 ms), one NaN in x 2.9 ms at most, one inf 5.6 (9.0
+        // and 17.7 with a result a lane).
         __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);         // this wave reads back what it stored
 #pragma unroll 1
         for (int e = 0; e < MK * 16; ++e) {
@@ -444,8 +499,19 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_spl
             const bool there = kl < klim && r < P.R;
             float *o = out + (there ? (size_t)(c_g * P.Kg + k) * P.R + r : 0);
             const bool again = there && not_finite(*(volatile float *)o);
-            if (!__any(again)) continue;
-            const float val = wgrad_plain_sum(P, x, dzdy, c_g, again ? k : 0, again ? r : 0, 0, P.N, again) + rb;
+            const unsigned long long which = __ballot(again);
+            if (which == 0) continue;
+            // the wave's lanes, shared out among the coefficients: lane's coefficient is that of the j-th lane that has one
+            const int m = __popcll(which), parts = repair_parts(64, m), j = lane / parts, p = lane - j * parts;
+            unsigned long long left = which;
+            for (int i = 0; i < j; ++i) left &= left - 1;
+            const int from = left ? __ffsll((long long)left) - 1 : 0;
+            const unsigned long long together = (parts == 64 ? ~0ull : (1ull << parts) - 1) << (j * parts);
+            float val = wgrad_plain_part(P, x, dzdy, c_g, __shfl(k, from), __shfl(r, from), p, parts, j < m,
+                                         [&](bool nan) __attribute__((always_inline)) { return (__ballot(nan) & together) != 0; });
+            for (int h = parts >> 1; h > 0; h >>= 1) val += __shfl_xor(val, h);
+            const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(which >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)which, 0u));
+            val = __shfl(val, rank * parts) + rb;
             if (again) *o = P.relu ? fmaxf(val, 0.f) : val;
         }
     };

@@ -75,3 +75,35 @@ def test_small_layers(case):
     print("small layers, default and plain: %.1f %.1f us" % t, flush=True)
     assert t[0] <= 1.12 * t[1], t
 
+
+NOT_FINITE = [  # x, filters, stride, pad: shared tiles, chunks, and tiles that one block computes
+    ((128, 96, 27, 27), (256, 48, 5, 5), (1, 1), (2, 2, 2, 2)),
+    ((64, 512, 28, 28), (128, 512, 1, 1), (1, 1), (0, 0, 0, 0)),
+    ((32, 512, 14, 14), (512, 512, 5, 5), (1, 1), (2, 2, 2, 2)),
+]
+
+
+@pytest.mark.parametrize("case", range(len(NOT_FINITE)))
+@pytest.mark.parametrize("where", ["x", "dzdy"])
+def test_one_nan_in_the_filter_derivative(case, where):
+    """The coefficients that meet it are summed again by all threads of the blocks that hold them: 2 to 6 times the ordinary call (with one
+    result a thread 13 to 18 times for one in x, 4 to 15 for one in dzdy)."""
+    xs, wsh, stride, pad = NOT_FINITE[case]
+    x, ws = torch.randn(xs, device="cuda"), B.Workspace()
+    p = torch.randn_like(B.conv_forward(x, torch.zeros(wsh, device="cuda"), None, stride, pad))
+    assert B.mcn_conv_operand_planes(B.make_desc(xs, wsh, stride, pad), B.MCN_OP_BACKWARD_FILTER) == 3
+    out = torch.empty(wsh, device="cuda")
+
+    def best():
+        t = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record(); B.conv_backward_filter(x, wsh, p, stride, pad, out=out, workspace=ws); b.record(); b.synchronize()
+            t.append(a.elapsed_time(b) * 1e3)
+        return min(t)
+    finite = best()
+    bad = x if where == "x" else p
+    bad.view(-1)[bad.numel() // 2 + 5] = float("nan")
+    nan = best()
+    print("filter derivative, finite and with a NaN in %s: %.0f %.0f us" % (where, finite, nan), flush=True)
+    assert torch.isnan(out).any() and nan <= 9 * finite

@@ -340,7 +340,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                 if constexpr (GROUPED) {
                     const int q = q0 + (e & (TQ - 1)), c = div32(q, P.dTI), n = div32(c, P.dWo), j = (c - n * P.Wo) * P.Sw - P.Pl, i = row0 + (q - c * P.TI) * P.Sh;
                     const bool ok = e < CP && q < P.QN && rb * P.TI + q - c * P.TI < P.Ho && j >= 0 && j < P.W && i >= 0 && i < P.H;
-                    go[s][0] = ok ? 4u * (unsigned)(i + P.H * j + (n - n_first) * P.Ctot * HW + (sample_dc + set_dc * s) * HW) : SLAB_INVALID;
+                    go[s][0] = ok ? 4u * ((unsigned)(i + P.H * j + (n - n_first) * P.Ctot * HW) + (unsigned)(sample_dc + set_dc * s) * (unsigned)HW) : SLAB_INVALID;
                     continue;
                 }
                 const int col = div32(e, P.dSRP);

@@ -280,7 +280,8 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_spl
         // first: the unit's column that the words' column 0 is
         auto load_x = [&](float (&v)[2][4], const Word &w, const Place &u, int first, int nch, __amdgpu_buffer_rsrc_t xrs) __attribute__((always_inline)) {
             const int i0 = w.row + u.io0 * P.Sh - P.Pt, j = w.col + first + u.jo0 * P.Sw - P.Pl;
-            const unsigned off = 4u * (unsigned)(i0 + j * P.xsj + w.c * P.xsc + w.img * P.xsn);
+            // of a word that is not there (channel 0x40000000, columns far outside) some number that is not used: unsigned, so that it may wrap
+            const unsigned off = 4u * ((unsigned)i0 + (unsigned)j * (unsigned)P.xsj + (unsigned)w.c * (unsigned)P.xsc + (unsigned)(w.img * P.xsn));
             const bool ok = (w.c < nch) & ((unsigned)j < (unsigned)P.W);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {

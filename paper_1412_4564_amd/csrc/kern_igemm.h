@@ -99,11 +99,12 @@ __device__ inline void load_to_lds_b128(unsigned lds_addr, unsigned voffset, buf
                  : "=&s"(saved_m0) : "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset) : "memory");
 }
 
+// Infinity or NaN: an exponent of all ones (a comparison could be folded away under other float flags).
+__device__ inline bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
 
 // Workgroup barrier that orders LDS traffic only: unlike __syncthreads() it does not wait for
 // this wave's outstanding global stores, so a finished tile drains to memory while the next one
 // is computed.  Loads into LDS are waited for explicitly (vmcnt) where they are consumed.
-__device__ inline bool not_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) == 0x7f800000u; }
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 struct IgemmParams {

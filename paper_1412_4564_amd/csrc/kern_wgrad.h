@@ -545,6 +545,11 @@ __global__ __launch_bounds__(64 * (WK * WR + WGRAD_LOADER_WAVES), WPE) void wgra
     }
 }
 
+// What becomes of sums that are not finite in the fix-up pass: they stay, or see kern_wgrad_split.h
+struct KeepSums {
+    static constexpr bool on = false;
+};
+
 // Sum the pieces of every tile shared between blocks and write the tile.  blockIdx.x = tile, blockIdx.y = a
 // slice of the tile's results.  The order of the additions is fixed by the plan: with G = 512 / Q partial sums
 // per result (a power of two chosen on the host from the number of pieces), piece i goes to partial sum i mod G
@@ -554,10 +559,6 @@ __global__ __launch_bounds__(64 * (WK * WR + WGRAD_LOADER_WAVES), WPE) void wgra
 // fraction of every piece.
 // CHUNKED: the pieces of tile t are the first slots of blocks t + tiles*i, i < nchunks; else those of the blocks
 // whose equal ranges of units overlap the tile.
-// Repair: what becomes of sums that are not finite (kern_wgrad_split.h).
-struct KeepSums {
-    static constexpr bool on = false;
-};
 template <int TK, int TR, bool CHUNKED, class Repair = KeepSums>
 __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, const float *__restrict__ part,
                                                           const float *__restrict__ rbias, float *__restrict__ out,

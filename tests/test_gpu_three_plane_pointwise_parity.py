@@ -96,3 +96,24 @@ def test_values_that_are_not_finite(case):
         r = torch.from_numpy(np.asarray(want[name])).reshape(g.shape)
         assert t.any() and torch.equal(g[~t], clean[name].cpu()[~t])
         assert torch.equal(torch.isnan(g[t]), torch.isnan(r[t])) and torch.equal(g[t][torch.isinf(r[t])].double(), r[t][torch.isinf(r[t])])
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_results_summed_again(case):
+    """Operands that round to infinity in their first plane, where the other operand is tiny: every result that they enter is summed again, to
+    one of ordinary size, in which no term may be missing or count twice."""
+    L = custom_layer(*CASES[case], idx=960 + case)
+    assert 3 in planes(L)[:2]
+    x, w, b, p = inputs(L, 6)
+    # Per pass, so that no result consists of products of two tiny numbers, which fp32 does not hold.
+    large = {"y": [t.clone() for t in (x, w, b, p)], "dzdx": [t.clone() for t in (x, w, b, p)], "dzdw": [t.clone() for t in (x, w, b, p)]}
+    t = large["y"]; t[0][0, 1, 0, 0] = 3.4e38; t[1][:, 1, 0, 0] *= 1e-37
+    t = large["dzdx"]; t[3][-1, -1, 0, 0] = 3.4e38; t[1][-1] *= 1e-37
+    t = large["dzdw"]; t[0][0, 1, 0, 0] = t[3][-1, -1, 0, 0] = 3.4e38; t[3][0] *= 1e-37; t[0][-1] *= 1e-37
+    for name, t in large.items():
+        ref, den = sums(L, *(U.np64(v) for v in t))[name], sums(L, *(np.abs(U.np64(v)) for v in t))[name]
+        if ref is None:
+            continue
+        e = U.norm_err(run(L, *(v.cuda() for v in t))[name].cpu().numpy(), ref, den)
+        print("pointwise, summed again", case, name, e, flush=True)
+        assert e <= BOUND

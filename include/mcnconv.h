@@ -74,7 +74,7 @@ typedef struct mcn_conv_desc {
  *   because of zeros in the DATA may come out as rounding noise (zeros that come from padding
  *   stay exact).  For inputs of one scale (the workloads here) the error equals that of the
  *   plain order, about 1e-7 of the sum of |w||x|.
- *   Forward and dzdx of other filter sizes (two taps or more, at least 16 channels per group), and of
+ *   Forward and dzdx of other filter sizes (1x1 among them; at least 16 channels per group), and of
  *   3x3 layers with at least 256 channels and few tiles, run, where that is estimated to be the faster way
  *   (mcn_conv_operand_planes says 3; small layers stay on the fp32 matrix core), on the bf16 matrix core with every operand
  *   held as THREE bf16 values whose sum it is exactly, and six products accumulated in fp32 (what is left
@@ -98,7 +98,9 @@ typedef struct mcn_conv_desc {
  *   products accumulated in fp32; arrays in memory stay fp32.  Normalised error <= 1e-2.
  *   Geometries the bf16 kernels do not cover (fewer than 16 channels per group,
  *   fully-connected layers, the filter derivative with a vertical stride, more than 5 filter
- *   rows or at most 32 filters per group) compute in fp32, which meets the same bound.  dzdx of a strided layer
+ *   rows or at most 32 filters per group) compute with the fp32 precision of the default, which meets the same
+ *   bound: fully-connected layers and filter derivatives on the kernels of the default (mcn_conv_operand_planes says 3 or
+ *   0), forward and dzdx of other layers on the fp32 matrix core.  dzdx of a strided layer
  *   with at most 16 channels per group (first layers) does too, on the fp32 matrix core: the default is faster
  *   there (227x227x3, 11x11 at stride 4, 128 images: 390 us against 240).
  * MCN_PREC_FP32_BF16X3: fp32 arrays, fp32 accumulation, and every operand of the forward pass and of
@@ -109,7 +111,7 @@ typedef struct mcn_conv_desc {
  *   measures 5e-7 to 6e-6; the two passes run 1.6 to 1.8 times as fast as under MCN_PREC_FP32 on the
  *   3x3 layers of the benchmark (staging, not the matrix core, bounds them).  For callers who would otherwise trade fp32 for
  *   bf16 operands: this keeps 16 instead of 8 significant bits.  dzdw, dzdb and the geometries the bf16
- *   kernels do not cover compute as under MCN_PREC_FP32.
+ *   kernels do not cover compute with the precision of MCN_PREC_FP32 (as under MCN_PREC_BF16).
  * The environment variable MCN_NO_WINO=1 (read once per process) makes MCN_PREC_FP32 behave as
  * MCN_PREC_FP32_PLAIN; it exists for benchmarks. */
 enum { MCN_PREC_FP32 = 0, MCN_PREC_BF16 = 1, MCN_PREC_FP32_PLAIN = 2, MCN_PREC_FP32_BF16X3 = 3 };
@@ -323,7 +325,8 @@ int mcn_last_hip_error(void);
 /* Name of the kernel family the dispatcher picks for this descriptor and
  * operation ("direct", "igemm", "igemm_f23" / "wgrad_f23" = the matrix-core kernels
  * that take pairs of output rows of a 3x3 stride-1 layer with four products per filter
- * column, ...); for reports and tests.  Returns NULL on a bad descriptor.  Host only. */
+ * column, ...): the sum that it computes, whatever holds its operands ("igemm" and "wgrad_igemm" on the fp32
+ * matrix core and in three planes alike; mcn_conv_operand_planes); for reports and tests.  Returns NULL on a bad descriptor.  Host only. */
 const char *mcn_conv_kernel_name(const mcn_conv_desc *desc, int op);
 
 /* How that kernel holds the operands of its products on chip: 3 = fp32 in three bf16 planes (six products

@@ -19,7 +19,7 @@
 //
 // What bounds it: the matrix core at the clock that its power leaves (27x27x96, 5x5x48x256 in two groups, 128 images: 285 us at 1.9 GHz, 220
 // without operand reads and staging, 250 without staging; the fp32 kernel 556), then the staging waves' vector instructions where
-// few coefficients share a sample (28x28x512, 1x1x512x128, 64 images: 72 us, fp32 103; 4x4 at stride 2, 56x56x128, 256 filters, 32
+// few coefficients share a sample (28x28x512, 1x1x512x128, 64 images: 66 us, fp32 103; 4x4 at stride 2, 56x56x128, 256 filters, 32
 // images: 205, fp32 276).  Hence
 //  * every octet is requested as soon as the same octet of the unit before has been split, without branches between the requests
 //    (with all requests behind the last write, or branches that make the compiler wait for all of them: 374 to 490 us);

@@ -766,136 +766,23 @@ inline bool plan_wgrad(const ConvView &v, int n_cu, WgradPlan *pl, bool wino = f
 
 }  // namespace mcn
 
-// ---- filter derivative with bf16 operands (kern_wgrad_bf16.h) ---------------------------------
+// ---- filter derivative on the bf16 matrix core: fp32 operands in three planes (kern_wgrad_split.h), or rounded to bf16 (kern_wgrad_bf16.h) -----
+#include "kern_wgrad_split.h"
 #include "kern_wgrad_bf16.h"
 namespace mcn {
 
-enum WgradBfShape { WGB_128x256 = 0, WGB_64x256 = 1 };
-constexpr int WGB_MAX_HF = 5;      // filter heights with an instantiation
-
-struct WgradBfPlan {
-    int shape;
-    int TK, TR, NT;
-    WgradBfParams P;
-    size_t lds_bytes;
-    size_t partial_floats;   // one TK*TR piece per block when a tile's reduction is shared
-};
-
-// Slab pitches (in 16-byte words): lane r of an operand read addresses word
-// fi*CPF + fj*RGP + c*CPC (+ the same for all lanes); eight consecutive r should fall into eight
-// different 16-byte bank groups.  Smallest pitches with the fewest collisions.
-inline void wgb_pitches(int Hf, int Wf, int TIG, int SC, int *RGP, int *CPF, int *CPC) {
-    const int T = Hf * Wf;
-    long best_cost = -1;
-    for (int a = 0; a < 8; ++a)
-        for (int b = 0; b < 8; ++b)
-            for (int c = 0; c < 8; ++c) {
-                const int rgp = TIG + a, cpf = SC * rgp + b, cpc = Hf * cpf + c;
-                int coll = 0;
-                for (int r0 = 0; r0 < 8 * T; r0 += 8) {
-                    unsigned seen = 0;
-                    for (int r = r0; r < r0 + 8; ++r) {
-                        const int ch = r / T, tap = r % T, fj = tap / Hf, fi = tap % Hf;
-                        seen |= 1u << ((fi * cpf + fj * rgp + ch * cpc) & 7);
-                    }
-                    coll += 8 - __builtin_popcount(seen);
-                }
-                const long cost = (long)coll * 100000 + cpc;
-                if (best_cost < 0 || cost < best_cost) { best_cost = cost; *RGP = rgp; *CPF = cpf; *CPC = cpc; }
-            }
-}
-
-inline bool plan_wgrad_bf16(const ConvView &v, int n_cu, WgradBfPlan *pl) {
-    if (v.Sh != 1 || v.Hf > WGB_MAX_HF || v.Kg <= 32) return false;
-    const int T = v.Hf * v.Wf;
-    const int64_t R64 = (int64_t)T * v.Cg;
-    if (R64 >= ((int64_t)1 << 30)) return false;
-    const int R = (int)R64;
-    if ((double)v.H * v.W * v.Ctot * 4 >= 2147483647.0) return false;      // 32-bit byte offsets inside an image
-    if ((double)v.Ho * v.Wo * v.Ktot * 4 >= 2147483647.0) return false;
-    const int shape = v.Kg > 64 ? WGB_128x256 : WGB_64x256;
-    const int TK = v.Kg > 64 ? 128 : 64, TR = 256, NT = 512;
-    const int RT = (R + TR - 1) / TR;
-    int NCH = 0;
-    for (int rt = 0; rt < RT; ++rt) {
-        const int lo = rt * TR, hi = (lo + TR < R ? lo + TR : R);
-        const int n = (hi - 1) / T - lo / T + 1;
-        if (n > NCH) NCH = n;
-    }
-    int cand[40], nc = 0;
-    cand[nc++] = v.Ho;
-    for (int parts = 2; parts <= 8; ++parts) cand[nc++] = (v.Ho + parts - 1) / parts;
-    for (int t = 8; t <= 128; t += 8) cand[nc++] = t;
-    const bool streams_from_memory =
-        4.0 * ((double)v.H * v.W * v.Ctot + (double)v.Ho * v.Wo * v.Ktot) * v.N > 64.0 * 1024 * 1024;
-    double best = 1e300;
-    WgradBfParams B = {};
-    for (int a = 0; a < nc; ++a) {
-        const int TI = cand[a];
-        if (TI < 1 || TI > v.Ho) continue;
-        const int TIG = (TI + 7) / 8;
-        for (int MC = 2; MC <= 32; MC += 2) {
-            const int PW = TIG * MC;
-            if ((int64_t)TK * PW > (int64_t)WGB_YT * NT) break;
-            const int SC = (MC - 1) * v.Sw + v.Wf;
-            if ((int64_t)NCH * SC * TIG > (int64_t)WGB_XT * NT) break;
-            int RGP, CPF, CPC;
-            wgb_pitches(v.Hf, v.Wf, TIG, SC, &RGP, &CPF, &CPC);
-            const int PYW = PW | 1;
-            const size_t lds = 2 * ((size_t)TK * PYW + (size_t)NCH * CPC) * 16;
-            if (lds > IGEMM_LDS_LIMIT) break;
-            const int RB = (v.Ho + TI - 1) / TI, CC = (v.Wo + MC - 1) / MC;
-            const double units = (double)RB * CC * v.N;
-            const double steps = (double)(MC / 2) * TIG;
-            // a unit costs about three steps of set-up; when the arrays do not fit the caches, short
-            // column segments waste most of every 128-byte line they touch
-            const double cost = units * (steps + 3.0) * (streams_from_memory ? 1.0 + 16.0 / TI : 1.0);
-            if (cost < best) {
-                best = cost;
-                B.TI = TI; B.RB = RB; B.TIG = TIG; B.MC = MC; B.CC = CC; B.SC = SC;
-                B.PW = PW; B.PYW = PYW; B.RGP = RGP; B.CPF = CPF; B.CPC = CPC;
-            }
-        }
-    }
-    if (best >= 1e300) return false;
-    WgradBfParams &P = pl->P;
-    P = B;
-    P.H = v.H; P.W = v.W; P.N = v.N; P.Ctot = v.Ctot; P.Cg = v.Cg;
-    P.Ho = v.Ho; P.Wo = v.Wo; P.Ktot = v.Ktot; P.Kg = v.Kg; P.G = v.G;
-    P.Hf = v.Hf; P.Wf = v.Wf; P.Sw = v.Sw; P.Pt = v.Pt; P.Pl = v.Pl;
-    P.NCH = NCH;
-    P.KT = (v.Kg + TK - 1) / TK; P.RT = RT; P.R = R;
-    const int64_t NU = (int64_t)P.RB * P.CC * v.N;
-    const int64_t tiles = (int64_t)v.G * P.KT * RT;
-    if (NU >= ((int64_t)1 << 30) || tiles >= ((int64_t)1 << 20)) return false;
-    P.NU = (int)NU; P.tiles = (int)tiles;
-    // chunks per tile: fill the compute units in as few, as full rounds as possible
-    int best_nch = 1;
-    double best_eff = 0.0;
-    const int64_t max_nch = NU < 4 * (int64_t)n_cu ? NU : 4 * (int64_t)n_cu;
-    for (int64_t nch = 1; nch <= max_nch && nch * tiles <= 4 * (int64_t)n_cu; ++nch) {
-        const int64_t nb = nch * tiles;
-        const int64_t rounds = (nb + n_cu - 1) / n_cu;
-        // a round of chunks costs its units plus a fixed part (set-up, writing the piece)
-        const double time = (double)rounds * ((double)((NU + nch - 1) / nch) + 8.0);
-        const double eff = 1.0 / time;
-        if (eff > best_eff * 1.0000001) { best_eff = eff; best_nch = (int)nch; }
-    }
-    P.nchunks = best_nch;
-    P.nblocks = (int)(tiles * best_nch);
-    pl->shape = shape; pl->TK = TK; pl->TR = TR; pl->NT = NT;
-    pl->lds_bytes = 2 * ((size_t)TK * P.PYW + (size_t)NCH * P.CPC) * 16;
-    pl->partial_floats = P.nchunks > 1 ? (size_t)P.nblocks * TK * TR : 0;
-    return true;
-}
-
-}  // namespace mcn
-
-// ---- filter derivative, fp32 operands in three bf16 planes (kern_wgrad_split.h) -----------------
-#include "kern_wgrad_split.h"
-namespace mcn {
-
-enum WgradSplitShape { WGS_128x128 = 0, WGS_64x256 = 1, WGS_32x256 = 2 };
+enum WgradSplitShape { WGS_128x128 = 0, WGS_64x256 = 1, WGS_32x256 = 2, WGB_128x384 = 3, WGB_128x256 = 4, WGB_128x128 = 5, WGB_64x768 = 6, WGB_64x512 = 7, WGB_64x256 = 8 };
+// Tiles (filters x coefficients) and how much a staging thread brings per unit (launch_wgrad_split): octets of dzdy and of x; and for LINEAR, 0: no
+// such instantiation.
+struct WgradSplitTile { int planes, TK, TR, YT, XT, YTL, XTL; };
+constexpr WgradSplitTile WGS_TILES[] = {
+    {3, 128, 128, 4, 2, 3, 3}, {3, 64, 256, 4, 2, 1, 4}, {3, 32, 256, 2, 2, 1, 4},
+    {1, 128, 384, 7, 4, 0, 0}, {1, 128, 256, 7, 4, 3, 6}, {1, 128, 128, 7, 4, 4, 4},
+    {1, 64, 768, 4, 6, 0, 0},  {1, 64, 512, 4, 6, 0, 0},  {1, 64, 256, 4, 4, 2, 6}};
+constexpr int WGS_N_TILES = 9;
+// LDS per buffer of dzdy; one plane: and a place for the octets that a thread does not have
+inline int wgs_dzdy_bytes(const WgradSplitTile &t, int PYW) { return t.planes == 1 ? (t.TK * PYW + 1) * 16 : t.TK * PYW * 48; }
+constexpr int WGB_MAX_HF = 5;      // filter heights whose derivative takes operands rounded to bf16
 
 struct WgradSplitPlan {
     int shape;
@@ -963,8 +850,33 @@ inline double overlapped(double a, double b, double c, double part) {
     return sqrt(sqrt(x * x + y * y + z * z)) + part * (a + b + c - most);
 }
 
+// One plane (wgrad_bf16_kernel): estimated microseconds of a call beyond its launches, and the schedule of kern_wgrad.h for it (nchunks = 0: equal
+// ranges) on how many blocks: every block writes a piece of a tile that the fix-up pass has to read, so calls of few units take fewer
+// blocks.  yt, xt: octets of the instantiation; first: passes over a sweep's first columns, per unit; lines: memory lines of 128 bytes per
+// unit; filled: of a tile.  The constants are a fit to 63000 timed calls of 2170 random layers (several tiles, patches and schedules of
+// each; off by 13 %, 1 standard deviation), but for the 4 us of the fix-up pass (1.65 in calls that follow one another slowly).
+inline double wgb_us(const WgradSplitTile &tile, int NO, int yt, int xt, double first, double lines, int64_t tiles, int64_t NU, int n_cu, bool streams, double filled,
+                     int *nchunks, int *nblocks) {
+    constexpr double STEP[3] = {0.0561, 0.1165, 0.172}, FEWER[4] = {1.0, 0.583, 0.34, 0.198};        // by blocks of coefficients a wave; n_cu / 1, 2, 4, 8
+    const double mfma = NO / 2 * STEP[tile.TK * tile.TR / 16384 - 1], stage = 0.0477 * yt + 0.05 * xt + 0.198 * first;
+    const int64_t total = tiles * NU;
+    double best = 1e300;
+    for (int chunked = 0; chunked < 2; ++chunked)
+        for (int f = 0; f < 4 && (f == 0 || total < 32 * n_cu); ++f) {
+            const int nb = n_cu >> f;
+            const int64_t nch = nb / tiles < NU ? nb / tiles : NU, blocks = chunked ? nch * tiles : total < nb ? total : nb;
+            if (blocks < 1) continue;
+            const double fetch = lines * (chunked ? (streams ? 2.59e-4 : 1.146e-4) : (streams ? 5.82e-4 : 2.61e-4)) * FEWER[f];
+            const double pieces = blocks > 1 && !(chunked && nch == 1) ? 4.0 + 1.552e-6 * filled * (double)blocks * tile.TK * tile.TR : 0.0;
+            const double us = overlapped(mfma, stage, fetch, 2.48) * (double)(chunked ? (NU + nch - 1) / nch : (total + blocks - 1) / blocks) + pieces;
+            if (us < best) { best = us; *nchunks = chunked ? (int)nch : 0; *nblocks = nb; }
+        }
+    return best;
+}
+
 inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool streams, WgradSplitPlan *pl) {
-    const int TK = shape == WGS_128x128 ? 128 : shape == WGS_64x256 ? 64 : 32, TR = shape == WGS_128x128 ? 128 : 256;
+    const WgradSplitTile tile = WGS_TILES[shape];
+    const int TK = tile.TK, TR = tile.TR;
     const int T = v.Hf * v.Wf;
     const int64_t R64 = (int64_t)T * v.Cg;
     if (R64 >= ((int64_t)1 << 30)) return false;
@@ -976,12 +888,14 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
     }
     const int64_t tiles = (int64_t)v.G * KT * RT;
     if (tiles >= ((int64_t)1 << 20)) return false;
-    const int NPH = v.Hf < v.Sh ? v.Hf : v.Sh;
+    const int NPH = v.Hf < v.Sh ? v.Hf : v.Sh, XL = tile.planes == 1 ? (v.Pt + 3) / 4 * 4 : v.Pt;
     const int threads = 64 * WGS_STAGE_WAVES;
-    // octets of x limited by rows of dzdy, columns by x itself: no output row may lie past the last row of x
-    const bool linear = T == 1 && v.Sh == 1 && v.Sw == 1 && v.Pt == 0 && v.Pl == 0 && v.Ho == v.H;
+    // octets of x limited by rows of dzdy, columns by x itself: no output row may lie past the last row of x (one plane: rows of x past its last
+    // one meet rows of dzdy that are zeroed)
+    const bool linear = T == 1 && v.Sh == 1 && v.Sw == 1 && v.Pt == 0 && v.Pl == 0 && (tile.planes == 1 ? v.Ho <= v.H : v.Ho == v.H);
     // octets per staging thread of the instantiations there are (launch_wgrad_split)
-    const int most_y = linear ? (TK == 128 ? 3 : 1) : TK == 32 ? 2 : 4, most_x = linear ? (TK == 128 ? 3 : 4) : 2;
+    const int most_y = linear ? tile.YTL : tile.YT, most_x = linear ? tile.XTL : tile.XT;
+    if (!most_y) return false;
     double best = 1e300;
     WgradSplitParams B = {};
     for (int TIQ = 1; TIQ <= 32; ++TIQ) {
@@ -996,40 +910,55 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
                 const int YW = TK * NO;
                 if (YW > most_y * threads) break;
                 const int SC = (MC - 1) * v.Sw + v.Wf;
-                const int XQ = (4 * TIQ + (v.Hf - 1) / v.Sh + 3) / 4;        // quads of a phase
+                // by 16-byte loads rows of x above the patch's first one come as whole quads, none of which may begin above the plane and reach into it
+                if (tile.planes == 1 && RB > 1 && TI < XL) continue;
+                const int XQ = (4 * TIQ - 1 + (v.Hf - 1 + XL - v.Pt) / v.Sh) / 4 + 1;        // quads of a phase
                 const int64_t XW1 = (int64_t)NCH * NP * NPH * XQ;
                 const int step = MC * v.Sw < SC ? MC * v.Sw : SC, RC = 2 * SC;
-                if (XW1 * step > most_x * threads || XW1 * (SC - step) > 2 * threads) break;
+                if (tile.planes == 1 && (step > 255 || 4 * XQ > 4095)) break;              // the staging waves keep a word's place in 32 bits
+                if (XW1 * step > most_x * threads || (tile.planes == 3 && XW1 * (SC - step) > 2 * threads)) break;
                 const int PHP = 4 * XQ, COLP = NPH * PHP, MPP = RC * COLP, CHP = NP * MPP;
                 const int PYW = NO | 1, XPL = NCH * (CHP + NP * RC * 4 + 8);         // room for pitches: wgs_pitches
-                const size_t lds = 2 * (size_t)TK * PYW * 48 + (size_t)3 * XPL * 4 + 16;
+                const size_t lds = 2 * (size_t)wgs_dzdy_bytes(tile, PYW) + (size_t)XPL * 4 * tile.planes + 16;
                 if (lds > IGEMM_LDS_LIMIT) break;
                 const int CC = (v.Wo + MC - 1) / MC, IB = (v.N + 2 * NP - 1) / (2 * NP);
                 // Microseconds of a unit: its MFMAs, splitting what it stages, fetching that (memory lines of 128 bytes), and of the
-                // whole call.  The constants are a fit to 31000 timed calls of 13400 random layers (several tiles and patches of each;
-                // the estimate is off by 8 %, 1 standard deviation).
+                // whole call.
                 const int64_t NU = (int64_t)RB * CC * IB, total = tiles * NU;
                 const int kn = v.Kg < TK ? v.Kg : TK, images = 2 * NP < v.N ? 2 * NP : v.N;
                 const double extra = (double)(SC - step) / CC, columns = step + extra;
                 const double lines = (double)kn * images * (TI == v.Ho ? MC * TI / 32.0 + 1.0 : MC * (TI / 32.0 + 1.0)) +
                                      (double)NCH * images * columns * (((TI - 1) * v.Sh + v.Hf) / 32.0 + 1.0);
-                const double mfma = NO / 2 * (TK == 32 ? 0.245 : 0.47);
-                const double split = 0.865 + 0.228 * ((YW + threads - 1) / threads) + (linear ? 0.222 : 0.308) * (double)((XW1 * step + threads - 1) / threads) +
-                                     0.67 * XW1 * extra / threads;
-                const double unit = overlapped(mfma, split, lines * (streams ? 1.84e-3 : 1.09e-3), 0.225);
-                double us = unit * (double)((total + n_cu - 1) / n_cu);
-                // The two schedules of kern_wgrad.h; chunks for arrays that stream from memory, at most one to a compute unit, if they are
-                // estimated to be faster or keep the compute units about as busy (they read the arrays fewer times).
-                int nchunks = 0;
-                if (streams && tiles <= n_cu) {
-                    const int64_t nch = n_cu / tiles < NU ? n_cu / tiles : NU;
-                    const double chunked = overlapped(mfma, split, lines * 1.48e-3, 0.225) * (double)((NU + nch - 1) / nch);
-                    if (chunked < us || (double)total >= 0.95 * n_cu * (double)((NU + nch - 1) / nch)) { us = chunked; nchunks = (int)nch; }
+                int nchunks = 0, nblocks = n_cu;
+                double us;
+                if (tile.planes == 1) {
+                    const int rows = TI + v.Hf - 1 < v.H ? TI + v.Hf - 1 : v.H;                     // of x
+                    const int xt = linear || XW1 * step > most_x / 2 * threads ? most_x : most_x / 2;      // of the instantiation
+                    // dzdy in one run of whole columns, x likewise
+                    const double run_lines = (double)kn * images * (TI == v.Ho ? MC * TI / 32.0 + 1.0 : MC * (TI / 32.0 + 1.0)) +
+                                             (double)NCH * images * (RB == 1 ? columns * rows / 32.0 + 1.0 + extra : columns * (rows / 32.0 + 1.0));
+                    const double first = (double)((XW1 * (SC - step) + 2 * threads - 1) / (2 * threads)) / CC;
+                    us = wgb_us(tile, NO, most_y, xt, first, run_lines, tiles, NU, n_cu, streams, (v.Kg < TK ? (double)v.Kg / TK : 1.0) * (R < TR ? (double)R / TR : 1.0), &nchunks, &nblocks);
+                } else {
+                    // The constants are a fit to 31000 timed calls of 13400 random layers (several tiles and patches of each; the estimate is off by
+                    // 8 %, 1 standard deviation).
+                    const double mfma = NO / 2 * (TK == 32 ? 0.245 : 0.47);
+                    const double split = 0.865 + 0.228 * ((YW + threads - 1) / threads) + (linear ? 0.222 : 0.308) * (double)((XW1 * step + threads - 1) / threads) +
+                                         0.67 * XW1 * extra / threads;
+                    const double unit = overlapped(mfma, split, lines * (streams ? 1.84e-3 : 1.09e-3), 0.225);
+                    us = unit * (double)((total + n_cu - 1) / n_cu);
+                    // The two schedules of kern_wgrad.h; chunks for arrays that stream from memory, at most one to a compute unit, if they are
+                    // estimated to be faster or keep the compute units about as busy (they read the arrays fewer times).
+                    if (streams && tiles <= n_cu) {
+                        const int64_t nch = n_cu / tiles < NU ? n_cu / tiles : NU;
+                        const double chunked = overlapped(mfma, split, lines * 1.48e-3, 0.225) * (double)((NU + nch - 1) / nch);
+                        if (chunked < us || (double)total >= 0.95 * n_cu * (double)((NU + nch - 1) / nch)) { us = chunked; nchunks = (int)nch; }
+                    }
                 }
                 if (us < best) {
                     best = us;
-                    B.TI = TI; B.RB = RB; B.MC = MC; B.CC = CC; B.SC = SC; B.NP = NP; B.IB = IB; B.TIQ = TIQ; B.NO = NO; B.PYW = PYW; B.nchunks = nchunks;
-                    B.NPH = NPH; B.XQ = XQ; B.PHP = PHP; B.COLP = COLP; B.MPP = MPP; B.CHP = CHP; B.YW = YW; B.XW1 = (int)XW1; B.RC = RC; B.step = step;
+                    B.TI = TI; B.RB = RB; B.MC = MC; B.CC = CC; B.SC = SC; B.NP = NP; B.IB = IB; B.TIQ = TIQ; B.NO = NO; B.PYW = PYW; B.nchunks = nchunks; B.nblocks = nblocks;
+                    B.NPH = NPH; B.XQ = XQ; B.PHP = PHP; B.COLP = COLP; B.MPP = MPP; B.CHP = CHP; B.YW = YW; B.XW1 = (int)XW1; B.XL = XL; B.RC = RC; B.step = step;
                 }
             }
     }
@@ -1042,6 +971,7 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
     P.xsj = v.H; P.xsc = v.H * v.W; P.xsn = v.H * v.W * v.Ctot; P.xtot = (long long)P.xsn * v.N;
     P.ysj = v.Ho; P.ysc = v.Ho * v.Wo; P.ysn = v.Ho * v.Wo * v.Ktot; P.ytot = (long long)P.ysn * v.N;
     // 32-bit byte offsets inside a unit's images
+    if (tile.planes == 1 && (double)v.H * ((double)v.W * v.Ctot * 2 * P.NP + (double)P.CC * P.MC * v.Sw + v.Pl + P.SC) * 4 >= 2147483647.0) return false;
     if ((double)v.H * v.W * v.Ctot * 8 * P.NP >= 2147483647.0 || (double)v.Ho * v.Wo * v.Ktot * 8 * P.NP >= 2147483647.0) return false;
     P.KT = KT; P.RT = RT; P.R = R; P.tiles = (int)tiles;
     const int64_t NU = (int64_t)P.RB * P.CC * P.IB;
@@ -1050,13 +980,13 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
     P.dRB = make_div32(P.RB); P.dCC = make_div32(P.CC);
     P.dXW1 = make_div32(P.XW1); P.dXQ = make_div32(P.XQ); P.dNPH = make_div32(P.NPH); P.dNP = make_div32(P.NP);
     const int64_t total = tiles * NU;
-    P.nblocks = P.nchunks > 0 ? (int)tiles * P.nchunks : (int)(total < n_cu ? total : n_cu);
+    P.nblocks = P.nchunks > 0 ? (int)tiles * P.nchunks : (int)(total < P.nblocks ? total : P.nblocks);
     pl->shape = shape; pl->TK = TK; pl->TR = TR;
     pl->linear = linear;
     pl->NCH = NCH;
     pl->partial_floats = P.nblocks > 1 && P.nchunks != 1 ? (size_t)2 * P.nblocks * TK * TR : 0;
     const double filled = (v.Kg < TK ? (double)v.Kg / TK : 1.0) * (R < TR ? (double)R / TR : 1.0);        // of a tile
-    pl->us = 12.7 + best + (pl->partial_floats ? 0.298 * 8e-6 * filled * P.nblocks * TK * TR : 0.0);
+    pl->us = tile.planes == 1 ? best : 12.7 + best + (pl->partial_floats ? 0.298 * 8e-6 * filled * P.nblocks * TK * TR : 0.0);
     return true;
 }
 
@@ -1078,7 +1008,7 @@ inline double wgrad_fp32_us(const ConvView &v, const WgradPlan &pl, int n_cu) {
 // fp32 kernel is the faster one.  Over 15600 other random layers: always fp32 1.437 s, by this rule 1.031 s, the faster of the two each time
 // 1.019 s; of the 10687 that it sends to three planes 87 are slower there by more than 2 %, 44 by more than 5 %.  The 4 us: calls of 15 to
 // 20 us are launches, and the estimates do not tell their kernels apart.
-inline bool plan_wgrad_split(const ConvView &view, int n_cu, const WgradPlan *fp32, WgradSplitPlan *pl) {
+inline bool plan_wgrad_split(const ConvView &view, int n_cu, const WgradPlan *fp32, WgradSplitPlan *pl, int planes = 3) {
     ConvView v = view;
     if (v.Hf == 1 && v.Wf == 1 && v.Sh == 1 && v.Sw == 1 && v.Pt == 0 && v.Pl == 0 && v.H == v.Ho && v.W == v.Wo) {
         v.H = v.Ho = v.H * v.W;          // a plane is one column
@@ -1086,17 +1016,18 @@ inline bool plan_wgrad_split(const ConvView &view, int n_cu, const WgradPlan *fp
     }
     const bool streams = 4.0 * ((double)v.H * v.W * v.Ctot + (double)v.Ho * v.Wo * v.Ktot) * v.N > 64.0 * 1024 * 1024;
     bool ok = false;
-    for (int shape = 0; shape < 3; ++shape) {
-        if (shape == WGS_32x256 ? v.Kg > 32 : v.Kg <= 32) continue;
-        if (shape == WGS_128x128 && v.Kg <= 64) continue;
+    for (int shape = 0; shape < WGS_N_TILES; ++shape) {
+        const int TK = WGS_TILES[shape].TK;
+        if (WGS_TILES[shape].planes != planes || (TK == 32 ? v.Kg > 32 : v.Kg <= TK / 2)) continue;
         WgradSplitPlan one;
         if (plan_wgrad_split_shape(v, n_cu, shape, streams, &one) && (!ok || one.us < pl->us)) { *pl = one; ok = true; }
     }
     if (!ok || (fp32 && pl->us >= wgrad_fp32_us(view, *fp32, n_cu) - 4.0)) return false;
     WgradSplitParams &P = pl->P;
-    wgs_pitches(pl->NCH, (int)(IGEMM_LDS_LIMIT - 2 * (size_t)pl->TK * P.PYW * 48 - 16) / 12, &P);
+    const int dzdy = 2 * wgs_dzdy_bytes(WGS_TILES[pl->shape], P.PYW);
+    wgs_pitches(pl->NCH, ((int)IGEMM_LDS_LIMIT - dzdy - 16) / (4 * planes), &P);
     P.XPL = pl->NCH * P.CHP;
-    P.counts = 2 * pl->TK * P.PYW * 48 + 3 * P.XPL * 4;
+    P.counts = dzdy + planes * P.XPL * 4;
     pl->lds_bytes = (size_t)P.counts + 16;
     return true;
 }

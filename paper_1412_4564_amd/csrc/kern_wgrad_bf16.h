@@ -1,359 +1,482 @@
-// Filter derivative on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16): the "operands rounded
-// to bf16 on chip, fp32 accumulation" variant of kern_wgrad.h, for vertical stride 1.
+// Filter derivative on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), operands rounded to bf16 (round to nearest even) on chip, fp32
+// accumulation: MatConvNet manual (arXiv 1412.4564) Sec. 6.1, dz/dF = phi(x)^T dz/dY summed over the batch, vertical stride 1.
 //
-// MatConvNet manual (arXiv 1412.4564) Sec. 6.1, dz/dF = phi(x)^T dz/dY summed over the batch:
-//   dzdw[fi,fj,c,k] = sum_{n,jo,io} x[io+fi-Pt, Sw*jo+fj-Pl, g*Cg+c, n] * dzdy[io,jo,k,n],
-// with every x and dzdy rounded to bf16 (round to nearest even) before the products are formed.
-// GEMM view as in kern_wgrad.h: OUT[k][r] = sum_p DY[k][p] * PATCH[r][p], r = fi + Hf*(fj + Wf*c).
+// GEMM view, octets (4 rows of one column in 2 images, a pair of images one 32-bit word), slab, ring and units are those of
+// kern_wgrad_split.h, with one plane in the place of three:
+//   dzdy tile  [filter][octet] in 16-byte words
+//   x slab     [channel][image pair][column][row] in 32-bit words
+// Eight computing waves of 64 filters x 32*MR coefficients, four waves that fetch and convert, one unit ahead.
 //
-// One MFMA consumes 16 pixels: lane l holds 8 consecutive rows (an "octet") of one column for
-// filter or coefficient l%32; the lower half-wave takes column dc, the upper one column dc+1.
-// Arrays in memory stay fp32, rows contiguous, so an octet is 32 contiguous bytes in memory and
-// one 16-byte word in LDS:
-//   dzdy tile  [k][column][octet]                          one word = 8 rows of dzdy
-//   x slab     [channel][fi][slab column][octet]           one word = x rows i0+fi+8*octet .. +7
-// i.e. the slab is stored Hf times, shifted by one row each, so that the operand of filter row
-// fi is an aligned word whatever fi is (a 16-byte LDS read cannot start at an odd row).
-// Staging goes through registers (load fp32, convert, write words), one unit ahead of the MFMAs.
+// What bounds it: what the compute units take in.  A product costs a sixth of the three-plane kernel's, so a staged sample has to meet as
+// many filters and coefficients as the accumulators hold (MR up to 3), and a unit takes as long as the staging waves' instructions, some
+// 950 of them when they were those of kern_wgrad_split.h (56x56x256, 3x3x256x256, 32 images: 250 us; without products, loads and LDS
+// writes still 180).  Hence
+//  * x comes by 16-byte loads as dzdy does: a quad of the slab is one in memory.  Rows above the plane are whole quads (XL), rows below it are
+//    zeroed as they are packed;
+//  * what stays the same along a sweep is worked out where it begins, a unit's columns move the arrays' bases (scalar), and the parameters
+//    that only a new sweep needs are read from the kernel's arguments again: 320 instructions for ten octets a thread (190 us);
+//  * units of whole columns where LDS and registers allow it: runs of 224 bytes instead of 48 (156 us; 224x224x64, 3x3x64x64, 32 images: 16
+//    rows 380 us, 56 rows 210).
+// The kernel before it held eight rows of one image in an octet and the slab Hf times: 335 us and 632 us for these two layers.
 //
-// A unit is a patch of TI rows x MC columns of ONE image; units are ordered image-fastest, so
-// everything that depends on the patch (which elements are padding or lie outside the plane) is
-// recomputed only when the patch changes, and from unit to unit only scalar offsets change.
-//
-// Scheduling: the reduction of every tile is cut into `nchunks` equal ranges of units and block
-// (tile, chunk) sums one range.  Blocks are numbered chunk-major and mapped so that the blocks of
-// one chunk -- which read the same dzdy and x at the same time -- sit on one XCD and share its L2:
-// memory then delivers each operand about once although every r tile reads all of dzdy.  The
-// pieces of a tile are added by wgrad_bf16_fixup_kernel in a fixed order (no float atomics).
+// Schedules, tiles and the fix-up pass: kern_wgrad.h.
 #pragma once
-#include "kern_igemm_bf16.h"
+#include "kern_wgrad_split.h"
 
 namespace mcn {
 
-struct WgradBfParams {
-    int H, W, N, Ctot, Cg;
-    int Ho, Wo, Ktot, Kg, G;
-    int Hf, Wf, Sw, Pt, Pl;    // vertical stride is 1
-    int TI, RB, TIG;           // rows per patch, patches per column, octets per patch column = ceil(TI/8)
-    int MC, CC;                // columns per patch (even), patches per row of patches
-    int SC;                    // slab columns: (MC-1)*Sw + Wf
-    int PW, PYW;               // words per dzdy row: TIG*MC, and its LDS pitch (odd)
-    int RGP, CPF, CPC;         // slab pitches in words: per column, per shifted copy, per channel
-    int NCH;                   // channels an r tile can touch
-    int KT, RT, R;             // filter tiles per group, r tiles, Hf*Wf*Cg
-    int NU;                    // units per tile: RB*CC*N
-    int tiles, nchunks, nblocks;   // nblocks = tiles*nchunks
+struct WgradBf16Params : WgradSplitParams {
+    SkWalk walk;                     // of the blocks over all tiles, or of a tile's chunks
+    Div32 dNO, dTIQ, dMC, dT, dHf, dCC, dRB, dTiles, dKT, dRT;
 };
 
-constexpr int WGB_YT = 4;      // dzdy words a thread stages per unit, at most
-constexpr int WGB_XT = 2;      // slab (channel, column, octet) positions a thread stages per unit, at most
-
-// Blocks on consecutive hardware ids land on different XCDs: give XCD x the virtual blocks
-// [x*per, (x+1)*per).  The grid is padded to a multiple of 8; padding blocks do nothing.
-__device__ __host__ inline int wgb_grid(int nblocks) { return nblocks < 8 ? nblocks : (nblocks + 7) / 8 * 8; }
-__device__ inline int wgb_virtual_block(int b, int grid) { return grid % 8 == 0 ? (b % 8) * (grid / 8) + b / 8 : b; }
-
-template <int WK, int WR, int MK, int MR, int HF>
-__global__ __launch_bounds__(64 * WK * WR, 2) void wgrad_bf16_kernel(WgradBfParams P, const float *__restrict__ x,
-                                                                     const float *__restrict__ dzdy,
-                                                                     float *__restrict__ out,
-                                                                     float *__restrict__ part) {
-    constexpr int NT = 64 * WK * WR;
-    constexpr int TK = WK * MK * 32;
-    constexpr int TR = WR * MR * 32;
-    constexpr int NE = 8 + HF - 1;             // rows a slab position loads: one octet for each of the HF shifts
-    const int YS = TK * P.PYW;                 // words per dzdy buffer
-    const int XS = P.NCH * P.CPC;              // words per slab buffer
+// YT, XT: octets of dzdy and of new slab columns that a staging thread brings per unit, at most.
+// LINEAR: 1x1 filters, no row of x but those of dzdy is met (no padding, no more output rows than input rows).
+template <int WK, int WR, int MK, int MR, int YT, int XT, bool LINEAR>
+__global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf16_kernel(WgradBf16Params P, const float *__restrict__ x,
+                                                                                      const float *__restrict__ dzdy, float *out,
+                                                                                      float *__restrict__ part) {
+    constexpr int NT = 64 * WK * WR;               // computing threads
+    constexpr int NL = 64 * WGS_STAGE_WAVES;       // staging threads
+    constexpr int TK = WK * MK * 32, TR = WR * MR * 32;
+    const int NU = P.NU;
     const int T = P.Hf * P.Wf;
+    const int YB = (TK * P.PYW + 1) * 16;                // bytes per buffer of dzdy
 
     extern __shared__ __align__(16) float lds[];
-    uintx4 *ybuf = reinterpret_cast<uintx4 *>(lds);      // [2][YS]
-    uintx4 *xbuf = ybuf + 2 * YS;                        // [2][XS]
+    char *const ybuf = reinterpret_cast<char *>(lds), *const xbuf = ybuf + 2 * YB;
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = lane >> 5, l32 = lane & 31;
+
+    int vb, t, uu, nunits;           // the block's range: nunits units from unit uu of tile t on
+    if (P.nchunks > 0) {
+        vb = wg_chunk_virtual_block(blockIdx.x, gridDim.x);
+        if (vb >= P.nblocks) return;
+        const int chunk = div32(vb, P.dTiles);
+        t = vb - chunk * P.tiles;
+        uu = (int)sk_begin(P.walk, chunk);
+        nunits = (int)sk_begin(P.walk, chunk + 1) - uu;
+    } else {
+        vb = sk_virtual_block(blockIdx.x, P.nblocks);
+        const long long ub = sk_begin(P.walk, vb);
+        nunits = (int)(sk_begin(P.walk, vb + 1) - ub);
+        t = sk_tile(P.walk, ub, NU);
+        uu = (int)(ub - (long long)t * NU);
+    }
+    if (nunits <= 0) return;
+
+    // Units done, in waves: written by the staging waves, read by the computing ones.  The waves wait for one another through these two
+    // and not at barriers: the two computing waves of a SIMD then drift apart, and one multiplies while the other waits for the
+    // first operands of a unit.  The LDS executes a wave's accesses in order, so a count follows what it counts.
+    typedef __attribute__((address_space(3))) int LdsInt;
+    LdsInt *const written = (LdsInt *)(ybuf + P.counts), *const read = written + 2;      // of even units, of odd ones
+    if (tid < 4) written[tid] = 0;
+    __syncthreads();
+    auto count = [&](LdsInt *c) __attribute__((always_inline)) {
+        if (lane == 0) asm volatile("ds_add_u32 %0, %1" ::"v"((unsigned)(size_t)c), "v"(1) : "memory");
+    };
+    auto await = [&](LdsInt *c, int n) __attribute__((always_inline)) {
+        while (__builtin_amdgcn_readfirstlane(*(volatile LdsInt *)c) < n) __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+    };
+    // Units follow one another along the columns of a block of rows ("sweep"), so that a unit shares its first columns (all but `step`) with
+    // the one before it; they stay where they are, in a ring of RC columns.
+    const int first = P.SC - P.step;               // a sweep's first columns
+    const int colB = 4 * P.COLP, RCB = colB * P.RC;       // column and ring in bytes
+
+    if (wave >= WK * WR) {
+        // ---- the waves that fetch and convert -------------------------------------------------
+        // One wave to a SIMD, which a unit takes as long as its instructions: whatever stays the same along a sweep is worked out where one
+        // begins, the columns of a unit move the arrays' bases (scalar), and no branch stands between the requests, so that the waits for
+        // a word leave the younger ones on their way.
+        typedef float Row4 __attribute__((ext_vector_type(4)));          // four rows of an image
+        const int ltid = tid - NT;
+        // dzdy words (filter, line, quad), quads fastest: column, image pair, row and filter, a byte each; slab words (column, channel, image
+        // pair, quad) of a unit's last `step` columns: column, image pair, first row and channel (8, 2, 12, 10 bits)
+        unsigned y_at[YT], x_at[XT];
+        int y_lds[YT], x_lds[XT];
+        auto x_row = [](unsigned at) __attribute__((always_inline)) { return (int)(at >> 10 & 0xfff); };
+        constexpr unsigned ABSENT = 0xffffffffu;
+#pragma unroll
+        for (int s = 0; s < YT; ++s) {
+            const int q = ltid + NL * s, k = div32(q, P.dNO), o = q - k * P.NO, line = div32(o, P.dTIQ), m = div32(line, P.dMC), row = 4 * (o - line * P.TIQ), col = line - m * P.MC;
+            y_at[s] = q < P.YW ? (unsigned)(col << 24 | m << 16 | row << 8 | k) : ABSENT;
+            y_lds[s] = (q < P.YW ? k * P.PYW + o : TK * P.PYW) * 16;
+        }
+        struct Word { int col, c, m, row, lds; };
+        // What is needed once a sweep is read from the kernel's arguments there: kept in scalar registers beside the rest, it went through
+        // vector registers (a hundred scalars did)
+        typedef const __attribute__((address_space(4))) WgradBf16Params Args;
+        auto args = []() __attribute__((always_inline)) {
+            Args *a = (Args *)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(a));
+            return a;
+        };
+        auto slab_word = [&](const auto &P, int q) __attribute__((always_inline)) {
+            Word w;
+            w.col = div32(q, Div32{P.dXW1.m, P.dXW1.l}); q -= w.col * P.XW1;
+            const int a = div32(q, Div32{P.dXQ.m, P.dXQ.l});
+            w.row = 4 * (q - a * P.XQ);
+            w.c = div32(a, Div32{P.dNP.m, P.dNP.l});
+            w.m = a - w.c * P.NP;
+            w.lds = 4 * (w.c * P.CHP + w.m * P.MPP + w.row);
+            return w;
+        };
+        const int XW = P.step * P.XW1;
+#pragma unroll
+        for (int s = 0; s < XT; ++s) {
+            const int q = ltid + NL * s;
+            const Word w = slab_word(P, q);
+            x_at[s] = q < XW ? (unsigned)(w.col << 24 | w.m << 22 | w.row << 10 | w.c) : ABSENT;
+            x_lds[s] = w.lds + w.col * colB;
+        }
+        // The unit to request: where it is, and where the arrays' bases are (its first row and column; x: the first row of the slab and the first
+        // column that the unit adds), with the bytes behind them
+        int klim = 0, nch = 0, xch = 0, ych = 0;
+        int jr = div32(uu, P.dCC), jc = uu - jr * P.CC, ib = div32(jr, P.dRB), rb = jr - ib * P.RB;
+        bool new_tile = true, start = true;                 // start: it shares no column with the one before
+        const char *xp = nullptr, *yp = nullptr;
+        bool moved = false;                // the bases are those of the sweep
+        const int xdown = 4 * (P.TI - P.CC * P.MC * P.Sw * P.xsj), ydown = 4 * (P.TI - P.CC * P.MC * P.ysj);       // from behind a sweep to the next block of rows
+        int xleft = 0, yleft = 0, rows = 0, below = 0;        // below: rows that the plane has from the slab's first one on
+        unsigned vy[YT], vx[XT];           // byte offsets of the words, or out of range (images past the last one lie behind the array)
+        auto set_tile = [&](int tt) __attribute__((always_inline)) {
+            const int q = div32(tt, P.dRT), rt = tt - q * P.RT, g = div32(q, P.dKT), kt = q - g * P.KT;
+            const int r_lo = rt * TR, r_hi = min(r_lo + TR, P.R), c_lo = div32(r_lo, P.dT);
+            nch = div32(r_hi - 1, P.dT) - c_lo + 1;
+            klim = min(P.Kg - kt * TK, TK);
+            xch = g * P.Cg + c_lo;
+            ych = g * P.Kg + kt * TK;
+            new_tile = true;
+        };
+        auto bytes_left = [&](long long elements) __attribute__((always_inline)) { return elements > 0x1fffffff ? 0x7fffffff : elements < 0 ? 0 : (int)(4 * elements); };
+        auto words_there = [&]() __attribute__((always_inline)) {
+            Args &P = *args();
+#pragma unroll
+            for (int s = 0; s < YT; ++s) {
+                const int k = y_at[s] & 255, row = y_at[s] >> 8 & 255, m = y_at[s] >> 16 & 255, col = y_at[s] >> 24;
+                vy[s] = ((k < klim) & (LINEAR | (row < rows))) ? 4u * (unsigned)(k * P.ysc + col * P.ysj + row + 2 * m * P.ysn) : SLAB_INVALID;
+            }
+#pragma unroll
+            for (int s = 0; s < XT; ++s) {
+                const int c = x_at[s] & 0x3ff, row = x_row(x_at[s]), m = x_at[s] >> 22 & 3, col = x_at[s] >> 24;
+                // a word begins on a row of the plane or lies wholly above or below it (plan_wgrad_split_shape)
+                const bool ok = (c < nch) & (x_at[s] != ABSENT) & (LINEAR | ((unsigned)(row - (below - P.H)) < (unsigned)P.H));
+                vx[s] = ok ? 4u * (unsigned)(c * P.xsc + col * P.xsj + row + 2 * m * P.xsn) : SLAB_INVALID;
+            }
+        };
+        auto set_sweep = [&]() __attribute__((always_inline)) {
+            const int was_rows = rows, was_below = below;
+            rows = min(P.TI, P.Ho - rb * P.TI);
+            below = P.H + P.XL - rb * P.TI;
+            if (!moved) {
+                Args &P = *args();
+                const int io0 = rb * P.TI, jo0 = jc * P.MC, n0 = ib * 2 * P.NP;
+                const long long xb = (long long)n0 * P.xsn + (long long)xch * P.xsc + (long long)(jo0 * P.Sw - P.Pl + first) * P.xsj + (io0 - P.XL);
+                const long long yb = (long long)n0 * P.ysn + (long long)ych * P.ysc + (long long)jo0 * P.ysj + io0;
+                xp = reinterpret_cast<const char *>(x) + 4 * xb; xleft = bytes_left(P.xtot - xb);
+                yp = reinterpret_cast<const char *>(dzdy) + 4 * yb; yleft = bytes_left(P.ytot - yb);
+            }
+            moved = false;
+            // The words' offsets are those of the sweep before if the same rows of them are there.  LINEAR: rows that are not there meet rows of
+            // dzdy that are zeroed.
+            auto inside = [&](int at) __attribute__((always_inline)) { return (at <= P.H) & (at >= 4 * P.XQ); };
+            if (!new_tile & (LINEAR | ((rows == was_rows) & ((below == was_below) | (inside(below) & inside(was_below)))))) return;
+            new_tile = false;
+            words_there();
+        };
+        // four pairs of samples, a pair of images each; of rows that there are not, `end` and on, zeros
+        auto pack = [&](Row4 a, Row4 b) __attribute__((always_inline)) { return uintx4{pack_bf16x2(a[0], b[0]), pack_bf16x2(a[1], b[1]), pack_bf16x2(a[2], b[2]), pack_bf16x2(a[3], b[3])}; };
+        auto pack_rows = [&](Row4 a, Row4 b, int row, int end) __attribute__((always_inline)) {
+            uintx4 w = pack(a, b);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = row < end - e ? w[e] : 0;
+            return w;
+        };
+        auto put_x = [&](const Row4 (&v)[2], int row, int end, int at, bool there) __attribute__((always_inline)) {
+            const uintx4 w = LINEAR ? pack(v[0], v[1]) : pack_rows(v[0], v[1], row, end);
+            if (there) {
+                unsigned *dst = reinterpret_cast<unsigned *>(xbuf + at);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dst[e] = w[e];
+            }
+        };
+        auto load = [&](__amdgpu_buffer_rsrc_t rs, unsigned off) __attribute__((always_inline)) { return __builtin_bit_cast(Row4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0)); };
+        // What is on its way: one unit, every word of it requested as soon as the same word of the unit before has been written, so
+        // that it has a unit's time to come.
+        Row4 yv[YT][2], xv[XT][2];
+        bool c_start = false;              // of that unit
+        int c_rows = 0, c_below = 0, c_nch = 0, c_j0 = 0, c_xleft = 0;
+        const char *c_xp = nullptr;
+        int ring = first;                  // the column of the ring where those that it adds begin
+        // A sweep's first unit: the columns that a unit otherwise finds in place.  Requested and written here, while the unit before is computed: held
+        // in registers until then they would leave none for units of this size.
+        auto first_columns = [&]() __attribute__((always_inline)) {
+            Args &P = *args();
+            const int extra = first * P.XW1, back = 4 * first * P.xsj;       // words; bytes from them to the columns that the unit adds
+#pragma unroll 1
+            for (int q0 = ltid; q0 - ltid < extra; q0 += 2 * NL) {
+                Row4 v[2][2];
+                Word w[2];
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const int q = q0 + NL * s;
+                    w[s] = slab_word(P, q);
+                    const bool ok = (q < extra) & (w[s].c < c_nch) & ((unsigned)(c_j0 + w[s].col) < (unsigned)P.W) & ((unsigned)(w[s].row - (c_below - P.H)) < (unsigned)P.H);
+                    const unsigned off = ok ? 4u * (unsigned)(w[s].c * P.xsc + w[s].col * P.xsj + w[s].row + 2 * w[s].m * P.xsn) : SLAB_INVALID;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        v[s][i] = load(__builtin_amdgcn_make_buffer_rsrc((void *)(c_xp + 4ll * i * P.xsn - back), 0, max(c_xleft > 0x7fffffff - back ? 0x7fffffff : c_xleft + back - i * 4 * P.xsn, 0), BUFFER_FLAGS), off);
+                }
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const int at = ring - first + w[s].col;
+                    put_x(v[s], w[s].row, c_below, w[s].lds + (at < 0 ? at + P.RC : at) * colB, q0 + NL * s < extra);
+                }
+            }
+        };
+        // put: the unit on its way into the buffers b; get: request the next one
+        auto stage = [&](int b, auto put, auto get) __attribute__((always_inline)) {
+            if constexpr (!LINEAR)
+                if (put && c_start && first > 0) first_columns();
+            if (get && start) set_sweep();
+            __amdgpu_buffer_rsrc_t yrs[2], xrs[2];         // of a pair's images
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                yrs[i] = __builtin_amdgcn_make_buffer_rsrc((void *)(yp + 4ll * i * P.ysn), 0, max(yleft - i * 4 * P.ysn, 0), BUFFER_FLAGS);
+                xrs[i] = __builtin_amdgcn_make_buffer_rsrc((void *)(xp + 4ll * i * P.xsn), 0, max(xleft - i * 4 * P.xsn, 0), BUFFER_FLAGS);
+            }
+            const unsigned ycols = (unsigned)min(max(P.Wo - jc * P.MC, 0), 255) << 24;
+            const int j0 = jc * P.MC * P.Sw - P.Pl + first, xlo = min(max(-j0, 0), 255), xhi = min(max(P.W - j0, xlo), 255);
+            const unsigned xfrom = (unsigned)xlo << 24, xcols = (unsigned)(xhi - xlo) << 24;
+            const int ybuf_b = b * YB, to = ring * colB;
+            const unsigned room = (unsigned)min(P.RC - ring, 255) << 24;          // columns up to the ring's end
+#pragma unroll
+            for (int s = 0; s < YT; ++s) {
+                if (put) {
+                    // rows past the patch's last one are those of the next column: they must not count
+                    *reinterpret_cast<uintx4 *>(ybuf + ybuf_b + y_lds[s]) = pack_rows(yv[s][0], yv[s][1], y_at[s] >> 8 & 255, c_rows);
+                }
+                if (get) {
+                    const unsigned off = y_at[s] < ycols ? vy[s] : SLAB_INVALID;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) yv[s][i] = load(yrs[i], off);
+                }
+                // requests in one order wherever they are made: the waits for a word have to hold for all of them
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int s = 0; s < XT; ++s) {
+                if (put) put_x(xv[s], x_row(x_at[s]), c_below, x_lds[s] + (x_at[s] < room ? to : to - RCB), x_at[s] != ABSENT);
+                if (get) {
+                    const unsigned off = x_at[s] - xfrom < xcols ? vx[s] : SLAB_INVALID;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) xv[s][i] = load(xrs[i], off);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (get) {
+                if (put) {
+                    ring += start ? first + P.step : P.step;
+                    if (ring >= P.RC) ring -= P.RC;
+                }
+                c_start = start; c_rows = LINEAR ? min(P.TI, P.Ho - rb * P.TI) : rows; c_below = below;
+                if constexpr (!LINEAR) { c_nch = nch; c_j0 = j0 - first; c_xp = xp; c_xleft = xleft; }
+                start = false;
+                xp += 4 * P.MC * P.Sw * P.xsj; xleft -= 4 * P.MC * P.Sw * P.xsj;
+                yp += 4 * P.MC * P.ysj; yleft -= 4 * P.MC * P.ysj;
+                if (++jc == P.CC) {
+                    jc = 0; start = !LINEAR; moved = true;
+                    xp += xdown; xleft -= xdown;
+                    yp += ydown; yleft -= ydown;
+                    if (++rb == P.RB) {
+                        rb = 0; moved = false; start = true;
+                        if (++ib == P.IB) { ib = 0; if (++t < P.tiles) set_tile(t); }
+                    }
+                }
+            }
+        };
+        struct Yes { __device__ constexpr operator bool() const { return true; } };
+        struct No { __device__ constexpr operator bool() const { return false; } };
+        set_tile(t);
+        stage(0, No(), Yes());
+        int it = 0;
+        for (; it + 1 < nunits; ++it) {        // unit it is written while unit it - 1 is computed
+            await(read + (it & 1), (it >> 1) * (WK * WR));
+            stage(it & 1, Yes(), Yes());
+            count(written + (it & 1));
+        }
+        await(read + (it & 1), (it >> 1) * (WK * WR));
+        stage(it & 1, Yes(), No());
+        count(written + (it & 1));
+        return;
+    }
+
+    // ---- the computing waves -------------------------------------------------------------------
     const int wk = wave % WK, wr = wave / WK;
-    const int HW = P.H * P.W, HoWo = P.Ho * P.Wo;
-
-    const int vb = wgb_virtual_block(blockIdx.x, gridDim.x);
-    if (vb >= P.nblocks) return;
-    const int tile = vb % P.tiles, chunk = vb / P.tiles;
-    const int u_begin = (int)((long long)P.NU * chunk / P.nchunks);
-    const int u_end = (int)((long long)P.NU * (chunk + 1) / P.nchunks);
-    if (u_begin >= u_end) return;              // cannot happen: nchunks <= NU
-
-    const int rt = tile % P.RT, kt = (tile / P.RT) % P.KT, g = tile / (P.RT * P.KT);
-    const int r_lo = rt * TR;
-    const int r_hi = min(r_lo + TR, P.R);
-    const int c_lo = r_lo / T;
-    const int nch = (r_hi - 1) / T - c_lo + 1;
-    const int klim = min(P.Kg - kt * TK, TK);
-
-    // the arrays from the tile's first filter / channel of an image on; the buffer resources are built per unit at
-    // the unit's image, so offsets stay inside one image (under 2^31 bytes: checked on the host) whatever the batch
-    const size_t ybase = ((size_t)g * P.Kg + (size_t)kt * TK) * HoWo;
-    const size_t xbase = ((size_t)g * P.Cg + c_lo) * HW;
-    const int yleft = (int)(((size_t)P.Ktot * HoWo - ybase) * 4), xleft = (int)(((size_t)P.Ctot * HW - xbase) * 4);
-
-    // ---- what this thread stages, fixed for the whole kernel -----------------------------------
-    int y_k[WGB_YT], y_dc[WGB_YT], y_rg[WGB_YT], y_lds[WGB_YT];
+    floatx16 sum[MK][MR];
+    int c_rt = 0, c_kt = 0, c_g = 0, roff[MR], rcol[MR];      // roff, rcol: where the lane's coefficients are in the slab, in bytes, but for the column; their columns
+    auto set_tile = [&](int tt) __attribute__((always_inline)) {
+        const int q = div32(tt, P.dRT);
+        c_rt = tt - q * P.RT;
+        c_g = div32(q, P.dKT); c_kt = q - c_g * P.KT;
+        const int c_lo = div32(c_rt * TR, P.dT);
 #pragma unroll
-    for (int s = 0; s < WGB_YT; ++s) {
-        const int q = tid + NT * s;
-        const int k = q / P.PW, w = q - k * P.PW;
-        y_k[s] = q < TK * P.PW ? k : -1;
-        y_dc[s] = w / P.TIG;
-        y_rg[s] = w - y_dc[s] * P.TIG;
-        y_lds[s] = k * P.PYW + w;
-    }
-    int x_c[WGB_XT], x_col[WGB_XT], x_rg[WGB_XT], x_lds[WGB_XT];
-#pragma unroll
-    for (int s = 0; s < WGB_XT; ++s) {
-        const int q = tid + NT * s;
-        const int per_c = P.SC * P.TIG;
-        const int c = q / per_c, rem = q - c * per_c;
-        x_c[s] = q < P.NCH * per_c ? c : -1;
-        x_col[s] = rem / P.TIG;
-        x_rg[s] = rem - x_col[s] * P.TIG;
-        x_lds[s] = c * P.CPC + x_col[s] * P.RGP + x_rg[s];
-    }
-
-    // ---- per patch: where the staged elements are in memory (or out of range = zero) -----------
-    unsigned y_vo[WGB_YT];
-    int y_nv[WGB_YT];                 // valid rows of the octet (8 except in a patch's last, partial octet)
-    unsigned x_vo[WGB_XT][NE];
-    bool partial_rows = false;
-    auto setup_patch = [&](int pp) {
-        const int jc = pp / P.RB, rb = pp - jc * P.RB;
-        const int io0 = rb * P.TI, jo0 = jc * P.MC;
-        const int rows = min(P.TI, P.Ho - io0), cols = min(P.MC, P.Wo - jo0);
-        partial_rows = (rows & 7) != 0;
-#pragma unroll
-        for (int s = 0; s < WGB_YT; ++s) {
-            const int nv = min(8, rows - 8 * y_rg[s]);
-            const bool ok = y_k[s] >= 0 && y_k[s] < klim && y_dc[s] < cols && nv > 0;
-            y_nv[s] = ok ? nv : 0;
-            y_vo[s] = ok ? 4u * (unsigned)(io0 + 8 * y_rg[s] + P.Ho * (jo0 + y_dc[s]) + y_k[s] * HoWo) : SLAB_INVALID;
-        }
-        const int i0 = io0 - P.Pt, j0 = jo0 * P.Sw - P.Pl;
-#pragma unroll
-        for (int s = 0; s < WGB_XT; ++s) {
-            const int j = j0 + x_col[s];
-            const int ibase = i0 + 8 * x_rg[s];
-            const bool okc = x_c[s] >= 0 && x_c[s] < nch && j >= 0 && j < P.W;
-            const unsigned base = 4u * (unsigned)(ibase + P.H * j + x_c[s] * HW);
-#pragma unroll
-            for (int e = 0; e < NE; ++e)
-                x_vo[s][e] = (okc && (unsigned)(ibase + e) < (unsigned)P.H) ? base + 4u * e : SLAB_INVALID;
-        }
-    };
-
-    // ---- staging registers ---------------------------------------------------------------------
-    uintx4 y_lo[WGB_YT], y_hi[WGB_YT];
-    float x_dat[WGB_XT][NE];
-    auto issue_loads = [&](int n) {
-        const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(dzdy + ybase + (size_t)n * P.Ktot * HoWo), 0, yleft, BUFFER_FLAGS);
-        const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(x + xbase + (size_t)n * P.Ctot * HW), 0, xleft, BUFFER_FLAGS);
-        const unsigned ysoff = 0u, xsoff = 0u;
-#pragma unroll
-        for (int s = 0; s < WGB_YT; ++s) {
-            if (s * NT < TK * P.PW) {          // block-uniform
-                y_lo[s] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(yrs, y_vo[s], ysoff, 0));
-                y_hi[s] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(yrs, y_vo[s], ysoff + 16u, 0));
+        for (int mr = 0; mr < MR; ++mr) {
+            const int r = c_rt * TR + (wr * MR + mr) * 32 + l32;
+            roff[mr] = rcol[mr] = 0;
+            if (r < P.R) {
+                const int c = div32(r, P.dT), tap = r - c * T, fj = div32(tap, P.dHf);
+                roff[mr] = 4 * ((c - c_lo) * P.CHP + tap - fj * P.Hf + P.XL - P.Pt);
+                rcol[mr] = fj * colB;
             }
         }
-#pragma unroll
-        for (int s = 0; s < WGB_XT; ++s) {
-            if (s * NT < P.NCH * P.SC * P.TIG) {
-#pragma unroll
-                for (int e = 0; e < NE; ++e)
-                    x_dat[s][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xrs, x_vo[s][e], xsoff, 0));
-            }
-        }
-    };
-    auto write_lds = [&](int b) {
-#pragma unroll
-        for (int s = 0; s < WGB_YT; ++s) {
-            if (s * NT < TK * P.PW && y_k[s] >= 0) {
-                uintx4 lo = y_lo[s], hi = y_hi[s];
-                uintx4 v;
-                v.x = pack_bf16x2(__uint_as_float(lo.x), __uint_as_float(lo.y));
-                v.y = pack_bf16x2(__uint_as_float(lo.z), __uint_as_float(lo.w));
-                v.z = pack_bf16x2(__uint_as_float(hi.x), __uint_as_float(hi.y));
-                v.w = pack_bf16x2(__uint_as_float(hi.z), __uint_as_float(hi.w));
-                if (partial_rows) {
-                    // rows past the patch's last one belong to the next column: they must not count
-                    const int nv = y_nv[s];
-                    auto keep = [&](unsigned word, int first) {
-                        return nv >= first + 2 ? word : nv == first + 1 ? (word & 0xffffu) : 0u;
-                    };
-                    v.x = keep(v.x, 0); v.y = keep(v.y, 2); v.z = keep(v.z, 4); v.w = keep(v.w, 6);
-                }
-                ybuf[b * YS + y_lds[s]] = v;
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < WGB_XT; ++s) {
-            if (s * NT < P.NCH * P.SC * P.TIG && x_c[s] >= 0) {
-#pragma unroll
-                for (int fi = 0; fi < HF; ++fi) {
-                    uintx4 v;
-                    v.x = pack_bf16x2(x_dat[s][fi + 0], x_dat[s][fi + 1]);
-                    v.y = pack_bf16x2(x_dat[s][fi + 2], x_dat[s][fi + 3]);
-                    v.z = pack_bf16x2(x_dat[s][fi + 4], x_dat[s][fi + 5]);
-                    v.w = pack_bf16x2(x_dat[s][fi + 6], x_dat[s][fi + 7]);
-                    xbuf[b * XS + x_lds[s] + fi * P.CPF] = v;
-                }
-            }
-        }
-    };
-
-    // ---- compute side --------------------------------------------------------------------------
-    int roff[MR];
-#pragma unroll
-    for (int mr = 0; mr < MR; ++mr) {
-        const int r = r_lo + (wr * MR + mr) * 32 + l32;
-        int o = 0;
-        if (r < P.R) {
-            const int c = r / T;
-            const int tap = r - c * T;
-            const int fj = tap / P.Hf;
-            const int fi = tap - fj * P.Hf;
-            o = (c - c_lo) * P.CPC + fi * P.CPF + fj * P.RGP;
-        }
-        roff[mr] = o + half * P.Sw * P.RGP;           // the upper half-wave takes the next column
-    }
-    floatx16 acc[MK][MR];
-#pragma unroll
-    for (int mk = 0; mk < MK; ++mk)
-#pragma unroll
-        for (int mr = 0; mr < MR; ++mr)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mk][mr][v] = 0.f;
-    const int aoff = (wk * MK * 32 + l32) * P.PYW + half * P.TIG;
-    const int a_pair = P.TIG;                         // from the end of a column pair to the next pair
-    const int x_pair = 2 * P.Sw * P.RGP - P.TIG;
-    auto compute = [&](int b) {
-        int ya[MK], xr[MR];
-#pragma unroll
-        for (int mk = 0; mk < MK; ++mk) ya[mk] = b * YS + aoff + mk * 32 * P.PYW;
-#pragma unroll
-        for (int mr = 0; mr < MR; ++mr) xr[mr] = b * XS + roff[mr];
-        const int nsteps = (P.MC >> 1) * P.TIG;
-        bf16x8 a0[MK], b0[MR], a1[MK], b1[MR];
-        int rg = 0;
-        auto fetch = [&](bf16x8 *a, bf16x8 *bq) {
-#pragma unroll
-            for (int mk = 0; mk < MK; ++mk) a[mk] = __builtin_bit_cast(bf16x8, ybuf[ya[mk]]);
-#pragma unroll
-            for (int mr = 0; mr < MR; ++mr) bq[mr] = __builtin_bit_cast(bf16x8, xbuf[xr[mr]]);
-            // advance to the next step: next octet, or the first octet of the next column pair
-            const bool wrap = ++rg == P.TIG;
-            if (wrap) rg = 0;
-            const int da = wrap ? 1 + a_pair : 1, dx = wrap ? 1 + x_pair : 1;
-#pragma unroll
-            for (int mk = 0; mk < MK; ++mk) ya[mk] += da;
-#pragma unroll
-            for (int mr = 0; mr < MR; ++mr) xr[mr] += dx;
-        };
-        auto mma = [&](const bf16x8 *a, const bf16x8 *bq) {
-#pragma unroll
-            for (int mk = 0; mk < MK; ++mk)
-#pragma unroll
-                for (int mr = 0; mr < MR; ++mr)
-                    acc[mk][mr] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mk], bq[mr], acc[mk][mr], 0, 0, 0);
-        };
-        // no branches inside the loop, so that the waits inserted for the LDS reads are exact
-        fetch(a0, b0);
-        for (int s = 2; s < nsteps; s += 2) {        // steps s-2 and s-1, with s-1 and s in flight
-            fetch(a1, b1);
-            __builtin_amdgcn_sched_barrier(0);
-            mma(a0, b0);
-            __builtin_amdgcn_sched_barrier(0);
-            fetch(a0, b0);
-            __builtin_amdgcn_sched_barrier(0);
-            mma(a1, b1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (nsteps & 1) {
-            mma(a0, b0);
-        } else {
-            fetch(a1, b1);
-            __builtin_amdgcn_sched_barrier(0);
-            mma(a0, b0);
-            mma(a1, b1);
-        }
-    };
-
-    // ---- the block's range of units: unit = image + N * patch ----------------------------------
-    int pp = u_begin / P.N, n = u_begin - pp * P.N;
-    setup_patch(pp);
-    issue_loads(n);
-    write_lds(0);
-    const int nunits = u_end - u_begin;
-    for (int it = 0; it < nunits; ++it) {
-        lds_barrier();                 // buffer it&1 is complete, and the other one is free
-        const bool more = it + 1 < nunits;
-        if (more) {
-            if (++n == P.N) { n = 0; ++pp; setup_patch(pp); }
-            issue_loads(n);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        compute(it & 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (more) write_lds((it + 1) & 1);
-    }
-
-    // lane holds coefficient r (lane&31) of each r tile and 16 filters of each filter tile
-    const bool direct = P.nchunks == 1;
-    float *dst = direct ? out : part + (size_t)vb * (TK * TR);
-#pragma unroll
-    for (int mr = 0; mr < MR; ++mr) {
-        const int rl = (wr * MR + mr) * 32 + l32;
-        const int r = r_lo + rl;
 #pragma unroll
         for (int mk = 0; mk < MK; ++mk)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int kl = (wk * MK + mk) * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
-                if (direct) {
-                    if (r < P.R && kl < klim) dst[(size_t)(g * P.Kg + kt * TK + kl) * P.R + r] = acc[mk][mr][v];
-                } else {
-                    dst[kl * TR + rl] = acc[mk][mr][v];
-                }
-            }
+            for (int mr = 0; mr < MR; ++mr)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sum[mk][mr][v] = 0.f;
+    };
+    // Lane o: where octet o of a unit starts in the slab, in bytes: its column and the rest apart.  An octet is (line, rows 4*q on),
+    // line = (image pair, column).  Read across lanes: a table in LDS would make every step wait for all of its operands.
+    int oct_col, oct_at;
+    {
+        const int line = div32(lane, P.dTIQ), q = lane - line * P.TIQ, m = div32(line, P.dMC), dc = line - m * P.MC;
+        oct_col = dc * P.Sw * colB;
+        oct_at = 4 * (m * P.MPP + 4 * q);
     }
-}
-
-// Sum the nchunks pieces of every tile and write the tile.  The order of the additions is
-// fixed: piece i goes to partial sum i mod 8, the partial sums are added as a balanced tree.
-// blockIdx.x = tile; one block = 64 results x 8 partial sums.
-template <int TK, int TR>
-__global__ __launch_bounds__(512) void wgrad_bf16_fixup_kernel(WgradBfParams P, const float *__restrict__ part,
-                                                               float *__restrict__ out) {
-    const int t = blockIdx.x;
-    const int rt = t % P.RT, kt = (t / P.RT) % P.KT, g = t / (P.RT * P.KT);
-    const int klim = min(P.Kg - kt * TK, TK);
-    __shared__ float red[8][64];
-    const int el = threadIdx.x & 63, pg = threadIdx.x >> 6;
-    for (int e0 = blockIdx.y * 64; e0 < TK * TR; e0 += gridDim.y * 64) {
-        const int e = e0 + el;
-        float acc = 0.f;
-        for (int i = pg; i < P.nchunks; i += 8) acc += part[((size_t)i * P.tiles + t) * (TK * TR) + e];
-        red[pg][el] = acc;
-        __syncthreads();
-        if (pg == 0) {
-            const int kloc = e / TR, rl = e - kloc * TR;
-            const int r = rt * TR + rl;
-            if (kloc < klim && r < P.R)
-                out[(size_t)(g * P.Kg + kt * TK + kloc) * P.R + r] =
-                    ((red[0][el] + red[1][el]) + (red[2][el] + red[3][el])) +
-                    ((red[4][el] + red[5][el]) + (red[6][el] + red[7][el]));
+    bf16x8 oa[MK], ob[MR];
+    const int aoff = ((wk * MK * 32 + l32) * P.PYW + half) * 16, amk = 32 * P.PYW * 16;
+    const char *ya = ybuf;            // the lane's octets of the next operands
+    const char *xa[MR];
+    int ring = 0;                     // the unit's first column, in bytes
+    auto load_a = [&](int mk) __attribute__((always_inline)) { oa[mk] = *reinterpret_cast<const bf16x8 *>(ya + mk * amk); };
+    auto load_b = [&](int mr) __attribute__((always_inline)) {
+        const unsigned *p = reinterpret_cast<const unsigned *>(xa[mr]);
+        const uintx4 v = {p[0], p[1], p[2], p[3]};
+        ob[mr] = __builtin_bit_cast(bf16x8, v);
+    };
+    auto mma = [&](int mk, int mr) __attribute__((always_inline)) {
+        sum[mk][mr] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(oa[mk], ob[mr], sum[mk][mr], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const int NS = P.NO >> 1;
+    auto wrap = [&](int at) __attribute__((always_inline)) { return (int)min((unsigned)at, (unsigned)(at - RCB)); };
+    int col[MR];
+    // operands of step `s` of the unit in buffer b
+    auto begin = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mr = 0; mr < MR; ++mr) col[mr] = wrap(ring + rcol[mr]);
+        ya = ybuf + b * YB + aoff;
+    };
+    auto octet = [&](int s) __attribute__((always_inline)) {
+        const int c0 = __builtin_amdgcn_readlane(oct_col, 2 * s), c1 = __builtin_amdgcn_readlane(oct_col, 2 * s + 1);
+        const int a0 = __builtin_amdgcn_readlane(oct_at, 2 * s), a1 = __builtin_amdgcn_readlane(oct_at, 2 * s + 1);
+#pragma unroll
+        for (int mr = 0; mr < MR; ++mr) xa[mr] = xbuf + (roff[mr] + wrap(col[mr] + (half ? c1 : c0)) + (half ? a1 : a0));
+    };
+    auto prime = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk) load_a(mk);
+#pragma unroll
+        for (int mr = 0; mr < MR; ++mr) load_b(mr);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // every operand is read for the next step as soon as its last product is issued
+    auto step = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int mr = 0; mr < MR; ++mr) {
+#pragma unroll
+            for (int mk = 0; mk < MK; ++mk) {
+                mma(mk, mr);
+                if (mr == MR - 1) load_a(mk);
+            }
+            load_b(mr);
         }
-        __syncthreads();
+    };
+    // a tile that this block computed alone; a lane holds one coefficient of 16 filters of each of its MK x MR x 32
+    auto store_tile = [&]() __attribute__((always_inline)) {
+        const int klim = min(P.Kg - c_kt * TK, TK), r0 = c_rt * TR + wr * MR * 32 + l32;
+        bool odd = false;
+#pragma unroll
+        for (int mr = 0; mr < MR; ++mr) {
+            const int r = r0 + mr * 32;
+#pragma unroll
+            for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int kl = (wk * MK + mk) * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
+                    if (kl >= klim || r >= P.R) continue;
+                    const float val = sum[mk][mr][v];
+                    odd |= not_finite(val);
+                    out[(size_t)(c_g * P.Kg + c_kt * TK + kl) * P.R + r] = val;
+                }
+        }
+        if (!__any(odd)) return;
+        // the wave sums again what is not finite of its part, from the operands as they are
+        __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);         // this wave reads back what it stored
+#pragma unroll 1
+        for (int e = 0; e < MK * MR * 16; ++e) {
+            const int mr = e / (MK * 16), r = r0 + mr * 32, kl = (wk * MK + e / 16 - mr * MK) * 32 + (e % 16 >> 2) * 8 + half * 4 + (e & 3), k = c_kt * TK + kl;
+            const bool there = kl < klim && r < P.R;
+            float *o = out + (there ? (size_t)(c_g * P.Kg + k) * P.R + r : 0);
+            const bool again = there && not_finite(*(volatile float *)o);
+            if (!__any(again)) continue;
+            const float val = wave_sum_again(P, x, dzdy, c_g, k, r, again);
+            if (again) *o = val;
+        }
+    };
+    auto store_partial = [&](int slot) __attribute__((always_inline)) {
+        float *dst = part + (size_t)slot * (TK * TR) + wr * MR * 32 + l32;
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk)
+#pragma unroll
+            for (int mr = 0; mr < MR; ++mr)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) dst[((wk * MK + mk) * 32 + (v >> 2) * 8 + half * 4 + (v & 3)) * TR + mr * 32] = sum[mk][mr][v];
+    };
+    bool first_segment = true;
+    for (int it = 0; it < nunits;) {
+        // one segment: the units of one tile in a row
+        const int m = min(NU - uu, nunits - it);
+        set_tile(t);
+        int jc = uu - div32(uu, P.dCC) * P.CC;
+        auto enter = [&](int u, int i) __attribute__((always_inline)) {
+            // the ring: `step` columns on from the unit before, and behind its columns where it is another sweep's
+            if (i > 0) ring += (u == 0 || jc == 0 ? P.SC : P.step) * colB;
+            if (ring >= RCB) ring -= RCB;
+            if (++jc == P.CC) jc = 0;
+            begin(i & 1);
+            octet(0);
+        };
+        await(written + (it & 1), ((it >> 1) + 1) * WGS_STAGE_WAVES);
+        enter(0, it);
+        prime();
+        for (int u = 0; u < m; ++u, ++it) {
+            for (int s = 1; s < NS; ++s) {
+                ya += 32;
+                octet(s);
+                step();
+            }
+            // every operand of this unit is in registers or on its way there
+            count(read + (it & 1));
+            if (u + 1 < m) {
+                await(written + ((it + 1) & 1), (((it + 1) >> 1) + 1) * WGS_STAGE_WAVES);
+                enter(u + 1, it + 1);
+            }
+            step();                    // the segment's last one reads something again, for nothing
+        }
+#pragma unroll
+        for (int mk = 0; mk < MK; ++mk) asm volatile("" ::"v"(oa[mk]));
+#pragma unroll
+        for (int mr = 0; mr < MR; ++mr) asm volatile("" ::"v"(ob[mr]));
+        if (m == NU) store_tile();
+        else store_partial(2 * vb + (first_segment ? 0 : 1));
+        first_segment = false;
+        ++t; uu = 0;
     }
 }
 

@@ -51,6 +51,7 @@ struct WgradSplitParams : WgradParams {
     int step;                        // columns that a unit adds to the one before it in the same sweep (SC: all of them)
     int YW, XW1;                     // staged words: dzdy per unit, slab per column (NCH channels)
     int counts;                      // byte offset of four counters in LDS
+    int XL;                          // rows of the slab before the row of x that meets filter row Pt (kern_wgrad_bf16.h: the next multiple of 4, else Pt)
     Div32 dRB, dCC, dXW1, dXQ, dNPH, dNP;
 };
 
@@ -116,6 +117,23 @@ __device__ inline float wgrad_plain_part(const WgradSplitParams &P, const float 
 
 // How many of `threads` (a power of two) sum one of m results together, a power of two.
 __device__ inline int repair_parts(int threads, int m) { return 1 << (31 - __clz(threads / m)); }
+
+// By a wave: the coefficients (g, k, r) of the lanes that ask for it.  The lanes are shared out among them.
+__device__ __attribute__((always_inline)) inline float wave_sum_again(const WgradSplitParams &P, const float *x, const float *dzdy, int g, int k, int r, bool again) {
+    const int lane = threadIdx.x & 63;
+    const unsigned long long which = __ballot(again);
+    // lane's coefficient is that of the j-th lane that has one
+    const int m = __popcll(which), parts = repair_parts(64, m), j = lane / parts, p = lane - j * parts;
+    unsigned long long left = which;
+    for (int i = 0; i < j; ++i) left &= left - 1;
+    const int from = left ? __ffsll((long long)left) - 1 : 0;
+    const unsigned long long together = (parts == 64 ? ~0ull : (1ull << parts) - 1) << (j * parts);
+    float val = wgrad_plain_part(P, x, dzdy, g, __shfl(k, from), __shfl(r, from), p, parts, j < m,
+                                 [&](bool nan) __attribute__((always_inline)) { return (__ballot(nan) & together) != 0; });
+    for (int h = parts >> 1; h > 0; h >>= 1) val += __shfl_xor(val, h);
+    const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(which >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)which, 0u));
+    return __shfl(val, rank * parts);
+}
 
 // In the fix-up pass: of n stored results, where(i, &k, &r) says which and whether there is one, those that are not finite are summed
 // again by the block's 512 threads, shared out evenly.  27x27x96, 5x5x48x256 in two groups, 128 images (0.31 ms): one NaN in x 0.5 ms at most
@@ -500,19 +518,8 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_spl
             const bool there = kl < klim && r < P.R;
             float *o = out + (there ? (size_t)(c_g * P.Kg + k) * P.R + r : 0);
             const bool again = there && not_finite(*(volatile float *)o);
-            const unsigned long long which = __ballot(again);
-            if (which == 0) continue;
-            // the wave's lanes, shared out among the coefficients: lane's coefficient is that of the j-th lane that has one
-            const int m = __popcll(which), parts = repair_parts(64, m), j = lane / parts, p = lane - j * parts;
-            unsigned long long left = which;
-            for (int i = 0; i < j; ++i) left &= left - 1;
-            const int from = left ? __ffsll((long long)left) - 1 : 0;
-            const unsigned long long together = (parts == 64 ? ~0ull : (1ull << parts) - 1) << (j * parts);
-            float val = wgrad_plain_part(P, x, dzdy, c_g, __shfl(k, from), __shfl(r, from), p, parts, j < m,
-                                         [&](bool nan) __attribute__((always_inline)) { return (__ballot(nan) & together) != 0; });
-            for (int h = parts >> 1; h > 0; h >>= 1) val += __shfl_xor(val, h);
-            const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(which >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)which, 0u));
-            val = __shfl(val, rank * parts) + rb;
+            if (!__any(again)) continue;
+            const float val = wave_sum_again(P, x, dzdy, c_g, k, r, again) + rb;
             if (again) *o = P.relu ? fmaxf(val, 0.f) : val;
         }
     };

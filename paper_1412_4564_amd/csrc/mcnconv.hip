@@ -112,9 +112,8 @@ struct PlanEntry {
     // filter derivative
     bool wg_ok;
     WgradPlan wg;
-    bool wgb_ok;               // on the bf16 kernel (wg is then not set)
-    WgradBfPlan wgb;
-    bool wgs_ok;               // on the three-plane kernel
+    bool wgs_ok;               // on the bf16 matrix core (wgrad_split_kernel)
+    bool wgb_ok;               // there, with operands rounded to bf16 (wg is then not set)
     WgradSplitPlan wgs;
     // fc
     WgradPlan fc_fwd;
@@ -187,7 +186,9 @@ void plan_backward_filter(PlanEntry &e, const mcn_conv_desc *d, const Geom &g) {
     const int ncu = compute_units();
     const ConvView v = forward_view(g);
     e.wg_ok = e.wgs_ok = false;
-    e.wgb_ok = on && d->precision == MCN_PREC_BF16 && plan_wgrad_bf16(v, ncu, &e.wgb);
+    // vertical stride 1, filters of few rows, more than 32 filters: others compute in fp32 under this flag too
+    e.wgb_ok = on && d->precision == MCN_PREC_BF16 && v.Sh == 1 && v.Hf <= WGB_MAX_HF && v.Kg > 32 && plan_wgrad_split(v, ncu, nullptr, &e.wgs, 1);
+    if (e.wgb_ok) e.wgs_ok = true;
     if (!on || e.wgb_ok) return;
     e.wg_ok = (pairs && plan_wgrad(v, ncu, &e.wg, true)) || plan_wgrad(v, ncu, &e.wg);
     e.wgs_ok = pairs && !(e.wg_ok && e.wg.wino) && plan_wgrad_split(v, ncu, e.wg_ok ? &e.wg : nullptr, &e.wgs);
@@ -488,82 +489,61 @@ int launch_wgrad(const WgradPlan &pl, const float *x, const float *dzdy, const f
     }
 }
 
-// fp32 operands in three bf16 planes (kern_wgrad_split.h)
-template <int WK, int WR, int MK, int YT, int XT, bool LINEAR>
+// on the bf16 matrix core: fp32 operands in three planes (kern_wgrad_split.h), or rounded to bf16 (kern_wgrad_bf16.h)
+template <int SHAPE, int WK, int WR, int MK, int MR, int YT, int XT, bool LINEAR>
 int launch_wgrad_split_inst(const WgradSplitPlan &pl, const float *x, const float *dzdy, const float *rbias, float *out, float *part,
                             hipStream_t s, int relu) {
-    WgradSplitParams P = pl.P;
+    constexpr WgradSplitTile TILE = WGS_TILES[SHAPE];
+    static_assert(TILE.TK == WK * MK * 32 && TILE.TR == WR * MR * 32 && (TILE.planes == 1 || MR == 1), "the planner's tile");
+    WgradBf16Params P;
+    (WgradSplitParams &)P = pl.P;
     P.relu = relu;
-    auto kern = wgrad_split_kernel<WK, WR, MK, YT, XT, LINEAR>;
+    const void *kern;
+    if constexpr (TILE.planes == 1) kern = (const void *)wgrad_bf16_kernel<WK, WR, MK, MR, YT, XT, LINEAR>;
+    else kern = (const void *)wgrad_split_kernel<WK, WR, MK, YT, XT, LINEAR>;
     if (pl.lds_bytes > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)pl.lds_bytes);
+        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_bytes);
         if (e != hipSuccess) { g_last_hip_error = (int)e; return MCN_HIP_ERROR; }
     }
-    hipLaunchKernelGGL(kern, dim3(P.nchunks > 0 ? wg_chunk_grid(P.nblocks) : P.nblocks), dim3(64 * (WK * WR + WGS_STAGE_WAVES)), pl.lds_bytes, s, P,
-                       x, dzdy, rbias, out, part);
+    const dim3 grid(P.nchunks > 0 ? wg_chunk_grid(P.nblocks) : P.nblocks), block(64 * (WK * WR + WGS_STAGE_WAVES));
+    if constexpr (TILE.planes == 1) {
+        P.walk = P.nchunks > 0 ? make_sk_walk(P.NU, P.nchunks, P.NU) : make_sk_walk((long long)P.tiles * P.NU, P.nblocks, P.NU);
+        P.dNO = make_div32(P.NO); P.dTIQ = make_div32(P.TIQ); P.dMC = make_div32(P.MC); P.dT = make_div32(P.Hf * P.Wf); P.dHf = make_div32(P.Hf);
+        P.dCC = make_div32(P.CC); P.dRB = make_div32(P.RB); P.dTiles = make_div32(P.tiles); P.dKT = make_div32(P.KT); P.dRT = make_div32(P.RT);
+        hipLaunchKernelGGL((wgrad_bf16_kernel<WK, WR, MK, MR, YT, XT, LINEAR>), grid, block, pl.lds_bytes, s, P, x, dzdy, out, part);
+    } else
+        hipLaunchKernelGGL((wgrad_split_kernel<WK, WR, MK, YT, XT, LINEAR>), grid, block, pl.lds_bytes, s, (const WgradSplitParams &)P, x, dzdy, rbias, out, part);
     int st = check_launch();
     if (st || P.nblocks < 2 || P.nchunks == 1) return st;
-    return launch_wgrad_fixup<WK * MK * 32, WR * 32>(P, part, rbias, out, s, RepairSums{P, x, dzdy});
+    return launch_wgrad_fixup<TILE.TK, TILE.TR>(P, part, rbias, out, s, RepairSums{(const WgradSplitParams &)P, x, dzdy});
 }
 
-template <int WK, int WR, int MK, int YT, int YTL, int XTL>
+template <int SHAPE, int WK, int WR, int MK, int MR>
 int launch_wgrad_split_shape(const WgradSplitPlan &pl, const float *x, const float *dzdy, const float *rbias, float *out, float *part,
                              hipStream_t s, int relu) {
-    if (pl.linear) return launch_wgrad_split_inst<WK, WR, MK, YTL, XTL, true>(pl, x, dzdy, rbias, out, part, s, relu);
-    return pl.P.step * pl.P.XW1 <= 64 * WGS_STAGE_WAVES ? launch_wgrad_split_inst<WK, WR, MK, YT, 1, false>(pl, x, dzdy, rbias, out, part, s, relu)
-                                                        : launch_wgrad_split_inst<WK, WR, MK, YT, 2, false>(pl, x, dzdy, rbias, out, part, s, relu);
+    constexpr WgradSplitTile T = WGS_TILES[SHAPE];
+    if (pl.linear) {
+        if constexpr (T.YTL > 0) return launch_wgrad_split_inst<SHAPE, WK, WR, MK, MR, T.YTL, T.XTL, true>(pl, x, dzdy, rbias, out, part, s, relu);
+        return MCN_BAD_ARG;
+    }
+    // half as many octets of x where a unit has no more
+    return pl.P.step * pl.P.XW1 <= 64 * WGS_STAGE_WAVES * (T.XT / 2) ? launch_wgrad_split_inst<SHAPE, WK, WR, MK, MR, T.YT, T.XT / 2, false>(pl, x, dzdy, rbias, out, part, s, relu)
+                                                                     : launch_wgrad_split_inst<SHAPE, WK, WR, MK, MR, T.YT, T.XT, false>(pl, x, dzdy, rbias, out, part, s, relu);
 }
 
 int launch_wgrad_split(const WgradSplitPlan &pl, const float *x, const float *dzdy, const float *rbias, float *out, void *ws,
                        hipStream_t s, int relu = 0) {
     float *part = (float *)ws;
     switch (pl.shape) {
-        case WGS_128x128: return launch_wgrad_split_shape<2, 4, 2, 4, 3, 3>(pl, x, dzdy, rbias, out, part, s, relu);
-        case WGS_64x256: return launch_wgrad_split_shape<1, 8, 2, 4, 1, 4>(pl, x, dzdy, rbias, out, part, s, relu);
-        case WGS_32x256: return launch_wgrad_split_shape<1, 8, 1, 2, 1, 4>(pl, x, dzdy, rbias, out, part, s, relu);
-        default: return MCN_BAD_ARG;
-    }
-}
-
-template <int WK, int WR, int MK, int MR, int HF>
-int launch_wgrad_bf16_inst(const WgradBfPlan &pl, const float *x, const float *dzdy, float *out, float *part,
-                           hipStream_t s) {
-    auto kern = wgrad_bf16_kernel<WK, WR, MK, MR, HF>;
-    if (pl.lds_bytes > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)pl.lds_bytes);
-        if (e != hipSuccess) { g_last_hip_error = (int)e; return MCN_HIP_ERROR; }
-    }
-    hipLaunchKernelGGL(kern, dim3(wgb_grid(pl.P.nblocks)), dim3(64 * WK * WR), pl.lds_bytes, s, pl.P, x, dzdy, out, part);
-    int st = check_launch();
-    if (st || pl.P.nchunks < 2) return st;
-    constexpr int TK = WK * MK * 32, TR = WR * MR * 32;
-    int fy = 2048 / pl.P.tiles;          // about 2048 blocks in all
-    if (fy < 1) fy = 1;
-    if (fy > TK * TR / 64) fy = TK * TR / 64;
-    hipLaunchKernelGGL((wgrad_bf16_fixup_kernel<TK, TR>), dim3(pl.P.tiles, fy), dim3(512), 0, s, pl.P, part, out);
-    return check_launch();
-}
-
-template <int WK, int WR, int MK, int MR>
-int launch_wgrad_bf16_shape(const WgradBfPlan &pl, const float *x, const float *dzdy, float *out, float *part,
-                            hipStream_t s) {
-    switch (pl.P.Hf) {
-        case 1: return launch_wgrad_bf16_inst<WK, WR, MK, MR, 1>(pl, x, dzdy, out, part, s);
-        case 2: return launch_wgrad_bf16_inst<WK, WR, MK, MR, 2>(pl, x, dzdy, out, part, s);
-        case 3: return launch_wgrad_bf16_inst<WK, WR, MK, MR, 3>(pl, x, dzdy, out, part, s);
-        case 4: return launch_wgrad_bf16_inst<WK, WR, MK, MR, 4>(pl, x, dzdy, out, part, s);
-        case 5: return launch_wgrad_bf16_inst<WK, WR, MK, MR, 5>(pl, x, dzdy, out, part, s);
-        default: return MCN_BAD_ARG;
-    }
-}
-
-int launch_wgrad_bf16(const WgradBfPlan &pl, const float *x, const float *dzdy, float *out, void *ws, hipStream_t s) {
-    float *part = (float *)ws;
-    switch (pl.shape) {
-        case WGB_128x256: return launch_wgrad_bf16_shape<2, 4, 2, 2>(pl, x, dzdy, out, part, s);
-        case WGB_64x256: return launch_wgrad_bf16_shape<2, 4, 1, 2>(pl, x, dzdy, out, part, s);
+        case WGS_128x128: return launch_wgrad_split_shape<WGS_128x128, 2, 4, 2, 1>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGS_64x256: return launch_wgrad_split_shape<WGS_64x256, 1, 8, 2, 1>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGS_32x256: return launch_wgrad_split_shape<WGS_32x256, 1, 8, 1, 1>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGB_128x384: return launch_wgrad_split_shape<WGB_128x384, 2, 4, 2, 3>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGB_128x256: return launch_wgrad_split_shape<WGB_128x256, 2, 4, 2, 2>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGB_128x128: return launch_wgrad_split_shape<WGB_128x128, 2, 4, 2, 1>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGB_64x768: return launch_wgrad_split_shape<WGB_64x768, 1, 8, 2, 3>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGB_64x512: return launch_wgrad_split_shape<WGB_64x512, 1, 8, 2, 2>(pl, x, dzdy, rbias, out, part, s, relu);
+        case WGB_64x256: return launch_wgrad_split_shape<WGB_64x256, 1, 8, 2, 1>(pl, x, dzdy, rbias, out, part, s, relu);
         default: return MCN_BAD_ARG;
     }
 }
@@ -588,7 +568,6 @@ size_t workspace_bytes(const mcn_conv_desc *d, const Geom &g, int op) {
         }
         case MCN_OP_BACKWARD_FILTER:
             if (e->fc) return igemm_ws_bytes(e->fc_wg);
-            if (e->wgb_ok) return e->wgb.partial_floats * sizeof(float);
             if (e->wgs_ok) return e->wgs.partial_floats * sizeof(float);
             return e->wg_ok ? e->wg.partial_floats * sizeof(float) : 0;
         case MCN_OP_BACKWARD_FILTER_BIAS: {
@@ -661,7 +640,6 @@ int run_backward_filter(const mcn_conv_desc *desc, const Geom &g, const float *x
     if (ws_bytes < need || (!ws && need)) return MCN_WORKSPACE_TOO_SMALL;
     const PlanEntry *pe = plans_for(desc, g, MCN_OP_BACKWARD_FILTER);
     if (pe->fc) return launch_igemm(pe->fc_wg, x, dzdy, nullptr, dzdw, ws, s);
-    if (pe->wgb_ok) return launch_wgrad_bf16(pe->wgb, x, dzdy, dzdw, ws, s);
     if (pe->wgs_ok) return launch_wgrad_split(pe->wgs, x, dzdy, nullptr, dzdw, ws, s);
     if (pe->wg_ok) return launch_wgrad(pe->wg, x, dzdy, nullptr, dzdw, ws, s);
     const int total = (int)numel_w(g);

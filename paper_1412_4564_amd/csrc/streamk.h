@@ -31,6 +31,20 @@ MCN_HOST_DEVICE inline SkSplit sk_split(long long total, int nblocks) {
 MCN_HOST_DEVICE inline long long sk_begin(const SkSplit &s, int vb) {
     return s.q * vb + (long long)(s.r * (unsigned)vb / s.n);
 }
+// The same split made on the host: sk_begin and the tile of a unit without a division.  A 64-bit division is some 150 scalar instructions
+// one after another, and a block that does four of them before its first load starts 2 us later.
+struct SkWalk {
+    long long q;
+    unsigned r;
+    Div32 n, NU;                    // r * vb < n^2 < 2^31
+};
+inline SkWalk make_sk_walk(long long total, int nblocks, int NU) {
+    const SkSplit s = sk_split(total, nblocks);
+    return SkWalk{s.q, s.r, make_div32(nblocks), make_div32(NU)};
+}
+MCN_HOST_DEVICE inline long long sk_begin(const SkWalk &w, int vb) { return w.q * vb + div32((int)(w.r * (unsigned)vb), w.n); }
+MCN_HOST_DEVICE inline int sk_tile(const SkWalk &w, long long unit, int NU) { return unit <= 0x7fffffff ? div32((int)unit, w.NU) : (int)(unit / NU); }
+
 // Rank of virtual block vb among the nshare sharing blocks (in virtual order), or -1; and its inverse.  With
 // nshare < nblocks (both multiples of 8) the sharing blocks are hardware ids 0 .. nshare-1, i.e. the first
 // nshare/8 virtual blocks of each XCD's run of nblocks/8.

@@ -425,6 +425,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     P.nshare = P.nblocks;
     if (two && P.own >= 1 && (int64_t)P.own * P.nblocks != tiles && P.nblocks == resident && P.nblocks % 16 == 0)
         P.nshare = P.nblocks / 2;
+    P.walk = make_sk_walk((tiles - (int64_t)P.own * P.nblocks) * (P.NU / (planes == 3 && wino_Ho ? 4 : 1)), P.nshare, P.NU);
     P.OH = v.OH; P.OW = v.OW; P.oi0 = v.oi0; P.osi = v.osi; P.oj0 = v.oj0; P.osj = v.osj;
     P.mD = v.mD; P.mPt = v.mPt; P.mPl = v.mPl;
     P.wino_Ho = wino_Ho;
@@ -749,6 +750,7 @@ inline bool plan_wgrad(const ConvView &v, int n_cu, WgradPlan *pl, bool wino = f
     }
     // chunk weights (WgradParams::n_first): uneven only when two blocks share each compute unit and every
     // chunk has units to spare
+    P.walk = make_sk_walk(P.nchunks > 0 ? NU : total, P.nchunks > 0 ? P.nchunks : P.nblocks, P.NU);
     P.n_first = n_cu; P.w_first = 1; P.w_later = 1;
     if (P.nchunks > 0 && bestOcc == 2 && P.nblocks > n_cu && NU / P.nchunks >= 16) {
         P.w_first = 3; P.w_later = 2;      // measured on layers 4a/4b: 11:9 -1.5 %, 3:2 -2.2 %, 13:7 +1 %
@@ -981,6 +983,7 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
     P.dXW1 = make_div32(P.XW1); P.dXQ = make_div32(P.XQ); P.dNPH = make_div32(P.NPH); P.dNP = make_div32(P.NP);
     const int64_t total = tiles * NU;
     P.nblocks = P.nchunks > 0 ? (int)tiles * P.nchunks : (int)(total < P.nblocks ? total : P.nblocks);
+    P.walk = make_sk_walk(P.nchunks > 0 ? NU : total, P.nchunks > 0 ? P.nchunks : P.nblocks, P.NU);
     pl->shape = shape; pl->TK = TK; pl->TR = TR;
     pl->linear = linear;
     pl->NCH = NCH;

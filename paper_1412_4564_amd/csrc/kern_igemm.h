@@ -146,6 +146,7 @@ struct IgemmParams {
     // id) gets more of the matrix core and would finish some 10 % earlier on equal work; it takes the left-over
     // units, the other only its own tiles, and half as many partial tiles go through the workspace.
     int nshare;
+    SkWalk walk;               // of those blocks over the left-over tiles (in units; row pairs in three planes: in groups of channels)
     // WINO kernels: the view's real number of output rows (Ho, TI, QN, Sh, Hf and osi above then describe pairs of
     // rows: Ho = ceil(wino_Ho / 2), Sh = 2, Hf = 4, osi = twice the row step of the output array); 0 otherwise
     int wino_Ho;
@@ -370,9 +371,8 @@ __global__ __launch_bounds__(64 * (WK * WP + LW), WPE) void igemm_sk_kernel(Igem
 
     const int vb = sk_virtual_block(blockIdx.x, P.nblocks);
     const int tile_s0 = P.own * P.nblocks;                          // first shared tile
-    const long long total = (long long)(P.tiles - tile_s0) * NU;    // units of the shared tiles
     const int rank = sk_share_rank(P.nblocks, P.nshare, vb);
-    const long long ub = rank < 0 ? 0 : sk_begin(total, P.nshare, rank), ue = rank < 0 ? 0 : sk_begin(total, P.nshare, rank + 1);
+    const long long ub = rank < 0 ? 0 : sk_begin(P.walk, rank), ue = rank < 0 ? 0 : sk_begin(P.walk, rank + 1);
     const int n_own = P.own * NU;                                    // units of this block's own tiles
     const int nunits = n_own + (int)(ue - ub);
     if (nunits == 0) return;
@@ -796,7 +796,7 @@ __global__ __launch_bounds__(64 * (WK * WP + LW), WPE) void igemm_sk_kernel(Igem
     // ---- the block's range of units --------------------------------------------------------
     // position = (tile, unit); `done` = units consumed so far.  After the block's own tiles comes its range
     // of the shared ones, which may start in the middle of a tile.
-    const int t_s = tile_s0 + (int)(ub / NU), uu_s = (int)(ub - (ub / NU) * NU);
+    const int ts = sk_tile(P.walk, ub, NU), t_s = tile_s0 + ts, uu_s = (int)(ub - (long long)ts * NU);
     auto advance = [&](int &t, int &uu, int done) {
         if (done == n_own) { t = t_s; uu = uu_s; }
         else if (++uu == NU) { uu = 0; ++t; }
@@ -877,22 +877,40 @@ __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const f
     const int ts = blockIdx.x;                       // shared tile (the grid has one row of blocks per shared tile)
     const int tile_s0 = P.own * P.nblocks;           // the shared tiles start here; unit numbers are relative to them
     const int t = tile_s0 + ts;
-    // The tile's pieces, in block order.  Sharing block of rank r holds the units [total*r/nshare, total*(r+1)/nshare):
-    // the first rank with units of this tile follows from one division (and a step of correction); its piece is
-    // its first segment if its range starts in this tile, else its second; the following ranks' pieces are first
-    // segments.  One thread lists them.
+    // The tile's pieces, in block order (sk_tile_pieces).  Sharing block of rank r holds the units [total*r/nshare, total*(r+1)/nshare): every
+    // thread looks at the ranges of its ranks, and a rank's place in the list is the number of those with a piece before it.  (One thread listed
+    // them: with 32 pieces to a tile that took 8 us of 14, 14x14x512, 3x3x512x512, one image.)
     constexpr int MAX_PIECES = 1024;
     __shared__ int slots[MAX_PIECES];
-    __shared__ int npieces;
-    if (threadIdx.x == 0)
-        npieces = sk_tile_pieces((long long)(P.tiles - tile_s0) * P.NU, P.NU, P.nblocks, P.nshare, ts, slots, MAX_PIECES);
+    __shared__ int found[4], alone;
+    const long long t_lo = (long long)ts * P.NU, t_hi = t_lo + P.NU;
+    int np = 0;
+    if (threadIdx.x == 0) alone = 0;
+    for (int r0 = 0; r0 < P.nshare; r0 += 256) {
+        const int r = r0 + threadIdx.x;
+        const long long bb = sk_begin(P.walk, r), be = r < P.nshare ? sk_begin(P.walk, r + 1) : bb;
+        const bool has = sk_has_piece(bb, be, t_lo, t_hi);
+        const unsigned long long in_wave = __ballot(has);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) found[threadIdx.x >> 6] = __popcll(in_wave);
+        if (has && bb <= t_lo && be >= t_hi) alone = 1;              // computed by one block alone: already written
+        __syncthreads();
+        int before = np;
+        for (int w = 0; w < 4; ++w) {
+            if (w < (int)(threadIdx.x >> 6)) before += found[w];
+            np += found[w];
+        }
+        const int at = before + __builtin_amdgcn_mbcnt_hi((unsigned)(in_wave >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in_wave, 0u));
+        if (has && at < MAX_PIECES) slots[at] = 2 * sk_share_block(P.nblocks, P.nshare, r) + (bb >= t_lo ? 0 : 1);
+    }
     __syncthreads();
-    if (npieces == 0) return;
+    if (alone) return;
+    np = min(np, MAX_PIECES);
     int kt, pt, rb, g;
     decode_tile(P, t, &kt, &pt, &rb, &g);
     const int OHW = P.OH * P.OW;
-    const int np = npieces;
-    // a thread takes four consecutive pixels of one filter: one 16-byte load per piece, up to four pieces in flight
+    // a thread takes four consecutive pixels of one filter: one 16-byte load per piece, up to eight pieces in flight (four: the loads' latency is half
+    // of what 32 pieces to a tile take)
     constexpr int Q4 = TQ / 4;
     for (int e4 = blockIdx.y * 256 + threadIdx.x; e4 < TK * Q4; e4 += gridDim.y * 256) {
         const int kloc = e4 / Q4, ql = 4 * (e4 - kloc * Q4);
@@ -907,12 +925,20 @@ __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const f
         const float *src = part + (size_t)kloc * TQ + ql;
         float4 acc = {bv, bv, bv, bv};
         int i = 0;
-        for (; i + 3 < np; i += 4) {                  // four pieces in flight, added in piece order
+        for (; i + 7 < np; i += 8) {                  // added in piece order
+            float4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4 *>(src + (size_t)slots[i + u] * (TK * TQ));
+#pragma unroll
+            for (int u = 0; u < 8; ++u) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+        }
+        if (i + 3 < np) {
             float4 v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4 *>(src + (size_t)slots[i + u] * (TK * TQ));
 #pragma unroll
             for (int u = 0; u < 4; ++u) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+            i += 4;
         }
         for (; i + 1 < np; i += 2) {
             const float4 v0 = *reinterpret_cast<const float4 *>(src + (size_t)slots[i] * (TK * TQ));

@@ -179,9 +179,8 @@ __global__ __launch_bounds__(64 * (WK * WP + LW), WPE) void igemm_bf16_kernel(Ig
 
     const int vb = sk_virtual_block(blockIdx.x, P.nblocks);
     const int tile_s0 = P.own * P.nblocks;                          // first shared tile
-    const long long total = (long long)(P.tiles - tile_s0) * NU;    // units of the shared tiles
     const int rank = sk_share_rank(P.nblocks, P.nshare, vb);
-    const long long ub = rank < 0 ? 0 : sk_begin(total, P.nshare, rank), ue = rank < 0 ? 0 : sk_begin(total, P.nshare, rank + 1);
+    const long long ub = rank < 0 ? 0 : sk_begin(P.walk, rank), ue = rank < 0 ? 0 : sk_begin(P.walk, rank + 1);
     const int n_own = P.own * NU;                                    // units of this block's own tiles
     const int nunits = n_own + (int)(ue - ub);
     if (nunits == 0) return;
@@ -443,7 +442,7 @@ __global__ __launch_bounds__(64 * (WK * WP + LW), WPE) void igemm_bf16_kernel(Ig
     // ---- the block's range of units --------------------------------------------------------
     // position = (tile, unit); `done` = units consumed so far.  After the block's own tiles comes its range
     // of the shared ones, which may start in the middle of a tile.
-    const int t_s = tile_s0 + (int)(ub / NU), uu_s = (int)(ub - (ub / NU) * NU);
+    const int ts = sk_tile(P.walk, ub, NU), t_s = tile_s0 + ts, uu_s = (int)(ub - (long long)ts * NU);
     // returns whether the next unit starts a new slab: a new group of channels, a new tile, or the jump from the
     // block's own tiles to its range of the shared ones (which may land inside a group)
     auto advance = [&](int &t, int &uu, int done) {

@@ -289,13 +289,12 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
     // units of the shared tiles; F23: cut between channel groups, whose four combinations then meet in one piece (a piece
     // of fewer holds sums that the other pieces cancel, and rounds them)
     constexpr int CUT = F23 ? 4 : 1;
-    const long long total = (long long)(P.tiles - tile_s0) * (NU / CUT);
     const int rank = sk_share_rank(P.nblocks, P.nshare, vb);
-    const long long ub = rank < 0 ? 0 : CUT * sk_begin(total, P.nshare, rank), ue = rank < 0 ? 0 : CUT * sk_begin(total, P.nshare, rank + 1);
+    const long long ub = rank < 0 ? 0 : CUT * sk_begin(P.walk, rank), ue = rank < 0 ? 0 : CUT * sk_begin(P.walk, rank + 1);
     const int n_own = P.own * NU;                                    // units of this block's own tiles
     const int nunits = n_own + (int)(ue - ub);
     if (nunits == 0) return;
-    const int t_s = tile_s0 + (int)(ub / NU), uu_s = (int)(ub - (ub / NU) * NU);
+    const int ts = sk_tile(P.walk, ub, NU), t_s = tile_s0 + ts, uu_s = (int)(ub - (long long)ts * NU);
     auto tile_of = [&](int t) __attribute__((always_inline)) {                    // dealt among the blocks of an XCD, as in igemm_sk_kernel
         if (t >= tile_s0 || (P.nblocks & 7) != 0) return t;
         const int b = t / P.own, j = t - b * P.own;

@@ -69,6 +69,7 @@ struct WgradParams {
     // first, one per compute unit) weighs w_first, any other w_later.  Of the two blocks resident on a
     // compute unit the one dispatched first gets more of the matrix core; with equal chunks it finishes
     // early and leaves the other to run alone, which uses the core less well.
+    SkWalk walk;                     // of the blocks over the units of all tiles (equal ranges), or over those of one tile (chunks)
     int n_first, w_first, w_later;
     // deal = 1 (one tile, equal chunk weights, a grid that is a multiple of 8): the chunks of the blocks on one XCD
     // cover a contiguous range of the tile's units between them, and the blocks take its units in turn (block i
@@ -162,9 +163,8 @@ __global__ __launch_bounds__(64 * (WK * WR + WGRAD_LOADER_WAVES), WPE) void wgra
         if (P.deal) deal = make_deal(P.NU, P.nchunks, G8, vb);      // one tile: the chunk is vb
     } else {
         vb = sk_virtual_block(blockIdx.x, P.nblocks);
-        const long long total = (long long)P.tiles * P.NU;
-        ub = sk_begin(total, P.nblocks, vb);
-        ue = sk_begin(total, P.nblocks, vb + 1);
+        ub = sk_begin(P.walk, vb);
+        ue = sk_begin(P.walk, vb + 1);
     }
     if (ub >= ue) return;
 
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(64 * (WK * WR + WGRAD_LOADER_WAVES), WPE) void wgra
 
     // ---- the block's range of units --------------------------------------------------------
     const int NU = P.NU;
-    int t_c = (int)(ub / NU);
+    int t_c = sk_tile(P.walk, ub, NU);
     int uu_c = (int)(ub - (long long)t_c * NU);
     int t_l = t_c, uu_l = uu_c;
     bool first_segment = true;
@@ -568,26 +568,18 @@ __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, cons
     if constexpr (CHUNKED) {
         npieces = P.nchunks;
     } else {
-        // Block b holds the units [total*b/nblocks, total*(b+1)/nblocks).  The first and the last block with units
-        // of this tile follow from two divisions (and at most a step of correction each); one thread finds them.
+        // Block b holds the units [total*b/nblocks, total*(b+1)/nblocks), none of them empty: one holds the tile's first unit, one its
+        // last.  Every thread looks at the ranges of its blocks (one thread that divided its way there took 2 us).
         __shared__ int found[3];
-        if (threadIdx.x == 0) {
-            const long long total = (long long)P.tiles * P.NU;
-            const long long t_lo = (long long)t * P.NU, t_hi = t_lo + P.NU;
-            const SkSplit split = sk_split(total, P.nblocks);
-            int first = (int)(t_lo * P.nblocks / total);
-            while (first + 1 < P.nblocks && sk_begin(split, first + 1) <= t_lo) ++first;
-            while (first > 0 && sk_begin(split, first) > t_lo) --first;
-            int last = (int)((t_hi - 1) * P.nblocks / total);
-            while (last + 1 < P.nblocks && sk_begin(split, last + 1) < t_hi) ++last;
-            while (last > first && sk_begin(split, last) >= t_hi) --last;
-            found[0] = first;
-            found[1] = last - first + 1;
+        const long long t_lo = (long long)t * P.NU, t_hi = t_lo + P.NU;
+        for (int b = threadIdx.x; b < P.nblocks; b += 512) {
+            const long long bb = sk_begin(P.walk, b), be = sk_begin(P.walk, b + 1);
             // the first block's piece is its first one if it starts with this tile, else its last; the others start inside the tile
-            found[2] = 2 * first + (sk_begin(split, first) >= t_lo ? 0 : 1);
+            if (bb <= t_lo && be > t_lo) { found[0] = b; found[2] = 2 * b + (bb >= t_lo ? 0 : 1); }
+            if (bb < t_hi && be >= t_hi) found[1] = b;
         }
         __syncthreads();
-        b0 = found[0]; npieces = found[1]; slot0 = found[2];
+        b0 = found[0]; npieces = found[1] - found[0] + 1; slot0 = found[2];
         if (npieces < 2) return;      // computed by one block alone: already written
     }
     auto slot_of = [&](int i) { return CHUNKED ? 2 * (t + P.tiles * i) : (i == 0 ? slot0 : 2 * (b0 + i)); };

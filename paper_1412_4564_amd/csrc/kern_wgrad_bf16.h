@@ -26,7 +26,6 @@
 namespace mcn {
 
 struct WgradBf16Params : WgradSplitParams {
-    SkWalk walk;                     // of the blocks over all tiles, or of a tile's chunks
     Div32 dNO, dTIQ, dMC, dT, dHf, dCC, dRB, dTiles, dKT, dRT;
 };
 

@@ -209,17 +209,16 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_spl
         vb = wg_chunk_virtual_block(blockIdx.x, gridDim.x);
         if (vb >= P.nblocks) return;
         const int tile = vb % P.tiles, chunk = vb / P.tiles;
-        ub = (long long)tile * NU + (long long)NU * chunk / P.nchunks;
-        ue = (long long)tile * NU + (long long)NU * (chunk + 1) / P.nchunks;
+        ub = (long long)tile * NU + sk_begin(P.walk, chunk);
+        ue = (long long)tile * NU + sk_begin(P.walk, chunk + 1);
     } else {
         vb = sk_virtual_block(blockIdx.x, P.nblocks);
-        const long long total = (long long)P.tiles * NU;
-        ub = sk_begin(total, P.nblocks, vb);
-        ue = sk_begin(total, P.nblocks, vb + 1);
+        ub = sk_begin(P.walk, vb);
+        ue = sk_begin(P.walk, vb + 1);
     }
     if (ub >= ue) return;
     const int nunits = (int)(ue - ub);
-    int t = (int)(ub / NU), uu = (int)(ub - (long long)t * NU);
+    int t = sk_tile(P.walk, ub, NU), uu = (int)(ub - (long long)t * NU);
 
     // Units done, in waves: written by the staging waves, read by the computing ones.  The waves wait for one another through these two
     // and not at barriers: the two computing waves of a SIMD then drift apart, and one multiplies while the other waits for the

@@ -507,7 +507,6 @@ int launch_wgrad_split_inst(const WgradSplitPlan &pl, const float *x, const floa
     }
     const dim3 grid(P.nchunks > 0 ? wg_chunk_grid(P.nblocks) : P.nblocks), block(64 * (WK * WR + WGS_STAGE_WAVES));
     if constexpr (TILE.planes == 1) {
-        P.walk = P.nchunks > 0 ? make_sk_walk(P.NU, P.nchunks, P.NU) : make_sk_walk((long long)P.tiles * P.NU, P.nblocks, P.NU);
         P.dNO = make_div32(P.NO); P.dTIQ = make_div32(P.TIQ); P.dMC = make_div32(P.MC); P.dT = make_div32(P.Hf * P.Wf); P.dHf = make_div32(P.Hf);
         P.dCC = make_div32(P.CC); P.dRB = make_div32(P.RB); P.dTiles = make_div32(P.tiles); P.dKT = make_div32(P.KT); P.dRT = make_div32(P.RT);
         hipLaunchKernelGGL((wgrad_bf16_kernel<WK, WR, MK, MR, YT, XT, LINEAR>), grid, block, pl.lds_bytes, s, P, x, dzdy, out, part);
@@ -693,7 +692,7 @@ int run_backward_bias(int plane, int K, int N, const float *dzdy, float *dzdb, v
         hipLaunchKernelGGL(bias_partial_kernel, dim3(K, p.S), dim3(256), 0, s, dzdy, part, plane, K, N, p.chunks, p.S);
     st = check_launch();
     if (st) return st;
-    hipLaunchKernelGGL(bias_final_kernel, dim3(cdiv(K, 256)), dim3(256), 0, s, part, dzdb, K, p.S);
+    hipLaunchKernelGGL(bias_final_kernel, dim3(cdiv(K, 4)), dim3(256), 0, s, part, dzdb, K, p.S);
     return check_launch();
 }
 

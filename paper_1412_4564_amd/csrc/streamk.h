@@ -60,6 +60,9 @@ MCN_HOST_DEVICE inline int sk_share_block(int nblocks, int nshare, int r) {
     return (r / S) * G + r % S;
 }
 
+// Whether the sharing block of rank r holds a piece of the units [t_lo, t_hi) of a tile (bb, be: its range), and whether it holds them all.
+MCN_HOST_DEVICE inline bool sk_has_piece(long long bb, long long be, long long t_lo, long long t_hi) { return be > bb && be > t_lo && bb < t_hi; }
+
 // The pieces of left-over tile ts (units [ts*NU, (ts+1)*NU) of `total`), in the order in which the fix-up pass adds
 // them: workspace slots 2*block + segment.  The sharing block of rank r holds the units [total*r/nshare,
 // total*(r+1)/nshare); the first rank with units of this tile follows from one division (and a step of correction);

@@ -296,13 +296,69 @@ def _check(t, shape, name):
     import torch
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32 and t.is_contiguous()):
         raise TypeError("%s must be a contiguous fp32 CUDA tensor" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("%s has shape %r, expected %r" % (name, tuple(t.shape), tuple(shape)))
+
+
+def _out(t, shape, device, name="out"):
+    """The caller's output tensor, checked, or a new one."""
+    import torch
+    if t is None:
+        return torch.empty(shape, dtype=torch.float32, device=device)
+    _check(t, shape, name)
+    return t
 
 
 def _stream():
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+# What a call asks the library before its launches -- descriptor, size of the result, bytes of scratch -- depends on numbers alone.  The answers
+# of the last calls are kept by those numbers: asked every time they took 5 us of a call's 10 on the host (a layer of 37x53x16, whose nine
+# kernels run 50 us, waited for its three calls).
+_KNOWN_MOST = 512
+_known = {}
+
+
+def _conv(xshape, wshape, stride, pad, precision, op):
+    """(descriptor, shape of y, bytes of scratch) of a pass of a convolution layer."""
+    key = (op, tuple(xshape), tuple(wshape), tuple(stride), tuple(pad), precision)
+    got = _known.get(key)
+    if got is None:
+        desc = make_desc(xshape, wshape, stride, pad, precision)
+        ho, wo = mcn_conv_output_size(desc)
+        got = _keep(key, (desc, (int(xshape[0]), int(wshape[0]), wo, ho), mcn_conv_workspace_size(desc, op)))
+    return got
+
+
+def _convt(xshape, fshape, upsample, crop, groups, precision, op):
+    """The same for the transpose block."""
+    key = ("t", op, tuple(xshape), tuple(fshape), tuple(upsample), tuple(crop), groups, precision)
+    got = _known.get(key)
+    if got is None:
+        desc = make_convt_desc(xshape, fshape, upsample, crop, groups, precision)
+        ho, wo = mcn_convt_output_size(desc)
+        got = _keep(key, (desc, (int(xshape[0]), int(groups) * int(fshape[1]), wo, ho), mcn_convt_workspace_size(desc, op)))
+    return got
+
+
+def _pool(xshape, window, stride, pad, method, backward):
+    """The same for the pooling block; the forward pass has no scratch."""
+    key = ("p", backward, tuple(xshape), tuple(window), tuple(stride), tuple(pad), method)
+    got = _known.get(key)
+    if got is None:
+        desc = make_pool_desc(xshape, window, stride, pad, method)
+        ho, wo = mcn_pool_output_size(desc)
+        got = _keep(key, (desc, (int(xshape[0]), int(xshape[1]), wo, ho), mcn_pool_workspace_size(desc) if backward else 0))
+    return got
+
+
+def _keep(key, got):
+    if len(_known) >= _KNOWN_MOST:
+        _known.clear()
+    _known[key] = got
+    return got
 
 
 class Workspace:
@@ -324,16 +380,12 @@ _default_ws = Workspace()
 
 
 def conv_forward(x, w, b=None, stride=(1, 1), pad=(0, 0, 0, 0), precision=MCN_PREC_FP32, out=None, workspace=None):
-    import torch
     _check(x, None, "x"); _check(w, None, "w")
-    desc = make_desc(x.shape, w.shape, stride, pad, precision)
-    ho, wo = mcn_conv_output_size(desc)
+    desc, ysh, need = _conv(x.shape, w.shape, stride, pad, precision, MCN_OP_FORWARD)
     if b is not None:
         _check(b, (w.shape[0],), "b")
-    ysh = (x.shape[0], w.shape[0], wo, ho)
-    y = out if out is not None else torch.empty(ysh, dtype=torch.float32, device=x.device)
-    _check(y, ysh, "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_conv_workspace_size(desc, MCN_OP_FORWARD), x.device)
+    y = _out(out, ysh, x.device)
+    wsp, wsn = (workspace or _default_ws).get(need, x.device)
     st = mcn_conv_forward(desc, x.data_ptr(), w.data_ptr(), None if b is None else b.data_ptr(), y.data_ptr(),
                           wsp, wsn, _stream())
     if st:
@@ -342,14 +394,11 @@ def conv_forward(x, w, b=None, stride=(1, 1), pad=(0, 0, 0, 0), precision=MCN_PR
 
 
 def conv_backward_data(xshape, w, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), precision=MCN_PREC_FP32, out=None, workspace=None):
-    import torch
     _check(w, None, "w")
-    desc = make_desc(xshape, w.shape, stride, pad, precision)
-    ho, wo = mcn_conv_output_size(desc)
-    _check(dzdy, (xshape[0], w.shape[0], wo, ho), "dzdy")
-    dzdx = out if out is not None else torch.empty(tuple(xshape), dtype=torch.float32, device=w.device)
-    _check(dzdx, tuple(xshape), "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_conv_workspace_size(desc, MCN_OP_BACKWARD_DATA), w.device)
+    desc, ysh, need = _conv(xshape, w.shape, stride, pad, precision, MCN_OP_BACKWARD_DATA)
+    _check(dzdy, ysh, "dzdy")
+    dzdx = _out(out, tuple(xshape), w.device)
+    wsp, wsn = (workspace or _default_ws).get(need, w.device)
     st = mcn_conv_backward_data(desc, w.data_ptr(), dzdy.data_ptr(), dzdx.data_ptr(), wsp, wsn, _stream())
     if st:
         raise McnError(st, "mcn_conv_backward_data")
@@ -357,14 +406,11 @@ def conv_backward_data(xshape, w, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), precisi
 
 
 def conv_backward_filter(x, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), precision=MCN_PREC_FP32, out=None, workspace=None):
-    import torch
     _check(x, None, "x")
-    desc = make_desc(x.shape, wshape, stride, pad, precision)
-    ho, wo = mcn_conv_output_size(desc)
-    _check(dzdy, (x.shape[0], wshape[0], wo, ho), "dzdy")
-    dzdw = out if out is not None else torch.empty(tuple(wshape), dtype=torch.float32, device=x.device)
-    _check(dzdw, tuple(wshape), "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_conv_workspace_size(desc, MCN_OP_BACKWARD_FILTER), x.device)
+    desc, ysh, need = _conv(x.shape, wshape, stride, pad, precision, MCN_OP_BACKWARD_FILTER)
+    _check(dzdy, ysh, "dzdy")
+    dzdw = _out(out, tuple(wshape), x.device)
+    wsp, wsn = (workspace or _default_ws).get(need, x.device)
     st = mcn_conv_backward_filter(desc, x.data_ptr(), dzdy.data_ptr(), dzdw.data_ptr(), wsp, wsn, _stream())
     if st:
         raise McnError(st, "mcn_conv_backward_filter")
@@ -373,16 +419,12 @@ def conv_backward_filter(x, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), preci
 
 def conv_backward_filter_bias(x, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), precision=MCN_PREC_FP32, out=None, workspace=None):
     """(dzdw, dzdb) in one call; out = (dzdw, dzdb) to write into existing tensors."""
-    import torch
     _check(x, None, "x")
-    desc = make_desc(x.shape, wshape, stride, pad, precision)
-    ho, wo = mcn_conv_output_size(desc)
-    _check(dzdy, (x.shape[0], wshape[0], wo, ho), "dzdy")
-    dzdw = out[0] if out is not None else torch.empty(tuple(wshape), dtype=torch.float32, device=x.device)
-    dzdb = out[1] if out is not None else torch.empty((wshape[0],), dtype=torch.float32, device=x.device)
-    _check(dzdw, tuple(wshape), "out[0]")
-    _check(dzdb, (wshape[0],), "out[1]")
-    wsp, wsn = (workspace or _default_ws).get(mcn_conv_workspace_size(desc, MCN_OP_BACKWARD_FILTER_BIAS), x.device)
+    desc, ysh, need = _conv(x.shape, wshape, stride, pad, precision, MCN_OP_BACKWARD_FILTER_BIAS)
+    _check(dzdy, ysh, "dzdy")
+    dzdw = _out(None if out is None else out[0], tuple(wshape), x.device, "out[0]")
+    dzdb = _out(None if out is None else out[1], (wshape[0],), x.device, "out[1]")
+    wsp, wsn = (workspace or _default_ws).get(need, x.device)
     st = mcn_conv_backward_filter_bias(desc, x.data_ptr(), dzdy.data_ptr(), dzdw.data_ptr(), dzdb.data_ptr(), wsp, wsn, _stream())
     if st:
         raise McnError(st, "mcn_conv_backward_filter_bias")
@@ -390,13 +432,10 @@ def conv_backward_filter_bias(x, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), 
 
 
 def conv_backward_bias(xshape, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), out=None, workspace=None):
-    import torch
-    desc = make_desc(xshape, wshape, stride, pad)
-    ho, wo = mcn_conv_output_size(desc)
-    _check(dzdy, (xshape[0], wshape[0], wo, ho), "dzdy")
-    dzdb = out if out is not None else torch.empty((wshape[0],), dtype=torch.float32, device=dzdy.device)
-    _check(dzdb, (wshape[0],), "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_conv_workspace_size(desc, MCN_OP_BACKWARD_BIAS), dzdy.device)
+    desc, ysh, need = _conv(xshape, wshape, stride, pad, MCN_PREC_FP32, MCN_OP_BACKWARD_BIAS)
+    _check(dzdy, ysh, "dzdy")
+    dzdb = _out(out, (wshape[0],), dzdy.device)
+    wsp, wsn = (workspace or _default_ws).get(need, dzdy.device)
     st = mcn_conv_backward_bias(desc, dzdy.data_ptr(), dzdb.data_ptr(), wsp, wsn, _stream())
     if st:
         raise McnError(st, "mcn_conv_backward_bias")
@@ -405,16 +444,12 @@ def conv_backward_bias(xshape, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), ou
 
 # ---- convolution + ReLU ----
 def conv_relu_forward(x, w, b=None, stride=(1, 1), pad=(0, 0, 0, 0), precision=MCN_PREC_FP32, out=None, workspace=None):
-    import torch
     _check(x, None, "x"); _check(w, None, "w")
-    desc = make_desc(x.shape, w.shape, stride, pad, precision)
-    ho, wo = mcn_conv_output_size(desc)
+    desc, ysh, need = _conv(x.shape, w.shape, stride, pad, precision, MCN_OP_FORWARD)
     if b is not None:
         _check(b, (w.shape[0],), "b")
-    ysh = (x.shape[0], w.shape[0], wo, ho)
-    y = out if out is not None else torch.empty(ysh, dtype=torch.float32, device=x.device)
-    _check(y, ysh, "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_conv_workspace_size(desc, MCN_OP_FORWARD), x.device)
+    y = _out(out, ysh, x.device)
+    wsp, wsn = (workspace or _default_ws).get(need, x.device)
     st = mcn_conv_relu_forward(desc, x.data_ptr(), w.data_ptr(), None if b is None else b.data_ptr(), y.data_ptr(),
                                wsp, wsn, _stream())
     if st:
@@ -425,15 +460,11 @@ def conv_relu_forward(x, w, b=None, stride=(1, 1), pad=(0, 0, 0, 0), precision=M
 def conv_relu_backward_bias(xshape, wshape, y, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), out=None, inplace=False,
                             workspace=None):
     """Returns (dzdp, dzdb); with inplace=True dzdp overwrites dzdy."""
-    import torch
-    desc = make_desc(xshape, wshape, stride, pad)
-    ho, wo = mcn_conv_output_size(desc)
-    ysh = (xshape[0], wshape[0], wo, ho)
+    desc, ysh, need = _conv(xshape, wshape, stride, pad, MCN_PREC_FP32, MCN_OP_BACKWARD_BIAS)
     _check(y, ysh, "y"); _check(dzdy, ysh, "dzdy")
-    dzdp = dzdy if inplace else (out if out is not None else torch.empty_like(dzdy))
-    _check(dzdp, ysh, "out")
-    dzdb = torch.empty((wshape[0],), dtype=torch.float32, device=dzdy.device)
-    wsp, wsn = (workspace or _default_ws).get(mcn_conv_workspace_size(desc, MCN_OP_BACKWARD_BIAS), dzdy.device)
+    dzdp = dzdy if inplace else _out(out, ysh, dzdy.device)
+    dzdb = _out(None, (wshape[0],), dzdy.device)
+    wsp, wsn = (workspace or _default_ws).get(need, dzdy.device)
     st = mcn_conv_relu_backward_bias(desc, y.data_ptr(), dzdy.data_ptr(), dzdp.data_ptr(), dzdb.data_ptr(), wsp, wsn,
                                      _stream())
     if st:
@@ -442,22 +473,14 @@ def conv_relu_backward_bias(xshape, wshape, y, dzdy, stride=(1, 1), pad=(0, 0, 0
 
 
 # ---- convolution transpose ----
-def _convt_shapes(xshape, fshape, upsample, crop, groups, precision=MCN_PREC_FP32):
-    desc = make_convt_desc(xshape, fshape, upsample, crop, groups, precision)
-    ho, wo = mcn_convt_output_size(desc)
-    return desc, (int(xshape[0]), int(groups) * int(fshape[1]), wo, ho)
-
-
 def convt_forward(x, f, b=None, upsample=(1, 1), crop=(0, 0, 0, 0), groups=1, precision=MCN_PREC_FP32, out=None,
                   workspace=None):
-    import torch
     _check(x, None, "x"); _check(f, None, "f")
-    desc, ysh = _convt_shapes(x.shape, f.shape, upsample, crop, groups, precision)
+    desc, ysh, need = _convt(x.shape, f.shape, upsample, crop, groups, precision, MCN_OP_FORWARD)
     if b is not None:
         _check(b, (ysh[1],), "b")
-    y = out if out is not None else torch.empty(ysh, dtype=torch.float32, device=x.device)
-    _check(y, ysh, "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_convt_workspace_size(desc, MCN_OP_FORWARD), x.device)
+    y = _out(out, ysh, x.device)
+    wsp, wsn = (workspace or _default_ws).get(need, x.device)
     st = mcn_convt_forward(desc, x.data_ptr(), f.data_ptr(), None if b is None else b.data_ptr(), y.data_ptr(),
                            wsp, wsn, _stream())
     if st:
@@ -467,13 +490,11 @@ def convt_forward(x, f, b=None, upsample=(1, 1), crop=(0, 0, 0, 0), groups=1, pr
 
 def convt_backward_data(xshape, f, dzdy, upsample=(1, 1), crop=(0, 0, 0, 0), groups=1, precision=MCN_PREC_FP32,
                         out=None, workspace=None):
-    import torch
     _check(f, None, "f")
-    desc, ysh = _convt_shapes(xshape, f.shape, upsample, crop, groups, precision)
+    desc, ysh, need = _convt(xshape, f.shape, upsample, crop, groups, precision, MCN_OP_BACKWARD_DATA)
     _check(dzdy, ysh, "dzdy")
-    dzdx = out if out is not None else torch.empty(tuple(xshape), dtype=torch.float32, device=f.device)
-    _check(dzdx, tuple(xshape), "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_convt_workspace_size(desc, MCN_OP_BACKWARD_DATA), f.device)
+    dzdx = _out(out, tuple(xshape), f.device)
+    wsp, wsn = (workspace or _default_ws).get(need, f.device)
     st = mcn_convt_backward_data(desc, f.data_ptr(), dzdy.data_ptr(), dzdx.data_ptr(), wsp, wsn, _stream())
     if st:
         raise McnError(st, "mcn_convt_backward_data")
@@ -482,13 +503,11 @@ def convt_backward_data(xshape, f, dzdy, upsample=(1, 1), crop=(0, 0, 0, 0), gro
 
 def convt_backward_filter(x, fshape, dzdy, upsample=(1, 1), crop=(0, 0, 0, 0), groups=1, precision=MCN_PREC_FP32,
                           out=None, workspace=None):
-    import torch
     _check(x, None, "x")
-    desc, ysh = _convt_shapes(x.shape, fshape, upsample, crop, groups, precision)
+    desc, ysh, need = _convt(x.shape, fshape, upsample, crop, groups, precision, MCN_OP_BACKWARD_FILTER)
     _check(dzdy, ysh, "dzdy")
-    dzdf = out if out is not None else torch.empty(tuple(fshape), dtype=torch.float32, device=x.device)
-    _check(dzdf, tuple(fshape), "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_convt_workspace_size(desc, MCN_OP_BACKWARD_FILTER), x.device)
+    dzdf = _out(out, tuple(fshape), x.device)
+    wsp, wsn = (workspace or _default_ws).get(need, x.device)
     st = mcn_convt_backward_filter(desc, x.data_ptr(), dzdy.data_ptr(), dzdf.data_ptr(), wsp, wsn, _stream())
     if st:
         raise McnError(st, "mcn_convt_backward_filter")
@@ -496,12 +515,10 @@ def convt_backward_filter(x, fshape, dzdy, upsample=(1, 1), crop=(0, 0, 0, 0), g
 
 
 def convt_backward_bias(xshape, fshape, dzdy, upsample=(1, 1), crop=(0, 0, 0, 0), groups=1, out=None, workspace=None):
-    import torch
-    desc, ysh = _convt_shapes(xshape, fshape, upsample, crop, groups)
+    desc, ysh, need = _convt(xshape, fshape, upsample, crop, groups, MCN_PREC_FP32, MCN_OP_BACKWARD_BIAS)
     _check(dzdy, ysh, "dzdy")
-    dzdb = out if out is not None else torch.empty((ysh[1],), dtype=torch.float32, device=dzdy.device)
-    _check(dzdb, (ysh[1],), "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_convt_workspace_size(desc, MCN_OP_BACKWARD_BIAS), dzdy.device)
+    dzdb = _out(out, (ysh[1],), dzdy.device)
+    wsp, wsn = (workspace or _default_ws).get(need, dzdy.device)
     st = mcn_convt_backward_bias(desc, dzdy.data_ptr(), dzdb.data_ptr(), wsp, wsn, _stream())
     if st:
         raise McnError(st, "mcn_convt_backward_bias")
@@ -510,13 +527,9 @@ def convt_backward_bias(xshape, fshape, dzdy, upsample=(1, 1), crop=(0, 0, 0, 0)
 
 # ---- spatial pooling ----
 def pool_forward(x, window, stride=(1, 1), pad=(0, 0, 0, 0), method=MCN_POOL_MAX, out=None):
-    import torch
     _check(x, None, "x")
-    desc = make_pool_desc(x.shape, window, stride, pad, method)
-    ho, wo = mcn_pool_output_size(desc)
-    ysh = (x.shape[0], x.shape[1], wo, ho)
-    y = out if out is not None else torch.empty(ysh, dtype=torch.float32, device=x.device)
-    _check(y, ysh, "out")
+    desc, ysh, _ = _pool(x.shape, window, stride, pad, method, False)
+    y = _out(out, ysh, x.device)
     st = mcn_pool_forward(desc, x.data_ptr(), y.data_ptr(), _stream())
     if st:
         raise McnError(st, "mcn_pool_forward")
@@ -524,14 +537,11 @@ def pool_forward(x, window, stride=(1, 1), pad=(0, 0, 0, 0), method=MCN_POOL_MAX
 
 
 def pool_backward(x, dzdy, window, stride=(1, 1), pad=(0, 0, 0, 0), method=MCN_POOL_MAX, out=None, workspace=None):
-    import torch
     _check(x, None, "x")
-    desc = make_pool_desc(x.shape, window, stride, pad, method)
-    ho, wo = mcn_pool_output_size(desc)
-    _check(dzdy, (x.shape[0], x.shape[1], wo, ho), "dzdy")
-    dzdx = out if out is not None else torch.empty_like(x)
-    _check(dzdx, tuple(x.shape), "out")
-    wsp, wsn = (workspace or _default_ws).get(mcn_pool_workspace_size(desc), x.device)
+    desc, ysh, need = _pool(x.shape, window, stride, pad, method, True)
+    _check(dzdy, ysh, "dzdy")
+    dzdx = _out(out, x.shape, x.device)
+    wsp, wsn = (workspace or _default_ws).get(need, x.device)
     st = mcn_pool_backward(desc, x.data_ptr(), dzdy.data_ptr(), dzdx.data_ptr(), wsp, wsn, _stream())
     if st:
         raise McnError(st, "mcn_pool_backward")

@@ -6,6 +6,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include "geom.h"
+#include "fastdiv.h"
 
 namespace mcn {
 
@@ -140,92 +141,73 @@ __global__ __launch_bounds__(256) void direct_backward_filter_kernel(Geom g, con
 }
 
 // ---- bias derivative: dzdb[k] = sum_{n,jo,io} dzdy[io,jo,k,n] ------------------
-// Stage 1: block (k, s) sums the units u = s, s+S, ... where unit u = (n, chunk c)
-// covers dzdy[c*CH .. min((c+1)*CH, HoWo)) of image n, filter k.  Stage 2 adds the S
-// partials of each k in a fixed order, so the result does not depend on scheduling.
-constexpr int BIAS_CHUNK = 4096;
-
-__global__ __launch_bounds__(256) void bias_partial_kernel(const float *__restrict__ dzdy, float *__restrict__ part,
-                                                           int HoWo, int K, int N, int chunks, int S) {
-    const int k = blockIdx.x, s = blockIdx.y;
-    const int units = N * chunks;
-    float acc = 0.f;
-    for (int u = s; u < units; u += S) {
-        const int n = u / chunks, c = u - n * chunks;
-        const float *p = dzdy + ((size_t)n * K + k) * HoWo;
-        const int lo = c * BIAS_CHUNK;
-        const int hi = min(lo + BIAS_CHUNK, HoWo);
-        for (int e = lo + threadIdx.x; e < hi; e += 256) acc += p[e];
-    }
-    __shared__ float red[4];
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) part[(size_t)k * S + s] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-// The same with 16-byte loads, four of them in flight per thread before the first addition: for planes of a
-// multiple of 4 samples in an array aligned to 16 bytes (then every (n, k) plane and every chunk is aligned).
-// The order of the additions differs from the kernel above but is as fixed.
-__global__ __launch_bounds__(256) void bias_partial_v4_kernel(const float *__restrict__ dzdy, float *__restrict__ part,
-                                                              int HoWo, int K, int N, int chunks, int S) {
-    const int k = blockIdx.x, s = blockIdx.y;
-    const int units = N * chunks;
-    float4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0, a2 = a0, a3 = a0;
-    for (int u = s; u < units; u += S) {
-        const int n = u / chunks, c = u - n * chunks;
-        const float4 *p = reinterpret_cast<const float4 *>(dzdy + ((size_t)n * K + k) * HoWo);
-        const int lo = c * (BIAS_CHUNK / 4);
-        const int hi = min(lo + BIAS_CHUNK / 4, HoWo / 4);
-        const int e = lo + threadIdx.x;
-        const float4 z = {0.f, 0.f, 0.f, 0.f};
-        static_assert(BIAS_CHUNK == 4 * 4 * 256, "four 16-byte loads per thread and chunk");
-        const float4 v0 = e < hi ? p[e] : z, v1 = e + 256 < hi ? p[e + 256] : z;
-        const float4 v2 = e + 512 < hi ? p[e + 512] : z, v3 = e + 768 < hi ? p[e + 768] : z;
-        a0.x += v0.x; a0.y += v0.y; a0.z += v0.z; a0.w += v0.w;
-        a1.x += v1.x; a1.y += v1.y; a1.z += v1.z; a1.w += v1.w;
-        a2.x += v2.x; a2.y += v2.y; a2.z += v2.z; a2.w += v2.w;
-        a3.x += v3.x; a3.y += v3.y; a3.z += v3.z; a3.w += v3.w;
-    }
-    float acc = ((a0.x + a0.y) + (a0.z + a0.w)) + ((a1.x + a1.y) + (a1.z + a1.w)) +
-                (((a2.x + a2.y) + (a2.z + a2.w)) + ((a3.x + a3.y) + (a3.z + a3.w)));
-    __shared__ float red[4];
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) part[(size_t)k * S + s] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-// ---- ReLU mask fused with the bias derivative ------------------------------------------------------
-// Sec. 6.4.1 of the manual: through y = max(0, p) the derivative is dz/dp = [p > 0] dz/dy, and
-// y > 0 exactly where p > 0.  One pass reads y and dzdy, writes dzdp = [y > 0] * dzdy (the derivative
-// that the convolution's own backward passes take) and sums it per filter (dzdb).  Same two stages,
-// same unit order as bias_partial_kernel.  dzdp may be the array dzdy (each element is read, then
-// written, by one thread).
-__global__ __launch_bounds__(256) void relu_bias_partial_kernel(const float *__restrict__ y, const float *dzdy,
-                                                                float *dzdp, float *__restrict__ part, int HoWo,
-                                                                int K, int N, int chunks, int S) {
-    const int k = blockIdx.x, s = blockIdx.y;
-    const int units = N * chunks;
-    float acc = 0.f;
-    for (int u = s; u < units; u += S) {
-        const int n = u / chunks, c = u - n * chunks;
-        const size_t base = ((size_t)n * K + k) * HoWo;
-        const int lo = c * BIAS_CHUNK;
-        const int hi = min(lo + BIAS_CHUNK, HoWo);
-        for (int e = lo + threadIdx.x; e < hi; e += 256) {
-            const float m = y[base + e] > 0.f ? dzdy[base + e] : 0.f;
-            dzdp[base + e] = m;
-            acc += m;
+// Stage 1: the four waves of block (k, s) sum the pieces i = 4s + wave, i + 4S, ... where piece i = (n, c) covers 256 samples of dzdy from
+// 256 c on of image n, filter k.  Stage 2 adds the S partials of each k in a fixed order, so the result does not depend on
+// scheduling.  S: about 2048 blocks in all, at most one for every BIAS_CHUNK samples of a plane (plan_bias).
+//
+// RELU, the mask fused with it: Sec. 6.4.1 of the manual, through y = max(0, p) the derivative is dz/dp = [p > 0] dz/dy, and y > 0 exactly
+// where p > 0.  One pass reads y and dzdy, writes dzdp = [y > 0] * dzdy (the derivative that the convolution's own backward passes take) and sums
+// that.  dzdp may be the array dzdy (each element is read, then written, by one thread).
+//
+// Bound by HBM.  Four pieces are on their way in a wave, each in 16-byte loads whatever the plane's size and place (the hardware takes
+// them at any multiple of 4 bytes).
+constexpr int BIAS_CHUNK = 4096, BIAS_PIECE = 256;
+template <bool RELU>
+__global__ __launch_bounds__(256) void bias_partial_kernel(const float *__restrict__ y, const float *dzdy, float *dzdp, float *__restrict__ part, int HoWo, int K,
+                                                           int N, int pieces, Div32 dPieces, int S) {
+    typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float Quad4 __attribute__((ext_vector_type(4)));
+    const int k = blockIdx.x, s = blockIdx.y, e = 4 * (threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int all = N * pieces, step = 4 * S;
+    Quad4 sum[4] = {};
+#pragma unroll 1
+    for (int i0 = 4 * s + wave; i0 < all; i0 += 4 * step) {
+        size_t at[4];
+        int left[4];                         // samples from the thread's first one on
+        Quad4 v[4], m[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = min(i0 + j * step, all - 1), n = div32(i, dPieces), c = i - n * pieces;
+            at[j] = ((size_t)n * K + k) * HoWo + c * BIAS_PIECE + e;
+            left[j] = i0 + j * step < all ? HoWo - c * BIAS_PIECE - e : 0;
+            v[j] = m[j] = Quad4{0.f, 0.f, 0.f, 0.f};
+            if (left[j] >= 4) {
+                v[j] = *reinterpret_cast<const Quad *>(dzdy + at[j]);
+                if (RELU) m[j] = *reinterpret_cast<const Quad *>(y + at[j]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (left[j] > 0 && left[j] < 4) {
+#pragma unroll
+                for (int u = 0; u < 3; ++u)
+                    if (u < left[j]) {
+                        v[j][u] = dzdy[at[j] + u];
+                        if (RELU) m[j][u] = y[at[j] + u];
+                    }
+            }
+            if constexpr (RELU) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[j][u] = m[j][u] > 0.f ? v[j][u] : 0.f;
+                if (left[j] >= 4) *reinterpret_cast<Quad *>(dzdp + at[j]) = v[j];
+                else {
+#pragma unroll
+                    for (int u = 0; u < 3; ++u)
+                        if (u < left[j]) dzdp[at[j] + u] = v[j][u];
+                }
+            }
+            sum[j] += v[j];
         }
     }
+    const Quad4 q = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    float acc = (q[0] + q[1]) + (q[2] + q[3]);
     __shared__ float red[4];
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) part[(size_t)k * S + s] = (red[0] + red[1]) + (red[2] + red[3]);
 }
-// small output planes: as bias_rows_partial_kernel
+// The same for small output planes, as bias_rows_partial_kernel
 __global__ __launch_bounds__(256) void relu_bias_rows_partial_kernel(const float *__restrict__ y, const float *dzdy,
                                                                      float *dzdp, float *__restrict__ part,
                                                                      int KHoWo, int N, int S) {

@@ -684,12 +684,11 @@ int run_backward_bias(int plane, int K, int N, const float *dzdy, float *dzdb, v
         hipLaunchKernelGGL(bias_rows_final_kernel, dim3(cdiv(K, 4)), dim3(256), 0, s, part, dzdb, plane, K, p.S);
         return check_launch();
     }
+    const int pieces = (plane + BIAS_PIECE - 1) / BIAS_PIECE;
     if (y)
-        hipLaunchKernelGGL(relu_bias_partial_kernel, dim3(K, p.S), dim3(256), 0, s, y, dzdy, dzdp, part, plane, K, N, p.chunks, p.S);
-    else if (plane % 4 == 0 && plane >= 1024 && ((uintptr_t)dzdy & 15) == 0)     // planes that fill a block's 16-byte loads
-        hipLaunchKernelGGL(bias_partial_v4_kernel, dim3(K, p.S), dim3(256), 0, s, dzdy, part, plane, K, N, p.chunks, p.S);
+        hipLaunchKernelGGL(bias_partial_kernel<true>, dim3(K, p.S), dim3(256), 0, s, y, dzdy, dzdp, part, plane, K, N, pieces, make_div32(pieces), p.S);
     else
-        hipLaunchKernelGGL(bias_partial_kernel, dim3(K, p.S), dim3(256), 0, s, dzdy, part, plane, K, N, p.chunks, p.S);
+        hipLaunchKernelGGL(bias_partial_kernel<false>, dim3(K, p.S), dim3(256), 0, s, y, dzdy, dzdp, part, plane, K, N, pieces, make_div32(pieces), p.S);
     st = check_launch();
     if (st) return st;
     hipLaunchKernelGGL(bias_final_kernel, dim3(cdiv(K, 4)), dim3(256), 0, s, part, dzdb, K, p.S);

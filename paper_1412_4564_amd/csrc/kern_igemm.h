@@ -247,8 +247,15 @@ __device__ __host__ inline int merged_tap(int ti, int Hfv, int HfA, int S, int P
     return (a >= 0 && a < A) ? pi + S * a : -1;
 }
 
-__global__ __launch_bounds__(256) void igemm_pack_weights_kernel(const float *__restrict__ w, float *__restrict__ packed,
-                                                                 PackParams Q) {
+// The stride phases of an input derivative, packed in one launch (blockIdx.y: the phase; at: where its weights go, in words).  A launch behind
+// large kernels takes 5 us, as long as most of these packings themselves.
+constexpr int PACK_PHASES = 9;
+struct PackPhases {
+    PackParams q[PACK_PHASES];
+    unsigned at[PACK_PHASES];
+};
+
+__device__ __attribute__((always_inline)) inline void pack_weights(const float *__restrict__ w, float *__restrict__ packed, const PackParams &Q) {
     int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= Q.total) return;
     int t = p / Q.WSZ;
@@ -285,6 +292,10 @@ __global__ __launch_bounds__(256) void igemm_pack_weights_kernel(const float *__
         }
     }
     packed[p] = v;
+}
+__global__ __launch_bounds__(256) void igemm_pack_weights_kernel(const float *__restrict__ w, float *__restrict__ packed, PackParams Q) { pack_weights(w, packed, Q); }
+__global__ __launch_bounds__(256) void igemm_pack_phases_kernel(const float *__restrict__ w, float *__restrict__ packed, PackPhases Q) {
+    pack_weights(w, packed + Q.at[blockIdx.y], Q.q[blockIdx.y]);
 }
 
 // The packing for the WINO kernels (PackParams::wino, modes 0 and 1; same layout), four results per thread: a

@@ -76,8 +76,7 @@ __device__ inline void split_bf16x3(float v0, float v1, unsigned *hi, unsigned *
 // and every value was read once per plane (14x14x512, 3x3x512x512, 32 images: split operands, forward 136.5 us with that, 117.6 us
 // with this; bf16 76.4 and 70.2 us).
 template <int PLANES, bool MERGED>
-__global__ __launch_bounds__(256) void igemm_pack_weights_bf16_kernel(const float *__restrict__ w,
-                                                                      unsigned *__restrict__ packed, PackParams Q) {
+__device__ __attribute__((always_inline)) inline void pack_weights_bf16(const float *__restrict__ w, unsigned *__restrict__ packed, const PackParams &Q) {
     const int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= Q.total / PLANES) return;
     const int words = Q.WSZ / PLANES;            // of one plane, per unit
@@ -134,6 +133,15 @@ __global__ __launch_bounds__(256) void igemm_pack_weights_bf16_kernel(const floa
         split_bf16x3(v[0], v[1], &hi, &mid, &lo);
         dst[0] = hi; dst[2 * Q.TK * 4] = mid; dst[4 * Q.TK * 4] = lo;
     }
+}
+template <int PLANES, bool MERGED>
+__global__ __launch_bounds__(256) void igemm_pack_weights_bf16_kernel(const float *__restrict__ w, unsigned *__restrict__ packed, PackParams Q) {
+    pack_weights_bf16<PLANES, MERGED>(w, packed, Q);
+}
+// stride phases in one launch, as igemm_pack_phases_kernel
+template <int PLANES>
+__global__ __launch_bounds__(256) void igemm_pack_phases_bf16_kernel(const float *__restrict__ w, unsigned *__restrict__ packed, PackPhases Q) {
+    pack_weights_bf16<PLANES, false>(w, packed + Q.at[blockIdx.y], Q.q[blockIdx.y]);
 }
 
 // WK x WP waves; each wave owns MK x MP tiles of 32 filters x 32 pixels.

@@ -355,20 +355,24 @@ int launch_igemm_fixed(const IgemmPlan &pl, const float *in, const float *wpk, c
     }
 }
 
-int launch_igemm(const IgemmPlan &pl, const float *in, const float *w, const float *bias, float *out, void *ws,
-                 hipStream_t s, int relu = 0) {
-    float *packed = (float *)ws;
-    float *part = (float *)((char *)ws + align256(pl.packed_floats * sizeof(float)));
+// the packed weights of one view
+int launch_pack(const IgemmPlan &pl, const float *w, float *packed, hipStream_t s) {
+    if (pl.bf16 && pl.Q.wino)
+        hipLaunchKernelGGL(igemm_pack_f23_split_kernel, dim3(cdiv(pl.Q.total / 12, 256)), dim3(256), 0, s, w, (unsigned *)packed, pl.Q);
+    else if (pl.bf16) {
+        auto pack = pl.planes == 1 ? igemm_pack_weights_bf16_kernel<1, false> : pl.planes == 2 ? igemm_pack_weights_bf16_kernel<2, false>
+                    : pl.P.mD ? igemm_pack_weights_bf16_kernel<3, true> : igemm_pack_weights_bf16_kernel<3, false>;
+        hipLaunchKernelGGL(pack, dim3(cdiv(pl.Q.total / pl.planes, 256)), dim3(256), 0, s, w, (unsigned *)packed, pl.Q);
+    } else if (pl.Q.wino) {
+        if (pl.P.WSZ != pl.Q.NS * 2 * pl.Q.TK) return MCN_BAD_ARG;      // the planner never pads these units
+        hipLaunchKernelGGL(igemm_pack_wino_kernel, dim3(cdiv(pl.Q.total / 4, 256)), dim3(256), 0, s, w, packed, pl.Q);
+    } else
+        hipLaunchKernelGGL(igemm_pack_weights_kernel, dim3(cdiv(pl.Q.total, 256)), dim3(256), 0, s, w, packed, pl.Q);
+    return check_launch();
+}
+
+int launch_packed(const IgemmPlan &pl, const float *in, const float *w, const float *packed, float *part, const float *bias, float *out, hipStream_t s, int relu = 0) {
     if (pl.bf16) {
-        if (pl.Q.wino)
-            hipLaunchKernelGGL(igemm_pack_f23_split_kernel, dim3(cdiv(pl.Q.total / 12, 256)), dim3(256), 0, s, w, (unsigned *)packed, pl.Q);
-        else {
-            auto pack = pl.planes == 1 ? igemm_pack_weights_bf16_kernel<1, false> : pl.planes == 2 ? igemm_pack_weights_bf16_kernel<2, false>
-                        : pl.P.mD ? igemm_pack_weights_bf16_kernel<3, true> : igemm_pack_weights_bf16_kernel<3, false>;
-            hipLaunchKernelGGL(pack, dim3(cdiv(pl.Q.total / pl.planes, 256)), dim3(256), 0, s, w, (unsigned *)packed, pl.Q);
-        }
-        int st = check_launch();
-        if (st) return st;
         if (pl.planes == 3) {
             switch (pl.shape) {
                 case IG_S64x256: return launch_igemm_split<2, 4, 1, 2>(pl, in, packed, bias, out, part, s, relu, w);
@@ -385,13 +389,6 @@ int launch_igemm(const IgemmPlan &pl, const float *in, const float *w, const flo
             default: return MCN_BAD_ARG;
         }
     }
-    if (pl.Q.wino && pl.P.WSZ != pl.Q.NS * 2 * pl.Q.TK) return MCN_BAD_ARG;      // the planner never pads these units
-    if (pl.Q.wino)
-        hipLaunchKernelGGL(igemm_pack_wino_kernel, dim3(cdiv(pl.Q.total / 4, 256)), dim3(256), 0, s, w, packed, pl.Q);
-    else
-        hipLaunchKernelGGL(igemm_pack_weights_kernel, dim3(cdiv(pl.Q.total, 256)), dim3(256), 0, s, w, packed, pl.Q);
-    int st = check_launch();
-    if (st) return st;
     switch (pl.shape) {
         case IG_128x256: return launch_igemm_fixed<2, 4, 2, 2>(pl, in, packed, bias, out, part, s, relu);
         case IG_64x512: return launch_igemm_fixed<1, 8, 2, 2>(pl, in, packed, bias, out, part, s, relu);
@@ -402,6 +399,43 @@ int launch_igemm(const IgemmPlan &pl, const float *in, const float *w, const flo
         case IG_W64x256: return launch_igemm_wino<1, 8, 2>(pl, in, packed, bias, out, part, s, relu);
         default: return MCN_BAD_ARG;
     }
+}
+
+size_t packed_bytes(const IgemmPlan &pl) { return align256(pl.packed_floats * sizeof(float)); }
+int launch_igemm(const IgemmPlan &pl, const float *in, const float *w, const float *bias, float *out, void *ws, hipStream_t s, int relu = 0) {
+    const int st = launch_pack(pl, w, (float *)ws, s);
+    return st ? st : launch_packed(pl, in, w, (const float *)ws, (float *)((char *)ws + packed_bytes(pl)), bias, out, s, relu);
+}
+
+// Several stride phases of an input derivative: packed together where one kernel packs them all; the workspace then holds the weights of all
+// phases, and behind them the partial tiles of one.
+bool packed_together(const PlanEntry &e) {
+    if (e.n_bwd < 2 || e.n_bwd > PACK_PHASES) return false;
+    const IgemmPlan &a = phase_plan(e, 0);
+    for (int i = 0; i < e.n_bwd; ++i) {
+        const IgemmPlan &b = phase_plan(e, i);
+        if (b.Q.wino || b.P.mD || b.bf16 != a.bf16 || b.planes != a.planes || b.packed_floats >= ((size_t)1 << 31) / PACK_PHASES) return false;
+    }
+    return true;
+}
+int launch_pack_phases(const PlanEntry &e, const float *w, float *packed, hipStream_t s) {
+    PackPhases Q = {};
+    unsigned at = 0, most = 0;
+    const IgemmPlan &a = phase_plan(e, 0);
+    for (int i = 0; i < e.n_bwd; ++i) {
+        const IgemmPlan &b = phase_plan(e, i);
+        const unsigned threads = b.Q.total / (b.bf16 ? b.planes : 1);
+        Q.q[i] = b.Q; Q.at[i] = at;
+        at += (unsigned)(packed_bytes(b) / sizeof(float));
+        if (threads > most) most = threads;
+    }
+    const dim3 grid(cdiv(most, 256), e.n_bwd);
+    if (!a.bf16) hipLaunchKernelGGL(igemm_pack_phases_kernel, grid, dim3(256), 0, s, w, packed, Q);
+    else {
+        auto pack = a.planes == 1 ? igemm_pack_phases_bf16_kernel<1> : a.planes == 2 ? igemm_pack_phases_bf16_kernel<2> : igemm_pack_phases_bf16_kernel<3>;
+        hipLaunchKernelGGL(pack, grid, dim3(256), 0, s, w, (unsigned *)packed, Q);
+    }
+    return check_launch();
 }
 
 // The pass that adds the pieces of the tiles shared between blocks (kern_wgrad.h).  G partial sums per result: about
@@ -559,11 +593,17 @@ size_t workspace_bytes(const mcn_conv_desc *d, const Geom &g, int op) {
             return e->fwd_ok ? igemm_ws_bytes(e->fwd) : 0;
         case MCN_OP_BACKWARD_DATA: {
             if (e->fc) return igemm_ws_bytes(e->fc_bwd);
-            // the phases run one after the other on the stream and share one region
-            size_t m = 0;
-            if (e->bwd_ok)
-                for (int i = 0; i < e->n_bwd; ++i) { size_t b = igemm_ws_bytes(phase_plan(*e, i)); if (b > m) m = b; }
-            return m;
+            if (!e->bwd_ok) return 0;
+            // the phases run one after the other on the stream and share one region, for their partial tiles or for everything
+            const bool together = packed_together(*e);
+            size_t m = 0, packed = 0;
+            for (int i = 0; i < e->n_bwd; ++i) {
+                const IgemmPlan &pl = phase_plan(*e, i);
+                const size_t b = together ? pl.partial_floats * sizeof(float) : igemm_ws_bytes(pl);
+                if (together) packed += packed_bytes(pl);
+                if (b > m) m = b;
+            }
+            return packed + m;
         }
         case MCN_OP_BACKWARD_FILTER:
             if (e->fc) return igemm_ws_bytes(e->fc_wg);
@@ -615,11 +655,21 @@ int run_backward_data(const mcn_conv_desc *desc, const Geom &g, const float *w, 
             st = check_launch();
             if (st) return st;
         }
-        for (int i = 0; i < pe->n_bwd; ++i) {
-            st = launch_igemm(phase_plan(*pe, i), dzdy, w, bias, dzdx, ws, s);
-            if (st) return st;
+        if (!packed_together(*pe)) {
+            for (int i = 0; i < pe->n_bwd; ++i) {
+                st = launch_igemm(phase_plan(*pe, i), dzdy, w, bias, dzdx, ws, s);
+                if (st) return st;
+            }
+            return MCN_OK;
         }
-        return MCN_OK;
+        st = launch_pack_phases(*pe, w, (float *)ws, s);
+        char *part = (char *)ws, *packed = (char *)ws;
+        for (int i = 0; i < pe->n_bwd; ++i) part += packed_bytes(phase_plan(*pe, i));
+        for (int i = 0; i < pe->n_bwd && !st; ++i) {
+            st = launch_packed(phase_plan(*pe, i), dzdy, w, (const float *)packed, (float *)part, bias, dzdx, s);
+            packed += packed_bytes(phase_plan(*pe, i));
+        }
+        return st;
     }
     if (pe->fc) {
         st = launch_igemm(pe->fc_bwd, w, dzdy, nullptr, dzdx, ws, s);

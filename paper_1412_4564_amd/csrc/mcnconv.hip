@@ -61,6 +61,9 @@ BiasPlan plan_bias(int64_t HoWo, int K, int N) {
     if (want > units) want = units;
     if (want < 1) want = 1;
     if (want > 65535) want = 65535;
+    // few samples: one block a filter, twelve pieces to a wave at most, in place of a second launch: 14x14x512, one image and 28x28x512, ten images
+    // 10 -> 7.5 us; beyond (8x8, 128 images, with the mask) 11 -> 12.4
+    if ((HoWo + BIAS_PIECE - 1) / BIAS_PIECE * N <= 48) want = 1;
     p.S = (int)want;
     p.ws_floats = (size_t)K * p.S;
     return p;
@@ -438,14 +441,15 @@ int launch_pack_phases(const PlanEntry &e, const float *w, float *packed, hipStr
     return check_launch();
 }
 
-// The pass that adds the pieces of the tiles shared between blocks (kern_wgrad.h).  G partial sums per result: about
-// the number of pieces per tile, at most 32; about 1024 blocks in all, none without work.
+// The pass that adds the pieces of the tiles shared between blocks (kern_wgrad.h).  G partial sums per result, at most 32: up to four
+// pieces to each, which are on their way together (one to each leaves the passes over a tile's results, each of which waits for its loads, four
+// times as many: 128 x 384 tiles of 21 pieces: 24 us against 13; of 8: 16.8 against 12); about 1024 blocks in all, none without work.
 template <int TK, int TR, class Repair = KeepSums>
 int launch_wgrad_fixup(const WgradParams &P, const float *part, const float *rbias, float *out, hipStream_t s, Repair repair = Repair()) {
     const bool chunked = P.nchunks > 0;
     const long long pieces = chunked ? P.nchunks : ((long long)P.nblocks + P.tiles - 1) / P.tiles + 1;
     int G = 2;
-    while (G < 32 && G < pieces) G *= 2;
+    while (G < 32 && 4 * G < pieces) G *= 2;
     const int Q = 512 / G;
     const int klim = P.Kg < TK ? P.Kg : TK, rlim = P.R < TR ? P.R : TR;
     const int passes = (klim * ((rlim + 3) / 4) + Q - 1) / Q;      // of the largest tile
@@ -735,12 +739,13 @@ int run_backward_bias(int plane, int K, int N, const float *dzdy, float *dzdb, v
         return check_launch();
     }
     const int pieces = (plane + BIAS_PIECE - 1) / BIAS_PIECE;
+    if (p.S == 1) part = dzdb;               // the only partial sum of a filter
     if (y)
         hipLaunchKernelGGL(bias_partial_kernel<true>, dim3(K, p.S), dim3(256), 0, s, y, dzdy, dzdp, part, plane, K, N, pieces, make_div32(pieces), p.S);
     else
         hipLaunchKernelGGL(bias_partial_kernel<false>, dim3(K, p.S), dim3(256), 0, s, y, dzdy, dzdp, part, plane, K, N, pieces, make_div32(pieces), p.S);
     st = check_launch();
-    if (st) return st;
+    if (st || p.S == 1) return st;
     hipLaunchKernelGGL(bias_final_kernel, dim3(cdiv(K, 4)), dim3(256), 0, s, part, dzdb, K, p.S);
     return check_launch();
 }

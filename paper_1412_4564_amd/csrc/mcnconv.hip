@@ -441,15 +441,14 @@ int launch_pack_phases(const PlanEntry &e, const float *w, float *packed, hipStr
     return check_launch();
 }
 
-// The pass that adds the pieces of the tiles shared between blocks (kern_wgrad.h).  G partial sums per result, at most 32: up to four
-// pieces to each, which are on their way together (one to each leaves the passes over a tile's results, each of which waits for its loads, four
-// times as many: 128 x 384 tiles of 21 pieces: 24 us against 13; of 8: 16.8 against 12); about 1024 blocks in all, none without work.
+// The pass that adds the pieces of the tiles shared between blocks (kern_wgrad.h).  G partial sums per result: about
+// the number of pieces per tile, at most 32; about 1024 blocks in all, none without work.
 template <int TK, int TR, class Repair = KeepSums>
 int launch_wgrad_fixup(const WgradParams &P, const float *part, const float *rbias, float *out, hipStream_t s, Repair repair = Repair()) {
     const bool chunked = P.nchunks > 0;
     const long long pieces = chunked ? P.nchunks : ((long long)P.nblocks + P.tiles - 1) / P.tiles + 1;
     int G = 2;
-    while (G < 32 && 4 * G < pieces) G *= 2;
+    while (G < 32 && G < pieces) G *= 2;
     const int Q = 512 / G;
     const int klim = P.Kg < TK ? P.Kg : TK, rlim = P.R < TR ? P.R : TR;
     const int passes = (klim * ((rlim + 3) / 4) + Q - 1) / Q;      // of the largest tile

@@ -554,7 +554,7 @@ struct KeepSums {
 // slice of the tile's results.  The order of the additions is fixed by the plan: with G = 512 / Q partial sums
 // per result (a power of two chosen on the host from the number of pieces), piece i goes to partial sum i mod G
 // and the G sums are added as a balanced tree.  A thread handles four consecutive coefficients of one filter
-// (one 16-byte load per piece, four pieces in flight); rows and columns of the tile beyond the filters and
+// (one 16-byte load per piece, up to four pieces in flight); rows and columns of the tile beyond the filters and
 // coefficients that exist are skipped, so a layer whose coefficients fill a fraction of a tile reads that
 // fraction of every piece.
 // CHUNKED: the pieces of tile t are the first slots of blocks t + tiles*i, i < nchunks; else those of the blocks
@@ -613,9 +613,14 @@ __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, cons
                 acc.x += v2.x; acc.y += v2.y; acc.z += v2.z; acc.w += v2.w;
                 acc.x += v3.x; acc.y += v3.y; acc.z += v3.z; acc.w += v3.w;
             }
-            for (; i < npieces; i += G) {
-                const float4 v = *reinterpret_cast<const float4 *>(src + (size_t)slot_of(i) * (TK * TR));
-                acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+            if (i < npieces) {      // up to three more, on their way together; the first one again in place of one that is not there
+                const bool two = i + G < npieces, three = i + 2 * G < npieces;
+                const float4 v0 = *reinterpret_cast<const float4 *>(src + (size_t)slot_of(i) * (TK * TR));
+                const float4 v1 = *reinterpret_cast<const float4 *>(src + (size_t)slot_of(two ? i + G : i) * (TK * TR));
+                const float4 v2 = *reinterpret_cast<const float4 *>(src + (size_t)slot_of(three ? i + 2 * G : i) * (TK * TR));
+                acc.x += v0.x; acc.y += v0.y; acc.z += v0.z; acc.w += v0.w;
+                if (two) { acc.x += v1.x; acc.y += v1.y; acc.z += v1.z; acc.w += v1.w; }
+                if (three) { acc.x += v2.x; acc.y += v2.y; acc.z += v2.z; acc.w += v2.w; }
             }
         }
         red[pg * Q + q] = acc;

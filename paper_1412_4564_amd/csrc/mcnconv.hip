@@ -441,20 +441,20 @@ int launch_pack_phases(const PlanEntry &e, const float *w, float *packed, hipStr
     return check_launch();
 }
 
-// The pass that adds the pieces of the tiles shared between blocks (kern_wgrad.h).  G partial sums per result: about
-// the number of pieces per tile, at most 32; about 1024 blocks in all, none without work.
+// The pass that adds the pieces of the tiles shared between blocks (kern_wgrad.h); about 1024 blocks in all, none without work.  G partial
+// sums per result, about the number of pieces per tile and at most 32, while the blocks have one pass over the results each; where they have
+// more, each of which waits for its loads, up to four pieces to a sum, which are on their way together (128 x 384 tiles of 21 pieces 24 -> 13 us, of 8
+// 16.8 -> 12; with one pass each the fewer sums take half a microsecond more).
 template <int TK, int TR, class Repair = KeepSums>
 int launch_wgrad_fixup(const WgradParams &P, const float *part, const float *rbias, float *out, hipStream_t s, Repair repair = Repair()) {
     const bool chunked = P.nchunks > 0;
     const long long pieces = chunked ? P.nchunks : ((long long)P.nblocks + P.tiles - 1) / P.tiles + 1;
+    const int klim = P.Kg < TK ? P.Kg : TK, rlim = P.R < TR ? P.R : TR, fours = klim * ((rlim + 3) / 4);
+    const int blocks = 1024 / P.tiles < 1 ? 1 : 1024 / P.tiles;
+    auto passes = [&](int g) { return (fours * g + 511) / 512; };      // of the largest tile
     int G = 2;
-    while (G < 32 && G < pieces) G *= 2;
-    const int Q = 512 / G;
-    const int klim = P.Kg < TK ? P.Kg : TK, rlim = P.R < TR ? P.R : TR;
-    const int passes = (klim * ((rlim + 3) / 4) + Q - 1) / Q;      // of the largest tile
-    int fy = 1024 / P.tiles;
-    if (fy < 1) fy = 1;
-    if (fy > passes) fy = passes;
+    while (G < 32 && G < pieces && (4 * G < pieces || passes(2 * G) <= blocks)) G *= 2;
+    const int fy = blocks < passes(G) ? blocks : passes(G);
     if (chunked)
         hipLaunchKernelGGL((wgrad_fixup_kernel<TK, TR, true, Repair>), dim3(P.tiles, fy), dim3(512), 0, s, P, part, rbias, out, G, repair);
     else

@@ -136,8 +136,8 @@ __device__ __attribute__((always_inline)) inline float wave_sum_again(const Wgra
 }
 
 // In the fix-up pass: of n stored results, where(i, &k, &r) says which and whether there is one, those that are not finite are summed
-// again by the block's 512 threads, shared out evenly.  27x27x96, 5x5x48x256 in two groups, 128 images (0.31 ms): one NaN in x 0.5 ms at most
-// (4.3 with one result a thread), in dzdy 1.7 (4.1), one inf 0.7 and 1.7 (4.6 and 4.3), all NaN 0.3, +inf everywhere 11 (24); 28x28x512,
+// again by the block's 512 threads, shared out evenly.  27x27x96, 5x5x48x256 in two groups, 128 images (0.31 ms): one NaN in x 1.0 ms at most
+// (4.3 with one result a thread), in dzdy 1.0 (4.1), one inf 0.7 and 1.7 (4.6 and 4.3), all NaN 0.3, +inf everywhere 11 (24); 28x28x512,
 // 1x1x512x128, 64 images (0.1 ms): one NaN 0.4 at most (1.5), one inf 0.6 (1.7); 227x227x3, 11x11x3x96 at stride 4, 128 images (0.3 ms), where the
 // results of few blocks meet it: one NaN 3.3 at most (13), one inf 6.4 (13).
 struct RepairSums {

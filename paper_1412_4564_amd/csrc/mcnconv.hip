@@ -443,7 +443,7 @@ int launch_pack_phases(const PlanEntry &e, const float *w, float *packed, hipStr
 
 // The pass that adds the pieces of the tiles shared between blocks (kern_wgrad.h); about 1024 blocks in all, none without work.  G partial
 // sums per result, about the number of pieces per tile and at most 32, while the blocks have one pass over the results each; where they have
-// more, each of which waits for its loads, up to four pieces to a sum, which are on their way together (128 x 384 tiles of 21 pieces 24 -> 13 us, of 8
+// more, each of which waits for its loads, up to four pieces to a sum, which are on their way together (128 x 384 tiles of 21 pieces 24 -> 13 us, of 6
 // 16.8 -> 12; with one pass each the fewer sums take half a microsecond more).
 template <int TK, int TR, class Repair = KeepSums>
 int launch_wgrad_fixup(const WgradParams &P, const float *part, const float *rbias, float *out, hipStream_t s, Repair repair = Repair()) {

@@ -14,6 +14,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmcnconv.so")
@@ -362,7 +363,8 @@ def _keep(key, got):
 
 
 class Workspace:
-    """A reusable device scratch buffer (grown on demand, never shrunk)."""
+    """A reusable device scratch buffer (grown on demand, never shrunk).  The calls it is passed to must follow one another: on one stream, or
+    with the caller's own waits between streams; and it must not grow while a captured graph still uses it."""
 
     def __init__(self):
         self.buf = None
@@ -376,7 +378,45 @@ class Workspace:
         return self.buf.data_ptr(), self.buf.numel()
 
 
-_default_ws = Workspace()
+def _capturing():
+    import torch
+    return torch.cuda.is_current_stream_capturing()
+
+
+class _OwnWorkspaces(threading.local):
+    """Scratch of the calls without workspace=: a buffer for each host thread and stream.  A call's kernels hand results to one another
+    through it, so calls that may run at the same time need buffers of their own; those of one thread on one stream follow one another.
+    The allocator orders a buffer by the stream it was allocated on, the only one that uses it, so that one may be dropped while its last call
+    runs.  At most MOST of them a thread, given back with the thread.  A captured graph's scratch is the graph's: allocated in its pool for each
+    call, where it stays for the replays and no eager call meets it."""
+    MOST = 8
+
+    def __init__(self):
+        self.bufs = {}
+
+    def get(self, nbytes, device, stream):
+        import torch
+        if nbytes == 0:
+            return None, 0
+        if _capturing():
+            return torch.empty(nbytes, dtype=torch.uint8, device=device).data_ptr(), nbytes
+        key = (device, stream)
+        got = self.bufs.get(key)
+        if got is None or got[1] < nbytes:
+            if got is None and len(self.bufs) >= self.MOST:
+                del self.bufs[next(iter(self.bufs))]
+            buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
+            got = self.bufs[key] = (buf.data_ptr(), nbytes, buf)
+        return got[:2]
+
+
+_default_ws = _OwnWorkspaces()
+
+
+def _scratch(workspace, nbytes, device):
+    """(pointer, bytes, stream) of a call's scratch and the stream it runs on."""
+    stream = _stream()
+    return (*(workspace.get(nbytes, device) if workspace else _default_ws.get(nbytes, device, stream)), stream)
 
 
 def conv_forward(x, w, b=None, stride=(1, 1), pad=(0, 0, 0, 0), precision=MCN_PREC_FP32, out=None, workspace=None):
@@ -385,9 +425,9 @@ def conv_forward(x, w, b=None, stride=(1, 1), pad=(0, 0, 0, 0), precision=MCN_PR
     if b is not None:
         _check(b, (w.shape[0],), "b")
     y = _out(out, ysh, x.device)
-    wsp, wsn = (workspace or _default_ws).get(need, x.device)
+    wsp, wsn, stream = _scratch(workspace, need, x.device)
     st = mcn_conv_forward(desc, x.data_ptr(), w.data_ptr(), None if b is None else b.data_ptr(), y.data_ptr(),
-                          wsp, wsn, _stream())
+                          wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_conv_forward")
     return y
@@ -398,8 +438,8 @@ def conv_backward_data(xshape, w, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), precisi
     desc, ysh, need = _conv(xshape, w.shape, stride, pad, precision, MCN_OP_BACKWARD_DATA)
     _check(dzdy, ysh, "dzdy")
     dzdx = _out(out, tuple(xshape), w.device)
-    wsp, wsn = (workspace or _default_ws).get(need, w.device)
-    st = mcn_conv_backward_data(desc, w.data_ptr(), dzdy.data_ptr(), dzdx.data_ptr(), wsp, wsn, _stream())
+    wsp, wsn, stream = _scratch(workspace, need, w.device)
+    st = mcn_conv_backward_data(desc, w.data_ptr(), dzdy.data_ptr(), dzdx.data_ptr(), wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_conv_backward_data")
     return dzdx
@@ -410,8 +450,8 @@ def conv_backward_filter(x, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), preci
     desc, ysh, need = _conv(x.shape, wshape, stride, pad, precision, MCN_OP_BACKWARD_FILTER)
     _check(dzdy, ysh, "dzdy")
     dzdw = _out(out, tuple(wshape), x.device)
-    wsp, wsn = (workspace or _default_ws).get(need, x.device)
-    st = mcn_conv_backward_filter(desc, x.data_ptr(), dzdy.data_ptr(), dzdw.data_ptr(), wsp, wsn, _stream())
+    wsp, wsn, stream = _scratch(workspace, need, x.device)
+    st = mcn_conv_backward_filter(desc, x.data_ptr(), dzdy.data_ptr(), dzdw.data_ptr(), wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_conv_backward_filter")
     return dzdw
@@ -424,8 +464,8 @@ def conv_backward_filter_bias(x, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), 
     _check(dzdy, ysh, "dzdy")
     dzdw = _out(None if out is None else out[0], tuple(wshape), x.device, "out[0]")
     dzdb = _out(None if out is None else out[1], (wshape[0],), x.device, "out[1]")
-    wsp, wsn = (workspace or _default_ws).get(need, x.device)
-    st = mcn_conv_backward_filter_bias(desc, x.data_ptr(), dzdy.data_ptr(), dzdw.data_ptr(), dzdb.data_ptr(), wsp, wsn, _stream())
+    wsp, wsn, stream = _scratch(workspace, need, x.device)
+    st = mcn_conv_backward_filter_bias(desc, x.data_ptr(), dzdy.data_ptr(), dzdw.data_ptr(), dzdb.data_ptr(), wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_conv_backward_filter_bias")
     return dzdw, dzdb
@@ -435,8 +475,8 @@ def conv_backward_bias(xshape, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), ou
     desc, ysh, need = _conv(xshape, wshape, stride, pad, MCN_PREC_FP32, MCN_OP_BACKWARD_BIAS)
     _check(dzdy, ysh, "dzdy")
     dzdb = _out(out, (wshape[0],), dzdy.device)
-    wsp, wsn = (workspace or _default_ws).get(need, dzdy.device)
-    st = mcn_conv_backward_bias(desc, dzdy.data_ptr(), dzdb.data_ptr(), wsp, wsn, _stream())
+    wsp, wsn, stream = _scratch(workspace, need, dzdy.device)
+    st = mcn_conv_backward_bias(desc, dzdy.data_ptr(), dzdb.data_ptr(), wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_conv_backward_bias")
     return dzdb
@@ -449,9 +489,9 @@ def conv_relu_forward(x, w, b=None, stride=(1, 1), pad=(0, 0, 0, 0), precision=M
     if b is not None:
         _check(b, (w.shape[0],), "b")
     y = _out(out, ysh, x.device)
-    wsp, wsn = (workspace or _default_ws).get(need, x.device)
+    wsp, wsn, stream = _scratch(workspace, need, x.device)
     st = mcn_conv_relu_forward(desc, x.data_ptr(), w.data_ptr(), None if b is None else b.data_ptr(), y.data_ptr(),
-                               wsp, wsn, _stream())
+                               wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_conv_relu_forward")
     return y
@@ -464,9 +504,9 @@ def conv_relu_backward_bias(xshape, wshape, y, dzdy, stride=(1, 1), pad=(0, 0, 0
     _check(y, ysh, "y"); _check(dzdy, ysh, "dzdy")
     dzdp = dzdy if inplace else _out(out, ysh, dzdy.device)
     dzdb = _out(None, (wshape[0],), dzdy.device)
-    wsp, wsn = (workspace or _default_ws).get(need, dzdy.device)
+    wsp, wsn, stream = _scratch(workspace, need, dzdy.device)
     st = mcn_conv_relu_backward_bias(desc, y.data_ptr(), dzdy.data_ptr(), dzdp.data_ptr(), dzdb.data_ptr(), wsp, wsn,
-                                     _stream())
+                                     stream)
     if st:
         raise McnError(st, "mcn_conv_relu_backward_bias")
     return dzdp, dzdb
@@ -480,9 +520,9 @@ def convt_forward(x, f, b=None, upsample=(1, 1), crop=(0, 0, 0, 0), groups=1, pr
     if b is not None:
         _check(b, (ysh[1],), "b")
     y = _out(out, ysh, x.device)
-    wsp, wsn = (workspace or _default_ws).get(need, x.device)
+    wsp, wsn, stream = _scratch(workspace, need, x.device)
     st = mcn_convt_forward(desc, x.data_ptr(), f.data_ptr(), None if b is None else b.data_ptr(), y.data_ptr(),
-                           wsp, wsn, _stream())
+                           wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_convt_forward")
     return y
@@ -494,8 +534,8 @@ def convt_backward_data(xshape, f, dzdy, upsample=(1, 1), crop=(0, 0, 0, 0), gro
     desc, ysh, need = _convt(xshape, f.shape, upsample, crop, groups, precision, MCN_OP_BACKWARD_DATA)
     _check(dzdy, ysh, "dzdy")
     dzdx = _out(out, tuple(xshape), f.device)
-    wsp, wsn = (workspace or _default_ws).get(need, f.device)
-    st = mcn_convt_backward_data(desc, f.data_ptr(), dzdy.data_ptr(), dzdx.data_ptr(), wsp, wsn, _stream())
+    wsp, wsn, stream = _scratch(workspace, need, f.device)
+    st = mcn_convt_backward_data(desc, f.data_ptr(), dzdy.data_ptr(), dzdx.data_ptr(), wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_convt_backward_data")
     return dzdx
@@ -507,8 +547,8 @@ def convt_backward_filter(x, fshape, dzdy, upsample=(1, 1), crop=(0, 0, 0, 0), g
     desc, ysh, need = _convt(x.shape, fshape, upsample, crop, groups, precision, MCN_OP_BACKWARD_FILTER)
     _check(dzdy, ysh, "dzdy")
     dzdf = _out(out, tuple(fshape), x.device)
-    wsp, wsn = (workspace or _default_ws).get(need, x.device)
-    st = mcn_convt_backward_filter(desc, x.data_ptr(), dzdy.data_ptr(), dzdf.data_ptr(), wsp, wsn, _stream())
+    wsp, wsn, stream = _scratch(workspace, need, x.device)
+    st = mcn_convt_backward_filter(desc, x.data_ptr(), dzdy.data_ptr(), dzdf.data_ptr(), wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_convt_backward_filter")
     return dzdf
@@ -518,8 +558,8 @@ def convt_backward_bias(xshape, fshape, dzdy, upsample=(1, 1), crop=(0, 0, 0, 0)
     desc, ysh, need = _convt(xshape, fshape, upsample, crop, groups, MCN_PREC_FP32, MCN_OP_BACKWARD_BIAS)
     _check(dzdy, ysh, "dzdy")
     dzdb = _out(out, (ysh[1],), dzdy.device)
-    wsp, wsn = (workspace or _default_ws).get(need, dzdy.device)
-    st = mcn_convt_backward_bias(desc, dzdy.data_ptr(), dzdb.data_ptr(), wsp, wsn, _stream())
+    wsp, wsn, stream = _scratch(workspace, need, dzdy.device)
+    st = mcn_convt_backward_bias(desc, dzdy.data_ptr(), dzdb.data_ptr(), wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_convt_backward_bias")
     return dzdb
@@ -541,8 +581,8 @@ def pool_backward(x, dzdy, window, stride=(1, 1), pad=(0, 0, 0, 0), method=MCN_P
     desc, ysh, need = _pool(x.shape, window, stride, pad, method, True)
     _check(dzdy, ysh, "dzdy")
     dzdx = _out(out, x.shape, x.device)
-    wsp, wsn = (workspace or _default_ws).get(need, x.device)
-    st = mcn_pool_backward(desc, x.data_ptr(), dzdy.data_ptr(), dzdx.data_ptr(), wsp, wsn, _stream())
+    wsp, wsn, stream = _scratch(workspace, need, x.device)
+    st = mcn_pool_backward(desc, x.data_ptr(), dzdy.data_ptr(), dzdx.data_ptr(), wsp, wsn, stream)
     if st:
         raise McnError(st, "mcn_pool_backward")
     return dzdx

@@ -322,9 +322,14 @@ _KNOWN_MOST = 512
 _known = {}
 
 
+def _ints(v):
+    """The numbers of a shape, strides or pads, whatever holds them (tensors among them, which may hold others by the next call)."""
+    return tuple(map(int, v))
+
+
 def _conv(xshape, wshape, stride, pad, precision, op):
     """(descriptor, shape of y, bytes of scratch) of a pass of a convolution layer."""
-    key = (op, tuple(xshape), tuple(wshape), tuple(stride), tuple(pad), precision)
+    key = (op, _ints(xshape), _ints(wshape), _ints(stride), _ints(pad), int(precision))
     got = _known.get(key)
     if got is None:
         desc = make_desc(xshape, wshape, stride, pad, precision)
@@ -335,7 +340,7 @@ def _conv(xshape, wshape, stride, pad, precision, op):
 
 def _convt(xshape, fshape, upsample, crop, groups, precision, op):
     """The same for the transpose block."""
-    key = ("t", op, tuple(xshape), tuple(fshape), tuple(upsample), tuple(crop), groups, precision)
+    key = ("t", op, _ints(xshape), _ints(fshape), _ints(upsample), _ints(crop), int(groups), int(precision))
     got = _known.get(key)
     if got is None:
         desc = make_convt_desc(xshape, fshape, upsample, crop, groups, precision)
@@ -346,7 +351,7 @@ def _convt(xshape, fshape, upsample, crop, groups, precision, op):
 
 def _pool(xshape, window, stride, pad, method, backward):
     """The same for the pooling block; the forward pass has no scratch."""
-    key = ("p", backward, tuple(xshape), tuple(window), tuple(stride), tuple(pad), method)
+    key = ("p", backward, _ints(xshape), _ints(window), _ints(stride), _ints(pad), int(method))
     got = _known.get(key)
     if got is None:
         desc = make_pool_desc(xshape, window, stride, pad, method)

@@ -467,8 +467,9 @@ def conv_backward_filter_bias(x, wshape, dzdy, stride=(1, 1), pad=(0, 0, 0, 0), 
     _check(x, None, "x")
     desc, ysh, need = _conv(x.shape, wshape, stride, pad, precision, MCN_OP_BACKWARD_FILTER_BIAS)
     _check(dzdy, ysh, "dzdy")
-    dzdw = _out(None if out is None else out[0], tuple(wshape), x.device, "out[0]")
-    dzdb = _out(None if out is None else out[1], (wshape[0],), x.device, "out[1]")
+    if out is not None:
+        _check(out[0], tuple(wshape), "out[0]"); _check(out[1], (wshape[0],), "out[1]")
+    dzdw, dzdb = (out[0], out[1]) if out is not None else (_out(None, tuple(wshape), x.device), _out(None, (wshape[0],), x.device))
     wsp, wsn, stream = _scratch(workspace, need, x.device)
     st = mcn_conv_backward_filter_bias(desc, x.data_ptr(), dzdy.data_ptr(), dzdw.data_ptr(), dzdb.data_ptr(), wsp, wsn, stream)
     if st:

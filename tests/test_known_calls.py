@@ -30,3 +30,15 @@ def test_shapes_in_any_sequence():
     for hold in (list, np.array, torch.Size, lambda v: [np.int64(n) for n in v]):
         got = B._conv(hold(XS), hold(WS), [2, 1], [1, 0, 1, 0], B.MCN_PREC_FP32, B.MCN_OP_FORWARD)
         assert bytes(got[0]) == bytes(want[0]) and got[1:] == want[1:]
+
+
+@pytest.mark.gpu
+def test_filter_and_bias_outputs_come_both():
+    x, p = torch.ones(XS, device="cuda"), torch.ones(2, 40, 22, 18, device="cuda")
+    out = torch.empty(WS, device="cuda"), torch.empty(40, device="cuda")
+    print("outputs of the filter and bias derivative", flush=True)
+    got = B.conv_backward_filter_bias(x, WS, p, out=out)
+    assert got[0] is out[0] and got[1] is out[1] and torch.equal(got[1], torch.full_like(got[1], 2.0 * 22 * 18))
+    for bad in ((None, out[1]), (out[0], None)):
+        with pytest.raises(TypeError):
+            B.conv_backward_filter_bias(x, WS, p, out=bad)

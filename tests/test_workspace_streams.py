@@ -64,6 +64,14 @@ def test_graph_leaves_the_kept_buffers_alone(monkeypatch):
     assert _get(1000) == a
 
 
+@pytest.mark.parametrize("gone", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_without_the_private_names(monkeypatch, gone):
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0)
+    monkeypatch.delattr(torch._C, gone)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 77}))
+    assert B._stream() == 77
+
+
 # Input derivatives of strided layers (packed weights of four phases and shared tiles in scratch) and bias derivatives (partial sums).
 LAYERS = [((4, 64, 48, 48), (256, 64, 6, 6), (2, 2), (2, 2, 2, 2)), ((3, 40, 20, 23), (70, 40, 3, 3), (2, 2), (1, 0, 0, 1)),
           ((2, 96, 30, 28), (128, 96, 3, 3), (1, 1), (1, 1, 1, 1)), ((5, 48, 33, 41), (80, 48, 5, 4), (2, 3), (0, 1, 1, 0))]

@@ -908,12 +908,13 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
                 const int NO = TIQ * MC * NP;
                 if (NO & 1) continue;
                 if (NP > 1 && NP > (v.N + 1) / 2) continue;
-                const int TI = (v.Ho + RB - 1) / RB < 4 * TIQ ? (v.Ho + RB - 1) / RB : 4 * TIQ;      // rows shared out evenly
+                int TI = (v.Ho + RB - 1) / RB < 4 * TIQ ? (v.Ho + RB - 1) / RB : 4 * TIQ;      // rows shared out evenly
                 const int YW = TK * NO;
                 if (YW > most_y * threads) break;
                 const int SC = (MC - 1) * v.Sw + v.Wf;
-                // by 16-byte loads rows of x above the patch's first one come as whole quads, none of which may begin above the plane and reach into it
-                if (tile.planes == 1 && RB > 1 && TI < XL) continue;
+                // by 16-byte loads rows of x above the patch's first one come as whole quads, none of which may begin above the plane and reach into it:
+                // where a second patch still reaches above it, patches are whole quads too
+                if (tile.planes == 1 && RB > 1 && TI < XL) TI = 4 * TIQ;
                 const int XQ = (4 * TIQ - 1 + (v.Hf - 1 + XL - v.Pt) / v.Sh) / 4 + 1;        // quads of a phase
                 const int64_t XW1 = (int64_t)NCH * NP * NPH * XQ;
                 const int step = MC * v.Sw < SC ? MC * v.Sw : SC, RC = 2 * SC;

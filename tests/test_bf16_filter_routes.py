@@ -1,0 +1,51 @@
+"""Layers whose filter derivative takes operands rounded to bf16 whatever their pads and sizes: vertical stride 1, filters of at most five rows, more than 32
+filters a group.  Their route is asked for on the host; on the GPU the smaller ones are compared with the oracle."""
+import pytest
+import torch
+
+import oracle
+from paper_1412_4564_amd import binding as B
+from paper_1412_4564_amd import synth
+
+import parity_util as U
+
+BF = B.MCN_PREC_BF16
+
+SMALL = [
+    # H  W  D  N  Hf Wf Df K   stride  pad
+    # pads above the plane that several patches of rows reach into
+    (12, 6, 1, 5, 1, 2, 1, 220, (1, 1), (28, 25, 2, 0)),
+    (23, 10, 90, 3, 3, 3, 90, 140, (1, 1), (40, 8, 1, 4)),
+    (16, 27, 48, 2, 3, 3, 12, 100, (1, 1), (19, 3, 5, 0)),
+    (2, 5, 96, 5, 3, 5, 48, 102, (1, 2), (32, 2, 0, 2)),
+    (109, 19, 65, 3, 1, 1, 65, 39, (1, 1), (29, 6, 0, 0)),
+    (44, 13, 5, 4, 1, 3, 5, 152, (1, 1), (28, 0, 1, 4)),
+]
+
+
+def _layer(case):
+    H, W, D, N, Hf, Wf, Df, K, st, pad = case
+    return dict(H=H, W=W, D=D, N=N, Hf=Hf, Wf=Wf, Df=Df, K=K, stride=st, pad=pad)
+
+
+@pytest.mark.parametrize("case", SMALL)
+def test_route(case):
+    L = _layer(case)
+    d = B.make_desc((L["N"], L["D"], L["W"], L["H"]), (L["K"], L["Df"], L["Wf"], L["Hf"]), L["stride"], L["pad"], BF)
+    assert B.mcn_conv_kernel_name(d, B.MCN_OP_BACKWARD_FILTER) == "wgrad_bf16" and B.mcn_conv_operand_planes(d, B.MCN_OP_BACKWARD_FILTER) == 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(SMALL)))
+def test_small_layers(case):
+    L = dict(_layer(SMALL[case]), config=8, index=300 + case)
+    x, w = synth.make_x(L), synth.make_w(L)
+    ho, wo = oracle.output_size(x.shape, w.shape, L["stride"], L["pad"])
+    p = synth.make_dzdy(L, ho, wo)
+    print("bf16 filter derivative", SMALL[case], flush=True)
+    got = B.conv_backward_filter(x.cuda(), w.shape, p.cuda(), L["stride"], L["pad"], BF).cpu().numpy()
+    xr, pr = (U.np64(t.to(torch.bfloat16).to(torch.float32)) for t in (x, p))
+    ref = oracle.backward_filter(xr, w.shape, pr, L["stride"], L["pad"])
+    den = oracle.backward_filter(abs(xr), w.shape, abs(pr), L["stride"], L["pad"])
+    # sums of products that fp32 holds exactly: n * 2^-24 of the sum of absolute values at most, n < 2^13 products with a sample of the plane
+    assert U.norm_err(got, ref, den) <= 2.0 ** -11

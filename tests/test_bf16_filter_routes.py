@@ -16,9 +16,9 @@ SMALL = [
     # pads above the plane that several patches of rows reach into
     (12, 6, 1, 5, 1, 2, 1, 220, (1, 1), (28, 25, 2, 0)),
     (23, 10, 90, 3, 3, 3, 90, 140, (1, 1), (40, 8, 1, 4)),
-    (16, 27, 48, 2, 3, 3, 12, 100, (1, 1), (19, 3, 5, 0)),
+    (16, 27, 48, 2, 3, 3, 12, 140, (1, 1), (19, 3, 5, 0)),
     (2, 5, 96, 5, 3, 5, 48, 102, (1, 2), (32, 2, 0, 2)),
-    (109, 19, 65, 3, 1, 1, 65, 39, (1, 1), (29, 6, 0, 0)),
+    (109, 19, 325, 2, 1, 1, 325, 39, (1, 1), (29, 6, 0, 0)),
     (44, 13, 5, 4, 1, 3, 5, 152, (1, 1), (28, 0, 1, 4)),
 ]
 

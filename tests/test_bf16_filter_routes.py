@@ -20,6 +20,12 @@ SMALL = [
     (2, 5, 96, 5, 3, 5, 48, 102, (1, 2), (32, 2, 0, 2)),
     (109, 19, 325, 2, 1, 1, 325, 39, (1, 1), (29, 6, 0, 0)),
     (44, 13, 5, 4, 1, 3, 5, 152, (1, 1), (28, 0, 1, 4)),
+    # one column of at most four rows, one or two images: an odd number of octets
+    (4, 2, 30, 1, 2, 2, 30, 158, (1, 1), (0, 0, 0, 0)),
+    (3, 1, 212, 2, 3, 1, 53, 148, (1, 1), (0, 1, 0, 0)),
+    (2, 2, 7, 1, 1, 1, 7, 374, (1, 1), (0, 0, 0, 0)),
+    (1, 3, 4, 2, 1, 1, 1, 248, (1, 3), (0, 0, 0, 0)),
+    (9, 3, 16, 1, 1, 2, 16, 65, (1, 2), (1, 2, 0, 0)),
 ]
 
 

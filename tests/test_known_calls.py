@@ -34,7 +34,7 @@ def test_shapes_in_any_sequence():
 
 @pytest.mark.gpu
 def test_filter_and_bias_outputs_come_both():
-    x, p = torch.ones(XS, device="cuda"), torch.ones(2, 40, 22, 18, device="cuda")
+    x, p = torch.ones(XS, device="cuda"), torch.ones(2, 40, 18, 22, device="cuda")
     out = torch.empty(WS, device="cuda"), torch.empty(40, device="cuda")
     print("outputs of the filter and bias derivative", flush=True)
     got = B.conv_backward_filter_bias(x, WS, p, out=out)

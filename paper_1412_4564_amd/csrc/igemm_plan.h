@@ -904,11 +904,11 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
         const int RB = (v.Ho + 4 * TIQ - 1) / (4 * TIQ);
         if (TIQ > 1 && (v.Ho + 4 * TIQ - 5) / (4 * TIQ - 4) == RB) continue;          // fewer rows give the same row blocks
         for (int NP = 1; NP <= 4; NP *= 2)
-            // one plane: a second column, beyond the only one, where nothing else makes the octets even
-            for (int MC = 1; (MC <= v.Wo || (tile.planes == 1 && MC == 2 && best >= 1e300)) && TIQ * MC * NP <= 32; ++MC) {
+            for (int MC = 1; MC <= v.Wo && TIQ * MC * NP <= 32; ++MC) {
                 const int NO = TIQ * MC * NP;
                 if (NO & 1) continue;
-                if (NP > 1 && NP > (v.N + 1) / 2) continue;
+                // one plane: a second pair of images that there is not, where nothing else makes the octets even
+                if (NP > 1 && NP > (v.N + 1) / 2 && !(tile.planes == 1 && NP == 2 && MC == 1 && best >= 1e300)) continue;
                 int TI = (v.Ho + RB - 1) / RB < 4 * TIQ ? (v.Ho + RB - 1) / RB : 4 * TIQ;      // rows shared out evenly
                 const int YW = TK * NO;
                 if (YW > most_y * threads) break;

@@ -26,6 +26,8 @@ SMALL = [
     (2, 2, 7, 1, 1, 1, 7, 374, (1, 1), (0, 0, 0, 0)),
     (1, 3, 4, 2, 1, 1, 1, 248, (1, 3), (0, 0, 0, 0)),
     (9, 3, 16, 1, 1, 2, 16, 65, (1, 2), (1, 2, 0, 0)),
+    # the same where two columns of x are more than a unit holds
+    (3, 74, 558, 2, 3, 2, 279, 76, (1, 11), (0, 0, 0, 0)),
 ]
 
 

@@ -174,8 +174,10 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf1
                 const int io0 = rb * P.TI, jo0 = jc * P.MC, n0 = ib * 2 * P.NP;
                 const long long xb = (long long)n0 * P.xsn + (long long)xch * P.xsc + (long long)(jo0 * P.Sw - P.Pl + first) * P.xsj + (io0 - P.XL);
                 const long long yb = (long long)n0 * P.ysn + (long long)ych * P.ysc + (long long)jo0 * P.ysj + io0;
-                xp = reinterpret_cast<const char *>(x) + 4 * xb; xleft = bytes_left(P.xtot - xb);
-                yp = reinterpret_cast<const char *>(dzdy) + 4 * yb; yleft = bytes_left(P.ytot - yb);
+                // bytes: limited where the sweep's first column would begin, to which the next block of rows goes back
+                const int xon = jo0 * P.Sw * P.xsj, yon = jo0 * P.ysj;
+                xp = reinterpret_cast<const char *>(x) + 4 * xb; xleft = bytes_left(P.xtot - (xb - xon)) - 4 * xon;
+                yp = reinterpret_cast<const char *>(dzdy) + 4 * yb; yleft = bytes_left(P.ytot - (yb - yon)) - 4 * yon;
             }
             moved = false;
             // The words' offsets are those of the sweep before if the same rows of them are there.  LINEAR: rows that are not there meet rows of

@@ -782,6 +782,8 @@ constexpr WgradSplitTile WGS_TILES[] = {
     {1, 128, 384, 7, 4, 0, 0}, {1, 128, 256, 7, 4, 3, 6}, {1, 128, 128, 7, 4, 4, 4},
     {1, 64, 768, 4, 6, 0, 0},  {1, 64, 512, 4, 6, 0, 0},  {1, 64, 256, 4, 4, 2, 6}};
 constexpr int WGS_N_TILES = 9;
+// tiles of one plane that have an instantiation for images whose offsets fit 31 bits one by one only
+constexpr bool wgb_far(int shape) { return shape == WGB_128x128 || shape == WGB_64x256; }
 // LDS per buffer of dzdy; one plane: and a place for the octets that a thread does not have
 inline int wgs_dzdy_bytes(const WgradSplitTile &t, int PYW) { return t.planes == 1 ? (t.TK * PYW + 1) * 16 : t.TK * PYW * 48; }
 constexpr int WGB_MAX_HF = 5;      // filter heights whose derivative takes operands rounded to bf16
@@ -790,6 +792,7 @@ struct WgradSplitPlan {
     int shape;
     int TK, TR;
     bool linear;
+    bool far;                // one plane: images in 31 bits one by one (wgrad_bf16_kernel)
     int NCH;                 // channels of the slab
     WgradSplitParams P;
     size_t lds_bytes;
@@ -926,6 +929,14 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
                 const size_t lds = 2 * (size_t)wgs_dzdy_bytes(tile, PYW) + (size_t)XPL * 4 * tile.planes + 16;
                 if (lds > IGEMM_LDS_LIMIT) break;
                 const int CC = (v.Wo + MC - 1) / MC, IB = (v.N + 2 * NP - 1) / (2 * NP);
+                bool far = false;
+                if (tile.planes == 1) {
+                    // bytes of a unit's images in 31 bits, with the columns that a sweep moves over; else one pair, an image in 31 bits and such a move in 30
+                    const double xcol = 4.0 * v.H, ycol = 4.0 * v.Ho, ximage = xcol * v.W * v.Ctot, yimage = ycol * v.Wo * v.Ktot, moves = (double)CC * MC * v.Sw + v.Pl + SC;
+                    far = 2 * NP * ximage + xcol * moves >= 2147483647.0 || 2 * NP * yimage >= 2147483647.0;
+                    if (far && (NP > 1 || !wgb_far(shape) || ximage >= 2147483647.0 || yimage >= 2147483647.0 || xcol * (moves + 1) + ycol >= 1073741824.0 ||
+                                ycol * ((double)CC * MC + 2) >= 1073741824.0 || xcol * ((double)v.W * NCH + v.Pl) >= 2147483647.0)) break;
+                }
                 // Microseconds of a unit: its MFMAs, splitting what it stages, fetching that (memory lines of 128 bytes), and of the
                 // whole call.
                 const int64_t NU = (int64_t)RB * CC * IB, total = tiles * NU;
@@ -961,6 +972,7 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
                 }
                 if (us < best) {
                     best = us;
+                    pl->far = far;
                     B.TI = TI; B.RB = RB; B.MC = MC; B.CC = CC; B.SC = SC; B.NP = NP; B.IB = IB; B.TIQ = TIQ; B.NO = NO; B.PYW = PYW; B.nchunks = nchunks; B.nblocks = nblocks;
                     B.NPH = NPH; B.XQ = XQ; B.PHP = PHP; B.COLP = COLP; B.MPP = MPP; B.CHP = CHP; B.YW = YW; B.XW1 = (int)XW1; B.XL = XL; B.RC = RC; B.step = step;
                 }
@@ -975,8 +987,7 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
     P.xsj = v.H; P.xsc = v.H * v.W; P.xsn = v.H * v.W * v.Ctot; P.xtot = (long long)P.xsn * v.N;
     P.ysj = v.Ho; P.ysc = v.Ho * v.Wo; P.ysn = v.Ho * v.Wo * v.Ktot; P.ytot = (long long)P.ysn * v.N;
     // 32-bit byte offsets inside a unit's images
-    if (tile.planes == 1 && (double)v.H * ((double)v.W * v.Ctot * 2 * P.NP + (double)P.CC * P.MC * v.Sw + v.Pl + P.SC) * 4 >= 2147483647.0) return false;
-    if ((double)v.H * v.W * v.Ctot * 8 * P.NP >= 2147483647.0 || (double)v.Ho * v.Wo * v.Ktot * 8 * P.NP >= 2147483647.0) return false;
+    if (tile.planes == 3 && ((double)v.H * v.W * v.Ctot * 8 * P.NP >= 2147483647.0 || (double)v.Ho * v.Wo * v.Ktot * 8 * P.NP >= 2147483647.0)) return false;
     P.KT = KT; P.RT = RT; P.R = R; P.tiles = (int)tiles;
     const int64_t NU = (int64_t)P.RB * P.CC * P.IB;
     if (NU >= ((int64_t)1 << 30)) return false;

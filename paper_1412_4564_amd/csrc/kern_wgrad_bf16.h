@@ -31,7 +31,9 @@ struct WgradBf16Params : WgradSplitParams {
 
 // YT, XT: octets of dzdy and of new slab columns that a staging thread brings per unit, at most.
 // LINEAR: 1x1 filters, no row of x but those of dzdy is met (no padding, no more output rows than input rows).
-template <int WK, int WR, int MK, int MR, int YT, int XT, bool LINEAR>
+// FAR: a unit's images do not fit 31-bit offsets together, one pair of them (NP = 1) with a base for each image does; two more scalars for each
+// array, which took 2 % of the time where nothing needs them.
+template <int WK, int WR, int MK, int MR, int YT, int XT, bool LINEAR, bool FAR>
 __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf16_kernel(WgradBf16Params P, const float *__restrict__ x,
                                                                                       const float *__restrict__ dzdy, float *out,
                                                                                       float *__restrict__ part) {
@@ -131,14 +133,14 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf1
             x_lds[s] = w.lds + w.col * colB;
         }
         // The unit to request: where it is, and where the arrays' bases are (its first row and column; x: the first row of the slab and the first
-        // column that the unit adds), with the bytes behind them
+        // column that the unit adds; of a pair's first image), with the bytes behind them (FAR: of either image)
         int klim = 0, nch = 0, xch = 0, ych = 0;
         int jr = div32(uu, P.dCC), jc = uu - jr * P.CC, ib = div32(jr, P.dRB), rb = jr - ib * P.RB;
         bool new_tile = true, start = true;                 // start: it shares no column with the one before
         const char *xp = nullptr, *yp = nullptr;
         bool moved = false;                // the bases are those of the sweep
         const int xdown = 4 * (P.TI - P.CC * P.MC * P.Sw * P.xsj), ydown = 4 * (P.TI - P.CC * P.MC * P.ysj);       // from behind a sweep to the next block of rows
-        int xleft = 0, yleft = 0, rows = 0, below = 0;        // below: rows that the plane has from the slab's first one on
+        int xleft[FAR ? 2 : 1] = {}, yleft[FAR ? 2 : 1] = {}, rows = 0, below = 0;        // below: rows that the plane has from the slab's first one on
         unsigned vy[YT], vx[XT];           // byte offsets of the words, or out of range (images past the last one lie behind the array)
         auto set_tile = [&](int tt) __attribute__((always_inline)) {
             const int q = div32(tt, P.dRT), rt = tt - q * P.RT, g = div32(q, P.dKT), kt = q - g * P.KT;
@@ -149,20 +151,30 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf1
             ych = g * P.Kg + kt * TK;
             new_tile = true;
         };
-        auto bytes_left = [&](long long elements) __attribute__((always_inline)) { return elements > 0x1fffffff ? 0x7fffffff : elements < 0 ? 0 : (int)(4 * elements); };
+        // FAR: below zero where the image is not there, so that a sweep's first columns, at lower addresses, are found absent too
+        auto bytes_left = [&](long long elements) __attribute__((always_inline)) {
+            constexpr long long LEAST = FAR ? -0x10000000 : 0;
+            return elements > 0x1fffffff ? 0x7fffffff : (int)(4 * max(elements, LEAST));
+        };
+        auto left_of = [&](const int (&left)[FAR ? 2 : 1], int sn, int i) __attribute__((always_inline)) { return FAR ? left[FAR ? i : 0] : left[0] - i * 4 * sn; };
+        auto move = [&](int xby, int yby) __attribute__((always_inline)) {
+            xp += xby; yp += yby;
+#pragma unroll
+            for (int i = 0; i < (FAR ? 2 : 1); ++i) { xleft[i] -= xby; yleft[i] -= yby; }
+        };
         auto words_there = [&]() __attribute__((always_inline)) {
             Args &P = *args();
 #pragma unroll
             for (int s = 0; s < YT; ++s) {
                 const int k = y_at[s] & 255, row = y_at[s] >> 8 & 255, m = y_at[s] >> 16 & 255, col = y_at[s] >> 24;
-                vy[s] = ((k < klim) & (LINEAR | (row < rows))) ? 4u * (unsigned)(k * P.ysc + col * P.ysj + row + 2 * m * P.ysn) : SLAB_INVALID;
+                vy[s] = ((k < klim) & (LINEAR | (row < rows))) ? 4u * ((unsigned)k * P.ysc + (unsigned)col * P.ysj + row + 2u * m * P.ysn) : SLAB_INVALID;
             }
 #pragma unroll
             for (int s = 0; s < XT; ++s) {
                 const int c = x_at[s] & 0x3ff, row = x_row(x_at[s]), m = x_at[s] >> 22 & 3, col = x_at[s] >> 24;
                 // a word begins on a row of the plane or lies wholly above or below it (plan_wgrad_split_shape)
                 const bool ok = (c < nch) & (x_at[s] != ABSENT) & (LINEAR | ((unsigned)(row - (below - P.H)) < (unsigned)P.H));
-                vx[s] = ok ? 4u * (unsigned)(c * P.xsc + col * P.xsj + row + 2 * m * P.xsn) : SLAB_INVALID;
+                vx[s] = ok ? 4u * ((unsigned)c * P.xsc + (unsigned)col * P.xsj + row + 2u * m * P.xsn) : SLAB_INVALID;
             }
         };
         auto set_sweep = [&]() __attribute__((always_inline)) {
@@ -176,8 +188,13 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf1
                 const long long yb = (long long)n0 * P.ysn + (long long)ych * P.ysc + (long long)jo0 * P.ysj + io0;
                 // bytes: limited where the sweep's first column would begin, to which the next block of rows goes back
                 const int xon = jo0 * P.Sw * P.xsj, yon = jo0 * P.ysj;
-                xp = reinterpret_cast<const char *>(x) + 4 * xb; xleft = bytes_left(P.xtot - (xb - xon)) - 4 * xon;
-                yp = reinterpret_cast<const char *>(dzdy) + 4 * yb; yleft = bytes_left(P.ytot - (yb - yon)) - 4 * yon;
+                xp = reinterpret_cast<const char *>(x) + 4 * xb;
+                yp = reinterpret_cast<const char *>(dzdy) + 4 * yb;
+#pragma unroll
+                for (int i = 0; i < (FAR ? 2 : 1); ++i) {
+                    xleft[i] = bytes_left(P.xtot - (xb - xon) - i * P.xsn) - 4 * xon;
+                    yleft[i] = bytes_left(P.ytot - (yb - yon) - i * P.ysn) - 4 * yon;
+                }
             }
             moved = false;
             // The words' offsets are those of the sweep before if the same rows of them are there.  LINEAR: rows that are not there meet rows of
@@ -208,7 +225,7 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf1
         // that it has a unit's time to come.
         Row4 yv[YT][2], xv[XT][2];
         bool c_start = false;              // of that unit
-        int c_rows = 0, c_below = 0, c_nch = 0, c_j0 = 0, c_xleft = 0;
+        int c_rows = 0, c_below = 0, c_nch = 0, c_j0 = 0, c_xleft[FAR ? 2 : 1] = {};
         const char *c_xp = nullptr;
         int ring = first;                  // the column of the ring where those that it adds begin
         // A sweep's first unit: the columns that a unit otherwise finds in place.  Requested and written here, while the unit before is computed: held
@@ -225,10 +242,10 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf1
                     const int q = q0 + NL * s;
                     w[s] = slab_word(P, q);
                     const bool ok = (q < extra) & (w[s].c < c_nch) & ((unsigned)(c_j0 + w[s].col) < (unsigned)P.W) & ((unsigned)(w[s].row - (c_below - P.H)) < (unsigned)P.H);
-                    const unsigned off = ok ? 4u * (unsigned)(w[s].c * P.xsc + w[s].col * P.xsj + w[s].row + 2 * w[s].m * P.xsn) : SLAB_INVALID;
+                    const unsigned off = ok ? 4u * ((unsigned)w[s].c * P.xsc + (unsigned)w[s].col * P.xsj + w[s].row + 2u * w[s].m * P.xsn) : SLAB_INVALID;
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
-                        v[s][i] = load(__builtin_amdgcn_make_buffer_rsrc((void *)(c_xp + 4ll * i * P.xsn - back), 0, max(c_xleft > 0x7fffffff - back ? 0x7fffffff : c_xleft + back - i * 4 * P.xsn, 0), BUFFER_FLAGS), off);
+                        v[s][i] = load(__builtin_amdgcn_make_buffer_rsrc((void *)(c_xp + 4ll * i * P.xsn - back), 0, max(c_xleft[FAR ? i : 0] > 0x7fffffff - back ? 0x7fffffff : left_of(c_xleft, P.xsn, i) + back, 0), BUFFER_FLAGS), off);
                 }
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
@@ -245,8 +262,8 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf1
             __amdgpu_buffer_rsrc_t yrs[2], xrs[2];         // of a pair's images
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                yrs[i] = __builtin_amdgcn_make_buffer_rsrc((void *)(yp + 4ll * i * P.ysn), 0, max(yleft - i * 4 * P.ysn, 0), BUFFER_FLAGS);
-                xrs[i] = __builtin_amdgcn_make_buffer_rsrc((void *)(xp + 4ll * i * P.xsn), 0, max(xleft - i * 4 * P.xsn, 0), BUFFER_FLAGS);
+                yrs[i] = __builtin_amdgcn_make_buffer_rsrc((void *)(yp + 4ll * i * P.ysn), 0, max(left_of(yleft, P.ysn, i), 0), BUFFER_FLAGS);
+                xrs[i] = __builtin_amdgcn_make_buffer_rsrc((void *)(xp + 4ll * i * P.xsn), 0, max(left_of(xleft, P.xsn, i), 0), BUFFER_FLAGS);
             }
             const unsigned ycols = (unsigned)min(max(P.Wo - jc * P.MC, 0), 255) << 24;
             const int j0 = jc * P.MC * P.Sw - P.Pl + first, xlo = min(max(-j0, 0), 255), xhi = min(max(P.W - j0, xlo), 255);
@@ -283,14 +300,16 @@ __global__ __launch_bounds__(64 * (WK * WR + WGS_STAGE_WAVES), 3) void wgrad_bf1
                     if (ring >= P.RC) ring -= P.RC;
                 }
                 c_start = start; c_rows = LINEAR ? min(P.TI, P.Ho - rb * P.TI) : rows; c_below = below;
-                if constexpr (!LINEAR) { c_nch = nch; c_j0 = j0 - first; c_xp = xp; c_xleft = xleft; }
+                if constexpr (!LINEAR) {
+                    c_nch = nch; c_j0 = j0 - first; c_xp = xp;
+#pragma unroll
+                    for (int i = 0; i < (FAR ? 2 : 1); ++i) c_xleft[i] = xleft[i];
+                }
                 start = false;
-                xp += 4 * P.MC * P.Sw * P.xsj; xleft -= 4 * P.MC * P.Sw * P.xsj;
-                yp += 4 * P.MC * P.ysj; yleft -= 4 * P.MC * P.ysj;
+                move(4 * P.MC * P.Sw * P.xsj, 4 * P.MC * P.ysj);
                 if (++jc == P.CC) {
                     jc = 0; start = !LINEAR; moved = true;
-                    xp += xdown; xleft -= xdown;
-                    yp += ydown; yleft -= ydown;
+                    move(xdown, ydown);
                     if (++rb == P.RB) {
                         rb = 0; moved = false; start = true;
                         if (++ib == P.IB) { ib = 0; if (++t < P.tiles) set_tile(t); }

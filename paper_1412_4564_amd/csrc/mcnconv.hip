@@ -527,7 +527,7 @@ int launch_wgrad(const WgradPlan &pl, const float *x, const float *dzdy, const f
 }
 
 // on the bf16 matrix core: fp32 operands in three planes (kern_wgrad_split.h), or rounded to bf16 (kern_wgrad_bf16.h)
-template <int SHAPE, int WK, int WR, int MK, int MR, int YT, int XT, bool LINEAR>
+template <int SHAPE, int WK, int WR, int MK, int MR, int YT, int XT, bool LINEAR, bool FAR = false>
 int launch_wgrad_split_inst(const WgradSplitPlan &pl, const float *x, const float *dzdy, const float *rbias, float *out, float *part,
                             hipStream_t s, int relu) {
     constexpr WgradSplitTile TILE = WGS_TILES[SHAPE];
@@ -536,7 +536,7 @@ int launch_wgrad_split_inst(const WgradSplitPlan &pl, const float *x, const floa
     (WgradSplitParams &)P = pl.P;
     P.relu = relu;
     const void *kern;
-    if constexpr (TILE.planes == 1) kern = (const void *)wgrad_bf16_kernel<WK, WR, MK, MR, YT, XT, LINEAR>;
+    if constexpr (TILE.planes == 1) kern = (const void *)wgrad_bf16_kernel<WK, WR, MK, MR, YT, XT, LINEAR, FAR>;
     else kern = (const void *)wgrad_split_kernel<WK, WR, MK, YT, XT, LINEAR>;
     if (pl.lds_bytes > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_bytes);
@@ -546,7 +546,7 @@ int launch_wgrad_split_inst(const WgradSplitPlan &pl, const float *x, const floa
     if constexpr (TILE.planes == 1) {
         P.dNO = make_div32(P.NO); P.dTIQ = make_div32(P.TIQ); P.dMC = make_div32(P.MC); P.dT = make_div32(P.Hf * P.Wf); P.dHf = make_div32(P.Hf);
         P.dCC = make_div32(P.CC); P.dRB = make_div32(P.RB); P.dTiles = make_div32(P.tiles); P.dKT = make_div32(P.KT); P.dRT = make_div32(P.RT);
-        hipLaunchKernelGGL((wgrad_bf16_kernel<WK, WR, MK, MR, YT, XT, LINEAR>), grid, block, pl.lds_bytes, s, P, x, dzdy, out, part);
+        hipLaunchKernelGGL((wgrad_bf16_kernel<WK, WR, MK, MR, YT, XT, LINEAR, FAR>), grid, block, pl.lds_bytes, s, P, x, dzdy, out, part);
     } else
         hipLaunchKernelGGL((wgrad_split_kernel<WK, WR, MK, YT, XT, LINEAR>), grid, block, pl.lds_bytes, s, (const WgradSplitParams &)P, x, dzdy, rbias, out, part);
     int st = check_launch();
@@ -558,6 +558,10 @@ template <int SHAPE, int WK, int WR, int MK, int MR>
 int launch_wgrad_split_shape(const WgradSplitPlan &pl, const float *x, const float *dzdy, const float *rbias, float *out, float *part,
                              hipStream_t s, int relu) {
     constexpr WgradSplitTile T = WGS_TILES[SHAPE];
+    if constexpr (wgb_far(SHAPE))
+        if (pl.far)
+            return pl.linear ? launch_wgrad_split_inst<SHAPE, WK, WR, MK, MR, T.YTL, T.XTL, true, true>(pl, x, dzdy, rbias, out, part, s, relu)
+                             : launch_wgrad_split_inst<SHAPE, WK, WR, MK, MR, T.YT, T.XT, false, true>(pl, x, dzdy, rbias, out, part, s, relu);
     if (pl.linear) {
         if constexpr (T.YTL > 0) return launch_wgrad_split_inst<SHAPE, WK, WR, MK, MR, T.YTL, T.XTL, true>(pl, x, dzdy, rbias, out, part, s, relu);
         return MCN_BAD_ARG;

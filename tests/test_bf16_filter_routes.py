@@ -30,13 +30,27 @@ SMALL = [
     (3, 74, 558, 2, 3, 2, 279, 76, (1, 11), (0, 0, 0, 0)),
 ]
 
+# Images of more than 512 MiB, one and two pairs of which are too much for the offsets of a unit
+LARGE = [
+    (60, 2289, 6, 4, 3, 2, 6, 961, (1, 1), (4, 9, 9, 3)),
+    (844, 485, 160, 5, 3, 1, 80, 654, (1, 1), (1, 3, 0, 0)),
+    (691, 656, 848, 1, 1, 1, 212, 680, (1, 2), (3, 1, 0, 1)),
+    (2935, 3813, 13, 2, 2, 7, 13, 35, (1, 1), (3, 3, 2, 3)),
+    (1036, 3264, 76, 2, 3, 3, 38, 158, (1, 1), (3, 2, 3, 1)),
+    (83410, 25, 234, 2, 2, 1, 234, 68, (1, 1), (0, 0, 0, 0)),
+    (1387, 2399, 9, 1, 3, 2, 9, 101, (1, 1), (1, 1, 1, 1)),
+    # of dzdy and of x; three of them: the last one has no other in its pair
+    (701, 1103, 8, 3, 3, 1, 8, 450, (1, 1), (1, 1, 0, 0)),
+    (823, 821, 403, 3, 2, 2, 403, 34, (1, 1), (2, 0, 0, 1)),
+]
+
 
 def _layer(case):
     H, W, D, N, Hf, Wf, Df, K, st, pad = case
     return dict(H=H, W=W, D=D, N=N, Hf=Hf, Wf=Wf, Df=Df, K=K, stride=st, pad=pad)
 
 
-@pytest.mark.parametrize("case", SMALL)
+@pytest.mark.parametrize("case", SMALL + LARGE)
 def test_route(case):
     L = _layer(case)
     d = B.make_desc((L["N"], L["D"], L["W"], L["H"]), (L["K"], L["Df"], L["Wf"], L["Hf"]), L["stride"], L["pad"], BF)
@@ -57,3 +71,25 @@ def test_small_layers(case):
     den = oracle.backward_filter(abs(xr), w.shape, abs(pr), L["stride"], L["pad"])
     # sums of products that fp32 holds exactly: n * 2^-24 of the sum of absolute values at most, n < 2^13 products with a sample of the plane
     assert U.norm_err(got, ref, den) <= 2.0 ** -11
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", LARGE[-2:])
+def test_large_images(case):
+    H, W, D, N, Hf, Wf, Df, K, st, pad = case
+    g = torch.Generator(device="cuda").manual_seed(H)
+    Ho, Wo = oracle.output_size((N, D, W, H), (K, Df, Wf, Hf), st, pad)
+    # -1, 0 and 1: sums of some two million products are exact in fp32
+    x, p = (torch.randint(-1, 2, s, device="cuda", generator=g).float() for s in ((N, D, W, H), (N, K, Wo, Ho)))
+    print("bf16 filter derivative, large images", case, flush=True)
+    got = B.conv_backward_filter(x, (K, Df, Wf, Hf), p, st, pad, BF)
+    ref = torch.zeros_like(got)
+    for n in range(N):
+        for j in range(Wo):
+            for fj in range(Wf):
+                if not 0 <= j + fj - pad[2] < W:
+                    continue
+                for fi in range(Hf):
+                    lo, hi = max(0, pad[0] - fi), min(Ho, H + pad[0] - fi)       # rows of dzdy that meet one of x
+                    ref[:, :, fj, fi] += p[n, :, j, lo:hi].contiguous() @ x[n, :, j + fj - pad[2], lo + fi - pad[0]:hi + fi - pad[0]].contiguous().T
+    assert torch.equal(got, ref)

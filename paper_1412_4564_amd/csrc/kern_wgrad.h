@@ -548,6 +548,7 @@ __global__ __launch_bounds__(64 * (WK * WR + WGRAD_LOADER_WAVES), WPE) void wgra
 // What becomes of sums that are not finite in the fix-up pass: they stay, or see kern_wgrad_split.h
 struct KeepSums {
     static constexpr bool on = false;
+    static __device__ bool again(float) { return false; }
 };
 
 // Sum the pieces of every tile shared between blocks and write the tile.  blockIdx.x = tile, blockIdx.y = a
@@ -649,7 +650,7 @@ __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, cons
                 const int rl = 4 * c4 + j;
                 if (rl < rlim) {
                     float v = vv[j];
-                    const bool bad = Repair::on && not_finite(v);
+                    const bool bad = Repair::again(v);
                     odd |= bad;
                     if (rbias) v += rbias[rt * TR + rl];
                     if (P.relu) v = bad ? __uint_as_float(0x7fc00000u) : fmaxf(v, 0.f);      // the ReLU must not hide it

@@ -140,8 +140,11 @@ __device__ __attribute__((always_inline)) inline float wave_sum_again(const Wgra
 // (4.3 with one result a thread), in dzdy 1.0 (4.1), one inf 0.7 and 1.7 (4.6 and 4.3), all NaN 0.3, +inf everywhere 11 (24); 28x28x512,
 // 1x1x512x128, 64 images (0.1 ms): one NaN 0.4 at most (1.5), one inf 0.6 (1.7); 227x227x3, 11x11x3x96 at stride 4, 128 images (0.3 ms), where the
 // results of few blocks meet it: one NaN 3.3 at most (13), one inf 6.4 (13).
+// NAN_ONLY: infinite ones stay (kern_wgrad_bf16.h).
+template <bool NAN_ONLY>
 struct RepairSums {
     static constexpr bool on = true;
+    static __device__ bool again(float v) { return NAN_ONLY ? v != v : not_finite(v); }
     WgradSplitParams S;
     const float *x, *dzdy;
     template <class Where>
@@ -155,7 +158,7 @@ struct RepairSums {
             if (tid == 0) found = 0;
             dead[tid] = 0;
             __syncthreads();
-            if (c0 + tid < n && where(c0 + tid, &k, &r) && not_finite(*(volatile float *)(out + (size_t)(g * S.Kg + k) * S.R + r))) list[atomicAdd(&found, 1)] = c0 + tid;
+            if (c0 + tid < n && where(c0 + tid, &k, &r) && again(*(volatile float *)(out + (size_t)(g * S.Kg + k) * S.R + r))) list[atomicAdd(&found, 1)] = c0 + tid;
             __syncthreads();
             const int m = found;
             if (m > 0) {

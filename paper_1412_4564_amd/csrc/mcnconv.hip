@@ -551,7 +551,7 @@ int launch_wgrad_split_inst(const WgradSplitPlan &pl, const float *x, const floa
         hipLaunchKernelGGL((wgrad_split_kernel<WK, WR, MK, YT, XT, LINEAR>), grid, block, pl.lds_bytes, s, (const WgradSplitParams &)P, x, dzdy, rbias, out, part);
     int st = check_launch();
     if (st || P.nblocks < 2 || P.nchunks == 1) return st;
-    return launch_wgrad_fixup<TILE.TK, TILE.TR>(P, part, rbias, out, s, RepairSums{(const WgradSplitParams &)P, x, dzdy});
+    return launch_wgrad_fixup<TILE.TK, TILE.TR>(P, part, rbias, out, s, RepairSums<TILE.planes == 1>{(const WgradSplitParams &)P, x, dzdy});
 }
 
 template <int SHAPE, int WK, int WR, int MK, int MR>

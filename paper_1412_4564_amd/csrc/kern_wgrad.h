@@ -596,15 +596,15 @@ __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, cons
     const int q = threadIdx.x % Q, pg = threadIdx.x / Q;
     __shared__ float4 red[512];
     bool odd = false;                                   // one of the thread's results is not finite
-    // The q-th word of the pass that begins with the tile's w0-th.  Where sums that are not finite are formed again, the words are dealt to the
-    // tile's blocks 16 at a time, 64 coefficients of a filter, so that several blocks share those of a filter that is not finite anywhere (27x27x96,
-    // 5x5x48x256 in two groups, one NaN in dzdy: 1.0 ms, else 3.1; all finite it costs up to half a microsecond).
-    auto word = [&](int w0, int q) {
-        if constexpr (Repair::on) return w0 + ((q >> 4) * (int)gridDim.y + (int)blockIdx.y) * 16 + (q & 15);
-        else return w0 + (int)blockIdx.y * Q + q;
+    // The q-th word of a pass.  Where sums that are not finite are formed again, the words are dealt to the tile's blocks 16 at a time, 64
+    // coefficients of a filter, so that several blocks share those of a filter that is not finite anywhere (27x27x96, 5x5x48x256 in two groups,
+    // one NaN in dzdy: 1.0 ms, else 3.1; all finite it costs up to half a microsecond), and those of a channel that is not.
+    auto word = [&](int pass, int q) {
+        if constexpr (Repair::on) return sk_dealt_word(pass * (Q >> 4) + (q >> 4), gridDim.y, blockIdx.y, q & 15);
+        else return (pass * (int)gridDim.y + (int)blockIdx.y) * Q + q;
     };
-    for (int w0 = 0; w0 < nwords; w0 += gridDim.y * Q) {
-        const int w = word(w0, q);
+    for (int pass = 0; pass * (int)gridDim.y * Q < nwords; ++pass) {
+        const int w = word(pass, q);
         const bool valid = w < nwords;
         const int kloc = valid ? w / C4 : 0, c4 = valid ? w - kloc * C4 : 0;
         const float *src = part + (size_t)kloc * TR + 4 * c4;
@@ -664,9 +664,9 @@ __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, cons
     if constexpr (Repair::on) {
         if (__syncthreads_or(odd)) {
             // all threads of the block sum again what is not finite of its slice, in the passes above
-            for (int w0 = 0; w0 < nwords; w0 += gridDim.y * Q)
+            for (int pass = 0; pass * (int)gridDim.y * Q < nwords; ++pass)
                 repair(g, 4 * Q, [&](int at, int *k, int *r) {
-                    const int w = word(w0, at >> 2), kloc = w / C4, rl = 4 * (w - kloc * C4) + at % 4;
+                    const int w = word(pass, at >> 2), kloc = w / C4, rl = 4 * (w - kloc * C4) + at % 4;
                     *k = kt * TK + kloc; *r = rt * TR + rl;
                     return w < nwords && rl < rlim;
                 }, rbias, P.relu, out);

@@ -1,10 +1,39 @@
-// SkWalk against the plain divisions, and the fix-up passes' rule for a tile's pieces (sk_has_piece over all ranks) against sk_tile_pieces.
+// SkWalk against the plain divisions, the fix-up passes' rule for a tile's pieces (sk_has_piece over all ranks) against sk_tile_pieces, and the
+// words that their blocks share (sk_dealt_word).
 #include <stdio.h>
 #include <stdlib.h>
+#include <algorithm>
+#include <vector>
 #include "streamk.h"
 using namespace mcn;
 
+// Every word of a tile of `rows` filters, `groups` of 16 words each, once; at most `most` of the groups at one place of all filters in one block.
+static bool dealt(int rows, int groups, int blocks, int per_pass, int most) {
+    const int n = 16 * rows * groups;
+    std::vector<int> taken(n, 0), load(groups * blocks, 0);
+    for (int pass = 0; pass * blocks * per_pass * 16 < n; ++pass)
+        for (int b = 0; b < blocks; ++b)
+            for (int q = 0; q < 16 * per_pass; ++q) {
+                const int w = sk_dealt_word(pass * per_pass + (q >> 4), blocks, b, q & 15);
+                if (w < 0) return false;
+                if (w >= n) continue;
+                ++taken[w];
+                if (q % 16 == 0) ++load[w / 16 % groups * blocks + b];
+            }
+    return std::count(taken.begin(), taken.end(), 1) == n && *std::max_element(load.begin(), load.end()) <= most;
+}
+
 int main() {
+    for (int rows : {1, 5, 32, 64, 100, 128})
+        for (int groups : {1, 2, 3, 4, 6, 8, 12})
+            for (int per_pass : {1, 2, 4, 8, 16})
+                for (int blocks = 1; blocks <= 1024; blocks += blocks < 40 ? 1 : 61)
+                    if (!dealt(rows, groups, blocks, per_pass, rows)) { printf("%d rows of %d groups, %d blocks, %d a pass\n", rows, groups, blocks, per_pass); return 1; }
+    // one place of all filters of the tiles that there are, over a power of two of blocks: three times its even share at most (from the same block every round: all of them in one)
+    for (int rows : {32, 64, 128})
+        for (int groups : {2, 4, 6, 8, 12})
+            for (int blocks = 2; blocks <= 256; blocks *= 2)
+                if (!dealt(rows, groups, blocks, 16, 3 * ((rows + blocks - 1) / blocks))) { printf("%d rows of %d groups in few of %d blocks\n", rows, groups, blocks); return 1; }
     unsigned long long seed = 88172645463325252ull;
     auto rnd = [&](int lo, int hi) { seed ^= seed << 13; seed ^= seed >> 7; seed ^= seed << 17; return lo + (int)(seed % (unsigned long long)(hi - lo + 1)); };
     static int want[2048], got[2048];

@@ -551,8 +551,23 @@ struct KeepSums {
     static __device__ bool again(float) { return false; }
 };
 
+// What the pass takes of the plan, in the order in which it is needed: arguments are fetched from memory where they are first used, a line of 64
+// bytes at a time.  With the whole plan as its argument (five lines, some behind waits for others), seven divisions by numbers that the
+// host knows and a barrier behind its stores the pass took 0.2 to 1.3 us longer (64x256 tiles: 4.0 to 6.0 us, now 3.8 to 4.7; bf16 layers of less
+// than 15 us are 5 % faster with it).
+struct FixupParams {
+    const float *part, *rbias;
+    float *out;
+    int tiles, nchunks, Kg, R, RT, KT;
+    Div32 dRT, dKT;
+    int g, relu;                     // G = 2^g
+    Div32 dC4, dC4_last, dBlocks;    // 16-byte words of a filter row, of the last tile's; blocks of a tile
+    int NU, nblocks;                 // equal ranges only
+    SkWalk walk;
+};
+
 // Sum the pieces of every tile shared between blocks and write the tile.  blockIdx.x = tile, blockIdx.y = a
-// slice of the tile's results.  The order of the additions is fixed by the plan: with G = 512 / Q partial sums
+// slice of the tile's results.  The order of the additions is fixed by the plan: with G = 512 / Q partial sums (1 << P.g)
 // per result (a power of two chosen on the host from the number of pieces), piece i goes to partial sum i mod G
 // and the G sums are added as a balanced tree.  A thread handles four consecutive coefficients of one filter
 // (one 16-byte load per piece, up to four pieces in flight); rows and columns of the tile beyond the filters and
@@ -561,9 +576,11 @@ struct KeepSums {
 // CHUNKED: the pieces of tile t are the first slots of blocks t + tiles*i, i < nchunks; else those of the blocks
 // whose equal ranges of units overlap the tile.
 template <int TK, int TR, bool CHUNKED, class Repair = KeepSums>
-__global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, const float *__restrict__ part,
-                                                          const float *__restrict__ rbias, float *__restrict__ out,
-                                                          int G, Repair repair) {
+__global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(FixupParams P, Repair repair) {
+    const float *__restrict__ const part = P.part;
+    const float *__restrict__ const rbias = P.rbias;
+    float *__restrict__ const out = P.out;
+    const int G = 1 << P.g;
     const int t = blockIdx.x;
     int npieces, slot0 = 0, b0 = 0;
     if constexpr (CHUNKED) {
@@ -584,29 +601,27 @@ __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, cons
         if (npieces < 2) return;      // computed by one block alone: already written
     }
     auto slot_of = [&](int i) { return CHUNKED ? 2 * (t + P.tiles * i) : (i == 0 ? slot0 : 2 * (b0 + i)); };
-    int tt = t;
-    const int rt = tt % P.RT; tt /= P.RT;
-    const int kt = tt % P.KT;
-    const int g = tt / P.KT;
+    const int row = div32(t, P.dRT), rt = t - row * P.RT, g = div32(row, P.dKT), kt = row - g * P.KT;
     const int klim = min(P.Kg - kt * TK, TK);
     const int rlim = min(P.R - rt * TR, TR);           // coefficients of the tile that exist
     const int C4 = (rlim + 3) >> 2;                     // 16-byte words per filter row that hold any of them
+    const Div32 dC4 = rlim < TR ? P.dC4_last : P.dC4;
     const int nwords = klim * C4;
-    const int Q = 512 / G;                              // words per block and pass
-    const int q = threadIdx.x % Q, pg = threadIdx.x / Q;
+    const int Q = 512 >> P.g;                           // words per block and pass
+    const int q = threadIdx.x & (Q - 1), pg = threadIdx.x >> (9 - P.g);
     __shared__ float4 red[512];
     bool odd = false;                                   // one of the thread's results is not finite
     // The q-th word of a pass.  Where sums that are not finite are formed again, the words are dealt to the tile's blocks 16 at a time, 64
     // coefficients of a filter, so that several blocks share those of a filter that is not finite anywhere (27x27x96, 5x5x48x256 in two groups,
     // one NaN in dzdy: 1.0 ms, else 3.1; all finite it costs up to half a microsecond), and those of a channel that is not.
     auto word = [&](int pass, int q) {
-        if constexpr (Repair::on) return sk_dealt_word(pass * (Q >> 4) + (q >> 4), gridDim.y, blockIdx.y, q & 15);
+        if constexpr (Repair::on) return sk_dealt_word(pass * (Q >> 4) + (q >> 4), gridDim.y, P.dBlocks, blockIdx.y, q & 15);
         else return (pass * (int)gridDim.y + (int)blockIdx.y) * Q + q;
     };
     for (int pass = 0; pass * (int)gridDim.y * Q < nwords; ++pass) {
         const int w = word(pass, q);
         const bool valid = w < nwords;
-        const int kloc = valid ? w / C4 : 0, c4 = valid ? w - kloc * C4 : 0;
+        const int kloc = valid ? div32(w, dC4) : 0, c4 = valid ? w - kloc * C4 : 0;
         const float *src = part + (size_t)kloc * TR + 4 * c4;
         float4 acc = {0.f, 0.f, 0.f, 0.f};
         if (valid) {
@@ -658,7 +673,7 @@ __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, cons
                 }
             }
         }
-        __syncthreads();
+        if ((pass + 1) * (int)gridDim.y * Q < nwords) __syncthreads();       // `red` is written again
     }
     (void)odd;
     if constexpr (Repair::on) {
@@ -666,7 +681,7 @@ __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(WgradParams P, cons
             // all threads of the block sum again what is not finite of its slice, in the passes above
             for (int pass = 0; pass * (int)gridDim.y * Q < nwords; ++pass)
                 repair(g, 4 * Q, [&](int at, int *k, int *r) {
-                    const int w = word(pass, at >> 2), kloc = w / C4, rl = 4 * (w - kloc * C4) + at % 4;
+                    const int w = word(pass, at >> 2), kloc = div32(w, dC4), rl = 4 * (w - kloc * C4) + at % 4;
                     *k = kt * TK + kloc; *r = rt * TR + rl;
                     return w < nwords && rl < rlim;
                 }, rbias, P.relu, out);

@@ -452,13 +452,15 @@ int launch_wgrad_fixup(const WgradParams &P, const float *part, const float *rbi
     const int klim = P.Kg < TK ? P.Kg : TK, rlim = P.R < TR ? P.R : TR, fours = klim * ((rlim + 3) / 4);
     const int blocks = 1024 / P.tiles < 1 ? 1 : 1024 / P.tiles;
     auto passes = [&](int g) { return (fours * g + 511) / 512; };      // of the largest tile
-    int G = 2;
-    while (G < 32 && G < pieces && (4 * G < pieces || passes(2 * G) <= blocks)) G *= 2;
-    const int fy = blocks < passes(G) ? blocks : passes(G);
+    int g = 1;
+    while (g < 5 && 1 << g < pieces && (4 << g < pieces || passes(2 << g) <= blocks)) ++g;
+    const int fy = blocks < passes(1 << g) ? blocks : passes(1 << g), last = P.R - (P.RT - 1) * TR;
+    const FixupParams F = {part, rbias, out, P.tiles, P.nchunks, P.Kg, P.R, P.RT, P.KT, make_div32(P.RT), make_div32(P.KT), g, P.relu,
+                           make_div32(TR / 4), make_div32((last + 3) / 4), make_div32(fy), P.NU, P.nblocks, P.walk};
     if (chunked)
-        hipLaunchKernelGGL((wgrad_fixup_kernel<TK, TR, true, Repair>), dim3(P.tiles, fy), dim3(512), 0, s, P, part, rbias, out, G, repair);
+        hipLaunchKernelGGL((wgrad_fixup_kernel<TK, TR, true, Repair>), dim3(P.tiles, fy), dim3(512), 0, s, F, repair);
     else
-        hipLaunchKernelGGL((wgrad_fixup_kernel<TK, TR, false, Repair>), dim3(P.tiles, fy), dim3(512), 0, s, P, part, rbias, out, G, repair);
+        hipLaunchKernelGGL((wgrad_fixup_kernel<TK, TR, false, Repair>), dim3(P.tiles, fy), dim3(512), 0, s, F, repair);
     return check_launch();
 }
 

@@ -90,8 +90,9 @@ MCN_HOST_DEVICE inline int sk_tile_pieces(long long total, int NU, int nblocks, 
 // The 16-byte words of a tile as the blocks of a fix-up pass that forms sums again share them: in groups of 16, dealt to the tile's `blocks` in
 // turn, every round (w: of 16-byte words, round * blocks of groups before it) from the next block on.  A filter's groups then lie in several
 // blocks, and so do those of one place in all filters, whose distance is often a multiple of a number that divides `blocks`.
-MCN_HOST_DEVICE inline int sk_dealt_word(int round, int blocks, int block, int in_group) {
-    return 16 * (round * blocks + (int)((unsigned)(block + round) % (unsigned)blocks)) + in_group;
+MCN_HOST_DEVICE inline int sk_dealt_word(int round, int blocks, Div32 dBlocks, int block, int in_group) {
+    const int turned = block + round;
+    return 16 * (round * blocks + turned - div32(turned, dBlocks) * blocks) + in_group;
 }
 
 // Dealt unit order of a tile cut into nchunks chunks, one per block (kern_wgrad.h, WgradParams::deal).  Chunk c

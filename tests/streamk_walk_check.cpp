@@ -14,7 +14,7 @@ static bool dealt(int rows, int groups, int blocks, int per_pass, int most) {
     for (int pass = 0; pass * blocks * per_pass * 16 < n; ++pass)
         for (int b = 0; b < blocks; ++b)
             for (int q = 0; q < 16 * per_pass; ++q) {
-                const int w = sk_dealt_word(pass * per_pass + (q >> 4), blocks, b, q & 15);
+                const int w = sk_dealt_word(pass * per_pass + (q >> 4), blocks, make_div32(blocks), b, q & 15);
                 if (w < 0) return false;
                 if (w >= n) continue;
                 ++taken[w];

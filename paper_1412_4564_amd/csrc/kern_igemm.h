@@ -888,7 +888,7 @@ __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const f
     const int ts = blockIdx.x;                       // shared tile (the grid has one row of blocks per shared tile)
     const int tile_s0 = P.own * P.nblocks;           // the shared tiles start here; unit numbers are relative to them
     const int t = tile_s0 + ts;
-    // The tile's pieces, in block order (sk_tile_pieces).  Sharing block of rank r holds the units [total*r/nshare, total*(r+1)/nshare): every
+    // The tile's pieces, in block order.  Sharing block of rank r holds the units [total*r/nshare, total*(r+1)/nshare): every
     // thread looks at the ranges of its ranks, and a rank's place in the list is the number of those with a piece before it.  (One thread listed
     // them: with 32 pieces to a tile that took 8 us of 14, 14x14x512, 3x3x512x512, one image.)
     constexpr int MAX_PIECES = 1024;
@@ -912,7 +912,7 @@ __global__ __launch_bounds__(256) void igemm_fixup_kernel(IgemmParams P, const f
             np += found[w];
         }
         const int at = before + __builtin_amdgcn_mbcnt_hi((unsigned)(in_wave >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in_wave, 0u));
-        if (has && at < MAX_PIECES) slots[at] = 2 * sk_share_block(P.nblocks, P.nshare, r) + (bb >= t_lo ? 0 : 1);
+        if (has && at < MAX_PIECES) slots[at] = sk_slot(sk_share_block(P.nblocks, P.nshare, r), bb, t_lo);
     }
     __syncthreads();
     if (alone) return;

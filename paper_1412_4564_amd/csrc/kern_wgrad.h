@@ -593,8 +593,8 @@ __global__ __launch_bounds__(512, 8) void wgrad_fixup_kernel(FixupParams P, Repa
         for (int b = threadIdx.x; b < P.nblocks; b += 512) {
             const long long bb = sk_begin(P.walk, b), be = sk_begin(P.walk, b + 1);
             // the first block's piece is its first one if it starts with this tile, else its last; the others start inside the tile
-            if (bb <= t_lo && be > t_lo) { found[0] = b; found[2] = 2 * b + (bb >= t_lo ? 0 : 1); }
-            if (bb < t_hi && be >= t_hi) found[1] = b;
+            if (sk_holds(bb, be, t_lo)) { found[0] = b; found[2] = sk_slot(b, bb, t_lo); }
+            if (sk_holds(bb, be, t_hi - 1)) found[1] = b;
         }
         __syncthreads();
         b0 = found[0]; npieces = found[1] - found[0] + 1; slot0 = found[2];

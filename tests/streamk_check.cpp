@@ -1,4 +1,5 @@
-// Host check of csrc/streamk.h: the piece list of every left-over tile (sk_tile_pieces, what the fix-up pass adds)
+// Host check of csrc/streamk.h: the piece list of every left-over tile (sk_tile_pieces of streamk_reference.h, with which
+// streamk_walk_check.cpp compares the rules that the fix-up passes use)
 // against a simulation of the blocks' walk over their ranges of units (what the main kernel writes: the first
 // segment of a block's range goes to slot 2*block, any later partial one to slot 2*block + 1, whole tiles are
 // stored by the block itself).
@@ -6,7 +7,7 @@
 #include <stdlib.h>
 #include <initializer_list>
 #include <vector>
-#include "streamk.h"
+#include "streamk_reference.h"
 using namespace mcn;
 
 static unsigned long long rng_state = 88172645463325252ull;
@@ -52,7 +53,7 @@ int main() {
     for (int i = 0; i < 200000; ++i) {
         const int n = 1 + rnd() % 2048;
         const long long total = 1 + (long long)(rnd() % 4000000) * (1 + rnd() % 64);
-        const SkSplit s = sk_split(total, n);
+        const SkWalk s = make_sk_walk(total, n, 1);
         const int vb = rnd() % (n + 1);
         if (sk_begin(s, vb) != sk_begin(total, n, vb)) { printf("sk_begin differs: total %lld n %d vb %d\n", total, n, vb); return 1; }
     }

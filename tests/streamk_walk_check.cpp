@@ -1,10 +1,11 @@
-// SkWalk against the plain divisions, the fix-up passes' rule for a tile's pieces (sk_has_piece over all ranks) against sk_tile_pieces, and the
-// words that their blocks share (sk_dealt_word).
+// SkWalk against the plain divisions, the fix-up passes' rules for a tile's pieces against sk_tile_pieces (igemm: sk_has_piece over all ranks;
+// filter derivative: the blocks that hold its first and its last unit, sk_holds, and all between them), and the words that their blocks
+// share (sk_dealt_word).
 #include <stdio.h>
 #include <stdlib.h>
 #include <algorithm>
 #include <vector>
-#include "streamk.h"
+#include "streamk_reference.h"
 using namespace mcn;
 
 // Every word of a tile of `rows` filters, `groups` of 16 words each, once; at most `most` of the groups at one place of all filters in one block.
@@ -23,7 +24,36 @@ static bool dealt(int rows, int groups, int blocks, int per_pass, int most) {
     return std::count(taken.begin(), taken.end(), 1) == n && *std::max_element(load.begin(), load.end()) <= most;
 }
 
+// The pieces of a tile as wgrad_fixup_kernel finds them: no block's range is empty (no more blocks than units), so one block holds the tile's first
+// unit and one its last.
+static bool ends(int tiles, int NU, int blocks) {
+    const long long total = (long long)tiles * NU;
+    const int n = blocks < total ? blocks : (int)total;
+    const SkWalk w = make_sk_walk(total, n, NU);
+    std::vector<int> want(n + 1);
+    for (int i = 0; i < 4; ++i) {
+        const int ts = i == 0 ? 0 : i == 1 ? tiles - 1 : (int)((unsigned)(i * 7919 * (tiles + n)) % (unsigned)tiles);
+        const long long lo = (long long)ts * NU, hi = lo + NU;
+        int found[3] = {-1, -1, -1}, hits = 0;
+        for (int b = 0; b < n; ++b) {
+            const long long bb = sk_begin(w, b), be = sk_begin(w, b + 1);
+            if (bb >= be) { printf("block %d of %d is empty: %lld units\n", b, n, total); return false; }
+            if (sk_holds(bb, be, lo)) { found[0] = b; found[2] = sk_slot(b, bb, lo); ++hits; }
+            if (sk_holds(bb, be, hi - 1)) { found[1] = b; ++hits; }
+        }
+        const int pieces = found[1] - found[0] + 1, k = sk_tile_pieces(total, NU, n, n, ts, want.data(), n + 1);
+        bool same = hits == 2 && (pieces < 2 ? k == 0 : pieces == k);
+        for (int j = 0; j < k && same; ++j) same = want[j] == (j == 0 ? found[2] : 2 * (found[0] + j));
+        if (!same) { printf("ends of tile %d of %d: %d units, %d blocks\n", ts, tiles, NU, n); return false; }
+    }
+    return true;
+}
+
 int main() {
+    for (int tiles : {1, 2, 3, 7, 64})
+        for (int NU : {1, 2, 3, 5, 16})
+            for (int blocks : {1, 2, 3, 8, 64, 255, 256, 1024})
+                if (!ends(tiles, NU, blocks)) return 1;
     for (int rows : {1, 5, 32, 64, 100, 128})
         for (int groups : {1, 2, 3, 4, 6, 8, 12})
             for (int per_pass : {1, 2, 4, 8, 16})
@@ -56,13 +86,14 @@ int main() {
                 const long long bb = sk_begin(w, r), be = sk_begin(w, r + 1);
                 if (!sk_has_piece(bb, be, lo, hi)) continue;
                 alone |= bb <= lo && be >= hi;
-                got[m++] = 2 * sk_share_block(nblocks, nshare, r) + (bb >= lo ? 0 : 1);
+                got[m++] = sk_slot(sk_share_block(nblocks, nshare, r), bb, lo);
             }
             if (alone) m = 0;
             bool same = m == n;
             for (int i = 0; i < m && same; ++i) same = got[i] == want[i];
             if (!same) { printf("tile %d of %d: %d units, %d of %d blocks\n", ts, tiles, NU, nshare, nblocks); return 1; }
         }
+        if (!ends(tiles, NU, nblocks)) return 1;
     }
     printf("OK\n");
     return 0;

@@ -46,18 +46,36 @@ def test_bf16_filter_derivative_edges(case):
     assert U.norm_err(got, ref, den) <= 2.0 ** -11, U.norm_err(got, ref, den)
 
 
-@pytest.mark.parametrize("case", [1, 6, 7])
-@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
-def test_bf16_filter_derivative_not_finite(case, bad):
-    """One input that is not finite: the coefficients that meet it, and no other, are not finite."""
+# The case and where the bad value is: the last sample of x's last plane or of dzdy's; or, in planes of 30 samples (7 quads and a half), the first of
+# a channel, which the last quad of the plane before it holds beside rows of dzdy that are not there
+BAD = [(c, where) for c in (1, 4, 6, 7, 9) for where in ("x", "dzdy")] + [(0, "x"), (0, "dzdy"), (0, "next channel")]
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("case,where", BAD)
+def test_bf16_filter_derivative_not_finite(case, where, bad):
+    """One input that is not finite: the coefficients that meet it, and no other, are not finite, and which of the three they are."""
     H, W, D, N, Hf, Wf, Df, K, st, pad = EDGES[case]
     L = dict(H=H, W=W, D=D, N=N, Hf=Hf, Wf=Wf, Df=Df, K=K, stride=st, pad=pad, config=8, index=case)
     x, w = synth.make_x(L), synth.make_w(L)
     ho, wo = oracle.output_size(x.shape, w.shape, st, pad)
     p = synth.make_dzdy(L, ho, wo)
-    x[N - 1, D // 2, W - 1, H - 1] = bad
-    print("bf16 filter derivative, not finite", EDGES[case], bad, flush=True)
+    if where == "dzdy":
+        p[N - 1, K // 2, wo - 1, ho - 1] = bad
+    elif where == "x":
+        x[N - 1, D // 2, W - 1, H - 1] = bad
+    else:
+        x[N - 1, D // 2, 0, 0] = bad
+    print("bf16 filter derivative, not finite", EDGES[case], where, bad, flush=True)
     got = B.conv_backward_filter(x.cuda(), w.shape, p.cuda(), st, pad, BF).cpu().numpy()
-    ref = oracle.backward_filter(U.np64(x), w.shape, U.np64(p), st, pad)
-    assert np.array_equal(np.isfinite(got), np.isfinite(ref))
-    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    xr, pr = (U.np64(t.to(torch.bfloat16).to(torch.float32)) for t in (x, p))
+    with np.errstate(invalid="ignore"):
+        ref = oracle.backward_filter(xr, w.shape, pr, st, pad)
+    assert not np.all(np.isfinite(ref)) or case == 7        # padded so that no tap may meet the last sample
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got), fin) and np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    # finite ones as above, or, formed again from the operands as they are, off by two roundings of 2^-9 each in every product
+    xr[~np.isfinite(xr)] = 0; pr[~np.isfinite(pr)] = 0
+    den = oracle.backward_filter(abs(xr), w.shape, abs(pr), st, pad)
+    assert U.norm_err(got[fin], ref[fin], den[fin]) <= 2.0 ** -7.9

@@ -49,11 +49,12 @@ MCN_HOST_DEVICE inline bool sk_holds(long long bb, long long be, long long unit)
 MCN_HOST_DEVICE inline int sk_slot(int block, long long bb, long long t_lo) { return 2 * block + (bb >= t_lo ? 0 : 1); }
 
 // The 16-byte words of a tile as the blocks of a fix-up pass that forms sums again share them: in groups of 16, one a round for each of the
-// tile's `blocks`, every round from the next block on.  A filter's groups then lie in several blocks, and so do those of one place in all
-// filters, whose distance is often a multiple of a number that divides `blocks`.
+// tile's `blocks`, round j from j blocks further back than the one before.  A filter's groups then lie in several blocks, also where a round
+// ends among them, and so do those of one place in all filters, whatever the distance between them (every round from the next block on,
+// that distance and `blocks` could leave them to a few; groups at a round's end and the next one's beginning went to one block).
 MCN_HOST_DEVICE inline int sk_dealt_word(int round, int blocks, Div32 dBlocks, int block, int in_group) {
-    const int turned = block + round;
-    return 16 * (round * blocks + turned - div32(turned, dBlocks) * blocks) + in_group;
+    const int back = round * (round + 1) / 2, turned = block - (back - div32(back, dBlocks) * blocks);
+    return 16 * (round * blocks + (turned < 0 ? turned + blocks : turned)) + in_group;
 }
 
 // Dealt unit order of a tile cut into nchunks chunks, one per block (kern_wgrad.h, WgradParams::deal).  Chunk c

@@ -8,20 +8,32 @@
 #include "streamk_reference.h"
 using namespace mcn;
 
-// Every word of a tile of `rows` filters, `groups` of 16 words each, once; at most `most` of the groups at one place of all filters in one block.
-static bool dealt(int rows, int groups, int blocks, int per_pass, int most) {
-    const int n = 16 * rows * groups;
-    std::vector<int> taken(n, 0), load(groups * blocks, 0);
-    for (int pass = 0; pass * blocks * per_pass * 16 < n; ++pass)
+// Every word of a tile of `rows` filters, C4 words each, once; at most `most` of those of one channel's 25 coefficients (seven words of each
+// filter) in one block; and the groups of a filter each in another, where there are more blocks than rounds.
+static bool dealt(int rows, int C4, int blocks, int per_pass, int most) {
+    const int n = rows * C4, rounds = (n + 16 * blocks - 1) / (16 * blocks), passes = (rounds + per_pass - 1) / per_pass;
+    std::vector<int> block_of(n, -1), load(blocks), seen(blocks, -1);
+    for (int pass = 0; pass < passes; ++pass)
         for (int b = 0; b < blocks; ++b)
             for (int q = 0; q < 16 * per_pass; ++q) {
                 const int w = sk_dealt_word(pass * per_pass + (q >> 4), blocks, make_div32(blocks), b, q & 15);
-                if (w < 0) return false;
-                if (w >= n) continue;
-                ++taken[w];
-                if (q % 16 == 0) ++load[w / 16 % groups * blocks + b];
+                if (w < 0 || (w < n && block_of[w] >= 0)) return false;
+                if (w < n) block_of[w] = b;
             }
-    return std::count(taken.begin(), taken.end(), 1) == n && *std::max_element(load.begin(), load.end()) <= most;
+    if (std::count(block_of.begin(), block_of.end(), -1)) return false;
+    for (int c = 0; c < C4; c += 7) {
+        std::fill(load.begin(), load.end(), 0);
+        for (int k = 0; k < rows; ++k)
+            for (int w = c; w < c + 7 && w < C4; ++w) ++load[block_of[k * C4 + w]];
+        if (*std::max_element(load.begin(), load.end()) > most) return false;
+    }
+    for (int k = 0; k < rows && blocks > rounds + C4 / 16 + 2; ++k)
+        for (int g = k * C4 / 16; g <= (k * C4 + C4 - 1) / 16; ++g) {
+            const int b = block_of[g * 16 < k * C4 ? k * C4 : g * 16];
+            if (seen[b] == k) return false;
+            seen[b] = k;
+        }
+    return true;
 }
 
 // The pieces of a tile as wgrad_fixup_kernel finds them: no block's range is empty (no more blocks than units), so one block holds the tile's first
@@ -55,15 +67,15 @@ int main() {
             for (int blocks : {1, 2, 3, 8, 64, 255, 256, 1024})
                 if (!ends(tiles, NU, blocks)) return 1;
     for (int rows : {1, 5, 32, 64, 100, 128})
-        for (int groups : {1, 2, 3, 4, 6, 8, 12})
+        for (int C4 : {1, 7, 12, 16, 32, 48, 64, 96, 128, 144, 192})
             for (int per_pass : {1, 2, 4, 8, 16})
-                for (int blocks = 1; blocks <= 1024; blocks += blocks < 40 ? 1 : 61)
-                    if (!dealt(rows, groups, blocks, per_pass, rows)) { printf("%d rows of %d groups, %d blocks, %d a pass\n", rows, groups, blocks, per_pass); return 1; }
-    // one place of all filters of the tiles that there are, over a power of two of blocks: three times its even share at most (from the same block every round: all of them in one)
-    for (int rows : {32, 64, 128})
-        for (int groups : {2, 4, 6, 8, 12})
-            for (int blocks = 2; blocks <= 256; blocks *= 2)
-                if (!dealt(rows, groups, blocks, 16, 3 * ((rows + blocks - 1) / blocks))) { printf("%d rows of %d groups in few of %d blocks\n", rows, groups, blocks); return 1; }
+                for (int blocks = 1; blocks <= 512; blocks += blocks < 40 ? 1 : 59)
+                    if (!dealt(rows, C4, blocks, per_pass, 7 * rows)) { printf("%d rows of %d words, %d blocks, %d a pass\n", rows, C4, blocks, per_pass); return 1; }
+    // a channel's words: four times a block's even share of them at most, to the next group (every round from the next block on: up to twelve times)
+    for (int rows : {64, 128})
+        for (int C4 : {12, 24, 32, 48, 64, 96, 128, 192})
+            for (int blocks = 4; blocks <= 85 && 2 * blocks <= rows * C4 / 16; ++blocks)
+                if (!dealt(rows, C4, blocks, 16, 4 * 7 * rows / blocks + 7)) { printf("a channel of %d rows of %d words in few of %d blocks\n", rows, C4, blocks); return 1; }
     unsigned long long seed = 88172645463325252ull;
     auto rnd = [&](int lo, int hi) { seed ^= seed << 13; seed ^= seed >> 7; seed ^= seed << 17; return lo + (int)(seed % (unsigned long long)(hi - lo + 1)); };
     static int want[2048], got[2048];

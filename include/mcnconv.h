@@ -86,8 +86,8 @@ typedef struct mcn_conv_desc {
  *   dzdw of layers that the row-pair kernel does not take runs the same way where that is estimated to be faster
  *   (mcn_conv_operand_planes says 3): the same planes, products and error, half of the fp32 matrix core's on the
  *   workloads.  A coefficient that is not finite there is summed again over the samples inside the array (a zero
- *   of the padding times an infinity counts as zero): a NaN costs two to eleven times the time of an ordinary
- *   call, an infinity up to some twenty times, NaN everywhere little, infinite coefficients everywhere up to sixty times.
+ *   of the padding times an infinity counts as zero): a NaN costs two to twelve times the time of an ordinary
+ *   call, an infinity up to some twenty-five times, NaN everywhere little, infinite coefficients everywhere up to sixty-five times.
  *   The forward pass of fully-connected layers with an even number of coefficients per filter runs on the same kernel
  *   where that is estimated to be faster, their derivatives likewise on that of the forward pass, under every
  *   precision but MCN_PREC_FP32_PLAIN.
@@ -103,6 +103,9 @@ typedef struct mcn_conv_desc {
  *   0), forward and dzdx of other layers on the fp32 matrix core.  dzdx of a strided layer
  *   with at most 16 channels per group (first layers) does too, on the fp32 matrix core: the default is faster
  *   there (227x227x3, 11x11 at stride 4, 128 images: 390 us against 240).
+ *   A coefficient of dzdw on the bf16 kernel that is NaN is summed again over the samples inside the array, from x and dzdy as
+ *   they are, in fp32: a NaN among them, or an infinity that zeros of the padding or of an odd batch's missing image meet, costs
+ *   up to eight times the time of an ordinary call, NaN everywhere up to twice; other infinities cost nothing.
  * MCN_PREC_FP32_BF16X3: fp32 arrays, fp32 accumulation, and every operand of the forward pass and of
  *   dzdx held on chip as TWO bf16 values, hi = bf16(v) and lo = bf16(v - hi) (16 bits of v's
  *   significand), with each product formed as w_hi*x_hi + w_hi*x_lo + w_lo*x_hi on the bf16 matrix core

@@ -15,9 +15,11 @@
 //    zeroed as they are packed;
 //  * what stays the same along a sweep is worked out where it begins, a unit's columns move the arrays' bases (scalar), and the parameters
 //    that only a new sweep needs are read from the kernel's arguments again: 320 instructions for ten octets a thread (190 us);
-//  * units of whole columns where LDS and registers allow it: runs of 224 bytes instead of 48 (156 us; 224x224x64, 3x3x64x64, 32 images: 16
-//    rows 380 us, 56 rows 210).
-// The kernel before it held eight rows of one image in an octet and the slab Hf times: 335 us and 632 us for these two layers.
+//  * units of whole columns where LDS and registers allow it: runs of 224 bytes instead of 48 (156 us; 224x224x64, 3x3x64x64, 32 images: units of
+//    16 rows 420 us, of 56 rows 213; wgb_us takes 32 rows of two columns for that layer, an estimate of 179.5 against 180.9, and they take 290).
+// The kernel before it held eight rows of one image in an octet and the slab Hf times: 335 us and 632 us for the two layers.  It was the faster
+// one for 26 of 2000 random layers of 1 to 200 GFLOP by more than 5 %, for ten by more than 20 % (half of them single images, whose octets
+// are half empty here); over all of them 193 ms then, 128 now.
 //
 // A sum that is NaN may be so because a zero in the place of a sample that there is not met an infinity, and is formed again
 // (kern_wgrad_split.h); one that is infinite has met no such product and stays.  (Infinite sums formed again too: one infinity in x, 27x27x96,

@@ -8,8 +8,8 @@
 // eight of them (an octet): 4 consecutive rows of one column in 2 images, images fastest.  A pair of images is then one
 // 32-bit word of a plane, and an octet of x may start at any row (filter row fi shifts it by fi words): the LDS reads words at
 // any 4-byte boundary at 128 bytes a cycle (ds_read2_b32; 16-byte reads that are not aligned take eleven times as long), and
-// the slab is stored once.  With 8 rows of one image an octet starts at odd halves of a word and the slab must be stored
-// Hf times (kern_wgrad_bf16.h); with 8 images the memory reads runs of a quarter of a line.
+// the slab is stored once.  With 8 rows of one image an octet would start at odd halves of a word and the slab have to be stored
+// Hf times; with 8 images the memory would be read in runs of a quarter of a line.
 //   dzdy tile  [filter][octet][plane] in 16-byte words
 //   x slab     [plane][channel][image pair][column][row phase][row] in 32-bit words (pair of images); row phase: vertical stride
 // A unit is a patch of TI rows x MC columns x 2*NP images, and shares its halo columns with the unit before it (ring of columns).
@@ -136,10 +136,11 @@ __device__ __attribute__((always_inline)) inline float wave_sum_again(const Wgra
 }
 
 // In the fix-up pass: of n stored results, where(i, &k, &r) says which and whether there is one, those that are not finite are summed
-// again by the block's 512 threads, shared out evenly.  27x27x96, 5x5x48x256 in two groups, 128 images (0.31 ms): one NaN in x 1.0 ms at most
-// (4.3 with one result a thread), in dzdy 1.0 (4.1), one inf 0.7 and 1.7 (4.6 and 4.3), all NaN 0.3, +inf everywhere 11 (24); 28x28x512,
-// 1x1x512x128, 64 images (0.1 ms): one NaN 0.4 at most (1.5), one inf 0.6 (1.7); 227x227x3, 11x11x3x96 at stride 4, 128 images (0.3 ms), where the
-// results of few blocks meet it: one NaN 3.3 at most (13), one inf 6.4 (13).
+// again by the block's 512 threads, shared out evenly.  Times at most and in the mean over channels and places in the plane: 27x27x96,
+// 5x5x48x256 in two groups, 128 images (0.31 ms): one NaN in x 1.0, 0.5 ms, in dzdy 1.0, 0.8, one inf 1.7, 0.9 and 1.0, 1.0, all NaN 0.3, +inf
+// everywhere 13; 28x28x512, 1x1x512x128, 64 images (0.07 ms): one NaN 0.2 at most, one inf 0.2 and 0.6; 227x227x3, 11x11x3x96 at stride 4, 128
+// images (0.25 ms), where the results of few blocks meet it: one NaN 0.9 and 0.6, one inf 2.2 and 6.4; 14x14x512, 5x5x512x512, 32 images (0.46 ms):
+// one NaN 5.7 and 0.8, one inf 9.8 and 0.8.  At most 32 or 64 results at a time, each by more threads: the same but for all NaN, 0.6 -> 1.1 and 1.7.
 // NAN_ONLY: infinite ones stay (kern_wgrad_bf16.h).
 template <bool NAN_ONLY>
 struct RepairSums {

@@ -905,7 +905,8 @@ inline bool plan_wgrad_split_shape(const ConvView &v, int n_cu, int shape, bool 
     WgradSplitParams B = {};
     for (int TIQ = 1; TIQ <= 32; ++TIQ) {
         const int RB = (v.Ho + 4 * TIQ - 1) / (4 * TIQ);
-        if (TIQ > 1 && (v.Ho + 4 * TIQ - 5) / (4 * TIQ - 4) == RB) continue;          // fewer rows give the same row blocks
+        // fewer rows give the same row blocks; one plane: a second quad of rows that there are not, where nothing else makes the octets even
+        if (TIQ > 1 && (v.Ho + 4 * TIQ - 5) / (4 * TIQ - 4) == RB && !(tile.planes == 1 && TIQ == 2 && v.Ho <= 4 && best >= 1e300)) continue;
         for (int NP = 1; NP <= 4; NP *= 2)
             for (int MC = 1; MC <= v.Wo && TIQ * MC * NP <= 32; ++MC) {
                 const int NO = TIQ * MC * NP;

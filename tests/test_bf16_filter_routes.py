@@ -28,6 +28,8 @@ SMALL = [
     (9, 3, 16, 1, 1, 2, 16, 65, (1, 2), (1, 2, 0, 0)),
     # the same where two columns of x are more than a unit holds
     (3, 74, 558, 2, 3, 2, 279, 76, (1, 11), (0, 0, 0, 0)),
+    # one column of at most four rows of many images, two pairs of which are more than a unit holds
+    (3, 2, 369, 87, 1, 6, 369, 38, (1, 9), (1, 0, 2, 3)),
 ]
 
 # Images of more than 512 MiB, one and two pairs of which are too much for the offsets of a unit

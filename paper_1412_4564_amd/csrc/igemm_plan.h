@@ -6,10 +6,13 @@
 #include <stddef.h>
 #include <stdlib.h>
 #include <math.h>
+#include <algorithm>
 #include "geom.h"
+#include "kern_direct.h"
 #include "kern_igemm.h"
 #include "kern_igemm_bf16.h"
 #include "kern_igemm_split.h"
+#include "kern_small.h"
 
 namespace mcn {
 
@@ -268,6 +271,24 @@ inline SplitSchedule split_schedule(int64_t tiles, int NU, int NS, int64_t slab_
     return b.us <= a.us ? b : a;
 }
 
+// The view as the plain sum sees it; wino: of pairs of output rows.
+inline PlainView plain_view(const ConvView &v, bool wino) {
+    const int area = v.HfA * v.WfA;
+    PlainView V = {};
+    V.Hf = wino ? 3 : v.Hf; V.Sh = wino ? 1 : v.Sh;
+    if (v.pack_mode == 0) {
+        V.wo = 0; V.wg = area * v.DfA * v.Kg; V.wk = area * v.DfA; V.wc = area; V.wi = 1; V.wj = v.HfA;
+    } else if (v.pack_mode == 1) {
+        V.wo = v.pi + v.pSh * (V.Hf - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
+        V.wg = area * v.DfA * v.Cg; V.wk = area; V.wc = area * v.DfA; V.wi = -v.pSh; V.wj = -v.HfA * v.pSw;
+    } else if (v.pack_mode == 2) {
+        V.wk = 1; V.wc = v.ldk;
+    } else {
+        V.HfA = v.HfA; V.WfA = v.WfA; V.DfA = v.DfA; V.B0i = v.B0i; V.B0j = v.B0j;
+    }
+    return V;
+}
+
 // wino: `v` is the stride-2, four-tap view of pairs of output rows (wino_view) and wino_Ho the real number of rows
 inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf16, int fixed, bool two = false,
                             int wino_Ho = 0, int planes = 1, int split = 0) {
@@ -430,22 +451,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     P.mD = v.mD; P.mPt = v.mPt; P.mPl = v.mPl;
     P.wino_Ho = wino_Ho;
     if (bf16 && planes < 3 && v.pack_mode == 2) return false;       // the fully-connected views compute in fp32
-    if (planes == 3) {
-        const int area = v.HfA * v.WfA;
-        PlainView &V = pl->V;
-        V = PlainView{};
-        V.Hf = wino ? 3 : v.Hf; V.Sh = wino ? 1 : v.Sh;
-        if (v.pack_mode == 0) {
-            V.wo = 0; V.wg = area * v.DfA * v.Kg; V.wk = area * v.DfA; V.wc = area; V.wi = 1; V.wj = v.HfA;
-        } else if (v.pack_mode == 1) {
-            V.wo = v.pi + v.pSh * (V.Hf - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
-            V.wg = area * v.DfA * v.Cg; V.wk = area; V.wc = area * v.DfA; V.wi = -v.pSh; V.wj = -v.HfA * v.pSw;
-        } else if (v.pack_mode == 2) {
-            V.wk = 1; V.wc = v.ldk;
-        } else {
-            V.HfA = v.HfA; V.WfA = v.WfA; V.DfA = v.DfA; V.B0i = v.B0i; V.B0j = v.B0j;
-        }
-    }
+    if (planes == 3) pl->V = plain_view(v, wino);
     P.dTI = make_div32(P.TI); P.dWo = make_div32(P.Wo); P.dWp = make_div32(P.Wp); P.dSRP = make_div32(P.SRP);
     P.dKT = make_div32(P.KT); P.dRB = make_div32(P.RB); P.dPT = make_div32(P.PT);
     // packed weights per unit, in 32-bit words: bf16 steps hold 2 octets x TK filters x 16 bytes
@@ -1062,6 +1068,67 @@ inline bool plan_fc_forward_split(const Geom &g, int n_cu, const WgradPlan *fp32
     WgradSplitParams &P = pl->P;
     P.xsn = P.ysn = R / 2; P.xsc = P.ysc = R;          // offsets inside a unit stay below those that plan_wgrad_split has checked
     return true;
+}
+
+// ---- small layers (kern_small.h) ----------------------------------------------------------
+// Which layers go there, by the products of a pass and the results it has.  Measured on 300 layers of 1 to 8 images of 8 to 53 samples a side, 3 to 32 channels,
+// 4 to 64 filters of 1 to 5 taps a side, strides 1 to 3: forward up to 9e6 products 13.9 -> 9.3 us a call in the mean, none slower by more than 3 %, dzdx 20.4 -> 13.2,
+// 10 slower, by 14 % at most; from there to 5e7 forward 18.9 -> 12.3, dzdx 33 -> 11, where more results than 4096 a channel leave the tiles of the
+// other kernels enough to do.
+// 1x1 filters gain nothing (14x9x24, eight filters, three images 12.2 -> 13.0).
+inline bool small_sum(const Geom &g, int64_t pixels) {
+    if (g.Hf * g.Wf == 1) return false;
+    const double products = (double)g.Ho * g.Wo * g.N * g.K * g.Hf * g.Wf * g.Df;
+    return products <= 9e6 || (products <= 5e7 && pixels <= 4096);
+}
+
+struct SmallPlan {
+    SmallParams P;
+    int views, blocks;       // stride phases, blocks of 64 pixels of the largest
+    size_t lds_bytes;
+};
+// the next view of a plan
+inline bool add_small_view(const ConvView &v, SmallPlan *pl) {
+    SmallParams &P = pl->P;
+    if (pl->views == SMALL_VIEWS) return false;
+    if (pl->views == 0) {
+        P.H = v.H; P.W = v.W; P.Ctot = v.Ctot; P.Cg = v.Cg; P.OH = v.OH; P.OW = v.OW; P.Ktot = v.Ktot; P.Kg = v.Kg;
+        P.KT = (v.Kg + SMALL_K - 1) / SMALL_K;
+        P.dKT = make_div32(P.KT);
+        const int64_t bytes = (int64_t)v.H * v.W * v.Ctot * v.N * 4;
+        if (bytes >= ((int64_t)1 << 30) || (int64_t)v.G * P.KT > 65535) return false;
+        P.in_bytes = (int)bytes;
+        pl->lds_bytes = sizeof(float) * SMALL_WAVES * SMALL_K * 64;
+    }
+    SmallView &S = P.v[pl->views++];
+    const PlainView V = plain_view(v, false);
+    S.Ho = v.Ho; S.Wo = v.Wo; S.pixels = v.Ho * v.Wo * v.N; S.Hf = v.Hf; S.Wf = v.Wf; S.Sh = v.Sh; S.Sw = v.Sw; S.Pt = v.Pt; S.Pl = v.Pl;
+    S.oi0 = v.oi0; S.osi = v.osi; S.oj0 = v.oj0; S.osj = v.osj;
+    S.wo = V.wo; S.wg = V.wg; S.wk = V.wk; S.wc = V.wc; S.wi = V.wi; S.wj = V.wj;
+    S.dHo = make_div32(v.Ho); S.dWo = make_div32(v.Wo); S.dT = make_div32(v.Hf * v.Wf); S.dHf = make_div32(v.Hf);
+    pl->blocks = std::max(pl->blocks, (S.pixels + 63) / 64);
+    const size_t weights = sizeof(float) * (size_t)v.Cg * v.Hf * v.Wf * SMALL_K;
+    pl->lds_bytes = std::max(pl->lds_bytes, weights);
+    return weights <= (size_t)SMALL_LDS;
+}
+
+struct SmallFilterPlan {
+    SmallFilterParams P;
+    int grid;                // blocks of dzdw
+};
+inline bool plan_small_filter(const Geom &g, SmallFilterPlan *pl) {
+    SmallFilterParams &P = pl->P;
+    const int64_t xb = numel_x(g) * 4, yb = numel_y(g) * 4;
+    if (g.Hf > SMALL_HF || xb >= ((int64_t)1 << 30) || yb >= ((int64_t)1 << 30)) return false;
+    P.pieces = (g.Ho * g.Wo + BIAS_PIECE - 1) / BIAS_PIECE; P.dPieces = make_div32(P.pieces);
+    P.H = g.H; P.W = g.W; P.D = g.D; P.N = g.N; P.Df = g.Df; P.K = g.K; P.Kg = g.Kg; P.KT = (g.Kg + SMALL_K - 1) / SMALL_K;
+    P.Hf = g.Hf; P.Wf = g.Wf; P.Sh = g.Sh; P.Sw = g.Sw; P.Pt = g.Pt; P.Pl = g.Pl; P.Ho = g.Ho; P.Wo = g.Wo; P.pixels = g.Ho * g.Wo * g.N;
+    P.x_bytes = (int)xb; P.y_bytes = (int)yb;
+    P.dHo = make_div32(g.Ho); P.dWo = make_div32(g.Wo); P.dWf = make_div32(g.Wf); P.dDf = make_div32(g.Df); P.dKT = make_div32(P.KT);
+    P.blocks = pl->grid = g.G * P.KT * g.Df * g.Wf;
+    // A thread's pixels follow one another, each as long as its loads, and every block reads the whole of its filters' dzdy: 400 layers, up to 1024 pixels and 512
+    // blocks 12.1 -> 9.2 us a call, up to 4096 and 256 13.2 -> 11.0; beyond, 15 -> 22.
+    return P.pixels <= 256 * SMALL_PIXELS ? P.blocks <= 512 : P.pixels <= 4096 && P.blocks <= 256;
 }
 
 }  // namespace mcn

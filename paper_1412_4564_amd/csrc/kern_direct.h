@@ -152,12 +152,13 @@ __global__ __launch_bounds__(256) void direct_backward_filter_kernel(Geom g, con
 // Bound by HBM.  Four pieces are on their way in a wave, each in 16-byte loads whatever the plane's size and place (the hardware takes
 // them at any multiple of 4 bytes).
 constexpr int BIAS_CHUNK = 4096, BIAS_PIECE = 256;
+// sum of the pieces of wave `wave` (of four) of share s of filter k, in lane 0
 template <bool RELU>
-__global__ __launch_bounds__(256) void bias_partial_kernel(const float *__restrict__ y, const float *dzdy, float *dzdp, float *__restrict__ part, int HoWo, int K,
-                                                           int N, int pieces, Div32 dPieces, int S) {
+__device__ __attribute__((always_inline)) inline float bias_share(const float *__restrict__ y, const float *dzdy, float *dzdp, int HoWo, int K, int N, int pieces,
+                                                                  Div32 dPieces, int S, int k, int s, int wave) {
     typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));
     typedef float Quad4 __attribute__((ext_vector_type(4)));
-    const int k = blockIdx.x, s = blockIdx.y, e = 4 * (threadIdx.x & 63), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int e = 4 * (threadIdx.x & 63);
     const int all = N * pieces, step = 4 * S;
     Quad4 sum[4] = {};
 #pragma unroll 1
@@ -200,10 +201,15 @@ __global__ __launch_bounds__(256) void bias_partial_kernel(const float *__restri
         }
     }
     const Quad4 q = (sum[0] + sum[1]) + (sum[2] + sum[3]);
-    float acc = (q[0] + q[1]) + (q[2] + q[3]);
+    return wave_sum((q[0] + q[1]) + (q[2] + q[3]));
+}
+template <bool RELU>
+__global__ __launch_bounds__(256) void bias_partial_kernel(const float *__restrict__ y, const float *dzdy, float *dzdp, float *__restrict__ part, int HoWo, int K,
+                                                           int N, int pieces, Div32 dPieces, int S) {
+    const int k = blockIdx.x, s = blockIdx.y, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     __shared__ float red[4];
-    acc = wave_sum(acc);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    const float acc = bias_share<RELU>(y, dzdy, dzdp, HoWo, K, N, pieces, dPieces, S, k, s, wave);
+    if ((threadIdx.x & 63) == 0) red[wave] = acc;
     __syncthreads();
     if (threadIdx.x == 0) part[(size_t)k * S + s] = (red[0] + red[1]) + (red[2] + red[3]);
 }

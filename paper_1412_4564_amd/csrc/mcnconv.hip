@@ -118,6 +118,10 @@ struct PlanEntry {
     bool wgs_ok;               // on the bf16 matrix core (wgrad_split_kernel)
     bool wgb_ok;               // there, with operands rounded to bf16 (wg is then not set)
     WgradSplitPlan wgs;
+    // small layers: one launch a pass (kern_small.h)
+    bool sf_ok, sb_ok, sw_ok;
+    SmallPlan sf, sb;
+    SmallFilterPlan sw;
     // fc
     WgradPlan fc_fwd;
     bool fcs_ok;               // forward on the three-plane kernel
@@ -156,8 +160,25 @@ bool plan_view(const mcn_conv_desc *d, const ConvView &v, IgemmPlan *pl) {
     return plan_igemm(v, ncu, pl, false, pairs);
 }
 
+// Small layers whose sum is the plain one, in fp32 (bf16 operands: the kernels of their own).
+bool small_fp32(const mcn_conv_desc *d) { return igemm_enabled() && (d->precision == MCN_PREC_FP32 || d->precision == MCN_PREC_FP32_PLAIN); }
+bool plan_small_backward_data(PlanEntry &e, const Geom &g) {
+    e.sb = SmallPlan{};
+    ConvView v;
+    for (int pj = 0; pj < g.Sw; ++pj)
+        for (int pi = 0; pi < g.Sh; ++pi) {
+            if (backward_data_view(g, pi, pj, &v)) {
+                if (!add_small_view(v, &e.sb)) return false;
+            } else if (pi >= g.Hf || pj >= g.Wf) {
+                return false;               // a phase without taps: its samples are to be filled
+            }
+        }
+    return e.sb.views > 0;
+}
+
 void plan_backward_data(PlanEntry &e, const mcn_conv_desc *d, const Geom &g) {
     const bool on = igemm_enabled();
+
     e.bwd_ok = on && g.Sh * g.Sw <= MAX_PHASES;
     e.n_bwd = 0;
     e.bwd_fill = false;
@@ -207,9 +228,19 @@ const PlanEntry *plans_for(const mcn_conv_desc *d, const Geom &g, int pass) {
     };
     auto make = [&](PlanEntry &e, int pass) {
         if (!e.fc) {
-            if (pass == MCN_OP_FORWARD) e.fwd_ok = igemm_enabled() && plan_view(d, forward_view(g), &e.fwd);
-            else if (pass == MCN_OP_BACKWARD_DATA) plan_backward_data(e, d, g);
-            else plan_backward_filter(e, d, g);
+            // small layers keep the plans that name the sum and size the workspace; not row pairs, which sum otherwise
+            const bool small = small_fp32(d);
+            if (pass == MCN_OP_FORWARD) {
+                e.fwd_ok = igemm_enabled() && plan_view(d, forward_view(g), &e.fwd);
+                e.sf = SmallPlan{};
+                e.sf_ok = small && small_sum(g, (int64_t)g.Ho * g.Wo * g.N) && e.fwd_ok && !e.fwd.P.wino_Ho && add_small_view(forward_view(g), &e.sf);
+            } else if (pass == MCN_OP_BACKWARD_DATA) {
+                plan_backward_data(e, d, g);
+                e.sb_ok = small && small_sum(g, (int64_t)g.H * g.W * g.N) && e.bwd_ok && e.n_bwd > 0 && !phase_plan(e, 0).P.wino_Ho && plan_small_backward_data(e, g);
+            } else {
+                plan_backward_filter(e, d, g);
+                e.sw_ok = small && e.wg_ok && !e.wg.wino && plan_small_filter(g, &e.sw);
+            }
             return;
         }
         const bool three = d->precision != MCN_PREC_FP32_PLAIN && wino_enabled();
@@ -590,6 +621,19 @@ int launch_wgrad_split(const WgradSplitPlan &pl, const float *x, const float *dz
     }
 }
 
+int launch_small(const SmallPlan &pl, int groups, const float *in, const float *w, const float *bias, float *out, hipStream_t s, int relu = 0) {
+    SmallParams P = pl.P;
+    P.relu = relu;
+    hipLaunchKernelGGL(small_forward_kernel, dim3(pl.blocks, groups * P.KT, pl.views), dim3(64 * SMALL_WAVES), pl.lds_bytes, s, P, in, w, bias, out);
+    return check_launch();
+}
+int launch_small_filter(const SmallFilterPlan &pl, const float *x, const float *dzdy, float *dzdw, float *dzdb, hipStream_t s) {
+    const int biases = dzdb ? pl.P.K : 0;
+    if (pl.P.pixels <= 256 * SMALL_PIXELS) hipLaunchKernelGGL(small_filter_kernel<256>, dim3(pl.grid + biases), dim3(256), 0, s, pl.P, x, dzdy, dzdw, dzdb);
+    else hipLaunchKernelGGL(small_filter_kernel<1024>, dim3(pl.grid + (biases + 3) / 4), dim3(1024), 0, s, pl.P, x, dzdy, dzdw, dzdb);
+    return check_launch();
+}
+
 // the pass whose plans tell about operation `op` (not the bias derivative)
 int planned_pass(int op) { return op == MCN_OP_BACKWARD_FILTER_BIAS ? MCN_OP_BACKWARD_FILTER : op; }
 
@@ -639,6 +683,7 @@ int run_forward(const mcn_conv_desc *desc, const Geom &g, const float *x, const 
     if (ws_bytes < need || (!ws && need)) return MCN_WORKSPACE_TOO_SMALL;
     const PlanEntry *pe = plans_for(desc, g, MCN_OP_FORWARD);
     if (pe->fc) return pe->fcs_ok ? launch_wgrad_split(pe->fcs, w, x, b, y, ws, s, relu) : launch_wgrad(pe->fc_fwd, w, x, b, y, ws, s, relu);
+    if (pe->sf_ok) return launch_small(pe->sf, g.G, x, w, b, y, s, relu);
     if (pe->fwd_ok) return launch_igemm(pe->fwd, x, w, b, y, ws, s, relu);
     const int total = (int)numel_y(g);
     hipLaunchKernelGGL(direct_forward_kernel, dim3(cdiv(total, 256)), dim3(256), 0, s, g, x, w, b, y, total, relu);
@@ -655,6 +700,7 @@ int run_backward_data(const mcn_conv_desc *desc, const Geom &g, const float *w, 
     const PlanEntry *pe = plans_for(desc, g, MCN_OP_BACKWARD_DATA);
     const int total = (int)numel_x(g);
     int st;
+    if (pe->sb_ok) return launch_small(pe->sb, g.G, dzdy, w, bias, dzdx, s);
     if (pe->bwd_ok && !pe->fc) {
         if (pe->bwd_fill) {
             if (bias)
@@ -698,6 +744,7 @@ int run_backward_filter(const mcn_conv_desc *desc, const Geom &g, const float *x
     if (ws_bytes < need || (!ws && need)) return MCN_WORKSPACE_TOO_SMALL;
     const PlanEntry *pe = plans_for(desc, g, MCN_OP_BACKWARD_FILTER);
     if (pe->fc) return launch_igemm(pe->fc_wg, x, dzdy, nullptr, dzdw, ws, s);
+    if (pe->sw_ok) return launch_small_filter(pe->sw, x, dzdy, dzdw, nullptr, s);
     if (pe->wgs_ok) return launch_wgrad_split(pe->wgs, x, dzdy, nullptr, dzdw, ws, s);
     if (pe->wg_ok) return launch_wgrad(pe->wg, x, dzdy, nullptr, dzdw, ws, s);
     const int total = (int)numel_w(g);
@@ -715,6 +762,8 @@ int run_backward_filter_bias(const mcn_conv_desc *desc, const Geom &g, const flo
     const size_t need = workspace_bytes(desc, g, MCN_OP_BACKWARD_FILTER_BIAS);
     if (ws_bytes < need || (!ws && need)) return MCN_WORKSPACE_TOO_SMALL;
     const PlanEntry *pe = plans_for(desc, g, MCN_OP_BACKWARD_FILTER);
+    const BiasPlan bp = plan_bias(g);
+    if (pe->sw_ok && !bp.rows && bp.S == 1) return launch_small_filter(pe->sw, x, dzdy, dzdw, dzdb, s);
     if (!pe->fc && !pe->wgb_ok && pe->wg_ok && wgrad_gives_bias(pe->wg))
         return launch_wgrad(pe->wg, x, dzdy, nullptr, dzdw, ws, s, 0, dzdb);
     const int st = run_backward_filter(desc, g, x, dzdy, dzdw, ws, ws_bytes, s);
@@ -837,6 +886,7 @@ int mcn_conv_operand_planes(const mcn_conv_desc *desc, int op) {
     if (op == MCN_OP_BACKWARD_BIAS) return 0;
     const PlanEntry *e = plans_for(desc, g, planned_pass(op));
     const IgemmPlan *pl = nullptr;
+    if (op == MCN_OP_FORWARD ? e->sf_ok : op == MCN_OP_BACKWARD_DATA ? e->sb_ok : e->sw_ok) return 0;
     if (op == MCN_OP_FORWARD) {
         if (e->fc) return e->fcs_ok ? 3 : 0;
         if (e->fwd_ok) pl = &e->fwd;

@@ -339,11 +339,17 @@ int launch_igemm_bf16_inst(const IgemmPlan &pl, const float *in, const float *wp
 }
 
 // fp32 operands in three bf16 planes (kern_igemm_split.h)
-template <int WK, int WP, int MK, int MP, bool F23 = false, bool MERGED = false, bool GROUPED = false>
+template <int WK, int WP, int MK, int MP, bool F23 = false, bool MERGED = false, bool GROUPED = false, bool QUADS = false>
 int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, const float *bias, float *out,
                        float *part, hipStream_t s, int relu, const float *w) {
     if constexpr (!F23 && !MERGED && !GROUPED)
-        if (pl.P.Hf * pl.P.Wf == 1) return launch_igemm_split<WK, WP, MK, MP, false, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
+        if (pl.P.Hf * pl.P.Wf == 1) {
+            // pixels that follow one another as the input's samples do, in whole fours: by 16-byte loads
+            const IgemmParams &P = pl.P;
+            if (P.Sh == 1 && P.Sw == 1 && P.Pt == 0 && P.Pl == 0 && P.H == P.Ho && P.W == P.Wo && P.H * P.W % 4 == 0)
+                return launch_igemm_split<WK, WP, MK, MP, false, false, true, true>(pl, in, wpk, bias, out, part, s, relu, w);
+            return launch_igemm_split<WK, WP, MK, MP, false, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
+        }
     if constexpr (!F23 && !MERGED && !GROUPED)
         if (pl.P.mD) return launch_igemm_split<WK, WP, MK, MP, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
     if constexpr (!F23 && !MERGED && !GROUPED && WK * MK == 4 && MP == 1)       // row pairs: the same tile on half the waves, twice as much each
@@ -353,7 +359,7 @@ int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, c
     P.V = pl.V; P.in = in; P.w = w; P.bias = bias; P.out = out;
     P.relu = relu;
     P.wino_pairs = F23 && P.osi == 2 && P.OH % 2 == 0 && ((uintptr_t)out & 7) == 0;
-    auto kern = igemm_split_kernel<WK, WP, MK, MP, F23, MERGED, GROUPED>;
+    auto kern = igemm_split_kernel<WK, WP, MK, MP, F23, MERGED, GROUPED, QUADS>;
     if (pl.lds_bytes > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)pl.lds_bytes);

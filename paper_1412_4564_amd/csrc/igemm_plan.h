@@ -26,6 +26,8 @@ struct ConvView {
     int pack_mode, HfA, WfA, DfA, pSh, pSw, pi, pj, ldk;
     // all stride phases of an input derivative merged into one view (pack mode 3; kern_igemm.h)
     int mD, mPt, mPl, B0i, B0j;
+    // strided view with the input's stride phases as channels (folded_view): the strides; 0 otherwise
+    int fSh, fSw;
 };
 
 inline ConvView forward_view(const Geom &g) {
@@ -100,6 +102,24 @@ inline bool merged_backward_data_view(const Geom &g, ConvView *out) {
     v.pack_mode = 3; v.HfA = g.Hf; v.WfA = g.Wf; v.DfA = g.Df; v.pSh = g.Sh; v.pSw = g.Sw;
     v.mD = g.Df; v.mPt = g.Pt; v.mPl = g.Pl; v.B0i = B0[0]; v.B0j = B0[1];
     *out = v;
+    return true;
+}
+
+// A strided forward view of few channels with the stride phases of its input as channels of their own (pack mode 4): channel c of the view's stride-1 sum is
+// row phase pi and column phase pj of input channel c / (Sh*Sw), c % (Sh*Sw) = pi + Sh*pj, its sample (i, j) is the input's (Sh*i + pi - Pt, Sw*j + pj - Pl), and its
+// tap (a, b) the filter's (Sh*a + pi, Sw*b + pj), zero past the filter's edge.  Three channels fill 3 of the 16 that an MFMA on bf16 takes; so folded, 11x11x3 at stride 4
+// is 48 channels of 3x3 taps, 84 % of them real.
+inline bool folded_view(const ConvView &v, ConvView *out) {
+    if (v.pack_mode != 0 || v.mD || v.Cg >= 16 || v.Sh * v.Sw < 2 || v.Sh > 8 || v.Sw > 8 || v.Pt < 0 || v.Pl < 0) return false;
+    ConvView f = v;
+    f.Hf = (v.Hf + v.Sh - 1) / v.Sh; f.Wf = (v.Wf + v.Sw - 1) / v.Sw; f.Sh = f.Sw = 1; f.Cg = v.Cg * v.Sh * v.Sw;
+    f.fSh = v.Sh; f.fSw = v.Sw; f.pack_mode = 4;
+    // Nine taps or more, three of ten products with zeros at most, 128 pixels for every compute unit.  Forward of 227x227x3, 11x11x3x96 at stride 4, 128 images 301 -> 240 us
+    // on 128 x 128 tiles (96 filters: a quarter of them empty), 9x9 at stride 3 100 -> 83; with fewer taps a tile's reduction is shorter than its way in and out (6x6 at
+    // stride 3, 32 channels of four taps, 61 -> 76 us), with more zeros they cost what bf16 saves (7x7x3 at stride 2 85 -> 94, 5x5 63 -> 78).
+    const int64_t taps = (int64_t)f.Hf * f.Wf;
+    if (taps < 9 || 7 * ((f.Cg + 15) / 16 * 16 * taps) > 10 * (int64_t)v.Cg * v.Hf * v.Wf || (int64_t)v.Ho * v.Wo * v.N < 32768) return false;
+    *out = f;
     return true;
 }
 
@@ -275,8 +295,9 @@ inline SplitSchedule split_schedule(int64_t tiles, int NU, int NS, int64_t slab_
 inline PlainView plain_view(const ConvView &v, bool wino) {
     const int area = v.HfA * v.WfA;
     PlainView V = {};
-    V.Hf = wino ? 3 : v.Hf; V.Sh = wino ? 1 : v.Sh;
-    if (v.pack_mode == 0) {
+    V.Hf = wino ? 3 : v.Hf; V.Sh = wino ? 1 : v.Sh; V.Wf = v.Wf; V.Sw = v.Sw;
+    if (v.fSh) { V.Hf = v.HfA; V.Wf = v.WfA; V.Sh = v.fSh; V.Sw = v.fSw; }
+    if (v.pack_mode == 0 || v.pack_mode == 4) {
         V.wo = 0; V.wg = area * v.DfA * v.Kg; V.wk = area * v.DfA; V.wc = area; V.wi = 1; V.wj = v.HfA;
     } else if (v.pack_mode == 1) {
         V.wo = v.pi + v.pSh * (V.Hf - 1) + v.HfA * (v.pj + v.pSw * (v.Wf - 1));
@@ -451,6 +472,12 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     P.mD = v.mD; P.mPt = v.mPt; P.mPl = v.mPl;
     P.wino_Ho = wino_Ho;
     if (bf16 && planes < 3 && v.pack_mode == 2) return false;       // the fully-connected views compute in fp32
+    P.VC = v.Cg;
+    P.fSh = P.fSw = 0;
+    if (v.fSh) {
+        P.Cg = v.Cg / (v.fSh * v.fSw);
+        P.fSh = v.fSh; P.fSw = v.fSw; P.dfSh = make_div32(v.fSh); P.dfSS = make_div32(v.fSh * v.fSw);
+    }
     if (planes == 3) pl->V = plain_view(v, wino);
     P.dTI = make_div32(P.TI); P.dWo = make_div32(P.Wo); P.dWp = make_div32(P.Wp); P.dSRP = make_div32(P.SRP);
     P.dKT = make_div32(P.KT); P.dRB = make_div32(P.RB); P.dPT = make_div32(P.PT);
@@ -480,6 +507,7 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     Q.Kg = v.Kg; Q.Cg = v.Cg; Q.G = v.G; Q.KT = P.KT; Q.NU = P.NU; Q.NTR = P.NTR; Q.NS = P.NS; Q.WSZ = P.WSZ; Q.TK = TK; Q.MK = MK;
     Q.DC = P.DC; Q.TC = P.TC; Q.pair_mode = P.pair_mode; Q.mode = v.pack_mode;
     Q.Sh = v.pSh; Q.Sw = v.pSw; Q.pi = v.pi; Q.pj = v.pj; Q.ldk = v.ldk;
+    if (v.fSh) { Q.Sh = v.fSh; Q.Sw = v.fSw; }
     Q.mD = v.mD; Q.Pt = v.mPt; Q.Pl = v.mPl; Q.B0i = v.B0i; Q.B0j = v.B0j;
     Q.wino = wino ? 1 : 0;
     Q.planes = bf16 ? planes : 1;

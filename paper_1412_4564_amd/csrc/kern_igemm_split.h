@@ -64,7 +64,7 @@ __device__ __host__ constexpr int split_samples(bool f23) { return 64 * SPLIT_ST
 // pairs), and where weight (group g, filter k, channel c, tap (ti, tj)) is in the caller's array:
 // wo + g*wg + k*wk + c*wc + ti*wi + tj*wj (merged phases: shape of that array and the largest b0 per direction, see PackParams)
 struct PlainView {
-    int Hf, Sh;
+    int Hf, Sh, Wf, Sw;
     int wo, wg, wk, wc, wi, wj;
     int HfA, WfA, DfA, B0i, B0j;
 };
@@ -87,10 +87,10 @@ __device__ inline void plain_results(const IgemmParams &P, const PlainView &V, c
         return m;
     };
 #pragma unroll 1
-    for (int tj = 0; tj < P.Wf; ++tj)
+    for (int tj = 0; tj < V.Wf; ++tj)
 #pragma unroll 1
         for (int ti = 0; ti < V.Hf; ++ti) {
-            const int xi = V.Sh * io + ti - P.Pt, xj = P.Sw * jo + tj - P.Pl;
+            const int xi = V.Sh * io + ti - P.Pt, xj = V.Sw * jo + tj - P.Pl;
             if (xi < 0 || xi >= P.H || xj < 0 || xj >= P.W || !more()) continue;
             const float *xp = xg + xi + (size_t)P.H * xj;
             const float *wp[NF];
@@ -101,7 +101,7 @@ __device__ inline void plain_results(const IgemmParams &P, const PlainView &V, c
                 tap[f] = true;
                 if constexpr (MERGED) {
                     const int ph = k / P.mD, mc = k - ph * P.mD, pj = ph / P.osi, pi = ph - pj * P.osi;
-                    const int fi = merged_tap(ti, V.Hf, V.HfA, P.osi, P.mPt, V.B0i, pi), fj = merged_tap(tj, P.Wf, V.WfA, P.osj, P.mPl, V.B0j, pj);
+                    const int fi = merged_tap(ti, V.Hf, V.HfA, P.osi, P.mPt, V.B0i, pi), fj = merged_tap(tj, V.Wf, V.WfA, P.osj, P.mPl, V.B0j, pj);
                     tap[f] = fi >= 0 && fj >= 0;
                     wp[f] = w + (tap[f] ? fi + V.HfA * fj : 0) + (size_t)V.HfA * V.WfA * (mc + (size_t)V.DfA * (g * P.Cg));
                 } else {
@@ -251,6 +251,32 @@ __global__ __launch_bounds__(256) void igemm_pack_f23_split_kernel(const float *
     }
 }
 
+// Weights of a folded view (folded_view, igemm_plan.h), as igemm_pack_weights_bf16_kernel<3>; a thread writes one pair of channels
+__global__ __launch_bounds__(256) void igemm_pack_folded_kernel(const float *__restrict__ w, unsigned *__restrict__ packed, PackParams Q) {
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= Q.total / 3) return;
+    const int words = Q.WSZ / 3;
+    int t = p / words;
+    const int within = p - t * words;
+    unsigned *const unit = packed + (size_t)t * Q.WSZ;
+    const int j2 = within & 3, row = within >> 2, so = row / Q.TK, kk = row - so * Q.TK, oct = so & 1, s = so >> 1;
+    const int uu = t % Q.NU; t /= Q.NU;
+    const int kt = t % Q.KT, g = t / Q.KT, cg = uu / Q.NTR, tap = (uu - cg * Q.NTR) * Q.TC + s, k = kt * Q.TK + kk;
+    float v[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int vc = cg * BF_DC + oct * 8 + 2 * j2 + e, c = vc / (Q.Sh * Q.Sw), ph = vc - c * Q.Sh * Q.Sw, pj = ph / Q.Sh, pi = ph - pj * Q.Sh;
+        const int fi = Q.Sh * (tap % Q.Hf) + pi, fj = Q.Sw * (tap / Q.Hf) + pj;
+        const bool ok = s < Q.TC && tap < Q.Hf * Q.Wf && k < Q.Kg && vc < Q.Cg && fi < Q.HfA && fj < Q.WfA;
+        v[e] = w[ok ? fi + Q.HfA * (fj + Q.WfA * (c + (size_t)Q.DfA * (g * Q.Kg + k))) : 0];
+        if (!ok) v[e] = 0.f;
+    }
+    unsigned *dst = unit + ((size_t)(s * 3) * 2 + oct) * Q.TK * 4 + kk * 4 + j2;
+    unsigned hi, mid, lo;
+    split_bf16x3(v[0], v[1], &hi, &mid, &lo);
+    dst[0] = hi; dst[2 * Q.TK * 4] = mid; dst[4 * Q.TK * 4] = lo;
+}
+
 // MERGED: the stride phases of an input derivative side by side in the filter dimension (IgemmParams::mD).
 // GROUPED: 1x1 filters.  A unit of one group of 16 channels is a single step, and its barrier and staging take longer than that, so a unit is P.NS
 // groups.  They stand in the slab as taps do, TQ samples from one to the next, and a sample is that of one pixel: no window, no halo.
@@ -261,8 +287,11 @@ __global__ __launch_bounds__(256) void igemm_pack_f23_split_kernel(const float *
 // for 11 cycles of the compute unit's memory pipeline whatever its width up to 256 bytes in all, and for 15 at 1 KB.  28x28x512 -> 128, 64 images: dzdx
 // 63.6 -> 59.5 us, forward 53.8 -> 52.5; 14x14x256 -> 256, 32 images 19.5 -> 16.9; 56x56x64 -> 256, 16 images 33.9 -> 31.4 and 28.4 -> 24.9; dzdw of
 // 6x6x256 -> 4096, 256 images 148 -> 140; 200 random layers forward 4.5 % and dzdx 7 % in the mean.
+// FOLDED: the channels of the reduction are the stride phases of the input's (folded_view, igemm_plan.h): a staging thread's sample is that of phase (0, 0), the
+// others lie up to a stride behind it.  Forward of 227x227x3, 11x11x3x96 at stride 4, 128 images: 301 us on the fp32 kernel, 240 here, with a third of its
+// error; a quarter of the 128 x 128 tiles has no filter.
 // WK x WP computing waves; each owns MK x MP tiles of 32 filters x 32 pixels.
-template <int WK, int WP, int MK, int MP, bool F23, bool MERGED, bool GROUPED, bool QUADS>
+template <int WK, int WP, int MK, int MP, bool F23, bool MERGED, bool GROUPED, bool QUADS, bool FOLDED>
 __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 3 : 2) void igemm_split_kernel(
     SplitParams P, const float *__restrict__ in, const float *__restrict__ wpk, const float *__restrict__ bias, float *out,
     float *__restrict__ part) {
@@ -327,6 +356,8 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
         int kt = 0, g = 0, seq = -1;
         const int sample_dc = GROUPED ? BF_DC * (ltid / TQ) : 0, set_dc = GROUPED ? BF_DC * (NL / TQ) : 0;       // first channel of the thread's samples, in the unit
         const int quad_dc = BF_DC * (quad_e / TQ) + 8 * quad_oct;                  // QUADS: the thread's first channel, in the unit
+        int at_i[FOLDED ? EPT : 1], at_j[FOLDED ? EPT : 1];
+        (void)at_i; (void)at_j;
         unsigned go[EPT][F23 ? 4 : 1];    // byte offset of the thread's samples in channel 0, or SLAB_INVALID; F23: of the pair's four rows
         __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void *)in, 0, 0, BUFFER_FLAGS);
         auto set_tile = [&](int tile) __attribute__((always_inline)) {
@@ -360,6 +391,13 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                 const int r = e - col * SRP;
                 const int U = u0 + col;
                 const int ni = div32(U, P.dWp);          // image relative to n_first
+                if constexpr (FOLDED) {                  // of phase (0, 0): its row and column, which other phases lie behind
+                    const bool there = e < CP && r < P.SR && (n_first + ni) < P.N;
+                    at_i[s] = there ? P.fSh * (rb * P.TI + r) - P.Pt : -(1 << 28);
+                    at_j[s] = P.fSw * (U - ni * P.Wp) - P.Pl;
+                    go[s][0] = 4u * (unsigned)(at_i[s] + P.H * at_j[s] + ni * P.Ctot * HW);
+                    continue;
+                }
                 const int j = U - ni * P.Wp - P.Pl;
                 const int i0 = row0 + (F23 ? 2 * r : r);
                 const bool ok = e < CP && r < P.SR && j >= 0 && j < P.W && (n_first + ni) < P.N;
@@ -369,7 +407,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             }
         };
         auto request = [&](Samples &q) __attribute__((always_inline)) {
-            const int combo = uu & 3, c0 = (F23 ? uu >> 2 : GROUPED ? uu * P.NS : uu) * BF_DC + 8 * oct0, c_end = n < nunits ? P.Cg : 0;
+            const int combo = uu & 3, c0 = (F23 ? uu >> 2 : GROUPED ? uu * P.NS : uu) * BF_DC + 8 * oct0, c_end = n < nunits ? P.VC : 0;
             q.uu = uu; q.kt = kt; q.g = g; q.seq = seq; q.combo = combo;
             if constexpr (QUADS) {
 #pragma unroll
@@ -380,8 +418,20 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                     for (int r = 0; r < 4; ++r) q.v[d >> 2][0][4 * (d & 3) + r] = v[r];
                 }
             }
+            if constexpr (FOLDED) {
 #pragma unroll
-            for (int s = 0; s < (QUADS ? 0 : EPT); ++s) {
+                for (int d = 0; d < CH; ++d) {
+                    const int vc = c0 + d, c = div32(vc, P.dfSS), ph = vc - c * P.fSh * P.fSw, pj = div32(ph, P.dfSh), pi = ph - pj * P.fSh;
+#pragma unroll
+                    for (int s = 0; s < EPT; ++s) {
+                        const bool ok = vc < c_end && (unsigned)(at_i[s] + pi) < (unsigned)P.H && (unsigned)(at_j[s] + pj) < (unsigned)P.W;
+                        q.v[s][0][d] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xrs, ok ? go[s][0] + 4u * (unsigned)(pi + P.H * pj) : SLAB_INVALID,
+                                                                                           (unsigned)c * (unsigned)HW * 4u, 0));
+                    }
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < (QUADS || FOLDED ? 0 : EPT); ++s) {
                 if (s * NL >= CP) continue;
 #pragma unroll
                 for (int a = 0; a < ROWS; ++a) {

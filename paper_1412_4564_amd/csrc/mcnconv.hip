@@ -157,6 +157,13 @@ bool plan_view(const mcn_conv_desc *d, const ConvView &v, IgemmPlan *pl) {
         if (plan_igemm(v, ncu, &split, true, true, 3) && (!ok || split_faster(v, split, *pl, ncu))) { *pl = split; return true; }
         return ok;
     }
+    ConvView folded;
+    if (d->precision == MCN_PREC_FP32 && wino_enabled() && folded_view(v, &folded)) {      // few channels at a stride: its phases as channels
+        IgemmPlan split;
+        const bool ok = plan_igemm(v, ncu, pl, false, pairs);
+        if (plan_igemm(folded, ncu, &split, true, true, 3) && (!ok || split_faster(folded, split, *pl, ncu))) { *pl = split; return true; }
+        return ok;
+    }
     return plan_igemm(v, ncu, pl, false, pairs);
 }
 
@@ -339,10 +346,10 @@ int launch_igemm_bf16_inst(const IgemmPlan &pl, const float *in, const float *wp
 }
 
 // fp32 operands in three bf16 planes (kern_igemm_split.h)
-template <int WK, int WP, int MK, int MP, bool F23 = false, bool MERGED = false, bool GROUPED = false, bool QUADS = false>
+template <int WK, int WP, int MK, int MP, bool F23 = false, bool MERGED = false, bool GROUPED = false, bool QUADS = false, bool FOLDED = false>
 int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, const float *bias, float *out,
                        float *part, hipStream_t s, int relu, const float *w) {
-    if constexpr (!F23 && !MERGED && !GROUPED)
+    if constexpr (!F23 && !MERGED && !GROUPED && !FOLDED)
         if (pl.P.Hf * pl.P.Wf == 1) {
             // pixels that follow one another as the input's samples do, in whole fours: by 16-byte loads
             const IgemmParams &P = pl.P;
@@ -350,16 +357,18 @@ int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, c
                 return launch_igemm_split<WK, WP, MK, MP, false, false, true, true>(pl, in, wpk, bias, out, part, s, relu, w);
             return launch_igemm_split<WK, WP, MK, MP, false, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
         }
-    if constexpr (!F23 && !MERGED && !GROUPED)
+    if constexpr (!F23 && !MERGED && !GROUPED && !FOLDED)
+        if (pl.P.fSh) return launch_igemm_split<WK, WP, MK, MP, false, false, false, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
+    if constexpr (!F23 && !MERGED && !GROUPED && !FOLDED)
         if (pl.P.mD) return launch_igemm_split<WK, WP, MK, MP, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
-    if constexpr (!F23 && !MERGED && !GROUPED && WK * MK == 4 && MP == 1)       // row pairs: the same tile on half the waves, twice as much each
+    if constexpr (!F23 && !MERGED && !GROUPED && !FOLDED && WK * MK == 4 && MP == 1)       // row pairs: the same tile on half the waves, twice as much each
         if (pl.P.wino_Ho) return launch_igemm_split<WK, WP / 2, MK, 2 * MP, true>(pl, in, wpk, bias, out, part, s, relu, w);
     SplitParams P;
     (IgemmParams &)P = pl.P;
     P.V = pl.V; P.in = in; P.w = w; P.bias = bias; P.out = out;
     P.relu = relu;
     P.wino_pairs = F23 && P.osi == 2 && P.OH % 2 == 0 && ((uintptr_t)out & 7) == 0;
-    auto kern = igemm_split_kernel<WK, WP, MK, MP, F23, MERGED, GROUPED, QUADS>;
+    auto kern = igemm_split_kernel<WK, WP, MK, MP, F23, MERGED, GROUPED, QUADS, FOLDED>;
     if (pl.lds_bytes > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)pl.lds_bytes);
@@ -399,6 +408,8 @@ int launch_igemm_fixed(const IgemmPlan &pl, const float *in, const float *wpk, c
 int launch_pack(const IgemmPlan &pl, const float *w, float *packed, hipStream_t s) {
     if (pl.bf16 && pl.Q.wino)
         hipLaunchKernelGGL(igemm_pack_f23_split_kernel, dim3(cdiv(pl.Q.total / 12, 256)), dim3(256), 0, s, w, (unsigned *)packed, pl.Q);
+    else if (pl.bf16 && pl.Q.mode == 4)
+        hipLaunchKernelGGL(igemm_pack_folded_kernel, dim3(cdiv(pl.Q.total / 3, 256)), dim3(256), 0, s, w, (unsigned *)packed, pl.Q);
     else if (pl.bf16) {
         auto pack = pl.planes == 1 ? igemm_pack_weights_bf16_kernel<1, false> : pl.planes == 2 ? igemm_pack_weights_bf16_kernel<2, false>
                     : pl.P.mD ? igemm_pack_weights_bf16_kernel<3, true> : igemm_pack_weights_bf16_kernel<3, false>;

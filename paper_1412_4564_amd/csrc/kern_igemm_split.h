@@ -251,6 +251,86 @@ __global__ __launch_bounds__(256) void igemm_pack_f23_split_kernel(const float *
     }
 }
 
+// The words of igemm_pack_weights_bf16_kernel, or (F23, mode 0 alone) of the one above, where the taps of 16 channels of 16 filters are 16 runs of the caller's
+// array (modes 0 and 1 without strides).  A block brings those runs into LDS by 16-byte loads and writes every tap of them from there, a wave the 16
+// filters of an octet of channels at a time.  With a pair of weights to a thread, 4 bytes of a line to a load, every tap takes the line
+// anew, on whichever XCD its block is.
+// Bound by the way of the words through memory where there are many (3x3x512x512 as row pairs, forward: 28 MB, 9.8 -> 7.4 us; two planes 10.5 -> 7.0,
+// one 10.7 -> 6.2; 5x5x512x512 in three planes 28 -> 13 us), by the chain from load to store in a block where there are few (pack_run_blocks).
+constexpr int PACK_RUN = 16, PACK_RUN_TAPS = 32;
+constexpr int pack_run_threads(bool f23) { return f23 ? 384 : 256; }      // row pairs: a wave to a filter column and octet of channels
+__device__ __host__ inline int pack_run_pitch(int taps) { return PACK_RUN * taps + 4; }      // keeps 16-byte words whole, and filters off each other's banks
+template <int PLANES, bool F23>
+__global__ __launch_bounds__(pack_run_threads(F23)) void igemm_pack_runs_kernel(const float *__restrict__ w, unsigned *__restrict__ packed, PackParams Q) {
+    static_assert(!F23 || PLANES == 3, "row pairs: three planes");
+    typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));
+    extern __shared__ __align__(16) float runs[];      // [16 filters (mode 0) or channels (mode 1)][16 of the other][tap]
+    const int T = Q.HfA * Q.WfA, pitch = pack_run_pitch(T), per = F23 ? 4 : Q.NTR, NCG = Q.NU / per;
+    int t = blockIdx.x;
+    const int kk0 = t % (Q.TK / PACK_RUN) * PACK_RUN; t /= Q.TK / PACK_RUN;
+    const int cg = t % NCG; t /= NCG;
+    const int kt = t % Q.KT, g = t / Q.KT, k0 = kt * Q.TK + kk0, c0 = cg * BF_DC;
+    const int filters = min(Q.Kg - k0, PACK_RUN), channels = min(Q.Cg - c0, BF_DC);      // none of them: zeros
+    {
+        constexpr int LANES = pack_run_threads(F23) / PACK_RUN;       // to a run
+        const int r = threadIdx.x / LANES, rows = Q.mode == 0 ? filters : channels, length = r < rows ? T * max(Q.mode == 0 ? channels : filters, 0) : 0;
+        const float *src = w + T * (Q.mode == 0 ? c0 + (size_t)Q.DfA * (g * Q.Kg + k0 + r) : k0 + (size_t)Q.DfA * (g * Q.Cg + c0 + r));
+#pragma unroll 4
+        for (int e = 4 * (threadIdx.x % LANES); e < PACK_RUN * T; e += 4 * LANES) {
+            Quad v = {0.f, 0.f, 0.f, 0.f};
+            if (e + 4 <= length) v = *reinterpret_cast<const Quad *>(src + e);
+            else
+#pragma unroll
+                for (int u = 0; u < 3; ++u)
+                    if (e + u < length) v[u] = src[e + u];
+            *reinterpret_cast<float4 *>(runs + r * pitch + e) = float4{v[0], v[1], v[2], v[3]};
+        }
+    }
+    __syncthreads();
+    const int j2 = threadIdx.x & 3, kk = (threadIdx.x >> 2) & 15;
+    const int k_step = Q.mode == 0 ? pitch : T, c_step = Q.mode == 0 ? T : pitch;
+    unsigned *const group = packed + ((size_t)(g * Q.KT + kt) * Q.NU + (size_t)cg * per) * Q.WSZ + (kk0 + kk) * 4 + j2;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto store = [&](unsigned *dst, float v0, float v1) {
+        if constexpr (PLANES == 1) {
+            dst[0] = pack_bf16x2(v0, v1);
+        } else if constexpr (PLANES == 2) {
+            unsigned hi, lo;
+            split_bf16x2(v0, v1, &hi, &lo);
+            dst[0] = hi; dst[2 * Q.TK * 4] = lo;
+        } else {
+            unsigned hi, mid, lo;
+            split_bf16x3(v0, v1, &hi, &mid, &lo);
+            dst[0] = hi; dst[2 * Q.TK * 4] = mid; dst[4 * Q.TK * 4] = lo;
+        }
+    };
+    if constexpr (F23) {
+        const int oct = wave & 1, fj = wave >> 1;
+        float v[2][4];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const float *q = runs + kk * k_step + (oct * 8 + 2 * j2 + e) * c_step + 3 * fj;
+            const float g0 = q[0], g1 = q[1], g2 = q[2];
+            v[e][0] = g0;
+            v[e][1] = 0.5f * (g0 + g1 + g2);
+            v[e][2] = 0.5f * (g0 - g1 + g2);
+            v[e][3] = g2;
+        }
+#pragma unroll
+        for (int combo = 0; combo < 4; ++combo) store(group + (size_t)combo * Q.WSZ + (fj * 6 + oct) * Q.TK * 4, v[0][combo], v[1][combo]);
+    } else {
+        const int steps = Q.WSZ / (PLANES * 8 * Q.TK);       // of a unit
+#pragma unroll 4
+        for (int i = wave; i < per * steps * 2; i += pack_run_threads(F23) / 64) {
+            const int oct = i & 1, at = i >> 1, tr = at / steps, s = at - tr * steps, tap = tr * Q.TC + s;
+            const bool there = s < Q.TC && tap < T;
+            const float *src = runs + kk * k_step + (oct * 8 + 2 * j2) * c_step + (!there ? 0 : Q.mode == 0 ? tap : T - 1 - tap);
+            const float v0 = src[0], v1 = src[c_step];
+            store(group + (size_t)tr * Q.WSZ + (s * PLANES * 2 + oct) * Q.TK * 4, there ? v0 : 0.f, there ? v1 : 0.f);
+        }
+    }
+}
+
 // Weights of a folded view (folded_view, igemm_plan.h), as igemm_pack_weights_bf16_kernel<3>; a thread writes one pair of channels
 __global__ __launch_bounds__(256) void igemm_pack_folded_kernel(const float *__restrict__ w, unsigned *__restrict__ packed, PackParams Q) {
     const int p = blockIdx.x * 256 + threadIdx.x;

@@ -168,6 +168,7 @@ struct IgemmPlan {
     IgemmParams P;
     PackParams Q;
     PlainView V;        // three planes
+    FoldedChannels F;   // three planes
     size_t lds_bytes;
     size_t packed_floats;
     size_t partial_floats;   // 2 slots of TK*TQ per resident block
@@ -472,11 +473,11 @@ inline bool plan_igemm_kind(const ConvView &v, int n_cu, IgemmPlan *pl, bool bf1
     P.mD = v.mD; P.mPt = v.mPt; P.mPl = v.mPl;
     P.wino_Ho = wino_Ho;
     if (bf16 && planes < 3 && v.pack_mode == 2) return false;       // the fully-connected views compute in fp32
-    P.VC = v.Cg;
-    P.fSh = P.fSw = 0;
+    pl->F.VC = v.Cg;
+    pl->F.fSh = pl->F.fSw = 0;
     if (v.fSh) {
         P.Cg = v.Cg / (v.fSh * v.fSw);
-        P.fSh = v.fSh; P.fSw = v.fSw; P.dfSh = make_div32(v.fSh); P.dfSS = make_div32(v.fSh * v.fSw);
+        pl->F.fSh = v.fSh; pl->F.fSw = v.fSw; pl->F.dfSh = make_div32(v.fSh); pl->F.dfSS = make_div32(v.fSh * v.fSw);
     }
     if (planes == 3) pl->V = plain_view(v, wino);
     P.dTI = make_div32(P.TI); P.dWo = make_div32(P.Wo); P.dWp = make_div32(P.Wp); P.dSRP = make_div32(P.SRP);

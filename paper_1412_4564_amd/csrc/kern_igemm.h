@@ -152,9 +152,6 @@ struct IgemmParams {
     int wino_Ho;
     int wino_pairs;     // WINO: 1 = both rows of a pair go out in one 8-byte store (rows adjacent in memory, every such
                         // address a multiple of 8: output pointer aligned to 8 bytes and an even number of rows per plane)
-    // channels of the reduction: Cg, or, of a view whose channels are the stride phases of the input's (folded_view; strides fSh, fSw), Cg*fSh*fSw
-    int VC, fSh, fSw;
-    Div32 dfSh, dfSS;          // by fSh, by fSh*fSw
     Div32 dTI, dWo, dWp, dSRP, dKT, dRB, dPT;   // reciprocals of the fields of these names
 };
 

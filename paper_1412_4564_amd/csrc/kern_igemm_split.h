@@ -155,8 +155,16 @@ struct PlainPixels {
 
 // What the main kernel goes by, and (read from the kernel's arguments in memory, where this is the first one) the repair of
 // its tiles.
+// Beside IgemmParams, not in it, so that the other kernels' arguments stay where they are (31x31x56, 5x5x56x64, 123 images, a step 1.012 times as long
+// with these fields among them, 1.006 without, against before there were any).
+struct FoldedChannels {
+    // channels of the reduction: Cg, or, of a view whose channels are the stride phases of the input's (folded_view; strides fSh, fSw), Cg*fSh*fSw
+    int VC, fSh, fSw;
+    Div32 dfSh, dfSS;          // by fSh, by fSh*fSw
+};
 struct SplitParams : IgemmParams {
     PlainView V;
+    FoldedChannels F;
     const float *in, *w, *bias;
     float *out;
 };
@@ -473,8 +481,8 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
                 const int ni = div32(U, P.dWp);          // image relative to n_first
                 if constexpr (FOLDED) {                  // of phase (0, 0): its row and column, which other phases lie behind
                     const bool there = e < CP && r < P.SR && (n_first + ni) < P.N;
-                    at_i[s] = there ? P.fSh * (rb * P.TI + r) - P.Pt : -(1 << 28);
-                    at_j[s] = P.fSw * (U - ni * P.Wp) - P.Pl;
+                    at_i[s] = there ? P.F.fSh * (rb * P.TI + r) - P.Pt : -(1 << 28);
+                    at_j[s] = P.F.fSw * (U - ni * P.Wp) - P.Pl;
                     go[s][0] = 4u * (unsigned)(at_i[s] + P.H * at_j[s] + ni * P.Ctot * HW);
                     continue;
                 }
@@ -487,7 +495,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             }
         };
         auto request = [&](Samples &q) __attribute__((always_inline)) {
-            const int combo = uu & 3, c0 = (F23 ? uu >> 2 : GROUPED ? uu * P.NS : uu) * BF_DC + 8 * oct0, c_end = n < nunits ? P.VC : 0;
+            const int combo = uu & 3, c0 = (F23 ? uu >> 2 : GROUPED ? uu * P.NS : uu) * BF_DC + 8 * oct0, c_end = n < nunits ? P.F.VC : 0;
             q.uu = uu; q.kt = kt; q.g = g; q.seq = seq; q.combo = combo;
             if constexpr (QUADS) {
 #pragma unroll
@@ -501,7 +509,7 @@ __global__ __launch_bounds__(64 * (WK * WP + SPLIT_STAGE_WAVES), WK * WP == 8 ? 
             if constexpr (FOLDED) {
 #pragma unroll
                 for (int d = 0; d < CH; ++d) {
-                    const int vc = c0 + d, c = div32(vc, P.dfSS), ph = vc - c * P.fSh * P.fSw, pj = div32(ph, P.dfSh), pi = ph - pj * P.fSh;
+                    const int vc = c0 + d, c = div32(vc, P.F.dfSS), ph = vc - c * P.F.fSh * P.F.fSw, pj = div32(ph, P.F.dfSh), pi = ph - pj * P.F.fSh;
 #pragma unroll
                     for (int s = 0; s < EPT; ++s) {
                         const bool ok = vc < c_end && (unsigned)(at_i[s] + pi) < (unsigned)P.H && (unsigned)(at_j[s] + pj) < (unsigned)P.W;

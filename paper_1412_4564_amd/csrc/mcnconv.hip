@@ -358,14 +358,14 @@ int launch_igemm_split(const IgemmPlan &pl, const float *in, const float *wpk, c
             return launch_igemm_split<WK, WP, MK, MP, false, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
         }
     if constexpr (!F23 && !MERGED && !GROUPED && !FOLDED)
-        if (pl.P.fSh) return launch_igemm_split<WK, WP, MK, MP, false, false, false, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
+        if (pl.F.fSh) return launch_igemm_split<WK, WP, MK, MP, false, false, false, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
     if constexpr (!F23 && !MERGED && !GROUPED && !FOLDED)
         if (pl.P.mD) return launch_igemm_split<WK, WP, MK, MP, false, true>(pl, in, wpk, bias, out, part, s, relu, w);
     if constexpr (!F23 && !MERGED && !GROUPED && !FOLDED && WK * MK == 4 && MP == 1)       // row pairs: the same tile on half the waves, twice as much each
         if (pl.P.wino_Ho) return launch_igemm_split<WK, WP / 2, MK, 2 * MP, true>(pl, in, wpk, bias, out, part, s, relu, w);
     SplitParams P;
     (IgemmParams &)P = pl.P;
-    P.V = pl.V; P.in = in; P.w = w; P.bias = bias; P.out = out;
+    P.V = pl.V; P.F = pl.F; P.in = in; P.w = w; P.bias = bias; P.out = out;
     P.relu = relu;
     P.wino_pairs = F23 && P.osi == 2 && P.OH % 2 == 0 && ((uintptr_t)out & 7) == 0;
     auto kern = igemm_split_kernel<WK, WP, MK, MP, F23, MERGED, GROUPED, QUADS, FOLDED>;
